@@ -117,7 +117,7 @@ struct FactorItem {
     int64_t L;
     int32_t r, nchunks;
     double *part;    // nchunks x r x r partial Gram sums (upper triangles)
-    double *g;       // r x (r + 1): Cholesky scratch, or the Jacobi matrix
+    double *g;       // r x (r + 1): g[0] is the mark of the orthonormalisation, or the Jacobi matrix
     double *w;       // r x r: inverse factor (orthonormalisation only)
     int32_t *out;    // r' (effective rank only)
 };
@@ -137,6 +137,8 @@ int launch_effective_rank(int64_t L, int r, const float *q_bar, double tau, int3
 int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_t st);
 // fp64 Gram matrix partials of r x L factors: part[chunk][a][b] for a <= b (others untouched)
 int gram_chunks(int64_t L);
-int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, hipStream_t st);
+// (round 1: the second round of the orthonormalisation, which factors may not need; else 0)
+int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, int round,
+                               hipStream_t st);
 
 }  // namespace dlcx

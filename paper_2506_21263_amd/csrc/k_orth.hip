@@ -1,6 +1,5 @@
 // Orthonormalisation of the averaged factor P_bar (L x r, stored r x L): the thin-QR Q-factor
-// with positive diagonal of R, computed as CholeskyQR applied twice with all small-matrix work in
-// fp64:
+// with positive diagonal of R, as CholeskyQR with all small-matrix work in fp64:
 //   1. G = P^T P as fp64 partial sums over chunks of L (fixed chunking, summed in chunk order)
 //   2. one workgroup: scale G to unit diagonal, Cholesky G = R^T R, W = R^-1  (r x r, fp64)
 //   3. P <- P W, in place, fp64 accumulation
@@ -9,9 +8,19 @@
 // scaled matrix is (residual norm / column norm)^2, so the rule "residual <= 1e-6 of the column
 // norm => zero column" is a comparison of the pivot with 1e-12.
 //
+// The three steps run twice when the first round may have left an orthogonality error that shows
+// in fp32: that error is of the order of eps64 ||R^-1||^2, and step 2 has R^-1 at hand, so it
+// leaves a mark (kDone) beside its scratch and the kernels of the second round return at once.
+//
+// All three steps are contractions in fp64 and run on v_mfma_f64_16x16x4_f64.  Its operands, for
+// lane l: A[l % 16][l / 16], B[l / 16][l % 16], D[4 v + l / 16][l % 16] in register v.  An operand
+// that is already an accumulator (a 16 x 16 block X in D's layout) is, register by register, the
+// B operand X and the A operand X^T of a product over its rows.
+//
 // Every kernel here takes a batch of factors (one descriptor per matrix, passed by value): the
 // work per matrix is small and latency-bound, so the matrices of a stage go through each step
-// together, one workgroup (or one slice of the grid) per matrix.
+// together, one workgroup (or one slice of the grid) per matrix.  What a factor's result is made of
+// does not depend on the batch it comes in.
 #include "common.h"
 
 namespace dlcx {
@@ -19,18 +28,43 @@ namespace dlcx {
 constexpr int kGramChunk = 512;  // elements of L per partial sum
 constexpr int kGT = 256;
 
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4_t mfma64(double a, double b, f64x4_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// it.g[0] after the first round's step 2: a second round would change nothing that fp32 shows
+// (||R^-1||_F^2 of the unit-diagonal Gram matrix up to which that holds).  Measured against a 64-bit
+// QR at 512 x 8 .. 28672 x 256 and condition numbers 1 .. 1e5: up to 8e7 one round alone is as
+// close as two (2.5e-8, the rounding to fp32), at 1e9 it is at 3 - 7e-8; the line leaves a factor of 20.
+constexpr double kDone = 1.0;
+constexpr double kOneRoundNorm = 4e6;
+__device__ __forceinline__ bool second_round_idle(const FactorItem &it, int round) {
+    return round == 1 && it.g[0] == kDone;
+}
+
 int gram_chunks(int64_t L) { return (int)ceil_div(L, kGramChunk); }
 
-// part[chunk][a][b] = sum_{i in chunk} f[a][i] * f[b][i] for the 64 x 64 tile (ta, tb), ta <= tb.
-__global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch) {
-    __shared__ float at[16][64 + 4];
-    __shared__ float bt[16][64 + 4];
+// part[chunk][a][b] = sum_{i in chunk} f[a][i] * f[b][i] for the tile (ta, tb) of 16 NB x 16 NB
+// outputs, ta <= tb.  Each wavefront takes a quarter of the chunk and keeps the whole tile; lane
+// (row, q) loads the four consecutive elements 4 q .. 4 q + 3 of its row and feeds element s to
+// the s-th product (both operands agree on that order of the reduction index), so operands come
+// straight from memory, 64 consecutive bytes per row, and nothing waits at a barrier until the
+// four quarters are added in order at the end.
+// Bound by the fp64 matrix cores at high rank: seven factors of a 100B-class layer at r = 256
+// (77824 rows, 5.1 GFLOP over the upper triangle) take 117 us; through LDS tiles and vector
+// fp64 FMAs it was 200 us, and 40 us for a single 512 x 8 factor (64 barriers in a row), now 5.
+template <int NB>
+__global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch, int round) {
+    __shared__ double red[4][NB * NB * 4][64];
     const FactorItem it = batch.it[blockIdx.z];
+    const int r = it.r;
+    const int nt = (r + 16 * NB - 1) / (16 * NB);
+    if ((int)blockIdx.x >= it.nchunks || (int)blockIdx.y >= nt * (nt + 1) / 2) return;
+    if (second_round_idle(it, round)) return;
     const float *__restrict__ f = it.f;
     const int64_t L = it.L;
-    const int r = it.r;
-    const int nt = (r + 63) / 64;
-    if ((int)blockIdx.x >= it.nchunks || (int)blockIdx.y >= nt * (nt + 1) / 2) return;
     // tile index -> (ta, tb) with ta <= tb
     int t = blockIdx.y, ta = 0;
     while (t >= nt - ta) {
@@ -38,244 +72,425 @@ __global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch) {
         ++ta;
     }
     const int tb = ta + t;
-    const int a0 = ta * 64, b0 = tb * 64;
-    const int64_t i_begin = (int64_t)blockIdx.x * kGramChunk;
-    int64_t i_end = i_begin + kGramChunk;
-    if (i_end > L) i_end = L;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // 16 x 16 threads, 4 x 4 each
-    double acc[4][4];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, q = lane >> 4;
+    const float *pa[NB], *pb[NB];
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = 0.0;
-
-    for (int64_t i0 = i_begin; i0 < i_end; i0 += 16) {
-        // 64 factor columns x 16 elements for each operand: 256 float4, one per thread
-        {
-            const int col = threadIdx.x >> 2, c4 = threadIdx.x & 3;
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            if (i0 + c4 * 4 < i_end) {
-                if (a0 + col < r)
-                    va = *reinterpret_cast<const float4 *>(f + (int64_t)(a0 + col) * L + i0 + c4 * 4);
-                if (b0 + col < r)
-                    vb = *reinterpret_cast<const float4 *>(f + (int64_t)(b0 + col) * L + i0 + c4 * 4);
-            }
-            at[c4 * 4 + 0][col] = va.x; at[c4 * 4 + 1][col] = va.y;
-            at[c4 * 4 + 2][col] = va.z; at[c4 * 4 + 3][col] = va.w;
-            bt[c4 * 4 + 0][col] = vb.x; bt[c4 * 4 + 1][col] = vb.y;
-            bt[c4 * 4 + 2][col] = vb.z; bt[c4 * 4 + 3][col] = vb.w;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ii = 0; ii < 16; ++ii) {
-            const float4 a = *reinterpret_cast<const float4 *>(&at[ii][ty * 4]);
-            const float4 b = *reinterpret_cast<const float4 *>(&bt[ii][tx * 4]);
-            const double av[4] = {a.x, a.y, a.z, a.w};
-            const double bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fma(av[x], bv[y], acc[x][y]);
-        }
-        __syncthreads();
+    for (int x = 0; x < NB; ++x) {  // rows past r: any valid row, their outputs are not stored
+        const int a = (ta * NB + x) * 16 + row, b = (tb * NB + x) * 16 + row;
+        pa[x] = f + (int64_t)(a < r ? a : r - 1) * L + 4 * q;
+        pb[x] = f + (int64_t)(b < r ? b : r - 1) * L + 4 * q;
     }
+    constexpr int kQuarter = kGramChunk / 4;
+    const int64_t begin = (int64_t)blockIdx.x * kGramChunk + wave * kQuarter;
+    int64_t end = begin + kQuarter;
+    if (end > L) end = L;  // L is a multiple of 16: a step of 16 is whole or not there
+    f64x4_t acc[NB][NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y) acc[x][y] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    if (begin < end) {
+        float4 va[NB], vb[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            va[x] = *reinterpret_cast<const float4 *>(pa[x] + begin);
+            vb[x] = *reinterpret_cast<const float4 *>(pb[x] + begin);
+        }
+        for (int64_t i = begin; i < end; i += 16) {
+            const int64_t nx = i + 16 < end ? i + 16 : begin;
+            float4 na[NB], nb[NB];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                na[x] = *reinterpret_cast<const float4 *>(pa[x] + nx);
+                nb[x] = *reinterpret_cast<const float4 *>(pb[x] + nx);
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+#pragma unroll
+                for (int x = 0; x < NB; ++x)
+#pragma unroll
+                    for (int y = 0; y < NB; ++y) {
+                        if (x > y && ta == tb) continue;  // below the diagonal
+                        const float fa = s == 0 ? va[x].x : s == 1 ? va[x].y : s == 2 ? va[x].z : va[x].w;
+                        const float fb = s == 0 ? vb[y].x : s == 1 ? vb[y].y : s == 2 ? vb[y].z : vb[y].w;
+                        acc[x][y] = mfma64((double)fa, (double)fb, acc[x][y]);
+                    }
+            }
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                va[x] = na[x];
+                vb[x] = nb[x];
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int y = 0; y < NB; ++y)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][(x * NB + y) * 4 + v][lane] = acc[x][y][v];
+    __syncthreads();
     double *dst = it.part + (int64_t)blockIdx.x * r * r;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-            const int a = a0 + ty * 4 + x, b = b0 + tx * 4 + y;
-            if (a < r && b < r && a <= b) dst[a * r + b] = acc[x][y];
-        }
+    for (int u = 0; u < NB * NB; ++u) {  // a quarter of the tile each, quarters of the chunk in order
+        const int e = wave * NB * NB + u;
+        const int x = e / (4 * NB), y = (e / 4) % NB, v = e % 4;
+        const int a = (ta * NB + x) * 16 + 4 * v + q, b = (tb * NB + y) * 16 + row;
+        const double s = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
+        if (a < r && b < r && a <= b) dst[a * r + b] = s;
+    }
 }
 
 // part[0][a][b] <- sum over the chunks, in chunk order, for a <= b: the sum that the one workgroup
-// per matrix of the Cholesky and eigenvalue kernels would otherwise form by itself (r^2 x chunks
-// loads by one workgroup: 1 - 2 ms of its 3 - 7 ms at r = 256 and L = 28672), here spread over
-// the GPU.  Same additions in the same order, so the same bits.
-__global__ __launch_bounds__(kGT) void gram_reduce_kernel(FactorBatch batch) {
+// per matrix of the Cholesky and eigenvalue kernels would otherwise form by itself, here spread
+// over the GPU.  Same additions in the same order, so the same bits.  Eight chunks are requested
+// before the first is added.
+__global__ __launch_bounds__(kGT) void gram_reduce_kernel(FactorBatch batch, int round) {
     const FactorItem it = batch.it[blockIdx.y];
     const int r = it.r;
     const int64_t rr = (int64_t)r * r;
     const int64_t x = (int64_t)blockIdx.x * kGT + threadIdx.x;
     if (x >= rr || it.nchunks < 2) return;
     if (x / r > x % r) return;  // lower triangle: never written, never read
+    if (second_round_idle(it, round)) return;
     double s = 0.0;
-    for (int c = 0; c < it.nchunks; ++c) s += it.part[(int64_t)c * rr + x];
+    int c = 0;
+    for (; c + 8 <= it.nchunks; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = it.part[(int64_t)(c + u) * rr + x];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; c < it.nchunks; ++c) s += it.part[(int64_t)c * rr + x];
     it.part[x] = s;
 }
 
 // Partial Gram sums of every factor of the batch, then their sum in part[0]: *reduced is the
-// batch as the kernels that consume the Gram matrices have to see it (one chunk each).
-int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, hipStream_t st) {
-    int max_chunks = 1, max_tiles = 1, max_r = 1;
+// batch as the kernels that consume the Gram matrices have to see it (one chunk each).  Small
+// sums are left to the consumer: a launch costs more than the few loads per entry it saves.
+int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, int round,
+                               hipStream_t st) {
+    int max_chunks = 1, max_r = 1;
+    int64_t max_sum = 1;
     for (int i = 0; i < batch.n; ++i) {
-        const int nt = (batch.it[i].r + 63) / 64;
+        const int r = batch.it[i].r;
+        const int64_t sum = (int64_t)batch.it[i].nchunks * r * r;
         if (batch.it[i].nchunks > max_chunks) max_chunks = batch.it[i].nchunks;
-        if (nt * (nt + 1) / 2 > max_tiles) max_tiles = nt * (nt + 1) / 2;
-        if (batch.it[i].r > max_r) max_r = batch.it[i].r;
+        if (r > max_r) max_r = r;
+        if (sum > max_sum) max_sum = sum;
     }
-    const dim3 grid((unsigned)max_chunks, (unsigned)max_tiles, (unsigned)batch.n);
+    const int nb = max_r <= 16 ? 1 : 2;  // 16 x 16 blocks per side of a tile
+    const int nt = (max_r + 16 * nb - 1) / (16 * nb);
+    const dim3 grid((unsigned)max_chunks, (unsigned)(nt * (nt + 1) / 2), (unsigned)batch.n);
     Timed timed(KID_GRAM, st);
-    hipLaunchKernelGGL(gram_partial_kernel, grid, dim3(kGT), 0, st, batch);
+    if (nb == 1)
+        hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, round);
+    else
+        hipLaunchKernelGGL(gram_partial_kernel<2>, grid, dim3(kGT), 0, st, batch, round);
     int rc = check_launch("gram_partials");
     if (rc != DLCX_OK) return rc;
     *reduced = batch;
-    if (max_chunks < 2) return DLCX_OK;
+    if (max_chunks < 2 || (max_chunks <= 16 && max_sum <= 16 * 1024)) return DLCX_OK;
     const dim3 rgrid((unsigned)ceil_div((int64_t)max_r * max_r, kGT), (unsigned)batch.n);
-    hipLaunchKernelGGL(gram_reduce_kernel, rgrid, dim3(kGT), 0, st, batch);
+    hipLaunchKernelGGL(gram_reduce_kernel, rgrid, dim3(kGT), 0, st, batch, round);
     for (int i = 0; i < batch.n; ++i) reduced->it[i].nchunks = 1;
     return check_launch("gram_reduce");
 }
 
-// One workgroup per matrix.  g (r rows of pitch r + 1, fp64, LDS or global) <- sum of the
-// partials (upper triangle), scaled to unit diagonal; right-looking Cholesky G = R^T R in place;
-// in-place inversion of R column by column; w <- diag(scale) R^-1.  A dead column (pivot <=
-// 1e-12, i.e. residual <= 1e-6 of the column norm, or zero norm) gives a zero row of R and a zero
-// column of w.
-constexpr int kCT = 256;        // threads, small matrices
-constexpr int kCTLarge = 1024;  // threads once the matrix no longer fits LDS and lives in L2
-constexpr size_t kCholLdsMax = 140 * 1024;
+// ---------------------------------------------------------------------------------------------
+// W = R^-1 of the scaled Gram matrix, one workgroup per matrix, the matrix in registers.
+// G is cut into 16 x 16 blocks; only the blocks (I, J), J <= I, exist, one accumulator each, dealt
+// to the wavefronts.  Eliminating [G | 1] block row by block row turns G into R and 1 into
+// R^-T = L^-1 (G = L L^T); a block (I, J) holds the rest of G (transposed: rows J, columns I)
+// until step J, and from then on block (I, J) of L^-1 under construction, which is final after
+// step I.  Step k:
+//   V = L_kk^-1 of the block (k, k), by one wavefront (factor_block);
+//   panel: block (I, k) -> V G_kI =: X_I (a block of R), block (k, J) -> V (k, J) =: X_J (final);
+//          both products take V as A operand and the accumulator as it is as B operand;
+//   every block with I > k:  J > k: -= X_J^T X_I ;  J <= k: -= X_I^T X_J  (X_k = V),
+//          operands from LDS in accumulator layout, no transposition anywhere.
+// The wavefront that owns block (k + 1, k + 1) updates it first and factors it while the others
+// are still updating.  r^3 2/3 fp64 operations on one compute unit's matrix cores: r = 256 takes
+// 162 us and r = 32 13 us (row by row with the matrix in L2 / LDS: 2530 and 49 us).
+// ---------------------------------------------------------------------------------------------
+constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
+constexpr int kVPitch = 17;
+constexpr int kCT = 512;  // at most 8 wavefronts: 17 blocks each at r = 256, 136 of 256 registers
 
-__global__ __launch_bounds__(kCTLarge) void chol_inverse_kernel(FactorBatch batch) {
-    extern __shared__ double smem[];
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// LDS written and read by the same wavefront: its instructions execute in order, so only the
+// compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// V = L^-1 of a symmetric 16 x 16 block G = L L^T (pitch kVPitch) by one wavefront: lane c < 16
+// holds column c of G, lane 16 + c column c of the unit matrix, and the elimination of row j is a
+// product of every column with a scalar read from lane i of row j (G is symmetric).  The square
+// roots are left to the end, so the chain from pivot to pivot is a reciprocal and two FMAs.
+// Dead pivots (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.  Returns
+// whether one of the first `live` pivots was dead.
+__device__ __forceinline__ bool factor_block(const double *g, double *v, int lane, int live) {
+    double c[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        c[i] = lane < 16 ? g[i * kVPitch + lane] : (lane == 16 + i ? 1.0 : 0.0);
+    double own = 0.0;  // lane i < 16: pivot i
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const double p = read_lane(c[j], j);
+        if (lane == j) own = p;
+        const bool dead = !(p > 1e-12);
+        double rp = __builtin_amdgcn_rcp(p);
+        rp = fma(fma(-p, rp, 1.0), rp, rp);
+        rp = fma(fma(-p, rp, 1.0), rp, rp);
+        const double t = dead ? 0.0 : c[j] * rp;
+#pragma unroll
+        for (int i = j + 1; i < 16; ++i) c[i] = fma(-read_lane(c[j], i), t, c[i]);
+    }
+    const bool dead = !(own > 1e-12);
+    const double rs = dead ? 0.0 : 1.0 / sqrt(own);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const double x = c[i] * read_lane(rs, i);
+        if (lane >= 16 && lane < 32) v[i * kVPitch + lane - 16] = x;
+    }
+    return __ballot(dead && lane < 16 && lane < live) != 0;
+}
+
+template <int SLOTS>
+__global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, int round) {
     const FactorItem it = batch.it[blockIdx.x];
+    if (second_round_idle(it, round)) return;
     const int r = it.r, nchunks = it.nchunks;
-    const int rp = r + 1;                                // odd pitch avoids LDS bank conflicts
-    const bool in_lds = (size_t)r * rp * sizeof(double) <= kCholLdsMax;
-    double *g = in_lds ? smem : it.g;
     const double *__restrict__ part = it.part;
     double *__restrict__ w = it.w;
-    __shared__ double dscale[DLCX_MAX_RANK];             // 1 / column norm (0 for a zero column)
-    __shared__ double dinv[DLCX_MAX_RANK];               // 1 / R_cc (0 for a dead column)
-    __shared__ double colbuf[DLCX_MAX_RANK];
-    __shared__ double psum[(kCTLarge / 256) * 256];      // shares of the inverse's sums
-    const int tid = threadIdx.x;
-    const int nt = blockDim.x, nty = nt >> 4;            // threads as nty rows of 16
-    const int ty = tid >> 4, tx = tid & 15;
-    for (int a = ty; a < r; a += nty)
-        for (int b = a + tx; b < r; b += 16) {  // sum of the partials in chunk order
-            double s = 0.0;
-            for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * r * r + a * r + b];
-            g[a * rp + b] = s;
-        }
-    __syncthreads();
-    for (int c = tid; c < r; c += nt) {
-        const double d = g[c * rp + c];
+    __shared__ double dscale[DLCX_MAX_RANK];  // 1 / column norm (0 for a zero column)
+    __shared__ double panel[kMaxBlocks][4][64];
+    __shared__ double vbuf[2][16 * kVPitch];
+    __shared__ double diag[16 * kVPitch];
+    __shared__ double red[kCT / 64];
+    __shared__ int any_dead;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int g = lane >> 4, col = lane & 15;
+    const int nb = (r + 15) >> 4, nblk = nb * (nb + 1) / 2;
+    const int64_t rr = (int64_t)r * r;
+    if (tid == 0) any_dead = 0;
+    for (int c = tid; c < 16 * nb; c += blockDim.x) {
+        double d = 0.0;
+        if (c < r)
+            for (int q = 0; q < nchunks; ++q) d += part[q * rr + (int64_t)c * r + c];
         dscale[c] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
     }
     __syncthreads();
-    for (int a = ty; a < r; a += nty)
-        for (int b = a + tx; b < r; b += 16) g[a * rp + b] *= dscale[a] * dscale[b];
+    f64x4_t t[SLOTS];
+    int id[SLOTS];  // I << 8 | J; past the last block I = 0xff... < 0, which no step asks for
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        const int b = wave + nw * s;
+        int I = 0;
+        while ((I + 1) * (I + 2) / 2 <= b) ++I;
+        const int J = b - I * (I + 1) / 2;
+        id[s] = b < nblk ? I << 8 | J : -1;
+        t[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+        if (b < nblk) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int x = 16 * J + 4 * v + g, y = 16 * I + col;
+                double sum = 0.0;
+                if (x < r && y < r) {  // the upper triangle is what is stored
+                    const double *src = part + (int64_t)(x < y ? x : y) * r + (x < y ? y : x);
+                    for (int q = 0; q < nchunks; ++q) sum += src[q * rr];
+                }
+                t[s][v] = sum * (dscale[x] * dscale[y]);
+            }
+            if (I == 0) {  // block (0, 0)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
+            }
+        }
+    }
+    // The slot's block, opaque to the compiler at every use: addresses derived from it would
+    // otherwise be kept for all slots across the loop, and the blocks spilled for them.
+    auto block_of = [&](int s, int &I, int &J) {
+        int x = id[s];
+        asm volatile("" : "+s"(x));
+        I = x >> 8;
+        J = x & 0xff;
+    };
+    bool dead = false;
+    double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
+    if (wave == 0) {
+        wave_sync();
+        dead = factor_block(diag, vbuf[0], lane, r);
+    }
     __syncthreads();
-    for (int c = 0; c < r; ++c) {
-        const double piv = g[c * rp + c];
-        const bool dead = !(piv > 1e-12);
-        const double inv = dead ? 0.0 : 1.0 / sqrt(piv);
-        __syncthreads();  // everyone has read the pivot
-        if (tid == 0) dinv[c] = inv;
-        for (int j = c + tid; j < r; j += nt) g[c * rp + j] *= inv;  // dead: whole row -> 0
+    for (int k = 0; k < nb; ++k) {
+        const double *vk = vbuf[k & 1];
+        double va[4];  // V as A operand
+#pragma unroll
+        for (int s = 0; s < 4; ++s) va[s] = vk[col * kVPitch + 4 * s + g];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            int I, J;
+            block_of(s, I, J);
+            if ((I == k) != (J == k) && (I == k || J == k)) {
+                f64x4_t x = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x = mfma64(va[q], t[s][q], x);
+                const int other = I == k ? J : I;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) panel[other][v][lane] = x[v];
+                if (I == k) {  // a final block of L^-1: W is its transpose, columns scaled
+                    t[s] = x;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        norm2 = fma(x[v], x[v], norm2);
+                        const int c = 16 * k + 4 * v + g, kk = 16 * J + col;
+                        if (c < r) w[(int64_t)kk * r + c] = dscale[kk] * x[v];
+                    }
+                } else {
+                    t[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+                }
+            } else if (I == k) {  // (k, k): V itself
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const double x = vk[(4 * v + g) * kVPitch + col];
+                    panel[k][v][lane] = x;
+                    norm2 = fma(x, x, norm2);
+                    const int c = 16 * k + 4 * v + g, kk = 16 * k + col;
+                    if (c < r && kk < r) w[(int64_t)kk * r + c] = dscale[kk] * x;
+                }
+            }
+        }
         __syncthreads();
-        for (int i = c + 1 + ty; i < r; i += nty) {
-            const double gi = g[c * rp + i];
-            for (int j = c + 1 + tx; j < r; j += 16)
-                if (i <= j) g[i * rp + j] -= gi * g[c * rp + j];
+        if (k + 1 == nb) break;
+        auto update = [&](f64x4_t &acc, int I, int J) {
+            const int a = J > k ? J : I, b = J > k ? I : J;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc = mfma64(-panel[a][q][lane], panel[b][q][lane], acc);
+        };
+        bool owner = false;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+            if (id[s] == ((k + 1) << 8 | (k + 1))) {
+                update(t[s], k + 1, k + 1);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
+                owner = true;
+            }
+        if (owner) {
+            wave_sync();
+            dead |= factor_block(diag, vbuf[(k + 1) & 1], lane, r - 16 * (k + 1));
+        }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            int I, J;
+            block_of(s, I, J);
+            if (I > k && !(I == k + 1 && J == k + 1)) update(t[s], I, J);
         }
         __syncthreads();
     }
-    // W = R^-1 in place by back substitution, row by row from the bottom (R W = I: the columns
-    // of W are independent, and the rows below row i already hold W).  Row i of R is staged;
-    // thread (group, j) adds its share of sum_{l = i+1 .. j} R[i][l] W[l][j], the shares are added
-    // in a fixed order, and W[i][j] = -sum / R[i][i] (1 / R[i][i] on the diagonal, 0 for a dead
-    // row).  Every access to the matrix in the sum is a row read by consecutive threads.
-    const int parts = nt >> 8;  // 1 or 4 groups of 256 threads
-    const int jcol = tid & 255, grp = tid >> 8;
-    for (int i = r - 1; i >= 0; --i) {
-        for (int l = i + 1 + tid; l < r; l += nt) colbuf[l] = g[i * rp + l];
-        __syncthreads();
-        double s = 0.0;
-        if (jcol < r && jcol > i)
-            for (int l = i + 1 + grp; l <= jcol; l += parts)
-                s = fma(colbuf[l], g[l * rp + jcol], s);
-        if (parts > 1) {
-            psum[grp * 256 + jcol] = s;
-            __syncthreads();
-            if (grp == 0) s = ((psum[jcol] + psum[256 + jcol]) + psum[512 + jcol]) + psum[768 + jcol];
-        }
-        if (grp == 0 && jcol < r && jcol >= i) g[i * rp + jcol] = jcol == i ? dinv[i] : -dinv[i] * s;
-        __syncthreads();
+    if (round != 0) return;
+    // The orthogonality error of P W is about eps64 ||R^-1||^2 (the Gram sums are good to a few
+    // eps64 of the unit diagonal); a factor with a dead column always takes the second round.
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) norm2 += __shfl_xor(norm2, off, 64);
+    if (lane == 0) {
+        red[wave] = norm2;
+        if (dead) any_dead = 1;
     }
-    for (int x = tid; x < r * r; x += nt) {
-        const int k = x / r, j = x % r;
-        w[x] = k <= j ? dscale[k] * g[k * rp + j] : 0.0;
+    __syncthreads();
+    if (tid == 0) {
+        double sum = 0.0;
+        for (int q = 0; q < nw; ++q) sum += red[q];
+        it.g[0] = any_dead == 0 && sum <= kOneRoundNorm ? kDone : 0.0;
     }
 }
 
-// P <- P W in place, fp64 accumulation.  Workgroup: 64 rows of P (= 64 consecutive elements of
-// every factor column) staged in LDS; W goes through LDS as well, 16 columns at a time (a
-// wavefront's reads of it are broadcasts; straight from memory every one was a round trip to
-// L2); thread (row, wave) produces 4 of the 16 columns.  W is upper triangular and stored with
-// zeros below the diagonal: column c needs rows k <= c only, and running k up to the last of the
-// thread's four columns adds exact zeros to the others.
-__global__ __launch_bounds__(kGT) void apply_w_kernel(FactorBatch batch) {
-    extern __shared__ float fl[];  // [r][64] floats, then [r][16] doubles of W
+// P <- P W in place, fp64 accumulation.  Workgroup: 64 consecutive elements of every factor column,
+// staged in LDS in fp32 (they are all read before the first is overwritten).  W is upper
+// triangular; a wavefront produces 16 columns at a time over the 64 elements: A = W^T (one double
+// per lane and step, 16 consecutive columns of four rows, straight from L2, four steps ahead),
+// B = P from LDS (16 bytes per lane: lane n holds elements 4 n .. 4 n + 3, element q feeds product
+// q), so one element of W serves four products.  The column blocks are dealt so that every
+// wavefront gets long and short ones.
+// Bound by the fp64 matrix cores: seven factors of a 100B-class layer at r = 256 (77824 rows,
+// 5.1 GFLOP) take 130 us (vector fp64 FMAs with W through LDS: 598 us).
+__global__ __launch_bounds__(kGT) void apply_w_kernel(FactorBatch batch, int round) {
+    extern __shared__ __attribute__((aligned(16))) float fl[];  // [16 nb][64]
     const FactorItem it = batch.it[blockIdx.y];
-    float *__restrict__ p = it.f;
-    const double *__restrict__ w = it.w;
     const int64_t L = it.L;
-    const int r = it.r;
     const int64_t i0 = (int64_t)blockIdx.x * 64;
     if (i0 >= L) return;
-    for (int idx = threadIdx.x; idx < r * 16; idx += kGT) {
+    if (second_round_idle(it, round)) return;
+    float *__restrict__ p = it.f;
+    const double *__restrict__ w = it.w;
+    const int r = it.r, nb = (r + 15) >> 4;
+    for (int idx = threadIdx.x; idx < nb * 256; idx += kGT) {
         const int c = idx >> 4, c4 = idx & 15;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i0 + c4 * 4 < L) v = *reinterpret_cast<const float4 *>(p + (int64_t)c * L + i0 + c4 * 4);
+        if (c < r && i0 + c4 * 4 < L)
+            v = *reinterpret_cast<const float4 *>(p + (int64_t)c * L + i0 + c4 * 4);
         *reinterpret_cast<float4 *>(fl + c * 64 + c4 * 4) = v;
     }
     __syncthreads();
-    const int row = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    double *wl = reinterpret_cast<double *>(fl + (size_t)r * 64);
-    for (int c0 = 0; c0 < r; c0 += 16) {
-        const int kmax = c0 + 15 < r ? c0 + 15 : r - 1;
-        for (int idx = threadIdx.x; idx < (kmax + 1) * 16; idx += kGT) {
-            const int k = idx >> 4, ci = idx & 15;
-            wl[idx] = c0 + ci < r ? w[k * r + c0 + ci] : 0.0;
-        }
-        __syncthreads();
-        const int cw = c0 + wave * 4;  // this wavefront's four columns
-        if (cw < r) {
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            const int kend = cw + 3 < r ? cw + 3 : r - 1;
-            // eight k at a time, their LDS reads requested before the first product (one
-            // wavefront per SIMD here, nothing else hides the LDS latency: 4.1 -> 2.3 ms for
-            // twelve 28672 x 256 factors); the sums keep their order.  (W read through the
-            // scalar cache instead of as broadcast LDS reads: 4.9 ms.)
-            int k = 0;
-            for (; k + 8 <= kend + 1; k += 8) {
-                float f[8];
-                double wv[8][4];
+    const int g = lane >> 4, n = lane & 15;
+    for (int u = 0; 4 * u < nb; ++u) {
+        // blocks w, 7 - w, 8 + w, 15 - w: the work of a block grows with its index
+        const int cb = 4 * u + ((u & 1) ? 3 - wave : wave);
+        if (cb >= nb) continue;
+        const int c = cb * 16 + n;  // A: column of W (any valid one past r, not stored)
+        const double *wc = w + (c < r ? c : r - 1);
+        auto load_w = [&](double (&dst)[4], int kb) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    f[u] = fl[(k + u) * 64 + row];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) wv[u][i] = wl[(k + u) * 16 + wave * 4 + i];
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] = fma((double)f[u], wv[u][i], acc[i]);
+            for (int s = 0; s < 4; ++s) {
+                const int k = kb * 16 + 4 * s + g;
+                dst[s] = wc[(int64_t)(k < r ? k : r - 1) * r];
             }
-            for (; k <= kend; ++k) {
-                const double f = (double)fl[k * 64 + row];
+        };
+        f64x4_t acc[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = fma(f, wl[k * 16 + wave * 4 + i], acc[i]);
+        for (int q = 0; q < 4; ++q) acc[q] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+        double a[4];
+        load_w(a, 0);
+        for (int kb = 0; kb <= cb; ++kb) {
+            double an[4];
+            load_w(an, kb < cb ? kb + 1 : cb);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float4 b = *reinterpret_cast<const float4 *>(fl + (kb * 16 + 4 * s + g) * 64 + n * 4);
+                acc[0] = mfma64(a[s], (double)b.x, acc[0]);
+                acc[1] = mfma64(a[s], (double)b.y, acc[1]);
+                acc[2] = mfma64(a[s], (double)b.z, acc[2]);
+                acc[3] = mfma64(a[s], (double)b.w, acc[3]);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (cw + i < r && i0 + row < L) p[(int64_t)(cw + i) * L + i0 + row] = (float)acc[i];
+            for (int s = 0; s < 4; ++s) a[s] = an[s];
         }
-        __syncthreads();  // the tile of W is free again
+        if (i0 + n * 4 < L) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int oc = cb * 16 + 4 * v + g;
+                if (oc < r)
+                    *reinterpret_cast<float4 *>(p + (int64_t)oc * L + i0 + n * 4) =
+                        make_float4((float)acc[0][v], (float)acc[1][v], (float)acc[2][v],
+                                    (float)acc[3][v]);
+            }
+        }
     }
 }
 
@@ -285,40 +500,39 @@ size_t orth_workspace_bytes(int64_t L, int r) {
                  sizeof(double));
 }
 
-static int cholqr_pass(const FactorBatch &batch, hipStream_t st) {
+static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
     FactorBatch summed;  // the same factors with their Gram sums in one chunk
-    int rc = launch_gram_partials_batch(batch, &summed, st);
+    int rc = launch_gram_partials_batch(batch, &summed, round, st);
     if (rc != DLCX_OK) return rc;
-    size_t g_bytes = 0, a_bytes = 0;
+    int max_nb = 1;
     int64_t max_rows = 1;
     for (int i = 0; i < batch.n; ++i) {
-        const size_t r = (size_t)batch.it[i].r;
-        const size_t gb = r * (r + 1) * sizeof(double);
-        if (gb <= kCholLdsMax && gb > g_bytes) g_bytes = gb;
-        const size_t ab = r * 64 * sizeof(float) + r * 16 * sizeof(double);
-        if (ab > a_bytes) a_bytes = ab;
+        const int nb = (batch.it[i].r + 15) / 16;
+        if (nb > max_nb) max_nb = nb;
         if (ceil_div(batch.it[i].L, 64) > max_rows) max_rows = ceil_div(batch.it[i].L, 64);
     }
-    static size_t chol_granted = 0, apply_granted = 0;
-    rc = grant_dynamic_lds(reinterpret_cast<const void *>(chol_inverse_kernel), g_bytes, &chol_granted,
-                       "chol_inverse attribute");
-    if (rc != DLCX_OK) return rc;
     {
+        // accumulator blocks per wavefront: 2 up to r = 80, 6 up to r = 144, else 17
         Timed timed(KID_CHOL, st);
-        bool large = false;
-        for (int i = 0; i < batch.n; ++i)
-            large = large || (size_t)batch.it[i].r * (batch.it[i].r + 1) * sizeof(double) > kCholLdsMax;
-        hipLaunchKernelGGL(chol_inverse_kernel, dim3((unsigned)batch.n),
-                           dim3(large ? kCTLarge : kCT), g_bytes, st, summed);
+        const int blocks = max_nb * (max_nb + 1) / 2, waves = kCT / 64;
+        const dim3 grid((unsigned)batch.n), threads((unsigned)(blocks < waves ? blocks : waves) * 64);
+        if (blocks <= 2 * waves)
+            hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
+        else if (blocks <= 6 * waves)
+            hipLaunchKernelGGL(chol_inverse_kernel<6>, grid, threads, 0, st, summed, round);
+        else
+            hipLaunchKernelGGL(chol_inverse_kernel<17>, grid, threads, 0, st, summed, round);
         rc = check_launch("chol_inverse");
     }
     if (rc != DLCX_OK) return rc;
+    const size_t a_bytes = (size_t)max_nb * 16 * 64 * sizeof(float);
+    static size_t apply_granted = 0;
     rc = grant_dynamic_lds(reinterpret_cast<const void *>(apply_w_kernel), a_bytes, &apply_granted,
                        "apply_w attribute");
     if (rc != DLCX_OK) return rc;
     Timed timed(KID_APPLY_W, st);
     hipLaunchKernelGGL(apply_w_kernel, dim3((unsigned)max_rows, (unsigned)batch.n), dim3(kGT),
-                       a_bytes, st, batch);
+                       a_bytes, st, batch, round);
     return check_launch("apply_w");
 }
 
@@ -336,9 +550,9 @@ void orth_item(FactorItem *it, float *p, int64_t L, int r, void *workspace) {
 
 int launch_orthonormalize_batch(const FactorBatch &batch, hipStream_t st) {
     if (batch.n == 0) return DLCX_OK;
-    int rc = cholqr_pass(batch, st);
+    int rc = cholqr_round(batch, 0, st);
     if (rc != DLCX_OK) return rc;
-    return cholqr_pass(batch, st);
+    return cholqr_round(batch, 1, st);
 }
 
 int launch_orthonormalize(int64_t L, int r, float *p_inout, void *workspace, hipStream_t st) {

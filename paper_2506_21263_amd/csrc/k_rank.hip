@@ -266,7 +266,7 @@ void effrank_item(FactorItem *it, const float *q_bar, int64_t L, int r, int32_t 
 int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_t st) {
     if (batch.n == 0) return DLCX_OK;
     FactorBatch summed;  // the same factors with their Gram sums in one chunk
-    int rc = launch_gram_partials_batch(batch, &summed, st);
+    int rc = launch_gram_partials_batch(batch, &summed, 0, st);
     if (rc != DLCX_OK) return rc;
     size_t bytes = 0;
     for (int i = 0; i < batch.n; ++i) {

@@ -312,6 +312,27 @@ def test_orthonormalize_matches_oracle(L, r):
     assert rel_l2(got, want) <= max(1e-5, 4e-7 * cond), cond
 
 
+@pytest.mark.parametrize("L,r", [(16, 16), (32, 17), (528, 15), (1040, 32), (2064, 33), (512, 80),
+                                  (656, 81), (1536, 144), (1040, 145), (1024, 255), (272, 256)])
+@pytest.mark.parametrize("cond", [3.0, 1e5])
+def test_orthonormalize_block_edges_both_rounds(L, r, cond):
+    # Ranks around the edges of the 16 x 16 blocks and of the launch shapes, lengths around those
+    # of the 512-element sums and 64-element tiles.  cond 3: the first round is enough and the
+    # second returns at once; cond 1e5: both run.  All sums are in 64 bits, so what is left is the
+    # rounding to fp32 after each round: 2^-24 of every element, at most 2 x 2^-24 in norm, times
+    # the 1 + cond 2^-53 ... of the 64-bit steps; twice that is allowed.
+    g = rng(L * 7 + r)
+    U = synth.orthonormal_columns(g, L, r)
+    W = synth.orthonormal_columns(g, r, r)
+    A = np.ascontiguousarray(((U * np.logspace(0, -np.log10(cond), r)) @ W.T).T.astype(np.float32))
+    q, t = np.linalg.qr(A.T.astype(np.float64))
+    want = (q * np.sign(np.diag(t))).T
+    d_A = to_dev(A)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    dlcx.dlcx_orthonormalize(L, r, d_A, ws)
+    assert rel_l2(to_np(d_A), want) <= 2.4e-7
+
+
 def test_orthonormalize_degenerate_columns():
     L, r = 256, 6
     g = rng(3)
