@@ -1,249 +1,444 @@
 // r' of Alg. 3 for one matrix: the smallest k whose k largest eigenvalues of S = Q_bar^T Q_bar
 // hold at least tau of the trace (with P_hat orthonormal these are the squared singular values of
 // the decompressed average).  S is accumulated in fp64 (same partial-sum kernel as the
-// orthonormalisation).  One workgroup per matrix finds its eigenvalues, all in fp64:
-//   r  < 32:  one-sided Jacobi iteration on the columns of S in LDS (S is symmetric positive
-//             semi-definite, so the column norms at convergence are the eigenvalues) with a
-//             round-robin pair schedule;
-//   r >= 32:  Householder reduction to tridiagonal form (each step one symmetric matrix-vector
-//             product and one rank-2 update of the trailing block; S in LDS up to r = 128, in
-//             global memory / L2 above), then every eigenvalue by bisection on the Sturm
-//             sequence, one thread each.  (Measured per batch of 12: r = 64 1.56 -> 0.55 ms,
-//             r = 128 9.6 -> 1.6 ms against the Jacobi route; r = 16 the same.)
-// Then sort, prefix sum and count.
+// orthonormalisation).  Everything after it is fp64 too:
+//   tridiag_kernel       Householder reduction to tridiagonal form, one workgroup per matrix
+//   eigenvalues          every eigenvalue by multisection on the Sturm sequence: G lanes evaluate
+//                        G points of an interval at once, so a round narrows it G + 1 times
+//   count                prefix sum over the eigenvalues (they come out in order) and count
+// Up to rank 64 the last two follow in the same workgroup; above, eigenvalues_kernel spreads them
+// over the GPU (one wavefront per eigenvalue) and count_kernel finishes.
+#include <type_traits>
+
 #include "common.h"
 
 namespace dlcx {
 
-constexpr int kJT = 1024;       // at most 64 teams of 16 lanes, one column pair per team
-constexpr int kMaxSweeps = 40;
+constexpr int kTT = 256;             // threads of the tridiagonal reduction
+constexpr int kFusedRank = 64;       // ranks up to here finish in the same workgroup
 
-__device__ __forceinline__ double team_sum(double v) {
+// the fp64 value of the lane that DPP control `kCtrl` pairs this lane with (inside rows of 16)
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor15 = 0x140;
+
+__device__ __forceinline__ double from_halves(uint32_t lo, uint32_t hi) {
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// sum of a over both halves of the wavefront in lanes 0 - 31, of b in lanes 32 - 63
+__device__ __forceinline__ double add_halves(double a, double b) {
+    const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)ua, (uint32_t)ub, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+    return from_halves(lo[0], hi[0]) + from_halves(lo[1], hi[1]);
+}
+// sum of a over a pair of rows of 16 lanes in the even row, of b in the odd row
+__device__ __forceinline__ double add_rows(double a, double b) {
+    const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+    return from_halves(lo[0], hi[0]) + from_halves(lo[1], hi[1]);
+}
+// sum over the wavefront, in every lane
+__device__ __forceinline__ double wave_sum(double x) {
+    x += dpp<kXor1>(x);
+    x += dpp<kXor2>(x);
+    x += dpp<kXor7>(x);
+    x += dpp<kXor15>(x);
+    x = add_rows(x, x);
+    return add_halves(x, x);
+}
+
+// N sums over the 16 lanes of a row at once (N = 4, 8 or 16): the lanes halve the values among
+// themselves as they add, lane t ends up with the sum of value t * N / 16.
+template <int kCtrl, int M, int N>
+__device__ __forceinline__ void halve(double (&v)[N], bool up) {
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 16);
-    return v;
+    for (int i = 0; i < M; ++i) {
+        const double keep = up ? v[i + M] : v[i], send = up ? v[i] : v[i + M];
+        v[i] = keep + dpp<kCtrl>(send);
+    }
+}
+template <int N>
+__device__ __forceinline__ double row_sums(double (&v)[N], int t) {
+    halve<kXor15, N / 2>(v, t & 8);
+    halve<kXor7, N / 4>(v, t & 4);
+    if constexpr (N >= 8) halve<kXor2, N / 8>(v, t & 2);
+    else v[0] += dpp<kXor2>(v[0]);
+    if constexpr (N >= 16) halve<kXor1, 1>(v, t & 1);
+    else v[0] += dpp<kXor1>(v[0]);
+    return v[0];
 }
 
-constexpr size_t kJacobiLdsMax = 128 * 1024;
-constexpr int kTriMinRank = 32;  // from here on the tridiagonal route is the faster one
+// f(0), f(1), .. f(N - 1) with the index as a compile-time constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        unrolled<N, I + 1>(f);
+    }
+}
 
-// Sum of one value per thread over the workgroup, in a fixed order; every thread gets it.
-__device__ __forceinline__ double block_sum(double v, double *red, int nthreads) {
+// The tridiagonal matrix as the Sturm sequence reads it: t[i] = (d_i, -e_i^2), e_i between i - 1
+// and i, scaled to magnitudes of at most one.
+__device__ __forceinline__ double2 sturm_term(double d, double e) {
+    // an off-diagonal below 2^-60 of the scale counts as that: p_i = 0 with e = 0 would end the
+    // sequence, and 2^-60 moves no eigenvalue by more than the arithmetic does
+    return make_double2(d, -fmax(e * e, 0x1p-120));
+}
+
+// The table is filled up to whole blocks of 16 terms, and one half block more is read, never used:
+// diagonal elements above every x, coupled to nothing, which add no sign change.
+constexpr int kSturmPad = 24;
+__device__ __forceinline__ int sturm_blocks(int r) { return (r + 15) >> 4; }
+__device__ __forceinline__ double2 sturm_fill() { return make_double2(4.0, 0.0); }
+
+// Number of eigenvalues below x: sign changes of p_i = (d_i - x) p_{i-1} - e_i^2 p_{i-2}, where the
+// quotients p_i / p_{i-1} would need a division per term.  The sign bits are collected and compared
+// 16 at a time; every eight terms the pair is scaled back (a term is at most 5 x the larger of the
+// two before it and, over two steps, at least 2^-120 x, so nothing overflows or vanishes between).
+// Eight terms are read while the eight before are worked on.
+__device__ __forceinline__ int count_below(const double2 *t, int blocks, double x) {
+    double p0 = 0.0, p1 = 1.0;  // t[0].y multiplies p0
+    uint32_t signs = 0;
+    int cnt = 0;
+    double2 even[8], odd[8];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    __syncthreads();  // earlier readers of red are done
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int w = 0; w < nthreads / 64; ++w) s += red[w];
-    return s;
+    for (int u = 0; u < 8; ++u) even[u] = t[u];
+    auto eight = [&](const double2 (&c)[8]) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double p = fma(c[u].x - x, p1, c[u].y * p0);
+            signs = __builtin_amdgcn_alignbit(signs, (uint32_t)((uint64_t)__double_as_longlong(p) >> 32), 31);
+            p0 = p1;
+            p1 = p;
+        }
+        const int ex = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+        p0 = ldexp(p0, ex);
+        p1 = ldexp(p1, ex);
+    };
+    for (int i = 0; i < blocks; ++i) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) odd[u] = t[16 * i + 8 + u];
+        __builtin_amdgcn_sched_barrier(0);
+        eight(even);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) even[u] = t[16 * i + 16 + u];
+        __builtin_amdgcn_sched_barrier(0);
+        eight(odd);
+        cnt += __popc((signs ^ (signs >> 1)) & 0xffffu);  // the 16 newest against those before them
+    }
+    return cnt;
 }
 
-// Eigenvalues of the symmetric r x r matrix a (column-major, leading dimension ld, both halves
-// stored, in LDS or global memory), descending, negative ones clamped to zero, into out[0..r).
-// d, e, v, w: r doubles each; psum: (nthreads / 256) * 256 doubles; red: 16 doubles (all LDS).
-__device__ void tridiagonal_eigenvalues(double *a, int r, int ld, double *d, double *e, double *v,
-                                        double *w, double *psum, double *red, double *out,
-                                        int nthreads) {
-    const int tid = threadIdx.x;
-    const int parts = nthreads / 256;
-    for (int k = 0; k + 2 < r; ++k) {
-        const int L = r - k - 1;
-        double *x = a + (int64_t)k * ld + k + 1;  // column k below the diagonal
-        const double xt = tid < L ? x[tid] : 0.0;
-        const double sumsq = block_sum(xt * xt, red, nthreads);
-        const double x0 = x[0];
-        const double tail = sumsq - x0 * x0;
-        if (tid == 0) d[k] = a[(int64_t)k * ld + k];
-        if (!(tail > 0.0)) {  // already tridiagonal in this column: no reflection
-            if (tid == 0) e[k] = x0;
-            __syncthreads();
-            continue;
-        }
-        const double alpha = -copysign(sqrt(sumsq), x0);
-        const double v0 = x0 - alpha;
-        const double beta = 2.0 / (tail + v0 * v0);
-        if (tid < L) v[tid] = tid == 0 ? v0 : xt;
-        if (tid == 0) e[k] = alpha;
-        __syncthreads();
-        // p = beta * A22 v: thread (part, i) sums its quarter of the columns of row i
-        double *a22 = a + (int64_t)(k + 1) * ld + k + 1;
-        {
-            const int i = tid & 255, part = tid >> 8;
-            const int per = (L + parts - 1) / parts;
-            const int j0 = part * per, j1 = j0 + per < L ? j0 + per : L;
-            double acc = 0.0;
-            if (i < L)
-                for (int j = j0; j < j1; ++j) acc = fma(a22[(int64_t)j * ld + i], v[j], acc);
-            psum[part * 256 + i] = acc;
-        }
-        __syncthreads();
-        double pi = 0.0;
-        if (tid < L) {
-            for (int q = 0; q < parts; ++q) pi += psum[q * 256 + tid];
-            pi *= beta;
-        }
-        const double vp = block_sum(tid < L ? v[tid] * pi : 0.0, red, nthreads);
-        const double kk = 0.5 * beta * vp;
-        if (tid < L) w[tid] = pi - kk * v[tid];
-        __syncthreads();
-        // A22 <- A22 - v w^T - w v^T
-        for (int idx = tid; idx < L * L; idx += nthreads) {
-            const int i = idx % L, j = idx / L;
-            double *p = a22 + (int64_t)j * ld + i;
-            *p = *p - (v[i] * w[j] + w[i] * v[j]);
-        }
-        __threadfence_block();
-        __syncthreads();
+// The c-th largest eigenvalue (c from 0) by groups of G lanes, every lane of the wavefront calling;
+// lo, hi: an interval with all eigenvalues, narrowed to 2^-48 of its width, which is about the error
+// the reduction to tridiagonal form leaves (r 2^-53).
+template <int G>
+__device__ __forceinline__ double nth_largest(const double2 *t, int r, int c, double lo, double hi,
+                                              int lane) {
+    constexpr int kRounds = G == 64 ? 8 : G == 32 ? 10 : G == 16 ? 12 : G == 8 ? 16 : 21;
+    const int below = r - 1 - c;  // eigenvalues smaller than the one wanted
+    const int sub = lane & (G - 1), base = lane - sub;
+    constexpr uint64_t mask = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
+    for (int itn = 0; itn < kRounds; ++itn) {
+        const double step = (hi - lo) * (1.0 / (double)(G + 1));
+        const double x = fma((double)(sub + 1), step, lo);
+        const bool above = count_below(t, sturm_blocks(r), x) > below;  // x is above the eigenvalue
+        const uint64_t m = (__ballot(above) >> base) & mask;
+        const int first = m ? __builtin_ctzll(m) : G;  // points 0 .. first - 1 are not
+        const double nlo = first > 0 ? fma((double)first, step, lo) : lo;
+        const double nhi = first < G ? fma((double)(first + 1), step, lo) : hi;
+        lo = nlo;
+        hi = nhi;
     }
-    if (tid == 0) {
-        if (r >= 2) {
-            d[r - 2] = a[(int64_t)(r - 2) * ld + r - 2];
-            e[r - 2] = a[(int64_t)(r - 2) * ld + r - 1];
-        }
-        d[r - 1] = a[(int64_t)(r - 1) * ld + r - 1];
-    }
-    __syncthreads();
-    // Gershgorin interval, then the c-th largest eigenvalue by bisection: the number of negative
-    // terms of the Sturm sequence at x is the number of eigenvalues below x
-    double lo0 = d[0], hi0 = d[0];
-    for (int i = 0; i < r; ++i) {
-        const double rad = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < r ? fabs(e[i]) : 0.0);
-        lo0 = fmin(lo0, d[i] - rad);
-        hi0 = fmax(hi0, d[i] + rad);
-    }
-    for (int c = tid; c < r; c += nthreads) {
-        const int below = r - 1 - c;  // eigenvalues smaller than the one wanted
-        double lo = lo0, hi = hi0;
-        for (int itn = 0; itn < 200; ++itn) {
-            const double mid = 0.5 * (lo + hi);
-            if (!(mid > lo && mid < hi)) break;
-            int cnt = 0;
-            double q = d[0] - mid;
-            cnt += q < 0.0;
-            for (int i = 1; i < r; ++i) {
-                if (fabs(q) < 1e-300) q = -1e-300;
-                q = d[i] - mid - e[i - 1] * e[i - 1] / q;
-                cnt += q < 0.0;
-            }
-            if (cnt > below) hi = mid;
-            else lo = mid;
-        }
-        out[c] = fmax(0.5 * (lo + hi), 0.0);
-    }
-    __syncthreads();
+    return fmax(0.5 * (lo + hi), 0.0);
 }
 
-__global__ __launch_bounds__(kJT) void jacobi_rank_kernel(FactorBatch batch, double tau) {
-    const int nthreads = blockDim.x;  // 256 .. 1024: one team of 16 lanes per column pair
-    extern __shared__ double smem[];
+// smallest k whose k largest of the descending values hold at least tau of their sum (0: all zero),
+// by one wavefront, four values a lane
+__device__ __forceinline__ int32_t count_share(const double *eig, int r, double tau, int lane) {
+    double cum[4], sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int c = 4 * lane + q;
+        sum += c < r ? eig[c] : 0.0;
+        cum[q] = sum;
+    }
+    double incl = sum;  // over this lane and those before it
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double v = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += v;
+    }
+    const double before = incl - sum, total = __shfl(incl, 63, 64);
+    int32_t k = r;
+#pragma unroll
+    for (int q = 3; q >= 0; --q)
+        if ((q < 3 ? before + cum[q] : incl) >= tau * total) k = 4 * lane + q + 1;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) k = min(k, __shfl_xor(k, off, 64));
+    return total > 0.0 ? min(k, r) : 0;
+}
+
+// What tridiag_kernel leaves in FactorItem::g above rank 64: (d_i, e_i^2) scaled, from double 0;
+// then lo, hi; then the eigenvalues (still scaled: r' does not depend on a power of two).
+__device__ __forceinline__ double2 *tri_of(const FactorItem &it) { return reinterpret_cast<double2 *>(it.g); }
+__device__ __forceinline__ double *bounds_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK; }
+__device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK + 8; }
+
+// Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
+// S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (ti, tj) holds element
+// (ti, tj) of every tile.  An off-diagonal tile serves S v twice, along its rows and its columns.
+// Per step k, with v and beta of row k in LDS:
+//   S v         row parts added over the 16 lanes of tj, column parts over ti: four rows of lanes
+//               in a wavefront and the four wavefronts (LDS)                        | barrier
+//   p = S v, v . p   one entry per thread                                           | barrier
+//   S -= v w^T + w v^T  with w = beta p - (beta^2 v.p / 2) v; the 16 lanes that hold row k + 1, in
+//               the first tile row still in use, turn it into the next v and beta   | barrier
+// Rows that are done have zeros in v and w; tile rows that are done are skipped.  What counts is
+// the number of instructions: four wavefronts, one per SIMD, so that nothing is done twice on a
+// SIMD (eight wavefronts that each formed v and beta for themselves took 1.45 us a step at r = 64,
+// this form
+// 1.05 us), and the registers of a whole SIMD for one wavefront (136 tiles at r = 256 are 272
+// of its 512; with eight wavefronts spilled registers made 16 us a step,
+// now 3.0).  Seven factors at r = 256: 784 us, and the eigenvalues 54 us after it (one thread per
+// eigenvalue and a division per term, after a reduction that walked S in L2: 4400 us together);
+// r = 32 whole: 50 us (246), r = 64: 89 us (510).
+template <int NT>
+__global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, double tau) {
+    constexpr int RS = NT <= 4 ? 4 : NT <= 8 ? 8 : 16;
+    constexpr int CG = NT / 4;              // column sums per lane after four rows of lanes are added
+    constexpr int R = 16 * NT;
+    __shared__ double vrow[2][R];           // v of row k, zeros up to the diagonal
+    __shared__ double betas[2];             // 0: the row is tridiagonal already
+    __shared__ double rowpart[R];
+    __shared__ double colpart[4][R];
+    __shared__ double pbuf[R];
+    __shared__ double red[4];
+    __shared__ double2 tri[R + kSturmPad];  // d_k and the off-diagonal element before it
+    __shared__ double eig[kFusedRank];
     const FactorItem it = batch.it[blockIdx.x];
     const int r = it.r, nchunks = it.nchunks;
     const double *__restrict__ part = it.part;
-    int32_t *__restrict__ rprime_out = it.out;
-    const int re = (r + 1) & ~1;                     // even number of columns (pad with zeros)
-    const bool a_in_lds = (size_t)re * re * sizeof(double) <= kJacobiLdsMax;
-    double *a = a_in_lds ? smem : it.g;              // column-major re x re: a[col * re + row]
-    __shared__ double eig[DLCX_MAX_RANK];
-    __shared__ double sorted[DLCX_MAX_RANK];
-    __shared__ double tri_e[DLCX_MAX_RANK], tri_v[DLCX_MAX_RANK], tri_w[DLCX_MAX_RANK];
-    __shared__ double tri_psum[(kJT / 256) * 256], tri_red[kJT / 64];
-    __shared__ int rotated;
-    const int tid = threadIdx.x;
-    for (int x = tid; x < re * re; x += nthreads) {
-        const int col = x / re, row = x % re;
-        double s = 0.0;
-        if (col < r && row < r) {
-            const int lo = row < col ? row : col, hi = row < col ? col : row;
-            for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * r * r + lo * r + hi];
-        }
-        a[x] = s;
-    }
-    __syncthreads();
-    const int team = tid >> 4, lane = tid & 15;
-    const int npairs = re / 2;
-    const bool tri = !a_in_lds || r >= kTriMinRank;
-    if (tri) {
-        __threadfence_block();
-        tridiagonal_eigenvalues(a, r, re, eig, tri_e, tri_v, tri_w, tri_psum, tri_red, sorted,
-                                nthreads);
-    }
-    for (int sweep = 0; !tri && sweep < kMaxSweeps; ++sweep) {
-        if (tid == 0) rotated = 0;
-        __syncthreads();
-        for (int step = 0; step < re - 1; ++step) {
-            for (int pr = team; pr < npairs; pr += nthreads / 16) {
-                // round-robin tournament: pair 0 is (re-1, step); pair k is
-                // ((step + k) mod (re-1), (step - k) mod (re-1))
-                int p, q;
-                if (pr == 0) {
-                    p = re - 1;
-                    q = step;
-                } else {
-                    p = (step + pr) % (re - 1);
-                    q = (step - pr + (re - 1)) % (re - 1);
-                }
-                double *cp = a + p * re, *cq = a + q * re;
-                double alpha = 0.0, beta = 0.0, gamma = 0.0;
-                for (int i = lane; i < re; i += 16) {
-                    const double x = cp[i], y = cq[i];
-                    alpha = fma(x, x, alpha);
-                    beta = fma(y, y, beta);
-                    gamma = fma(x, y, gamma);
-                }
-                alpha = team_sum(alpha);
-                beta = team_sum(beta);
-                gamma = team_sum(gamma);
-                if (gamma * gamma > 1e-26 * alpha * beta) {
-                    const double zeta = (beta - alpha) / (2.0 * gamma);
-                    const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    const double cs = 1.0 / sqrt(1.0 + t * t), sn = cs * t;
-                    for (int i = lane; i < re; i += 16) {
-                        const double x = cp[i], y = cq[i];
-                        cp[i] = cs * x - sn * y;
-                        cq[i] = sn * x + cs * y;
-                    }
-                    if (lane == 0) rotated = 1;
-                }
-            }
-            __syncthreads();
-        }
-        const int any = rotated;
-        __syncthreads();
-        if (!any) break;
-    }
-    if (!tri) {
-        for (int c = tid; c < r; c += nthreads) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tj = lane & 15, g = lane >> 4, ti = wave * 4 + g;
+    const int64_t rr = (int64_t)r * r;
+
+    double t[NT][NT];  // t[x][y], x <= y
+#pragma unroll
+    for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int y = x; y < NT; ++y) {
+            const int a = 16 * x + ti, b = 16 * y + tj;
             double s = 0.0;
-            for (int i = 0; i < re; ++i) s = fma(a[c * re + i], a[c * re + i], s);
-            eig[c] = sqrt(s);
-        }
-        __syncthreads();
-        for (int c = tid; c < r; c += nthreads) {  // rank sort, descending, ties by index
-            const double e = eig[c];
-            int pos = 0;
-            for (int u = 0; u < r; ++u) pos += (eig[u] > e) || (eig[u] == e && u < c);
-            sorted[pos] = e;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        double total = 0.0;
-        for (int c = 0; c < r; ++c) total += sorted[c];
-        int rp = 0;
-        if (total > 0.0) {
-            double cum = 0.0;
-            rp = r;
-            for (int c = 0; c < r; ++c) {
-                cum += sorted[c];
-                if (cum >= tau * total) {
-                    rp = c + 1;
-                    break;
-                }
+            if (a < r && b < r) {
+                const double *src = part + (int64_t)(a < b ? a : b) * r + (a < b ? b : a);
+                for (int c = 0; c < nchunks; ++c) s += src[c * rr];
             }
+            t[x][y] = s;
         }
-        *rprime_out = rp;
+    // Row `row`, whose tile row is x: its v, beta and elements of the result, by the lanes that
+    // hold it.  With s = |row right of the diagonal|^2, alpha = -+sqrt(s): v_0 = x_0 - alpha and
+    // beta = 2 / |v|^2 = 1 / (s + |x_0| sqrt(s)).
+    auto publish = [&](auto xc, int row, int buf) {
+        constexpr int x = decltype(xc)::value;
+        if (((row & 15) >> 2) != wave || g != (row & 3)) return;
+        const int d = row - 16 * x;  // the diagonal in tile column x
+        double *dst = &vrow[buf][tj];
+        double tail = 0.0;           // beyond the first element right of the diagonal
+        if (tj > d + 1) tail = t[x][x] * t[x][x];
+        double x0 = t[x][x];
+        int at = d + 1;
+        if constexpr (x + 1 < NT) {
+            const double e = t[x][x + 1];
+            if (d < 15 || tj > 0) tail = fma(e, e, tail);
+            if (d == 15) {
+                x0 = e;
+                at = 0;
+            }
+#pragma unroll
+            for (int y = x + 2; y < NT; ++y) tail = fma(t[x][y], t[x][y], tail);
+        }
+        tail += dpp<kXor1>(tail);
+        tail += dpp<kXor2>(tail);
+        tail += dpp<kXor7>(tail);
+        tail += dpp<kXor15>(tail);
+        const uint64_t u = (uint64_t)__double_as_longlong(x0);
+        const int from = ((row & 3) * 16 + (at & 15)) * 4;
+        x0 = from_halves((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)u),
+                         (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(u >> 32)));
+        const double s = fma(x0, x0, tail);
+        double y = __builtin_amdgcn_rsq(s);  // two Newton steps each: full fp64
+        y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
+        y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
+        const double norm = s * y, den = fma(fabs(x0), norm, s);
+        double beta = __builtin_amdgcn_rcp(den);
+        beta = fma(fma(-den, beta, 1.0), beta, beta);
+        beta = fma(fma(-den, beta, 1.0), beta, beta);
+        // (below 2^-960 a tail is rounding of roundings: S comes from fp32 values, its entries are
+        // above 2^-300 or zero; and v_rsq_f64 needs a normal number)
+        const bool reflect = tail > 0x1p-960;
+        const double alpha = reflect ? -copysign(norm, x0) : x0, v0 = x0 - alpha;
+        if (tj == d) tri[row].x = t[x][x];
+        if (tj == 0) {
+            if (row + 1 < R) tri[row + 1].y = alpha;
+            betas[buf] = reflect ? beta : 0.0;
+        }
+#pragma unroll
+        for (int y2 = 0; y2 < x; ++y2) dst[16 * y2] = 0.0;
+        dst[16 * x] = tj > d + 1 ? t[x][x] : tj == d + 1 ? v0 : 0.0;
+        if constexpr (x + 1 < NT) {
+            dst[16 * (x + 1)] = d == 15 && tj == 0 ? v0 : t[x][x + 1];
+#pragma unroll
+            for (int y2 = x + 2; y2 < NT; ++y2) dst[16 * y2] = t[x][y2];
+        }
+    };
+    publish(std::integral_constant<int, 0>(), 0, 0);
+    __syncthreads();
+    for (int k = 0; k + 1 < r; ++k) {
+        const int cur = k & 1;
+        const double beta = betas[cur];  // 0, with v = 0: nothing happens to S
+        const int live = (k + 1) >> 4;   // tile rows and columns before it are done
+        double cv[NT], rv[NT];
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            cv[y] = vrow[cur][16 * y + tj];
+            rv[y] = vrow[cur][16 * y + ti];
+        }
+        {
+            double cp[NT], rp[RS];
+#pragma unroll
+            for (int y = 0; y < NT; ++y) cp[y] = 0.0;
+#pragma unroll
+            for (int x = 0; x < RS; ++x) rp[x] = 0.0;
+#pragma unroll
+            for (int x = 0; x < NT; ++x)
+                if (x >= live) {
+                    double s = t[x][x] * cv[x];
+#pragma unroll
+                    for (int y = x + 1; y < NT; ++y) {
+                        s = fma(t[x][y], cv[y], s);
+                        cp[y] = fma(t[x][y], rv[x], cp[y]);
+                    }
+                    rp[x] = s;
+                }
+            double cs[NT / 2];
+#pragma unroll
+            for (int y = 0; y < NT / 2; ++y) cs[y] = add_halves(cp[y], cp[y + NT / 2]);
+#pragma unroll
+            for (int y = 0; y < CG; ++y)
+                colpart[wave][16 * (CG * g + y) + tj] = add_rows(cs[y], cs[y + CG]);
+            const double rsum = row_sums<RS>(rp, tj);
+            if (tj % (16 / RS) == 0 && tj / (16 / RS) < NT) rowpart[16 * (tj / (16 / RS)) + ti] = rsum;
+        }
+        __syncthreads();
+        if (tid < R) {
+            double p = rowpart[tid] + ((colpart[0][tid] + colpart[1][tid]) + (colpart[2][tid] + colpart[3][tid]));
+            if (tid <= k) p = 0.0;  // rows that are done
+            pbuf[tid] = p;
+            const double dot = wave_sum(p * vrow[cur][tid]);
+            if (lane == 0) red[wave] = dot;
+        }
+        __syncthreads();
+        double vp = red[0];
+#pragma unroll
+        for (int w = 1; w < R / 64; ++w) vp += red[w];
+        const double kk = 0.5 * beta * (beta * vp);  // (beta^2 may overflow)
+        double cw[NT], rw[NT];
+#pragma unroll
+        for (int y = 0; y < NT; ++y) {
+            cw[y] = fma(beta, pbuf[16 * y + tj], -kk * cv[y]);
+            rw[y] = fma(beta, pbuf[16 * y + ti], -kk * rv[y]);
+        }
+        unrolled<NT>([&](auto xc) {
+            constexpr int x = decltype(xc)::value;
+            if (x < live) return;
+#pragma unroll
+            for (int y = x; y < NT; ++y) t[x][y] = fma(-rv[x], cw[y], fma(-rw[x], cv[y], t[x][y]));
+            if (x == live) publish(xc, k + 1, cur ^ 1);
+        });
+        __syncthreads();
     }
+    if (wave != 0 && r > kFusedRank) return;
+    // Gershgorin interval and scale: a power of two that puts every magnitude at one or below
+    double lo = tri[0].x, hi = lo;
+    for (int i = lane; i < r; i += 64) {
+        const double rad = (i > 0 ? fabs(tri[i].y) : 0.0) + (i + 1 < r ? fabs(tri[i + 1].y) : 0.0);
+        lo = fmin(lo, tri[i].x - rad);
+        hi = fmax(hi, tri[i].x + rad);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    const double big = fmax(fabs(lo), fabs(hi));
+    const int ex = big > 0.0 && big < 1e300 ? -__builtin_amdgcn_frexp_exp(big) : 0;
+    lo = ldexp(lo, ex);
+    hi = ldexp(hi, ex);
+    auto scaled = [&](int i) {
+        return sturm_term(ldexp(tri[i].x, ex), i > 0 ? ldexp(tri[i].y, ex) : 0.0);
+    };
+    if (r > kFusedRank) {  // wavefront 0
+        for (int i = lane; i < r; i += 64) tri_of(it)[i] = scaled(i);  // filled up by the reader
+        if (lane == 0) {
+            bounds_of(it)[0] = lo;
+            bounds_of(it)[1] = hi;
+        }
+        return;
+    }
+    __syncthreads();  // every wavefront has its interval
+    if (wave == 0 && tid < r) tri[tid] = scaled(tid);  // r <= 64
+    if (tid >= r && tid < 16 * sturm_blocks(r) + 8) tri[tid] = sturm_fill();
+    __syncthreads();
+    // as many lanes per eigenvalue as 256 threads have for r of them
+    auto find = [&](auto gc) {
+        constexpr int G = decltype(gc)::value;
+        const int c = tid / G;
+        const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, lo, hi, lane);
+        if (c < r && (lane & (G - 1)) == 0) eig[c] = ev;
+    };
+    if (r <= 4) find(std::integral_constant<int, 64>());
+    else if (r <= 8) find(std::integral_constant<int, 32>());
+    else if (r <= 16) find(std::integral_constant<int, 16>());
+    else if (r <= 32) find(std::integral_constant<int, 8>());
+    else find(std::integral_constant<int, 4>());
+    __syncthreads();
+    if (wave == 0) {
+        const int32_t k = count_share(eig, r, tau, lane);
+        if (lane == 0) *it.out = k;
+    }
+}
+
+// Ranks above kFusedRank: one wavefront per eigenvalue, 64 points a round.
+__global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
+    __shared__ double2 tri[DLCX_MAX_RANK + kSturmPad];
+    const FactorItem it = batch.it[blockIdx.y];
+    const int r = it.r;
+    if (r <= kFusedRank || (int)blockIdx.x * 4 >= r) return;
+    for (int i = threadIdx.x; i < 16 * sturm_blocks(r) + 8; i += 256)
+        tri[i] = i < r ? tri_of(it)[i] : sturm_fill();
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (c >= r) return;
+    const double ev = nth_largest<64>(tri, r, c, bounds_of(it)[0], bounds_of(it)[1], lane);
+    if (lane == 0) eig_of(it)[c] = ev;
+}
+
+__global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {
+    const FactorItem it = batch.it[blockIdx.x];
+    if (it.r <= kFusedRank) return;
+    const int32_t k = count_share(eig_of(it), it.r, tau, threadIdx.x);
+    if (threadIdx.x == 0) *it.out = k;
 }
 
 size_t effrank_workspace_bytes(int64_t L, int r) {
@@ -265,29 +460,27 @@ void effrank_item(FactorItem *it, const float *q_bar, int64_t L, int r, int32_t 
 
 int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_t st) {
     if (batch.n == 0) return DLCX_OK;
-    FactorBatch summed;  // the same factors with their Gram sums in one chunk
+    FactorBatch summed;  // the same factors with their Gram sums in one chunk where that pays
     int rc = launch_gram_partials_batch(batch, &summed, 0, st);
     if (rc != DLCX_OK) return rc;
-    size_t bytes = 0;
-    for (int i = 0; i < batch.n; ++i) {
-        const size_t re = (size_t)((batch.it[i].r + 1) & ~1);
-        const size_t b = re * re * sizeof(double);
-        if (b <= kJacobiLdsMax && b > bytes) bytes = b;
-    }
-    static size_t granted = 0;
-    rc = grant_dynamic_lds(reinterpret_cast<const void *>(jacobi_rank_kernel), bytes, &granted,
-                           "jacobi attribute");
-    if (rc != DLCX_OK) return rc;
-    Timed timed(KID_JACOBI, st);
     int rmax = 0;
     for (int i = 0; i < batch.n; ++i) rmax = batch.it[i].r > rmax ? batch.it[i].r : rmax;
-    // a team of 16 lanes per column pair of the largest matrix (r / 2 pairs), so that a step of
-    // the pair schedule is one pass; 1024 threads for the tridiagonal path
-    int threads = ((rmax + 1) / 2 * 16 + 255) / 256 * 256;
-    threads = threads < 256 ? 256 : (threads > kJT || rmax > 128 ? kJT : threads);
-    hipLaunchKernelGGL(jacobi_rank_kernel, dim3((unsigned)batch.n), dim3((unsigned)threads), bytes,
-                       st, summed, tau);
-    return check_launch("jacobi_rank");
+    Timed timed(KID_JACOBI, st);
+    const dim3 grid((unsigned)batch.n), threads(kTT);
+    if (rmax <= 64)
+        hipLaunchKernelGGL(tridiag_kernel<4>, grid, threads, 0, st, summed, tau);
+    else if (rmax <= 128)
+        hipLaunchKernelGGL(tridiag_kernel<8>, grid, threads, 0, st, summed, tau);
+    else if (rmax <= 192)
+        hipLaunchKernelGGL(tridiag_kernel<12>, grid, threads, 0, st, summed, tau);
+    else
+        hipLaunchKernelGGL(tridiag_kernel<16>, grid, threads, 0, st, summed, tau);
+    if (rmax > kFusedRank) {
+        hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
+                           dim3(256), 0, st, summed);
+        hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
+    }
+    return check_launch("effective_rank");
 }
 
 int launch_effective_rank(int64_t L, int r, const float *q_bar, double tau, int32_t *rprime_dev,

@@ -391,6 +391,31 @@ def test_effective_rank_random_and_zero(n, r):
                 assert int(out.item()) == want, tau
 
 
+@pytest.mark.parametrize("r", [2, 3, 15, 16, 17, 48, 63, 65, 127, 191, 193, 240, 254])
+@pytest.mark.parametrize("kind", ["dense", "diagonal", "blocks"])
+def test_effective_rank_tile_edges_and_decoupled_rows(r, kind):
+    # Ranks around the edges of the 16 x 16 tiles and of the launch shapes.  "diagonal": columns
+    # with disjoint supports (S is diagonal bit for bit, no row is ever reflected, eigenvalues
+    # coincide); "blocks": half of the rows decoupled from the rest, with equal columns among them.
+    n = 768 if r <= 254 else 1024
+    g = rng(31 * r + len(kind))
+    q = (g.standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.8)).astype(np.float32)
+    if kind == "diagonal":
+        q = np.zeros((r, n), np.float32)
+        for c in range(r):
+            q[c, 3 * c: 3 * c + 3] = np.float32(2.0 ** -(c // 7))
+    elif kind == "blocks":
+        h = r // 2
+        q[:h, n // 2:] = 0.0
+        q[h:, : n // 2] = 0.0
+        q[h:] = q[h]
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for tau in (0.3, 0.9, 0.99, 0.9999):
+        dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
+        assert int(out.item()) == ref.effective_rank(q, tau), tau
+
+
 def test_select_rank_stage_value_and_window():
     # three matrices with known r' (3, 49, zero matrix -> rmin 4): mean 56/3 = 18.67 -> 19
     n, r = 512, 64
