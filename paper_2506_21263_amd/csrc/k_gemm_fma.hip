@@ -1,134 +1,216 @@
-// Rank-r products of the low-rank compressor on the vector ALU (DLCX_MMA_FMA): fp32 operands,
-// fp64 accumulation.  This is the accuracy mode: it is not meant to reach the roofline, it is the
-// GPU path whose rounding is closest to the exact products, and it accepts every shape the
-// interface allows.  The MFMA modes live in k_gemm_mfma.hip.
+// Rank-r products of the low-rank compressor with fp32 operands and fp64 accumulation
+// (DLCX_MMA_FMA): the accuracy mode, the GPU path whose rounding is closest to the exact products
+// (a product of two fp32 values is exact in fp64), for every shape the interface allows.  They run
+// on v_mfma_f64_16x16x4_f64, at 1/32 of the bf16 rate, which bounds them from
+// about rank 16 on; the modes with split operands live in k_gemm_mfma.hip.
+//
+// Operands of that instruction, lane l with g = l / 16, n = l % 16: A[n][g], B[g][n], result
+// D[4 v + g][n] in register v.  Where the reduction index is contiguous in memory a lane loads four
+// consecutive values and feeds one to each of four products (both operands agree on that order of
+// the reduction), where the other index is contiguous it loads four columns and feeds one to each
+// of four column blocks, 4 n + q being column n of block q: all loads are 16 bytes a lane, go
+// straight to registers and are requested a step ahead.  Every side is a multiple of 16.
 #include <type_traits>
 
 #include "common.h"
 
 namespace dlcx {
 
-constexpr int kT = 256;    // threads per workgroup
-constexpr int kRows = 64;  // rows (P phase) or columns (Q phase) per workgroup
-constexpr int kTk = 32;    // reduction chunk staged in LDS
+constexpr int kT = 256;  // threads per workgroup (4 wavefronts)
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4_t mfma64(float a, float b, f64x4_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0);
+}
+__device__ __forceinline__ float part_of(const float4 &v, int s) {
+    return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
+}
+__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 
 // ---------------------------------------------------------------------------------------------
-// P_k = delta_k * Q_in.  Workgroup: 64 rows of delta, all r outputs; wave w owns the outputs
-// c = w, w+4, ...; lanes are rows, so the Q_in operand is a wave-uniform LDS broadcast.
+// P_k = delta_k * Q_in:  D[c][i] = sum_j Q[c][j] delta[i][j].  Workgroup: 16 RB rows of delta and
+// all r outputs; each wavefront sums a quarter of the columns j, the four sums are added in order.
+// (One wavefront per row group and no split leaves most SIMDs idle below 16 K rows.)  Two row
+// blocks share a basis operand once that still gives every compute unit a workgroup.
+// 2048 x 2048, four workers, r = 32: 33 us (scalar fp64 FMAs on LDS operands: 693 us); the
+// matrix cores' own time is 14 us.
 // ---------------------------------------------------------------------------------------------
-template <int kAcc>  // accumulators per thread, >= ceil(r / 4)
-__global__ __launch_bounds__(kT) void project_p_fma_kernel(PtrPack<const float *> deltas,
+template <int CB, int RB>
+__global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *> deltas,
                                                            const float *__restrict__ q_in,
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r) {
-    extern __shared__ float lds[];
-    float *dl = lds;                        // [kRows][kTk + 1]
-    float *ql = lds + kRows * (kTk + 1);    // [r][kTk + 1]
+    constexpr int U = CB <= 4 ? 2 : 1;  // steps of 16 columns per set of operands
+    __shared__ double red[4][RB * 4][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y];
-    const int64_t i0 = (int64_t)blockIdx.x * kRows;
-    const int lane_row = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    double acc[kAcc];
-#pragma unroll
-    for (int u = 0; u < kAcc; ++u) acc[u] = 0.0;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, x = lane & 15;
+    const int64_t i0 = (int64_t)blockIdx.x * (16 * RB);
+    const int64_t steps = n >> 4, per = (steps + 3) >> 2;
+    const int64_t begin = wave * per, end = begin + per < steps ? begin + per : steps;
 
-    for (int64_t j0 = 0; j0 < n; j0 += kTk) {
-        for (int idx = threadIdx.x; idx < kRows * (kTk / 4); idx += kT) {
-            const int row = idx / (kTk / 4), c4 = idx % (kTk / 4);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 + row < m && j0 + c4 * 4 < n)
-                v = *reinterpret_cast<const float4 *>(delta + (i0 + row) * n + j0 + c4 * 4);
-            float *d = dl + row * (kTk + 1) + c4 * 4;
-            d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-        }
-        for (int idx = threadIdx.x; idx < r * (kTk / 4); idx += kT) {
-            const int c = idx / (kTk / 4), c4 = idx % (kTk / 4);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (j0 + c4 * 4 < n)
-                v = *reinterpret_cast<const float4 *>(q_in + (int64_t)c * n + j0 + c4 * 4);
-            float *d = ql + c * (kTk + 1) + c4 * 4;
-            d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int jj = 0; jj < kTk; ++jj) {
-            const double a = (double)dl[lane_row * (kTk + 1) + jj];
+    const float *pd[RB], *pq[CB];
 #pragma unroll
-            for (int u = 0; u < kAcc; ++u) {
-                const int c = wave + 4 * u;
-                if (c < r) acc[u] = fma(a, (double)ql[c * (kTk + 1) + jj], acc[u]);
-            }
-        }
-        __syncthreads();
+    for (int rb = 0; rb < RB; ++rb) {  // past the last row, or the last column of the factor: any
+        const int64_t i = i0 + rb * 16 < m ? i0 + rb * 16 + x : x;  // valid one, nothing is stored
+        pd[rb] = delta + i * n + 4 * g;
     }
-    if (i0 + lane_row < m) {
 #pragma unroll
-        for (int u = 0; u < kAcc; ++u) {
-            const int c = wave + 4 * u;
-            if (c < r) out[(int64_t)c * m + i0 + lane_row] = (float)acc[u];
+    for (int cb = 0; cb < CB; ++cb) {
+        const int c = cb * 16 + x;
+        pq[cb] = q_in + (int64_t)(c < r ? c : r - 1) * n + 4 * g;
+    }
+    f64x4_t acc[CB][RB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+
+    struct Set {
+        float4 a[U][CB], b[U][RB];
+    };
+    auto load = [&](Set &s, int64_t step) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t st = step + u < end ? step + u : end - 1;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) s.b[u][rb] = load4(pd[rb] + st * 16);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                if (cb * 16 < r) s.a[u][cb] = load4(pq[cb] + st * 16);
+        }
+    };
+    if (begin < end) {
+        Set cur, next;
+        load(cur, begin);
+        for (int64_t st = begin; st < end; st += U) {
+            load(next, st + U);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (st + u >= end) break;
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb)
+                    if (cb * 16 < r) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+#pragma unroll
+                            for (int rb = 0; rb < RB; ++rb)
+                                acc[cb][rb] = mfma64(part_of(cur.a[u][cb], s),
+                                                     part_of(cur.b[u][rb], s), acc[cb][rb]);
+                    }
+            }
+            cur = next;
+        }
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        if (cb * 16 >= r) break;
+        __syncthreads();
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][rb * 4 + v][lane] = acc[cb][rb][v];
+        __syncthreads();
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {  // wavefront v adds register v of the four
+            const int e = rb * 4 + wave, c = cb * 16 + 4 * wave + g;
+            const int64_t i = i0 + rb * 16 + x;
+            const double s = ((red[0][e][lane] + red[1][e][lane]) + red[2][e][lane]) + red[3][e][lane];
+            if (c < r && i < m) out[(int64_t)c * m + i] = (float)s;
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Q_k = delta_k^T * P_hat.  Workgroup: 64 columns of delta over the row range of split
-// blockIdx.z; partial results go to slab blockIdx.z (summed afterwards in slab order).
+// Q_k = delta_k^T * P_hat:  D[c][j] = sum_i P_hat[c][i] delta[i][j].  Workgroup: 64 columns of delta
+// over the row range of split blockIdx.z; partial results go to slab blockIdx.z (summed afterwards
+// in slab order).  The wavefronts are WC groups of CBW blocks of outputs by WK = 4 / WC quarters or
+// halves of the rows, added in order.  2048 x 2048, four workers, r = 32: 36 us with
+// the sum of the eight slabs (scalar fp64 FMAs on LDS operands: 114 us).
 // ---------------------------------------------------------------------------------------------
-template <int kAcc>
-__global__ __launch_bounds__(kT) void project_q_fma_kernel(PtrPack<const float *> deltas,
+template <int CBW, int WC>
+__global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *> deltas,
                                                            const float *__restrict__ p_hat,
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r, int64_t rows_per_split,
                                                            int64_t slab_stride) {
-    extern __shared__ float lds[];
-    float *dl = lds;                 // [kTk][kRows]
-    float *pl = lds + kTk * kRows;   // [r][kTk + 1]
+    constexpr int WK = 4 / WC;
+    __shared__ double red[4][16][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y] + (int64_t)blockIdx.z * slab_stride;
-    const int64_t j0 = (int64_t)blockIdx.x * kRows;
-    const int lane_col = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t i_begin = (int64_t)blockIdx.z * rows_per_split;
-    int64_t i_end = i_begin + rows_per_split;
-    if (i_end > m) i_end = m;
-    double acc[kAcc];
-#pragma unroll
-    for (int u = 0; u < kAcc; ++u) acc[u] = 0.0;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, x = lane & 15;
+    const int wc = wave % WC, wk = wave / WC;
+    const int64_t j = (int64_t)blockIdx.x * 64 + 4 * x;
+    const int cfirst = wc * CBW * 16;
+    // this wavefront's rows: multiples of 16 inside the split (rows_per_split is one of 64)
+    const int64_t share = rows_per_split / WK;
+    const int64_t begin = (int64_t)blockIdx.z * rows_per_split + wk * share;
+    const int64_t end = begin + share < m ? begin + share : m;
 
-    for (int64_t i0 = i_begin; i0 < i_end; i0 += kTk) {
-        for (int idx = threadIdx.x; idx < kTk * (kRows / 4); idx += kT) {
-            const int ii = idx / (kRows / 4), c4 = idx % (kRows / 4);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 + ii < i_end && j0 + c4 * 4 < n)
-                v = *reinterpret_cast<const float4 *>(delta + (i0 + ii) * n + j0 + c4 * 4);
-            *reinterpret_cast<float4 *>(dl + ii * kRows + c4 * 4) = v;
-        }
-        for (int idx = threadIdx.x; idx < r * (kTk / 4); idx += kT) {
-            const int c = idx / (kTk / 4), c4 = idx % (kTk / 4);
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 + c4 * 4 < i_end)  // split ranges are multiples of 4
-                v = *reinterpret_cast<const float4 *>(p_hat + (int64_t)c * m + i0 + c4 * 4);
-            float *d = pl + c * (kTk + 1) + c4 * 4;
-            d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int ii = 0; ii < kTk; ++ii) {
-            const double a = (double)dl[ii * kRows + lane_col];
+    const float *pd = delta + (4 * g) * n + (j < n ? j : 0);
+    const float *pp[CBW];
 #pragma unroll
-            for (int u = 0; u < kAcc; ++u) {
-                const int c = wave + 4 * u;
-                if (c < r) acc[u] = fma(a, (double)pl[c * (kTk + 1) + ii], acc[u]);
-            }
-        }
-        __syncthreads();
+    for (int cb = 0; cb < CBW; ++cb) {
+        const int c = cfirst + cb * 16 + x;
+        pp[cb] = p_hat + (int64_t)(c < r ? c : r - 1) * m + 4 * g;
     }
-    if (j0 + lane_col < n) {
+    f64x4_t acc[CBW][4];
 #pragma unroll
-        for (int u = 0; u < kAcc; ++u) {
-            const int c = wave + 4 * u;
-            if (c < r) out[(int64_t)c * n + j0 + lane_col] = (float)acc[u];
+    for (int cb = 0; cb < CBW; ++cb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[cb][q] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+
+    struct Set {
+        float4 a[CBW], b[4];
+    };
+    auto load = [&](Set &s, int64_t i) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s.b[u] = load4(pd + (i + u) * n);
+#pragma unroll
+        for (int cb = 0; cb < CBW; ++cb)
+            if (cfirst + cb * 16 < r) s.a[cb] = load4(pp[cb] + i);
+    };
+    if (begin < end) {
+        Set cur, next;
+        load(cur, begin);
+        for (int64_t i = begin; i < end; i += 16) {
+            load(next, i + 16 < end ? i + 16 : i);
+#pragma unroll
+            for (int cb = 0; cb < CBW; ++cb)
+                if (cfirst + cb * 16 < r) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            acc[cb][q] = mfma64(part_of(cur.a[cb], s), part_of(cur.b[s], q), acc[cb][q]);
+                }
+            cur = next;
+        }
+    }
+#pragma unroll
+    for (int cb = 0; cb < CBW; ++cb) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[wave][v * 4 + q][lane] = acc[cb][q][v];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4 / WK; ++u) {  // registers v of this wavefront's share, all four blocks q
+            const int v = wk * (4 / WK) + u, c = cfirst + cb * 16 + 4 * v + g;
+            float o[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                double s = red[wc][v * 4 + q][lane];
+#pragma unroll
+                for (int k = 1; k < WK; ++k) s += red[k * WC + wc][v * 4 + q][lane];
+                o[q] = (float)s;
+            }
+            if (c < r && j < n)
+                *reinterpret_cast<float4 *>(out + (int64_t)c * n + j) = make_float4(o[0], o[1], o[2], o[3]);
         }
     }
 }
@@ -158,98 +240,101 @@ int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<f
 }
 
 // ---------------------------------------------------------------------------------------------
-// delta_hat = P_hat Q_bar^T on 64 x 64 tiles, 4 x 4 outputs per thread; the epilogue writes the
-// tile (optional), subtracts it from the K error buffers (e_k <- delta_k - delta_hat) and, when
-// theta is given, applies the Nesterov outer update with the tile as the gradient.
+// delta_hat = P_hat Q_bar^T:  D[i][j] = sum_c P_hat[c][i] Q_bar[c][j], 16 rows x 64 columns per
+// wavefront (256 columns per workgroup), so that a lane ends up with four consecutive columns of
+// four rows; the epilogue writes the tile (optional), subtracts it from the K error buffers (e_k <-
+// delta_k - delta_hat) and, when theta is given, forms the next pseudo-gradients and applies the
+// Nesterov outer update with the tile as the gradient.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kT) void reconstruct_fma_kernel(const float *__restrict__ p_hat,
+__global__ __launch_bounds__(kT) void reconstruct_f64_kernel(const float *__restrict__ p_hat,
                                                              const float *__restrict__ q_bar,
                                                              ReconEpilogue ep, int64_t m,
-                                                             int64_t n, int r) {
-    __shared__ float pt[kTk][64];
-    __shared__ float qt[kTk][64];
-    const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
-    const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
-    double acc[4][4];
+                                                             int64_t n, int r, int col_wgs) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, x = lane & 15;
+    const int64_t i0 = (int64_t)(blockIdx.x / col_wgs) * 16;
+    const int64_t j = (int64_t)(blockIdx.x % col_wgs) * 256 + wave * 64 + 4 * x;
+    const float *pa = p_hat + i0 + x, *pb = q_bar + (j < n ? j : 0);
+    f64x4_t acc[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int q = 0; q < 4; ++q) acc[q] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    struct Set {
+        float a[4];
+        float4 b[4];
+    };
+    auto load = [&](Set &s, int c0) {  // columns c0 .. c0 + 15 of the factors, zeros from r on
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = 0.0;
-
-    for (int c0 = 0; c0 < r; c0 += kTk) {
-        for (int idx = threadIdx.x; idx < kTk * 16; idx += kT) {
-            const int cc = idx >> 4, c4 = idx & 15;
-            float4 pv = make_float4(0.f, 0.f, 0.f, 0.f), qv = pv;
-            if (c0 + cc < r) {
-                if (i0 + c4 * 4 < m)
-                    pv = *reinterpret_cast<const float4 *>(p_hat + (int64_t)(c0 + cc) * m + i0 + c4 * 4);
-                if (j0 + c4 * 4 < n)
-                    qv = *reinterpret_cast<const float4 *>(q_bar + (int64_t)(c0 + cc) * n + j0 + c4 * 4);
-            }
-            *reinterpret_cast<float4 *>(&pt[cc][c4 * 4]) = pv;
-            *reinterpret_cast<float4 *>(&qt[cc][c4 * 4]) = qv;
+        for (int u = 0; u < 4; ++u) {
+            const int c = c0 + 4 * u + g, cc = c < r ? c : r - 1;
+            const float a = pa[(int64_t)cc * m];
+            s.b[u] = load4(pb + (int64_t)cc * n);
+            s.a[u] = c < r ? a : 0.f;
+            if (c >= r) s.b[u] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int cc = 0; cc < kTk; ++cc) {
-            const float4 a = *reinterpret_cast<const float4 *>(&pt[cc][ti * 4]);
-            const float4 b = *reinterpret_cast<const float4 *>(&qt[cc][tj * 4]);
-            const double av[4] = {a.x, a.y, a.z, a.w};
-            const double bv[4] = {b.x, b.y, b.z, b.w};
+    };
+    Set cur, next;
+    load(cur, 0);
+    for (int c0 = 0; c0 < r; c0 += 16) {
+        load(next, c0 + 16);
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fma(av[x], bv[y], acc[x][y]);
-        }
-        __syncthreads();
+            for (int q = 0; q < 4; ++q) acc[q] = mfma64(cur.a[u], part_of(cur.b[u], q), acc[q]);
+        cur = next;
     }
-    const int64_t j = j0 + tj * 4;
     if (j >= n) return;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int64_t i = i0 + ti * 4 + x;
-        if (i >= m) break;
-        const float4 d = make_float4((float)acc[x][0], (float)acc[x][1], (float)acc[x][2],
-                                     (float)acc[x][3]);
-        if (ep.out) *reinterpret_cast<float4 *>(ep.out + i * n + j) = d;
-        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ep.tl_on || ep.apply) t = *reinterpret_cast<const float4 *>(ep.theta + i * n + j);
-        for (int k = 0; k < ep.K; ++k) {
-            float4 e = *reinterpret_cast<float4 *>(ep.ef.p[k] + i * n + j);
-            e.x -= d.x; e.y -= d.y; e.z -= d.z; e.w -= d.w;
-            if (ep.tl_on) {
-                float4 l;
-                if (ep.tl_bf16) {
+    for (int v = 0; v < 4; ++v) {
+        const int64_t off = (i0 + 4 * v + g) * n + j;
+        const float4 d = make_float4((float)acc[0][v], (float)acc[1][v], (float)acc[2][v],
+                                     (float)acc[3][v]);
+        if (ep.out) *reinterpret_cast<float4 *>(ep.out + off) = d;
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f), vel = t;
+        if (ep.tl_on || ep.apply) t = load4(ep.theta + off);
+        if (ep.apply) vel = load4(ep.vel + off);
+        for (int k0 = 0; k0 < ep.K; k0 += 4) {  // four workers' loads before the first store
+            float4 e[4], l[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (k0 + k >= ep.K) break;
+                e[k] = load4(ep.ef.p[k0 + k] + off);
+                if (ep.tl_on && ep.tl_bf16) {
                     const uint2 b = *reinterpret_cast<const uint2 *>(
-                        reinterpret_cast<const uint16_t *>(ep.tl.p[k]) + i * n + j);
-                    l = make_float4(__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u),
-                                    __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u));
-                } else {
-                    l = *reinterpret_cast<const float4 *>(
-                        reinterpret_cast<const float *>(ep.tl.p[k]) + i * n + j);
+                        reinterpret_cast<const uint16_t *>(ep.tl.p[k0 + k]) + off);
+                    l[k] = make_float4(__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xFFFF0000u),
+                                       __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xFFFF0000u));
+                } else if (ep.tl_on) {
+                    l[k] = load4(reinterpret_cast<const float *>(ep.tl.p[k0 + k]) + off);
                 }
-                e.x = (t.x - l.x) + e.x; e.y = (t.y - l.y) + e.y;
-                e.z = (t.z - l.z) + e.z; e.w = (t.w - l.w) + e.w;
             }
-            *reinterpret_cast<float4 *>(ep.ef.p[k] + i * n + j) = e;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (k0 + k >= ep.K) break;
+                float4 y = e[k];
+                y.x -= d.x; y.y -= d.y; y.z -= d.z; y.w -= d.w;
+                if (ep.tl_on) {
+                    y.x = (t.x - l[k].x) + y.x; y.y = (t.y - l[k].y) + y.y;
+                    y.z = (t.z - l[k].z) + y.z; y.w = (t.w - l[k].w) + y.w;
+                }
+                *reinterpret_cast<float4 *>(ep.ef.p[k0 + k] + off) = y;
+            }
         }
         if (ep.apply) {
-            float4 v = *reinterpret_cast<float4 *>(ep.vel + i * n + j);
-            v.x = fmaf(ep.mu, v.x, d.x); v.y = fmaf(ep.mu, v.y, d.y);
-            v.z = fmaf(ep.mu, v.z, d.z); v.w = fmaf(ep.mu, v.w, d.w);
-            t.x = fmaf(-ep.lr, fmaf(ep.mu, v.x, d.x), t.x);
-            t.y = fmaf(-ep.lr, fmaf(ep.mu, v.y, d.y), t.y);
-            t.z = fmaf(-ep.lr, fmaf(ep.mu, v.z, d.z), t.z);
-            t.w = fmaf(-ep.lr, fmaf(ep.mu, v.w, d.w), t.w);
-            *reinterpret_cast<float4 *>(ep.vel + i * n + j) = v;
-            *reinterpret_cast<float4 *>(ep.theta + i * n + j) = t;
+            vel.x = fmaf(ep.mu, vel.x, d.x); vel.y = fmaf(ep.mu, vel.y, d.y);
+            vel.z = fmaf(ep.mu, vel.z, d.z); vel.w = fmaf(ep.mu, vel.w, d.w);
+            t.x = fmaf(-ep.lr, fmaf(ep.mu, vel.x, d.x), t.x);
+            t.y = fmaf(-ep.lr, fmaf(ep.mu, vel.y, d.y), t.y);
+            t.z = fmaf(-ep.lr, fmaf(ep.mu, vel.z, d.z), t.z);
+            t.w = fmaf(-ep.lr, fmaf(ep.mu, vel.w, d.w), t.w);
+            *reinterpret_cast<float4 *>(ep.vel + off) = vel;
+            *reinterpret_cast<float4 *>(ep.theta + off) = t;
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 static int q_splits(int64_t m, int64_t n, int K) {
-    const int64_t wgs = ceil_div(n, kRows) * K;
+    const int64_t wgs = ceil_div(n, 64) * K;
     int64_t s = ceil_div(1024, wgs);
     const int64_t smax = ceil_div(m, 256);
     if (s > smax) s = smax;
@@ -262,47 +347,51 @@ size_t fma_project_workspace_bytes(int64_t m, int64_t n, int r, int K) {
     return (size_t)K * (size_t)q_splits(m, n, K) * (size_t)r * (size_t)n * sizeof(float);
 }
 
-template <typename F>
-static int by_rank(int r, F &&f) {
-    if (r <= 8) return f(std::integral_constant<int, 2>());
-    if (r <= 32) return f(std::integral_constant<int, 8>());
-    if (r <= 64) return f(std::integral_constant<int, 16>());
-    if (r <= 128) return f(std::integral_constant<int, 32>());
-    return f(std::integral_constant<int, 64>());
-}
-
 int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                          const float *q_in, const PtrPack<float *> &out, hipStream_t st) {
-    const dim3 grid((unsigned)ceil_div(m, kRows), (unsigned)K);
-    const size_t lds = (size_t)(kRows + r) * (kTk + 1) * sizeof(float);
     Timed timed(KID_PROJECT_P, st);
-    return by_rank(r, [&](auto acc) {
-        hipLaunchKernelGGL((project_p_fma_kernel<decltype(acc)::value>), grid, dim3(kT), lds, st,
-                           delta, q_in, out, m, n, r);
-        return check_launch("project_p_fma");
-    });
+    auto go = [&](auto cb, auto rb) {
+        const dim3 grid((unsigned)ceil_div(m, 16 * decltype(rb)::value), (unsigned)K);
+        hipLaunchKernelGGL((project_p_f64_kernel<decltype(cb)::value, decltype(rb)::value>), grid,
+                           dim3(kT), 0, st, delta, q_in, out, m, n, r);
+    };
+    typedef std::integral_constant<int, 1> one;
+    typedef std::integral_constant<int, 2> two;
+    const bool pair = ceil_div(m, 32) * K >= 512;  // two workgroups per compute unit
+    if (r <= 16) pair ? go(one(), two()) : go(one(), one());
+    else if (r <= 32) pair ? go(two(), two()) : go(two(), one());
+    else if (r <= 64) pair ? go(std::integral_constant<int, 4>(), two()) : go(std::integral_constant<int, 4>(), one());
+    else if (r <= 128) go(std::integral_constant<int, 8>(), one());
+    else go(std::integral_constant<int, 16>(), one());
+    return check_launch("project_p_f64");
 }
 
 int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                          const float *p_hat, const PtrPack<float *> &out, void *workspace,
                          hipStream_t st) {
-    const int S = q_splits(m, n, K);
-    int64_t rows = ceil_div(m, S);
-    rows = ceil_div(rows, kTk) * kTk;
+    const int64_t rows = ceil_div(ceil_div(m, q_splits(m, n, K)), 64) * 64;
+    const int S = (int)ceil_div(m, rows);  // no more than q_splits: the slabs fit
     const int64_t slab = (int64_t)r * n;
     PtrPack<float *> dst = out;
     if (S > 1)
         for (int k = 0; k < K; ++k) dst.p[k] = reinterpret_cast<float *>(workspace) + (int64_t)k * S * slab;
-    const dim3 grid((unsigned)ceil_div(n, kRows), (unsigned)K, (unsigned)S);
-    const size_t lds = (size_t)(kTk * kRows + r * (kTk + 1)) * sizeof(float);
     int rc;
     {
         Timed timed(KID_PROJECT_Q, st);
-        rc = by_rank(r, [&](auto acc) {
-        hipLaunchKernelGGL((project_q_fma_kernel<decltype(acc)::value>), grid, dim3(kT), lds, st,
-                           delta, p_hat, dst, m, n, r, rows, slab);
-        return check_launch("project_q_fma");
-        });
+        auto go = [&](auto cbw, auto wc) {
+            const dim3 grid((unsigned)ceil_div(n, 64), (unsigned)K, (unsigned)S);
+            hipLaunchKernelGGL((project_q_f64_kernel<decltype(cbw)::value, decltype(wc)::value>), grid,
+                               dim3(kT), 0, st, delta, p_hat, dst, m, n, r, rows, slab);
+        };
+        typedef std::integral_constant<int, 1> one;
+        typedef std::integral_constant<int, 2> two;
+        typedef std::integral_constant<int, 4> four;
+        if (r <= 16) go(one(), one());
+        else if (r <= 32) go(two(), one());
+        else if (r <= 64) go(four(), one());
+        else if (r <= 128) go(four(), two());
+        else go(four(), four());
+        rc = check_launch("project_q_f64");
     }
     if (rc != DLCX_OK || S == 1) return rc;
     PtrPack<const float *> src;
@@ -312,10 +401,12 @@ int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
 
 int launch_reconstruct_fma(int64_t m, int64_t n, int r, const float *p_hat, const float *q_bar,
                            const ReconEpilogue &ep, hipStream_t st) {
-    const dim3 grid((unsigned)ceil_div(n, 64), (unsigned)ceil_div(m, 64));
+    const int64_t col_wgs = ceil_div(n, 256);  // in one dimension: m / 16 may exceed the others'
+    const dim3 grid((unsigned)(col_wgs * ceil_div(m, 16)));
     Timed timed(KID_RECONSTRUCT, st);
-    hipLaunchKernelGGL(reconstruct_fma_kernel, grid, dim3(kT), 0, st, p_hat, q_bar, ep, m, n, r);
-    return check_launch("reconstruct_fma");
+    hipLaunchKernelGGL(reconstruct_f64_kernel, grid, dim3(kT), 0, st, p_hat, q_bar, ep, m, n, r,
+                       (int)col_wgs);
+    return check_launch("reconstruct_f64");
 }
 
 }  // namespace dlcx

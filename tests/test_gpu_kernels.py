@@ -159,6 +159,32 @@ def test_project_p_and_q(mma, m, n, r, K, group):
         assert close(to_np(outs[k]), want_q[k], TOL[mma]), ("Q", k)
 
 
+@pytest.mark.parametrize("m,n,r,K", [
+    (16, 16, 16, 1), (48, 272, 17, 3), (272, 80, 31, 2),      # fewer steps than wavefronts, ragged tiles
+    (1040, 208, 65, 1), (320, 336, 128, 2), (272, 528, 129, 1), (512, 256, 256, 1),
+    (8208, 64, 20, 2), (8208, 80, 48, 2),                     # two row blocks per wavefront in P
+])
+def test_fp64_products_at_tile_edges(m, n, r, K):
+    # The fp64-accumulating form: products of fp32 values are exact and their sums carry 2^-53 per
+    # addition, so P and the reconstruction are the 64-bit result rounded once (2^-24 relative);
+    # Q adds up to 16 partial sums in fp32: 2^-24 of the partial sums for each.
+    g = rng(m + 3 * n + r)
+    deltas = [g.standard_normal((m, n)).astype(np.float32) for _ in range(K)]
+    p, q = g.standard_normal((r, m)).astype(np.float32), g.standard_normal((r, n)).astype(np.float32)
+    d = dlcx.desc(m, n, r, 4, 16, dlcx.MMA_FMA)
+    ws = ws_for(d, K)
+    for phase, basis, L in ((dlcx.PHASE_P, q, m), (dlcx.PHASE_Q, p, n)):
+        outs = [torch.zeros(r, L, device=DEV) for _ in range(K)]
+        dlcx.dlcx_project(d, phase, [to_dev(x) for x in deltas], to_dev(basis), outs, ws)
+        for k in range(K):
+            x = deltas[k].astype(np.float64)
+            want = basis.astype(np.float64) @ (x.T if phase == dlcx.PHASE_P else x)
+            assert close(to_np(outs[k]), want, 2.0 ** -23), (phase, k)
+    out = torch.zeros(m, n, device=DEV)
+    dlcx.dlcx_decompress(d, to_dev(p), to_dev(q), out, workspace=ws)
+    assert close(to_np(out), p.astype(np.float64).T @ q.astype(np.float64), 2.0 ** -23)
+
+
 # ranks above 64 in the fp16 form: (Q only: few rows) / (P and Q: the two-role P kernel is used)
 SHAPES_F16 = [(640, 2048, 96, 2, 128), (2048, 512, 256, 1, 64), (4096, 320, 200, 8, 64),
               (4112, 336, 72, 8, 16), (4112, 336, 130, 8, 16)]
