@@ -167,6 +167,9 @@ __global__ __launch_bounds__(kGT) void gram_reduce_kernel(FactorBatch batch, int
     it.part[x] = s;
 }
 
+// Largest rank of a batch for which the consumers add up chunks themselves.
+constexpr int kSumRank = 144;
+
 // Partial Gram sums of every factor of the batch, then their sum in part[0]: *reduced is the
 // batch as the kernels that consume the Gram matrices have to see it (one chunk each).  Small
 // sums are left to the consumer: a launch costs more than the few loads per entry it saves.
@@ -192,7 +195,7 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
     int rc = check_launch("gram_partials");
     if (rc != DLCX_OK) return rc;
     *reduced = batch;
-    if (max_chunks < 2 || (max_chunks <= 16 && max_sum <= 16 * 1024)) return DLCX_OK;
+    if (max_chunks < 2 || (max_r <= kSumRank && max_chunks <= 16 && max_sum <= 16 * 1024)) return DLCX_OK;
     const dim3 rgrid((unsigned)ceil_div((int64_t)max_r * max_r, kGT), (unsigned)batch.n);
     hipLaunchKernelGGL(gram_reduce_kernel, rgrid, dim3(kGT), 0, st, batch, round);
     for (int i = 0; i < batch.n; ++i) reduced->it[i].nchunks = 1;
@@ -287,13 +290,6 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     const int nb = (r + 15) >> 4, nblk = nb * (nb + 1) / 2;
     const int64_t rr = (int64_t)r * r;
     if (tid == 0) any_dead = 0;
-    for (int c = tid; c < 16 * nb; c += blockDim.x) {
-        double d = 0.0;
-        if (c < r)
-            for (int q = 0; q < nchunks; ++q) d += part[q * rr + (int64_t)c * r + c];
-        dscale[c] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
-    }
-    __syncthreads();
     f64x4_t t[SLOTS];
     int id[SLOTS];  // I << 8 | J; past the last block I = 0xff... < 0, which no step asks for
 #pragma unroll
@@ -301,24 +297,54 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         const int b = wave + nw * s;
         int I = 0;
         while ((I + 1) * (I + 2) / 2 <= b) ++I;
-        const int J = b - I * (I + 1) / 2;
-        id[s] = b < nblk ? I << 8 | J : -1;
-        t[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        if (b < nblk) {
+        id[s] = b < nblk ? I << 8 | (b - I * (I + 1) / 2) : -1;
+    }
+    auto load = [&](int s, int v, int q) {  // this lane's element of partial sum q
+        const int x = 16 * (id[s] & 0xff) + 4 * v + g, y = 16 * (id[s] >> 8) + col;
+        const bool in = id[s] >= 0 && x < r && y < r;  // the upper triangle is what is stored
+        const double e = part[q * rr + (in ? (x < y ? x * r + y : y * r + x) : 0)];
+        return in ? e : 0.0;
+    };
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int x = 16 * J + 4 * v + g, y = 16 * I + col;
-                double sum = 0.0;
-                if (x < r && y < r) {  // the upper triangle is what is stored
-                    const double *src = part + (int64_t)(x < y ? x : y) * r + (x < y ? y : x);
-                    for (int q = 0; q < nchunks; ++q) sum += src[q * rr];
+    for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[s][v] = load(s, v, 0);
+    // chunk by chunk in order; with few blocks four chunks are requested before the first is added
+    constexpr int N = SLOTS <= 2 ? 4 : 1;
+    for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
+        double x[N][SLOTS][4];
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[u][s][v] = load(s, v, q + u < nchunks ? q + u : q);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) t[s][v] += q + u < nchunks ? x[u][s][v] : 0.0;
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+        if (id[s] >= 0 && (id[s] >> 8) == (id[s] & 0xff))
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (4 * v + g == col) {
+                    const double d = t[s][v];
+                    dscale[16 * (id[s] & 0xff) + col] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
                 }
-                t[s][v] = sum * (dscale[x] * dscale[y]);
-            }
-            if (I == 0) {  // block (0, 0)
+    __syncthreads();
 #pragma unroll
-                for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
-            }
+    for (int s = 0; s < SLOTS; ++s) {
+        if (id[s] < 0) continue;
+        const int I = id[s] >> 8, J = id[s] & 0xff;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) t[s][v] *= dscale[16 * J + 4 * v + g] * dscale[16 * I + col];
+        if (I == 0) {  // block (0, 0)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
         }
     }
     // The slot's block, opaque to the compiler at every use: addresses derived from it would
@@ -516,6 +542,7 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
         Timed timed(KID_CHOL, st);
         const int blocks = max_nb * (max_nb + 1) / 2, waves = kCT / 64;
         const dim3 grid((unsigned)batch.n), threads((unsigned)(blocks < waves ? blocks : waves) * 64);
+        static_assert(6 * 8 >= (kSumRank / 16) * (kSumRank / 16 + 1) / 2, "ranks that sum chunks have at most 6");
         if (blocks <= 2 * waves)
             hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
         else if (blocks <= 6 * waves)

@@ -187,6 +187,65 @@ __device__ __forceinline__ int32_t count_share(const double *eig, int r, double 
     return total > 0.0 ? min(k, r) : 0;
 }
 
+// The Householder reflection of a row whose first element right of the diagonal is x0 and whose
+// others have `tail` as their sum of squares.  With s = x0^2 + tail: alpha = -+sqrt(s), v = row with
+// v_0 = x0 - alpha, beta = 2 / |v|^2 = 1 / (s + |x0| sqrt(s)); v_rsq_f64 and v_rcp_f64 with two
+// Newton steps each are full fp64.  beta = 0: nothing to reflect, alpha = x0.  (Below 2^-960 a tail is
+// rounding of roundings: S comes from fp32 values, its entries are above 2^-300 or zero; and
+// v_rsq_f64 needs a normal number.)
+struct Reflection {
+    double alpha, beta;
+};
+__device__ __forceinline__ Reflection reflection(double x0, double tail) {
+    const double s = fma(x0, x0, tail);
+    double y = __builtin_amdgcn_rsq(s);
+    y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
+    y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
+    const double norm = s * y, den = fma(fabs(x0), norm, s);
+    double beta = __builtin_amdgcn_rcp(den);
+    beta = fma(fma(-den, beta, 1.0), beta, beta);
+    beta = fma(fma(-den, beta, 1.0), beta, beta);
+    const bool reflect = tail > 0x1p-960;
+    return Reflection{reflect ? -copysign(norm, x0) : x0, reflect ? beta : 0.0};
+}
+
+// Gershgorin interval of the tridiagonal matrix (tri[i] = d_i, e_{i-1}), by one wavefront, scaled by
+// 2^ex, the power of two that puts every magnitude at one or below.
+struct Interval {
+    double lo, hi;
+    int ex;
+};
+__device__ __forceinline__ Interval gershgorin(const double2 *tri, int r, int lane) {
+    double lo = tri[0].x, hi = lo;
+    for (int i = lane; i < r; i += 64) {
+        const double rad = (i > 0 ? fabs(tri[i].y) : 0.0) + (i + 1 < r ? fabs(tri[i + 1].y) : 0.0);
+        lo = fmin(lo, tri[i].x - rad);
+        hi = fmax(hi, tri[i].x + rad);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, off, 64));
+        hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    const double big = fmax(fabs(lo), fabs(hi));
+    const int ex = big > 0.0 && big < 1e300 ? -__builtin_amdgcn_frexp_exp(big) : 0;
+    return Interval{ldexp(lo, ex), ldexp(hi, ex), ex};
+}
+
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    return from_halves(__builtin_amdgcn_readlane((uint32_t)u, lane),
+                       __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane));
+}
+
+// LDS written and read by the same wavefront: its instructions execute in order, so only the
+// compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // What tridiag_kernel leaves in FactorItem::g above rank 64: (d_i, e_i^2) scaled, from double 0;
 // then lo, hi; then the eigenvalues (still scaled: r' does not depend on a power of two).
 __device__ __forceinline__ double2 *tri_of(const FactorItem &it) { return reinterpret_cast<double2 *>(it.g); }
@@ -205,15 +264,13 @@ __device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 
 // Rows that are done have zeros in v and w; tile rows that are done are skipped.  What counts is
 // the number of instructions: four wavefronts, one per SIMD, so that nothing is done twice on a
 // SIMD (eight wavefronts that each formed v and beta for themselves took 1.45 us a step at r = 64,
-// this form
-// 1.05 us), and the registers of a whole SIMD for one wavefront (136 tiles at r = 256 are 272
+// this form 1.05), and the registers of a whole SIMD for one wavefront (136 tiles at r = 256 are 272
 // of its 512; with eight wavefronts spilled registers made 16 us a step,
 // now 3.0).  Seven factors at r = 256: 784 us, and the eigenvalues 54 us after it (one thread per
-// eigenvalue and a division per term, after a reduction that walked S in L2: 4400 us together);
-// r = 32 whole: 50 us (246), r = 64: 89 us (510).
+// eigenvalue and a division per term, after a reduction that walked S in L2: 4400 us together).
 template <int NT>
-__global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, double tau) {
-    constexpr int RS = NT <= 4 ? 4 : NT <= 8 ? 8 : 16;
+__global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
+    constexpr int RS = NT <= 8 ? 8 : 16;
     constexpr int CG = NT / 4;              // column sums per lane after four rows of lanes are added
     constexpr int R = 16 * NT;
     __shared__ double vrow[2][R];           // v of row k, zeros up to the diagonal
@@ -222,8 +279,7 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, doub
     __shared__ double colpart[4][R];
     __shared__ double pbuf[R];
     __shared__ double red[4];
-    __shared__ double2 tri[R + kSturmPad];  // d_k and the off-diagonal element before it
-    __shared__ double eig[kFusedRank];
+    __shared__ double2 tri[R];              // d_k and the off-diagonal element before it
     const FactorItem it = batch.it[blockIdx.x];
     const int r = it.r, nchunks = it.nchunks;
     const double *__restrict__ part = it.part;
@@ -231,6 +287,7 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, doub
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tj = lane & 15, g = lane >> 4, ti = wave * 4 + g;
     const int64_t rr = (int64_t)r * r;
+    if (r <= kFusedRank) return;
 
     double t[NT][NT];  // t[x][y], x <= y
 #pragma unroll
@@ -246,8 +303,7 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, doub
             t[x][y] = s;
         }
     // Row `row`, whose tile row is x: its v, beta and elements of the result, by the lanes that
-    // hold it.  With s = |row right of the diagonal|^2, alpha = -+sqrt(s): v_0 = x_0 - alpha and
-    // beta = 2 / |v|^2 = 1 / (s + |x_0| sqrt(s)).
+    // hold it.
     auto publish = [&](auto xc, int row, int buf) {
         constexpr int x = decltype(xc)::value;
         if (((row & 15) >> 2) != wave || g != (row & 3)) return;
@@ -275,22 +331,12 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, doub
         const int from = ((row & 3) * 16 + (at & 15)) * 4;
         x0 = from_halves((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)u),
                          (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(u >> 32)));
-        const double s = fma(x0, x0, tail);
-        double y = __builtin_amdgcn_rsq(s);  // two Newton steps each: full fp64
-        y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
-        y = fma(0.5 * y, fma(-s * y, y, 1.0), y);
-        const double norm = s * y, den = fma(fabs(x0), norm, s);
-        double beta = __builtin_amdgcn_rcp(den);
-        beta = fma(fma(-den, beta, 1.0), beta, beta);
-        beta = fma(fma(-den, beta, 1.0), beta, beta);
-        // (below 2^-960 a tail is rounding of roundings: S comes from fp32 values, its entries are
-        // above 2^-300 or zero; and v_rsq_f64 needs a normal number)
-        const bool reflect = tail > 0x1p-960;
-        const double alpha = reflect ? -copysign(norm, x0) : x0, v0 = x0 - alpha;
+        const Reflection f = reflection(x0, tail);
+        const double v0 = x0 - f.alpha;
         if (tj == d) tri[row].x = t[x][x];
         if (tj == 0) {
-            if (row + 1 < R) tri[row + 1].y = alpha;
-            betas[buf] = reflect ? beta : 0.0;
+            if (row + 1 < R) tri[row + 1].y = f.alpha;
+            betas[buf] = f.beta;
         }
 #pragma unroll
         for (int y2 = 0; y2 < x; ++y2) dst[16 * y2] = 0.0;
@@ -367,49 +413,131 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch, doub
         });
         __syncthreads();
     }
-    if (wave != 0 && r > kFusedRank) return;
-    // Gershgorin interval and scale: a power of two that puts every magnitude at one or below
-    double lo = tri[0].x, hi = lo;
-    for (int i = lane; i < r; i += 64) {
-        const double rad = (i > 0 ? fabs(tri[i].y) : 0.0) + (i + 1 < r ? fabs(tri[i + 1].y) : 0.0);
-        lo = fmin(lo, tri[i].x - rad);
-        hi = fmax(hi, tri[i].x + rad);
+    if (wave == 0) {
+        const Interval in = gershgorin(tri, r, lane);
+        for (int i = lane; i < r; i += 64)  // filled up to whole blocks by the reader
+            tri_of(it)[i] = sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0);
+        if (lane == 0) {
+            bounds_of(it)[0] = in.lo;
+            bounds_of(it)[1] = in.hi;
+        }
+    }
+}
+
+// Ranks up to kFusedRank: the whole matrix in one wavefront, row i in lane i, and no barrier until
+// the eigenvalues.  Every lane sums its own row of S v; v and w go round through LDS.  The columns
+// are renumbered as they go: step k reflects register column 0 and the update writes column j into
+// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 40 us (50 with four
+// wavefronts and three barriers a step, 246 at 1024 threads), r = 64: 93 us (510).
+template <int RC>  // columns held: 32 or 64
+__global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, double tau) {
+    __shared__ double sm[RC][RC + 1];
+    __shared__ __attribute__((aligned(16))) double vb[64 + 8], wb[64 + 8];
+    __shared__ double2 tri[RC + kSturmPad];
+    __shared__ double eig[RC];
+    const FactorItem it = batch.it[blockIdx.x];
+    const int r = it.r, nchunks = it.nchunks;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t rr = (int64_t)r * r;
+    if (r > RC || r <= RC / 2 * (RC > 32)) return;  // another kernel's
+    constexpr int E = RC * RC / kTT;
+    int from[E];
+    double sum[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int x = (tid + kTT * e) / RC, y = (tid + kTT * e) % RC;
+        from[e] = x <= y && y < r ? x * r + y : -1;
+        sum[e] = 0.0;
+    }
+    for (int c = 0; c < nchunks; c += 2) {  // chunk by chunk in order, two requested at a time
+        double p[2][E];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                p[u][e] = it.part[(c + u < nchunks ? c + u : c) * rr + (from[e] < 0 ? 0 : from[e])];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < E; ++e) sum[e] += c + u < nchunks ? p[u][e] : 0.0;
     }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, off, 64));
-        hi = fmax(hi, __shfl_xor(hi, off, 64));
-    }
-    const double big = fmax(fabs(lo), fabs(hi));
-    const int ex = big > 0.0 && big < 1e300 ? -__builtin_amdgcn_frexp_exp(big) : 0;
-    lo = ldexp(lo, ex);
-    hi = ldexp(hi, ex);
-    auto scaled = [&](int i) {
-        return sturm_term(ldexp(tri[i].x, ex), i > 0 ? ldexp(tri[i].y, ex) : 0.0);
-    };
-    if (r > kFusedRank) {  // wavefront 0
-        for (int i = lane; i < r; i += 64) tri_of(it)[i] = scaled(i);  // filled up by the reader
-        if (lane == 0) {
-            bounds_of(it)[0] = lo;
-            bounds_of(it)[1] = hi;
+    for (int e = 0; e < E; ++e) {
+        const int x = (tid + kTT * e) / RC, y = (tid + kTT * e) % RC;
+        const double v = from[e] < 0 ? 0.0 : sum[e];
+        if (x <= y) {
+            sm[x][y] = v;
+            sm[y][x] = v;
         }
-        return;
     }
+    __syncthreads();
+    if (wave == 0) {
+        double t[RC];
+#pragma unroll
+        for (int j = 0; j < RC; ++j) {
+            const double e = sm[lane % RC][j];
+            t[j] = lane < RC ? e : 0.0;
+        }
+        for (int k = 0; k + 1 < r; ++k) {
+            const double x = t[0];
+            const double dk = read_lane(x, k), x0 = read_lane(x, k + 1);
+            const Reflection f = reflection(x0, wave_sum(lane > k + 1 ? x * x : 0.0));
+            const double v = f.beta == 0.0 ? 0.0 : lane > k + 1 ? x : lane == k + 1 ? x0 - f.alpha : 0.0;
+            if (lane == 0) {
+                tri[k].x = dk;
+                tri[k + 1].y = f.alpha;
+            }
+            // past the last row: zeros, as far as a group of eight columns may reach
+            if (lane >= k) vb[lane - k] = v;
+            if (lane < 8) vb[64 - k + lane] = 0.0;
+            wave_sync();
+            const int live = r - k;
+            double p[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < RC / 8; ++q)
+                if (8 * q < live) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (8 * q + u > 0) p[u & 3] = fma(t[8 * q + u], vb[8 * q + u], p[u & 3]);
+                }
+            const double pv = lane > k ? (p[0] + p[1]) + (p[2] + p[3]) : 0.0;
+            const double kk = 0.5 * f.beta * (f.beta * wave_sum(v * pv));  // (beta^2 may overflow)
+            const double w = fma(f.beta, pv, -kk * v);
+            if (lane >= k) wb[lane - k] = w;
+            if (lane < 8) wb[64 - k + lane] = 0.0;
+            wave_sync();
+#pragma unroll
+            for (int q = 0; q < RC / 8; ++q)
+                if (8 * q < live) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (8 * q + u > 0)
+                            t[8 * q + u - 1] = fma(-v, wb[8 * q + u], fma(-w, vb[8 * q + u], t[8 * q + u]));
+                }
+        }
+        const double last = read_lane(t[0], r - 1);
+        if (lane == 0) tri[r - 1].x = last;
+    }
+    __syncthreads();
+    const Interval in = gershgorin(tri, r, lane);
     __syncthreads();  // every wavefront has its interval
-    if (wave == 0 && tid < r) tri[tid] = scaled(tid);  // r <= 64
-    if (tid >= r && tid < 16 * sturm_blocks(r) + 8) tri[tid] = sturm_fill();
+    if (tid < r)
+        tri[tid] = sturm_term(ldexp(tri[tid].x, in.ex), tid > 0 ? ldexp(tri[tid].y, in.ex) : 0.0);
+    else if (tid < 16 * sturm_blocks(r) + 8)
+        tri[tid] = sturm_fill();
     __syncthreads();
     // as many lanes per eigenvalue as 256 threads have for r of them
     auto find = [&](auto gc) {
         constexpr int G = decltype(gc)::value;
         const int c = tid / G;
-        const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, lo, hi, lane);
+        const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, in.lo, in.hi, lane);
         if (c < r && (lane & (G - 1)) == 0) eig[c] = ev;
     };
     if (r <= 4) find(std::integral_constant<int, 64>());
     else if (r <= 8) find(std::integral_constant<int, 32>());
     else if (r <= 16) find(std::integral_constant<int, 16>());
-    else if (r <= 32) find(std::integral_constant<int, 8>());
+    else if (RC <= 32 || r <= 32) find(std::integral_constant<int, 8>());
     else find(std::integral_constant<int, 4>());
     __syncthreads();
     if (wave == 0) {
@@ -463,19 +591,26 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
     FactorBatch summed;  // the same factors with their Gram sums in one chunk where that pays
     int rc = launch_gram_partials_batch(batch, &summed, 0, st);
     if (rc != DLCX_OK) return rc;
-    int rmax = 0;
-    for (int i = 0; i < batch.n; ++i) rmax = batch.it[i].r > rmax ? batch.it[i].r : rmax;
+    int rmax = 0, rmin = DLCX_MAX_RANK;
+    bool rmid = false;
+    for (int i = 0; i < batch.n; ++i) {
+        const int r = batch.it[i].r;
+        rmax = r > rmax ? r : rmax;
+        rmin = r < rmin ? r : rmin;
+        rmid = rmid || (r > 32 && r <= kFusedRank);
+    }
     Timed timed(KID_JACOBI, st);
     const dim3 grid((unsigned)batch.n), threads(kTT);
-    if (rmax <= 64)
-        hipLaunchKernelGGL(tridiag_kernel<4>, grid, threads, 0, st, summed, tau);
-    else if (rmax <= 128)
-        hipLaunchKernelGGL(tridiag_kernel<8>, grid, threads, 0, st, summed, tau);
-    else if (rmax <= 192)
-        hipLaunchKernelGGL(tridiag_kernel<12>, grid, threads, 0, st, summed, tau);
-    else
-        hipLaunchKernelGGL(tridiag_kernel<16>, grid, threads, 0, st, summed, tau);
+    // each kernel leaves the factors of another rank class alone
+    if (rmin <= 32) hipLaunchKernelGGL(tridiag_small_kernel<32>, grid, threads, 0, st, summed, tau);
+    if (rmid) hipLaunchKernelGGL(tridiag_small_kernel<64>, grid, threads, 0, st, summed, tau);
     if (rmax > kFusedRank) {
+        if (rmax <= 128)
+            hipLaunchKernelGGL(tridiag_kernel<8>, grid, threads, 0, st, summed);
+        else if (rmax <= 192)
+            hipLaunchKernelGGL(tridiag_kernel<12>, grid, threads, 0, st, summed);
+        else
+            hipLaunchKernelGGL(tridiag_kernel<16>, grid, threads, 0, st, summed);
         hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
                            dim3(256), 0, st, summed);
         hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
