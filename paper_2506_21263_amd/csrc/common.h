@@ -58,6 +58,16 @@ int launch_nesterov(float *theta, float *v, const float *g, int64_t numel, float
 int launch_quantize(int K, const PtrPack<const float *> &x, int64_t count, int qbits, int group,
                     const PtrPack<uint8_t *> &codes, const PtrPack<float *> &scales,
                     hipStream_t st);
+// The same on sums that are still partial: x[k] = sum_s slabs[k][s] in slab order (S slabs `stride`
+// floats apart) is written to sums.p[k] and quantised in one pass.
+struct PartialSums {
+    int S = 1;  // 1: nothing to add, the sums are where they belong
+    int64_t stride = 0;
+    PtrPack<const float *> slabs;
+};
+int launch_sum_quantize(int K, const PartialSums &part, const PtrPack<float *> &sums,
+                        int64_t count, int qbits, int group, const PtrPack<uint8_t *> &codes,
+                        const PtrPack<float *> &scales, hipStream_t st);
 int launch_dequant_average(int K, const PtrPack<const uint8_t *> &codes,
                            const PtrPack<const float *> &scales, int64_t count, int qbits,
                            int group, float *mean_out, hipStream_t st);
@@ -83,10 +93,15 @@ int launch_traffic_probe(int K, const PtrPack<float *> &ef, const PtrPack<const 
 int launch_project_p(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *q_in,
                      const PtrPack<float *> &out, void *workspace, hipStream_t st);
-// Q_k = delta_k^T * P_hat (p_hat r x m, out r x n)
+// Q_k = delta_k^T * P_hat (p_hat r x m, out r x n).  Rows are split where the columns alone do not
+// fill the GPU: with `partial` the sums over the splits are left to the caller, else formed here.
 int launch_project_q(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *p_hat,
-                     const PtrPack<float *> &out, void *workspace, hipStream_t st);
+                     const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                     hipStream_t st);
+// out[k] = sum_s slabs[k][s], s in index order
+int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<float *> &outs,
+                     int64_t count, int S, int64_t slab_stride, hipStream_t st);
 // What happens to each tile d of delta_hat = P_hat Q_bar^T, in this order:
 //   out            : d is written
 //   K > 0          : e_k <- e_k - d                     (error buffers of Alg. 2)

@@ -65,7 +65,7 @@ Timed::~Timed() {
 int launch_project_p_fma(int64_t, int64_t, int, int, const PtrPack<const float *> &, const float *,
                          const PtrPack<float *> &, hipStream_t);
 int launch_project_q_fma(int64_t, int64_t, int, int, const PtrPack<const float *> &, const float *,
-                         const PtrPack<float *> &, void *, hipStream_t);
+                         const PtrPack<float *> &, void *, PartialSums *, hipStream_t);
 int launch_reconstruct_fma(int64_t, int64_t, int, const float *, const float *,
                            const ReconEpilogue &, hipStream_t);
 size_t fma_project_workspace_bytes(int64_t, int64_t, int, int);
@@ -73,14 +73,16 @@ size_t fma_project_workspace_bytes(int64_t, int64_t, int, int);
 int launch_project_p_mfma(int, int64_t, int64_t, int, int, const PtrPack<const float *> &,
                           const float *, const PtrPack<float *> &, void *, hipStream_t);
 int launch_project_q_mfma(int, int64_t, int64_t, int, int, const PtrPack<const float *> &,
-                          const float *, const PtrPack<float *> &, void *, hipStream_t);
+                          const float *, const PtrPack<float *> &, void *, PartialSums *,
+                          hipStream_t);
 int launch_reconstruct_mfma(int, int64_t, int64_t, int, const float *, const float *,
                             const ReconEpilogue &, void *, hipStream_t);
 size_t mfma_project_workspace_bytes(int, int64_t, int64_t, int, int);
 size_t mfma_reconstruct_workspace_bytes(int, int64_t, int64_t, int);
 size_t mfma_round_workspace_bytes(int, int64_t, int64_t, int, int, int);
 int launch_round_mfma(int, int64_t, int64_t, int, int, const float *, const float *, const float *,
-                      const ReconEpilogue &, const PtrPack<float *> &, void *, hipStream_t);
+                      const ReconEpilogue &, const PtrPack<float *> &, void *, PartialSums *,
+                      hipStream_t);
 
 static bool group_ok(int g) { return g == 16 || g == 32 || g == 64 || g == 128 || g == 256; }
 
@@ -116,9 +118,11 @@ int launch_project_p(int mma, int64_t m, int64_t n, int r, int K,
 
 int launch_project_q(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *p_hat,
-                     const PtrPack<float *> &out, void *workspace, hipStream_t st) {
-    if (mma == DLCX_MMA_FMA) return launch_project_q_fma(m, n, r, K, delta, p_hat, out, workspace, st);
-    return launch_project_q_mfma(mma, m, n, r, K, delta, p_hat, out, workspace, st);
+                     const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                     hipStream_t st) {
+    if (mma == DLCX_MMA_FMA)
+        return launch_project_q_fma(m, n, r, K, delta, p_hat, out, workspace, partial, st);
+    return launch_project_q_mfma(mma, m, n, r, K, delta, p_hat, out, workspace, partial, st);
 }
 
 size_t reconstruct_workspace_bytes(int mma, int64_t m, int64_t n, int r) {
@@ -417,9 +421,10 @@ int dlcx_plan_overlap(const dlcx_desc *descs_host, int n_matrices, double extra_
     return DLCX_OK;
 }
 
-int dlcx_project(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
-                 const float *basis, float *const *factors_out_host, void *workspace,
-                 void *stream) {
+// partial: the sums over row splits are left to the caller (nullptr: formed here)
+static int project(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
+                   const float *basis, float *const *factors_out_host, void *workspace,
+                   PartialSums *partial, void *stream) {
     int rc = check_desc(desc);
     if (rc != DLCX_OK) return rc;
     if (phase != DLCX_PHASE_P && phase != DLCX_PHASE_Q) return DLCX_EINVAL;
@@ -439,8 +444,14 @@ int dlcx_project(const dlcx_desc *desc, int phase, int K, const float *const *de
     if (phase == DLCX_PHASE_P)
         return launch_project_p(desc->mma, desc->m, desc->n, desc->r, K, d, basis, o, workspace,
                                 as_stream(stream));
-    return launch_project_q(desc->mma, desc->m, desc->n, desc->r, K, d, basis, o, workspace,
+    return launch_project_q(desc->mma, desc->m, desc->n, desc->r, K, d, basis, o, workspace, partial,
                             as_stream(stream));
+}
+
+int dlcx_project(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
+                 const float *basis, float *const *factors_out_host, void *workspace,
+                 void *stream) {
+    return project(desc, phase, K, deltas_host, basis, factors_out_host, workspace, nullptr, stream);
 }
 
 int dlcx_quantize(const float *x, int64_t count, int qbits, int group, uint8_t *codes_out,
@@ -472,22 +483,22 @@ int dlcx_compress_batched(const dlcx_desc *desc, int phase, int K,
     if (!aligned16(workspace)) return DLCX_EINVAL;
     const int64_t L = phase == DLCX_PHASE_P ? desc->m : desc->n;
     const int64_t count = (int64_t)desc->r * L;
-    float *factors[DLCX_MAX_WORKERS];
-    PtrPack<const float *> xs;
+    PtrPack<float *> factors;
     PtrPack<uint8_t *> cs;
     PtrPack<float *> ss;
     for (int k = 0; k < K; ++k) {
         if (!codes_out_host[k] || !scales_out_host[k]) return DLCX_EINVAL;
         if (!aligned16(codes_out_host[k]) || !aligned16(scales_out_host[k])) return DLCX_EINVAL;
-        factors[k] = reinterpret_cast<float *>(workspace) + (int64_t)k * count;
-        xs.p[k] = factors[k];
+        factors.p[k] = reinterpret_cast<float *>(workspace) + (int64_t)k * count;
         cs.p[k] = codes_out_host[k];
         ss.p[k] = scales_out_host[k];
     }
     void *inner = reinterpret_cast<char *>(workspace) + factor_region_bytes(desc, K);
-    rc = dlcx_project(desc, phase, K, deltas_host, basis, factors, inner, stream);
+    PartialSums partial;
+    rc = project(desc, phase, K, deltas_host, basis, factors.p, inner, &partial, stream);
     if (rc != DLCX_OK) return rc;
-    return launch_quantize(K, xs, count, desc->qbits, desc->group, cs, ss, as_stream(stream));
+    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss,
+                               as_stream(stream));
 }
 
 int dlcx_compress(const dlcx_desc *desc, int phase, const float *delta, const float *basis,
@@ -723,22 +734,22 @@ int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const fl
     ep.lr = lr;
     ep.mu = mu;
     PtrPack<float *> factors;
-    PtrPack<const float *> xs;
     PtrPack<uint8_t *> cs;
     PtrPack<float *> ss;
     for (int k = 0; k < K; ++k) {
         ep.ef.p[k] = ef_inout_host[k];
         ep.tl.p[k] = theta_l_host[k];
         factors.p[k] = reinterpret_cast<float *>(workspace) + (int64_t)k * count;
-        xs.p[k] = factors.p[k];
         cs.p[k] = codes_out_host[k];
         ss.p[k] = scales_out_host[k];
     }
     void *inner = reinterpret_cast<char *>(workspace) + factor_region_bytes(desc, K);
+    PartialSums partial;
     rc = launch_round_mfma(desc->mma, desc->m, desc->n, desc->r, r_prev, p_hat, q_bar, basis, ep,
-                           factors, inner, as_stream(stream));
+                           factors, inner, &partial, as_stream(stream));
     if (rc != DLCX_OK) return rc;
-    return launch_quantize(K, xs, count, desc->qbits, desc->group, cs, ss, as_stream(stream));
+    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss,
+                               as_stream(stream));
 }
 
 int dlcx_effective_rank(int64_t L, int32_t r, const float *q_bar, double tau,

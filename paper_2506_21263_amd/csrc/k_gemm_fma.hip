@@ -368,7 +368,7 @@ int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
 
 int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                          const float *p_hat, const PtrPack<float *> &out, void *workspace,
-                         hipStream_t st) {
+                         PartialSums *partial, hipStream_t st) {
     const int64_t rows = ceil_div(ceil_div(m, q_splits(m, n, K)), 64) * 64;
     const int S = (int)ceil_div(m, rows);  // no more than q_splits: the slabs fit
     const int64_t slab = (int64_t)r * n;
@@ -394,9 +394,15 @@ int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
         rc = check_launch("project_q_f64");
     }
     if (rc != DLCX_OK || S == 1) return rc;
-    PtrPack<const float *> src;
-    for (int k = 0; k < K; ++k) src.p[k] = dst.p[k];
-    return launch_sum_slabs(K, src, out, slab, S, slab, st);
+    PartialSums sums;
+    sums.S = S;
+    sums.stride = slab;
+    for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k];
+    if (partial) {
+        *partial = sums;
+        return DLCX_OK;
+    }
+    return launch_sum_slabs(K, sums.slabs, out, slab, S, slab, st);
 }
 
 int launch_reconstruct_fma(int64_t m, int64_t n, int r, const float *p_hat, const float *q_bar,

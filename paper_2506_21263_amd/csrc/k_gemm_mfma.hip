@@ -21,7 +21,8 @@
 // the operand layout with 128-byte row segments (Q phase, reduction down a column).
 //
 // Kernels in this file:
-//   pack_kcontig_kernel / pack_kstrided_kernel   fragments of a basis / of a factor
+//   pack_kcontig_kernel, pack_f16_kernel, pack_sweep_kernel   fragments of a basis, of both forms
+//                                                 of a basis, of all operands of a sweep
 //   project_p_mfma_kernel, project_q_mfma_kernel  projections, every wavefront does everything
 //                                                 (r <= 32, and P for matrices with few rows)
 //   project_p_ws_kernel, project_q_ws_kernel      projections with producer and consumer
@@ -144,34 +145,59 @@ __device__ __forceinline__ void stream_store4(float *p, const float4 &a) {
 // src is nrows x L with the reduction index contiguous (a basis: Q_in is r x n, P_hat is r x m).
 // Fragment (s, rb, h): rows rb*32 .. +32, reduction indices s*16 .. +16, piece h, at
 // frags[((s * RB + rb) * NS + h) * 64 + lane].  Rows >= nrows and indices >= L are zero.
-template <int NS>
-__global__ __launch_bounds__(kW) void pack_kcontig_kernel(const float *__restrict__ src,
-                                                          int nrows, int64_t L, int RB,
-                                                          int64_t KS, uint4 *__restrict__ frags,
-                                                          const float *__restrict__ row_scale) {
-    const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (f >= KS * RB) return;
-    const int64_t s = f / RB;
-    const int rb = (int)(f % RB);
-    const int row = rb * 32 + (lane & 31);
-    const int64_t k0 = s * 16 + (lane >> 5) * 8;
-    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (row < nrows && k0 < L) {  // L is a multiple of 8
-        const float4 a = *reinterpret_cast<const float4 *>(src + (int64_t)row * L + k0);
-        const float4 b = *reinterpret_cast<const float4 *>(src + (int64_t)row * L + k0 + 4);
-        x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-        x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-        if (row_scale) {  // a power of two per row: exact
-            const float sc = row_scale[row];
+struct KContig {
+    const float *src;
+    int nrows;
+    int64_t L;
+    int RB;
+    int64_t KS;
+    uint4 *frags;
+    __host__ __device__ int64_t count() const { return KS * RB; }
+};
+__device__ __forceinline__ bool load_kcontig(const KContig &p, int64_t f, int lane, float (&x)[8]) {
+    const int row = (int)(f % p.RB) * 32 + (lane & 31);
+    const int64_t k0 = f / p.RB * 16 + (lane >> 5) * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] *= sc;
-        }
-    }
+    for (int e = 0; e < 8; ++e) x[e] = 0.f;
+    if (row >= p.nrows || k0 >= p.L) return false;  // L is a multiple of 8
+    const float4 a = *reinterpret_cast<const float4 *>(p.src + (int64_t)row * p.L + k0);
+    const float4 b = *reinterpret_cast<const float4 *>(p.src + (int64_t)row * p.L + k0 + 4);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+    return true;
+}
+template <int NS>
+__device__ __forceinline__ void store_frags(uint4 *frags, int64_t f, int lane, const float (&x)[8]) {
     uint4 out[NS];
     split8<NS>(x, out);
 #pragma unroll
     for (int h = 0; h < NS; ++h) frags[(f * NS + h) * 64 + lane] = out[h];
+}
+
+template <int NS>
+__global__ __launch_bounds__(kW) void pack_kcontig_kernel(KContig p) {
+    const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (f >= p.count()) return;
+    float x[8];
+    load_kcontig(p, f, lane, x);
+    store_frags<NS>(p.frags, f, lane, x);
+}
+
+// Both forms a DLCX_MMA_F16 projection keeps ready, from one read of the basis: two bf16 pieces for
+// the stand-by and one fp16 piece of the rows scaled by row_scale (powers of two: exact).
+__global__ __launch_bounds__(kW) void pack_f16_kernel(KContig p, uint4 *__restrict__ frags_f16,
+                                                      const float *__restrict__ row_scale) {
+    const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (f >= p.count()) return;
+    float x[8];
+    const bool in = load_kcontig(p, f, lane, x);
+    store_frags<2>(p.frags, f, lane, x);
+    const float sc = in ? row_scale[(int)(f % p.RB) * 32 + (lane & 31)] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= sc;
+    store_frags<1>(frags_f16, f, lane, x);
 }
 
 // The fp16 form of a projection (NS == 1) needs its operands inside fp16's range.  delta is
@@ -227,25 +253,45 @@ __device__ __forceinline__ void record_amax(float a, uint32_t *record) {
 // src is r x L with the reduction index c strided (a factor used in the reconstruction).
 // Fragment (xb, s, h): positions xb*32 .. +32 along L, reduction indices s*16 .. +16, at
 // frags[((xb * KS + s) * NS + h) * 64 + lane].
+struct KStrided {
+    const float *src;
+    int r;
+    int64_t L;
+    int KS;
+    int64_t XB;
+    uint4 *frags;
+    __host__ __device__ int64_t count() const { return XB * KS; }
+};
 template <int NS>
-__global__ __launch_bounds__(kW) void pack_kstrided_kernel(const float *__restrict__ src, int r,
-                                                           int64_t L, int KS, int64_t XB,
-                                                           uint4 *__restrict__ frags) {
-    const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (f >= XB * KS) return;
-    const int64_t xb = f / KS;
-    const int s = (int)(f % KS);
-    const int64_t x0 = xb * 32 + (lane & 31);
-    const int c0 = s * 16 + (lane >> 5) * 8;
+__device__ __forceinline__ void pack_kstrided(const KStrided &p, int64_t f, int lane) {
+    const int64_t x0 = f / p.KS * 32 + (lane & 31);
+    const int c0 = (int)(f % p.KS) * 16 + (lane >> 5) * 8;
     float x[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-        x[e] = (x0 < L && c0 + e < r) ? src[(int64_t)(c0 + e) * L + x0] : 0.f;
-    uint4 out[NS];
-    split8<NS>(x, out);
-#pragma unroll
-    for (int h = 0; h < NS; ++h) frags[(f * NS + h) * 64 + lane] = out[h];
+        x[e] = (x0 < p.L && c0 + e < p.r) ? p.src[(int64_t)(c0 + e) * p.L + x0] : 0.f;
+    store_frags<NS>(p.frags, f, lane, x);
+}
+
+// Everything a sweep needs packed, in one launch (three of them in a row cost 4 - 5 us each, whatever
+// the size): the fragments of the basis (if any), then those of both factors of the reconstruction.
+template <int NS>
+__global__ __launch_bounds__(kW) void pack_sweep_kernel(KContig basis, KStrided p_hat, KStrided q_bar) {
+    int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (f < basis.count()) {
+        float x[8];
+        load_kcontig(basis, f, lane, x);
+        store_frags<NS>(basis.frags, f, lane, x);
+        return;
+    }
+    f -= basis.count();
+    if (f < p_hat.count()) {
+        pack_kstrided<NS>(p_hat, f, lane);
+        return;
+    }
+    f -= p_hat.count();
+    if (f < q_bar.count()) pack_kstrided<NS>(q_bar, f, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1329,13 +1375,20 @@ size_t mfma_project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K)
 }
 
 template <int NS>
-static int pack_kcontig(const float *src, int nrows, int64_t L, int RB, int64_t KS, uint4 *frags,
-                        hipStream_t st, const float *row_scale = nullptr) {
-    const int64_t nf = KS * RB;
+static int pack_kcontig(const KContig &p, hipStream_t st) {
     Timed timed(KID_PACK, st);
-    hipLaunchKernelGGL(pack_kcontig_kernel<NS>, dim3((unsigned)ceil_div(nf, 4)), dim3(kW), 0, st,
-                       src, nrows, L, RB, KS, frags, row_scale);
+    hipLaunchKernelGGL(pack_kcontig_kernel<NS>, dim3((unsigned)ceil_div(p.count(), 4)), dim3(kW), 0, st, p);
     return check_launch("pack_kcontig");
+}
+
+template <int NS>
+static int pack_sweep(const KContig &basis, const KStrided &p_hat, const KStrided &q_bar,
+                      hipStream_t st) {
+    const int64_t nf = basis.count() + p_hat.count() + q_bar.count();
+    Timed timed(KID_PACK, st);
+    hipLaunchKernelGGL(pack_sweep_kernel<NS>, dim3((unsigned)ceil_div(nf, 4)), dim3(kW), 0, st, basis,
+                       p_hat, q_bar);
+    return check_launch("pack_sweep");
 }
 
 // scales and record of the fp16 form inside its scratch block
@@ -1350,11 +1403,16 @@ static F16Scratch f16_scratch(void *block) {
     f.record = reinterpret_cast<uint32_t *>(f.out_scale + DLCX_MAX_RANK);
     return f;
 }
-static int basis_scales(const float *basis, int r, int64_t L, const F16Scratch &f, hipStream_t st) {
+// the scales of the fp16 form, then both forms of the fragments
+static int pack_f16(const KContig &p, uint4 *frags_f16, const F16Scratch &f, hipStream_t st) {
     Timed timed(KID_PACK, st);
-    hipLaunchKernelGGL(basis_scale_kernel, dim3((unsigned)r), dim3(kW), 0, st, basis, L, f.in_scale,
-                       f.out_scale, f.record);
-    return check_launch("basis_scale");
+    hipLaunchKernelGGL(basis_scale_kernel, dim3((unsigned)p.nrows), dim3(kW), 0, st, p.src, p.L,
+                       f.in_scale, f.out_scale, f.record);
+    int rc = check_launch("basis_scale");
+    if (rc != DLCX_OK) return rc;
+    hipLaunchKernelGGL(pack_f16_kernel, dim3((unsigned)ceil_div(p.count(), 4)), dim3(kW), 0, st, p,
+                       frags_f16, f.in_scale);
+    return check_launch("pack_f16");
 }
 
 template <int NS, int CBW, int WC, int WK, int WR, int RB>
@@ -1405,9 +1463,7 @@ static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<cons
     uint4 *frags2 = reinterpret_cast<uint4 *>(ws);                                // two bf16 pieces
     uint4 *frags1 = reinterpret_cast<uint4 *>(ws + (size_t)KS * cb * 2 * 1024);   // one fp16 piece
     const F16Scratch f = f16_scratch(ws + a256((size_t)KS * cb * 3 * 1024));
-    int rc = basis_scales(q_in, r, n, f, st);
-    if (rc == DLCX_OK) rc = pack_kcontig<1>(q_in, r, n, cb, KS, frags1, st, f.in_scale);
-    if (rc == DLCX_OK) rc = pack_kcontig<2>(q_in, r, n, cb, KS, frags2, st);
+    int rc = pack_f16(KContig{q_in, r, n, cb, KS, frags2}, frags1, f, st);
     if (rc == DLCX_OK) {
         Timed timed(KID_PROJECT_P, st);
         if (cb == 4) {
@@ -1432,7 +1488,7 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     const int cb = cb_of(r);
     const int64_t KS = ceil_div(n, 64) * 4;
     uint4 *frags = reinterpret_cast<uint4 *>(workspace);
-    int rc = pack_kcontig<NS>(q_in, r, n, cb, KS, frags, st);
+    int rc = pack_kcontig<NS>(KContig{q_in, r, n, cb, KS, frags}, st);
     if (rc != DLCX_OK) return rc;
     Timed timed(KID_PROJECT_P, st);
     switch (cb) {
@@ -1461,9 +1517,6 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     return check_launch("project_p_mfma");
 }
 
-int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<float *> &outs,
-                     int64_t count, int S, int64_t slab_stride, hipStream_t st);
-
 template <int NS, int CBW, int WCB>
 static int project_q_ws_launch(const dim3 &grid, hipStream_t st, const PtrPack<const float *> &delta,
                                const uint4 *frags, const PtrPack<float *> &dst, int64_t m,
@@ -1485,7 +1538,7 @@ static int project_q_ws_launch(const dim3 &grid, hipStream_t st, const PtrPack<c
 template <int NS, bool F16>
 static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                         const float *p_hat, const PtrPack<float *> &out, void *workspace,
-                        hipStream_t st) {
+                        PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
     const QPlan q = q_plan(m, n, r, K);
     const bool f16 = F16 && cb >= 4;
@@ -1498,11 +1551,10 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     if (f16) {
         const size_t slab_bytes = q.S > 1 ? a256((size_t)K * q.S * r * n * sizeof(float)) : 0;
         f = f16_scratch(wsb + a256((size_t)q.KS * cb * pieces * 1024) + slab_bytes);
-        rc = basis_scales(p_hat, r, m, f, st);
-        if (rc == DLCX_OK) rc = pack_kcontig<1>(p_hat, r, m, cb, q.KS, frags1, st, f.in_scale);
-        if (rc != DLCX_OK) return rc;
+        rc = pack_f16(KContig{p_hat, r, m, cb, q.KS, frags}, frags1, f, st);
+    } else {
+        rc = pack_kcontig<NS>(KContig{p_hat, r, m, cb, q.KS, frags}, st);
     }
-    rc = pack_kcontig<NS>(p_hat, r, m, cb, q.KS, frags, st);
     if (rc != DLCX_OK) return rc;
     const int64_t slab = (int64_t)r * n;
     PtrPack<float *> dst = out;
@@ -1528,9 +1580,15 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     if (rc == DLCX_OK) rc = check_launch("project_q_mfma");
     }
     if (rc != DLCX_OK || q.S == 1) return rc;
-    PtrPack<const float *> src;
-    for (int k = 0; k < K; ++k) src.p[k] = dst.p[k];
-    return launch_sum_slabs(K, src, out, slab, q.S, slab, st);
+    PartialSums sums;
+    sums.S = q.S;
+    sums.stride = slab;
+    for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k];
+    if (partial) {
+        *partial = sums;
+        return DLCX_OK;
+    }
+    return launch_sum_slabs(K, sums.slabs, out, slab, q.S, slab, st);
 }
 
 int launch_project_p_mfma(int mma, int64_t m, int64_t n, int r, int K,
@@ -1545,12 +1603,13 @@ int launch_project_p_mfma(int mma, int64_t m, int64_t n, int r, int K,
 
 int launch_project_q_mfma(int mma, int64_t m, int64_t n, int r, int K,
                           const PtrPack<const float *> &delta, const float *p_hat,
-                          const PtrPack<float *> &out, void *workspace, hipStream_t st) {
+                          const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                          hipStream_t st) {
     if (mma == DLCX_MMA_F32)
-        return project_q_ns<3, false>(m, n, r, K, delta, p_hat, out, workspace, st);
+        return project_q_ns<3, false>(m, n, r, K, delta, p_hat, out, workspace, partial, st);
     if (mma == DLCX_MMA_F16)
-        return project_q_ns<2, true>(m, n, r, K, delta, p_hat, out, workspace, st);
-    return project_q_ns<2, false>(m, n, r, K, delta, p_hat, out, workspace, st);
+        return project_q_ns<2, true>(m, n, r, K, delta, p_hat, out, workspace, partial, st);
+    return project_q_ns<2, false>(m, n, r, K, delta, p_hat, out, workspace, partial, st);
 }
 
 size_t mfma_reconstruct_workspace_bytes(int mma, int64_t m, int64_t n, int r) {
@@ -1584,20 +1643,8 @@ static int reconstruct_ns(int64_t m, int64_t n, int r, const float *p_hat, const
     uint4 *pf = reinterpret_cast<uint4 *>(workspace);
     uint4 *qf = reinterpret_cast<uint4 *>(reinterpret_cast<char *>(workspace) +
                                           a256((size_t)xbm * ks * NS * 1024));
-    int rc;
-    {
-        Timed timed(KID_PACK, st);
-        hipLaunchKernelGGL(pack_kstrided_kernel<NS>, dim3((unsigned)ceil_div(xbm * ks, 4)), dim3(kW), 0,
-                           st, p_hat, r, m, ks, xbm, pf);
-        rc = check_launch("pack p_hat");
-    }
-    if (rc != DLCX_OK) return rc;
-    {
-        Timed timed(KID_PACK, st);
-        hipLaunchKernelGGL(pack_kstrided_kernel<NS>, dim3((unsigned)ceil_div(xbn * ks, 4)), dim3(kW), 0,
-                           st, q_bar, r, n, ks, xbn, qf);
-        rc = check_launch("pack q_bar");
-    }
+    const int rc = pack_sweep<NS>(KContig{}, KStrided{p_hat, r, m, ks, xbm, pf},
+                                  KStrided{q_bar, r, n, ks, xbn, qf}, st);
     if (rc != DLCX_OK) return rc;
     return reconstruct_launch<NS>(m, n, ks, pf, qf, ep, st);
 }
@@ -1684,7 +1731,7 @@ static int round_launch(const uint4 *pf, const uint4 *qf, int ks, const uint4 *b
 template <int NS>
 static int round_ns(int64_t m, int64_t n, int r, int r_prev, const float *p_hat, const float *q_bar,
                     const float *basis, const ReconEpilogue &ep_all, const PtrPack<float *> &factors,
-                    void *workspace, hipStream_t st) {
+                    void *workspace, PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
     const RoundPlan pl = round_plan(m, n, r);
     const int ks = (r_prev + 15) / 16;
@@ -1697,24 +1744,11 @@ static int round_ns(int64_t m, int64_t n, int r, int r_prev, const float *p_hat,
     uint4 *qf = reinterpret_cast<uint4 *>(ws);
     ws += a256((size_t)xbn * ks * NS * 1024);
     float *slabs = reinterpret_cast<float *>(ws);
-    int rc = pack_kcontig<NS>(basis, r, n, cb, ceil_div(n, 64) * 4, bf, st);
+    // (r_prev == 0: no factors to pack)
+    int rc = pack_sweep<NS>(KContig{basis, r, n, cb, ceil_div(n, 64) * 4, bf},
+                            KStrided{p_hat, r_prev, m, ks, ks > 0 ? xbm : 0, pf},
+                            KStrided{q_bar, r_prev, n, ks, ks > 0 ? xbn : 0, qf}, st);
     if (rc != DLCX_OK) return rc;
-    if (ks > 0) {
-        {
-            Timed timed(KID_PACK, st);
-            hipLaunchKernelGGL(pack_kstrided_kernel<NS>, dim3((unsigned)ceil_div(xbm * ks, 4)),
-                               dim3(kW), 0, st, p_hat, r_prev, m, ks, xbm, pf);
-            rc = check_launch("pack p_hat");
-        }
-        if (rc != DLCX_OK) return rc;
-        {
-            Timed timed(KID_PACK, st);
-            hipLaunchKernelGGL(pack_kstrided_kernel<NS>, dim3((unsigned)ceil_div(xbn * ks, 4)),
-                               dim3(kW), 0, st, q_bar, r_prev, n, ks, xbn, qf);
-            rc = check_launch("pack q_bar");
-        }
-        if (rc != DLCX_OK) return rc;
-    }
     const int64_t slab = (int64_t)r * m;
     for (int k0 = 0; k0 < ep_all.K; k0 += pl.kc) {
         ReconEpilogue ep = ep_all;
@@ -1734,18 +1768,21 @@ static int round_ns(int64_t m, int64_t n, int r, int r_prev, const float *p_hat,
         }
         if (rc != DLCX_OK) return rc;
     }
-    if (pl.chunks == 1) return DLCX_OK;
-    PtrPack<const float *> src;
-    for (int k = 0; k < ep_all.K; ++k) src.p[k] = slabs + (int64_t)k * pl.chunks * slab;
-    return launch_sum_slabs(ep_all.K, src, factors, slab, pl.chunks, slab, st);
+    partial->S = pl.chunks;
+    partial->stride = slab;
+    for (int k = 0; k < ep_all.K; ++k) partial->slabs.p[k] = slabs + (int64_t)k * pl.chunks * slab;
+    return DLCX_OK;
 }
 
 int launch_round_mfma(int mma, int64_t m, int64_t n, int r, int r_prev, const float *p_hat,
                       const float *q_bar, const float *basis, const ReconEpilogue &ep,
-                      const PtrPack<float *> &factors, void *workspace, hipStream_t st) {
+                      const PtrPack<float *> &factors, void *workspace, PartialSums *partial,
+                      hipStream_t st) {
     if (mma == DLCX_MMA_F32)
-        return round_ns<3>(m, n, r, r_prev, p_hat, q_bar, basis, ep, factors, workspace, st);
-    return round_ns<2>(m, n, r, r_prev, p_hat, q_bar, basis, ep, factors, workspace, st);
+        return round_ns<3>(m, n, r, r_prev, p_hat, q_bar, basis, ep, factors, workspace, partial,
+                           st);
+    return round_ns<2>(m, n, r, r_prev, p_hat, q_bar, basis, ep, factors, workspace, partial,
+                           st);
 }
 
 }  // namespace dlcx

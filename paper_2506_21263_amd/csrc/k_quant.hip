@@ -17,17 +17,29 @@ __device__ __forceinline__ float group_max(float a) {
     return a;
 }
 
-template <int kQbits, int kLanes>
+// kSum: the input is S partial sums, added in order and written to sums[k] on the way (a pass of its
+// own over them, 4 - 5 us behind every projection, cost as much as the quantiser itself).
+template <int kQbits, int kLanes, bool kSum>
 __global__ __launch_bounds__(kQThreads) void quantize_kernel(PtrPack<const float *> xs,
                                                              int64_t nvec,
                                                              PtrPack<uint8_t *> codes,
-                                                             PtrPack<float *> scales) {
+                                                             PtrPack<float *> scales, int S,
+                                                             int64_t stride, PtrPack<float *> sums) {
     const int k = blockIdx.y;
     const float *__restrict__ x = xs.p[k];
     const int64_t v = (int64_t)blockIdx.x * kQThreads + threadIdx.x;
     const bool live = v < nvec;  // whole groups are live or dead together
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if (live) a = reinterpret_cast<const float4 *>(x)[v];
+    if constexpr (kSum) {
+        if (live) {
+            for (int s = 1; s < S; ++s) {
+                const float4 b = reinterpret_cast<const float4 *>(x + (int64_t)s * stride)[v];
+                a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+            }
+            reinterpret_cast<float4 *>(sums.p[k])[v] = a;
+        }
+    }
     float amax = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w)));
     amax = group_max<kLanes>(amax);
     constexpr float qmax = (float)((1 << (kQbits - 1)) - 1);
@@ -93,19 +105,19 @@ __global__ __launch_bounds__(kQThreads) void dequant_average_kernel(
     reinterpret_cast<float4 *>(out)[v] = make_float4((float)a0, (float)a1, (float)a2, (float)a3);
 }
 
-template <int kQbits>
+template <int kQbits, bool kSum>
 static int quantize_dispatch(int K, const PtrPack<const float *> &x, int64_t nvec, int group,
                              const PtrPack<uint8_t *> &codes, const PtrPack<float *> &scales,
-                             hipStream_t st) {
+                             int S, int64_t stride, const PtrPack<float *> &sums, hipStream_t st) {
     const dim3 grid((unsigned)ceil_div(nvec, kQThreads), (unsigned)K);
     const dim3 block(kQThreads);
     Timed timed(KID_QUANTIZE, st);
     switch (group) {
-        case 16: hipLaunchKernelGGL((quantize_kernel<kQbits, 4>), grid, block, 0, st, x, nvec, codes, scales); break;
-        case 32: hipLaunchKernelGGL((quantize_kernel<kQbits, 8>), grid, block, 0, st, x, nvec, codes, scales); break;
-        case 64: hipLaunchKernelGGL((quantize_kernel<kQbits, 16>), grid, block, 0, st, x, nvec, codes, scales); break;
-        case 128: hipLaunchKernelGGL((quantize_kernel<kQbits, 32>), grid, block, 0, st, x, nvec, codes, scales); break;
-        case 256: hipLaunchKernelGGL((quantize_kernel<kQbits, 64>), grid, block, 0, st, x, nvec, codes, scales); break;
+        case 16: hipLaunchKernelGGL((quantize_kernel<kQbits, 4, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
+        case 32: hipLaunchKernelGGL((quantize_kernel<kQbits, 8, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
+        case 64: hipLaunchKernelGGL((quantize_kernel<kQbits, 16, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
+        case 128: hipLaunchKernelGGL((quantize_kernel<kQbits, 32, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
+        case 256: hipLaunchKernelGGL((quantize_kernel<kQbits, 64, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
         default: return DLCX_EINVAL;
     }
     return check_launch("quantize");
@@ -116,8 +128,27 @@ int launch_quantize(int K, const PtrPack<const float *> &x, int64_t count, int q
                     hipStream_t st) {
     if (count == 0 || K == 0) return DLCX_OK;
     const int64_t nvec = count >> 2;
-    if (qbits == 4) return quantize_dispatch<4>(K, x, nvec, group, codes, scales, st);
-    return quantize_dispatch<8>(K, x, nvec, group, codes, scales, st);
+    const PtrPack<float *> none = {};
+    if (qbits == 4)
+        return quantize_dispatch<4, false>(K, x, nvec, group, codes, scales, 1, 0, none, st);
+    return quantize_dispatch<8, false>(K, x, nvec, group, codes, scales, 1, 0, none, st);
+}
+
+int launch_sum_quantize(int K, const PartialSums &part, const PtrPack<float *> &sums,
+                        int64_t count, int qbits, int group, const PtrPack<uint8_t *> &codes,
+                        const PtrPack<float *> &scales, hipStream_t st) {
+    if (count == 0 || K == 0) return DLCX_OK;
+    const int64_t nvec = count >> 2;
+    if (part.S == 1) {
+        PtrPack<const float *> x;
+        for (int k = 0; k < K; ++k) x.p[k] = sums.p[k];
+        return launch_quantize(K, x, count, qbits, group, codes, scales, st);
+    }
+    if (qbits == 4)
+        return quantize_dispatch<4, true>(K, part.slabs, nvec, group, codes, scales, part.S,
+                                          part.stride, sums, st);
+    return quantize_dispatch<8, true>(K, part.slabs, nvec, group, codes, scales, part.S, part.stride,
+                                      sums, st);
 }
 
 int launch_dequant_average(int K, const PtrPack<const uint8_t *> &codes,
