@@ -933,20 +933,27 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// LDS of one wavefront's tile: fp32, or bf16 pieces
+constexpr int round_tile_bytes(int ns) {
+    return 32 * kRPitch * 4 > ns * 32 * kPPitch ? 32 * kRPitch * 4 : ns * 32 * kPPitch;
+}
+
 template <int NS, int CB, int KC, bool TLBF16>
 __global__ __launch_bounds__(kW) void round_mfma_kernel(
     const uint4 *__restrict__ pfrags, const uint4 *__restrict__ qfrags, int KS,
     const uint4 *__restrict__ bfrags, ReconEpilogue ep, PtrPack<float *> pslab, int64_t m,
     int64_t n, int r, int64_t cols_per_wg, int64_t slab_stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int kTileBytes = 32 * kRPitch * 4;      // fp32 staging tile of one wavefront
-    constexpr int kBBytes = NS * 32 * kPPitch;        // bf16 pieces of one wavefront's delta tile
-    constexpr bool kBasisInLds = NS == 2 && CB <= 2;  // basis fragments of the 64 columns staged
-    constexpr int kBasisBytes = kBasisInLds ? 4 * CB * NS * 1024 : 0;
-    float *tile = reinterpret_cast<float *>(smem) + (threadIdx.x >> 6) * (32 * kRPitch);
-    unsigned char *btile = smem + 4 * kTileBytes + (threadIdx.x >> 6) * kBBytes;
-    uint4 *basis_lds = reinterpret_cast<uint4 *>(smem + 4 * kTileBytes + 4 * kBBytes +
-                                                 (threadIdx.x >> 6) * kBasisBytes);
+    // Per wavefront: the fp32 staging tile of d and the bf16 pieces of its delta tile, which are never
+    // in use together (round_tile_bytes), and the basis fragments of its 64 columns.  With three
+    // pieces and two basis blocks that is 151 KB of the compute unit's 160.  (Fragments read from L2
+    // inside the loop wait for every HBM request made before them: 320 us against @R3@ for 5008 x
+    // 3376 at r = 56 with three fp32 workers.)
+    constexpr int kTileBytes = round_tile_bytes(NS);
+    constexpr int kBasisBytes = 4 * CB * NS * 1024;
+    unsigned char *btile = smem + (threadIdx.x >> 6) * kTileBytes;
+    float *tile = reinterpret_cast<float *>(btile);
+    uint4 *basis_lds = reinterpret_cast<uint4 *>(smem + 4 * kTileBytes + (threadIdx.x >> 6) * kBasisBytes);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t ib = blockIdx.y;
     const int64_t jbegin = (int64_t)blockIdx.x * cols_per_wg;
@@ -1028,11 +1035,10 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
             }
         }
         wave_lds_sync();  // earlier readers of the staging tile and of the basis are done
-        if (kBasisInLds) {  // this tile's basis fragments: 4 k-steps x CB blocks x NS pieces
+        // this tile's basis fragments: 4 k-steps x CB blocks x NS pieces
 #pragma unroll
-            for (int f = 0; f < 4 * CB * NS; ++f)
-                basis_lds[f * 64 + lane] = bfrags[((jt >> 4) * CB * NS + f) * 64 + lane];
-        }
+        for (int f = 0; f < 4 * CB * NS; ++f)
+            basis_lds[f * 64 + lane] = bfrags[((jt >> 4) * CB * NS + f) * 64 + lane];
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -1111,12 +1117,8 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
                     for (int cb = 0; cb < CB; ++cb) {
                         uint4 a[NS];
 #pragma unroll
-                        for (int h = 0; h < NS; ++h) {
-                            if (kBasisInLds)
-                                a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
-                            else
-                                a[h] = bfrags[((((jt >> 4) + s) * CB + cb) * NS + h) * 64 + lane];
-                        }
+                        for (int h = 0; h < NS; ++h)
+                            a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
                         mfma_split<NS>(a, b, acc[k][cb]);
                     }
                 }
@@ -1703,8 +1705,7 @@ static int round_launch_t(const uint4 *pf, const uint4 *qf, int ks, const uint4 
                         const ReconEpilogue &ep, const PtrPack<float *> &pslab, int64_t m,
                         int64_t n, int r, const RoundPlan &pl, int64_t slab_stride,
                         hipStream_t st) {
-    const size_t basis = (NS == 2 && CB <= 2) ? (size_t)4 * CB * NS * 1024 : 0;
-    const size_t tiles = 4 * (32 * kRPitch * 4) + 4 * (size_t)(NS * 32 * kPPitch) + 4 * basis;
+    const size_t tiles = 4 * (size_t)round_tile_bytes(NS) + 4 * (size_t)(4 * CB * NS * 1024);
     const size_t red = (size_t)KC * CB * 16 * 64 * 4;
     const size_t lds = tiles > red ? tiles : red;
     static size_t granted = 0;
