@@ -947,7 +947,7 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
     // Per wavefront: the fp32 staging tile of d and the bf16 pieces of its delta tile, which are never
     // in use together (round_tile_bytes), and the basis fragments of its 64 columns.  With three
     // pieces and two basis blocks that is 151 KB of the compute unit's 160.  (Fragments read from L2
-    // inside the loop wait for every HBM request made before them: 320 us against @R3@ for 5008 x
+    // inside the loop wait for every HBM request made before them: 338 us against 312 for 5008 x
     // 3376 at r = 56 with three fp32 workers.)
     constexpr int kTileBytes = round_tile_bytes(NS);
     constexpr int kBasisBytes = 4 * CB * NS * 1024;
