@@ -942,7 +942,7 @@ template <int NS, int CB, int KC, bool TLBF16>
 __global__ __launch_bounds__(kW) void round_mfma_kernel(
     const uint4 *__restrict__ pfrags, const uint4 *__restrict__ qfrags, int KS,
     const uint4 *__restrict__ bfrags, ReconEpilogue ep, PtrPack<float *> pslab, int64_t m,
-    int64_t n, int r, int64_t cols_per_wg, int64_t slab_stride) {
+    int64_t n, int r, int tiles, int64_t slab_stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     // Per wavefront: the fp32 staging tile of d and the bf16 pieces of its delta tile, which are never
     // in use together (round_tile_bytes), and the basis fragments of its 64 columns.  With three
@@ -956,8 +956,10 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
     uint4 *basis_lds = reinterpret_cast<uint4 *>(smem + 4 * kTileBytes + (threadIdx.x >> 6) * kBasisBytes);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t ib = blockIdx.y;
-    const int64_t jbegin = (int64_t)blockIdx.x * cols_per_wg;
-    int64_t jend = jbegin + cols_per_wg;
+    // 256-column tiles of the row block, dealt evenly to its workgroups, the longer ranges first
+    const uint32_t chunks = gridDim.x, end_at = (blockIdx.x + 1) * (uint32_t)tiles + chunks - 1;
+    const int64_t jbegin = (int64_t)((end_at - (uint32_t)tiles) / chunks) * 256;
+    int64_t jend = (int64_t)(end_at / chunks) * 256;
     if (jend > n) jend = n;
     const int64_t nblk = (n + 31) >> 5;
     const int prow = lane >> 4, pc4 = lane & 15;
@@ -1340,21 +1342,56 @@ struct QPlan {
     int64_t ksteps_per_wave, KS;
 };
 
+constexpr int64_t kQUnits = 256;  // compute units
+static int64_t q_cols(int64_t n) { return ceil_div(n, 128); }
+// Most row splits the plan may choose, whatever the rows and the rank.
+static int64_t q_most_splits(int64_t cols, int64_t K) {
+    const int64_t wgs = cols * K;
+    const int64_t s = wgs >= kQUnits ? ceil_div(2 * kQUnits, wgs) : 2 * kQUnits / wgs;
+    return s < 1 ? 1 : (s > 64 ? 64 : s);
+}
+// Slabs a workspace for K workers has room for: enough for any smaller number of workers and any
+// smaller rank that is later run in it.
+static int64_t q_slab_room(int64_t n, int K) {
+    int64_t room = 0;
+    for (int k = 1; k <= K; ++k) {
+        const int64_t s = q_most_splits(q_cols(n), k);
+        if (s > 1 && s * k > room) room = s * k;
+    }
+    return room;
+}
+
 static QPlan q_plan(int64_t m, int64_t n, int r, int K) {
     QPlan p;
     const int cb = cb_of(r);
     // 128 columns per workgroup in both Q kernels
     p.JB = 4;
-    p.depth = 2;                           // k-steps (16 rows) of delta in flight per wavefront
-    const int64_t col_wgs = ceil_div(n, 32 * p.JB) * K;
-    // workgroups that run at once: two per compute unit; one at 8 basis blocks, where the
-    // two-role kernel fills a unit by itself
-    const int64_t cap = cb == 8 ? 256 : 512;
-    int64_t S = ceil_div(cap, col_wgs);
-    const int64_t smax = ceil_div(m, 64 * p.depth * 2);  // at least 2 pipeline rounds per wave
-    if (S > smax) S = smax;
-    if (S < 1) S = 1;
-    if (S > 64) S = 64;
+    p.depth = 2;  // k-steps (16 rows) of delta in flight per wavefront
+    const int64_t cols = q_cols(n);
+    int64_t smax = q_most_splits(cols, K);
+    const int64_t by_rows = ceil_div(m, 64 * p.depth * 2);  // at least 2 pipeline rounds per wave
+    if (smax > by_rows) smax = by_rows;
+    int64_t S = 1;
+    if (cols * K >= kQUnits) {
+        // every compute unit has a workgroup: two, except at 8 basis blocks, where one fills it
+        if (cb < 8) S = smax;
+    } else {
+        // Fewer column blocks than units: rounds of the launch x rows of a workgroup (and 128 more to
+        // start and drain), plus the slabs, written and read, in the same unit (rows of one workgroup).
+        // Two workgroups on some units and one on the others is as slow as two everywhere.  Measured
+        // (us, chosen | two per unit, the rule before): 8192 x 1024 r = 64 8 splits 39.7 | 16: 47; 2048 x
+        // 2048 r = 32 4: 27 | 8: 31; r = 64 4: 26 | 8: 33; 8192 x 3008 r = 32 5: 74 | 6: 101; 4096 x 4096
+        // r = 64 2: 59 | 4: 68; 5008 x 3376 r = 56 three workers, three pieces 3: 71 | 7: 94.
+        int64_t best = INT64_MAX;
+        for (int64_t s = 1; s <= smax; ++s) {
+            const int64_t cost = ceil_div(cols * K * s, kQUnits) * (ceil_div(m, s) + 128) +
+                                 s * K * r * n / 16384;
+            if (cost < best) {
+                best = cost;
+                S = s;
+            }
+        }
+    }
     p.S = (int)S;
     int64_t kpw = ceil_div(ceil_div(m, 16), (int64_t)p.S * 4);
     p.ksteps_per_wave = ceil_div(kpw, p.depth) * p.depth;
@@ -1369,9 +1406,12 @@ size_t mfma_project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K)
     // DLCX_MMA_F16: one fp16 piece beside the two bf16 pieces of the stand-by launch
     const int ns = mma == DLCX_MMA_F16 ? 3 : ns_of(mma), cb = cb_of(r);
     const size_t p_frags = (size_t)ceil_div(n, 64) * 4 * cb * ns * 1024;
-    const QPlan q = q_plan(m, n, r, K);
-    const size_t q_frags = (size_t)q.KS * cb * ns * 1024;
-    const size_t slabs = q.S > 1 ? (size_t)K * q.S * r * n * sizeof(float) : 0;
+    // k-steps are rounded up to `depth` per wavefront: 8 more for every split (most of them with one
+    // worker, if the workspace is later used for fewer workers)
+    int64_t splits = q_most_splits(q_cols(n), 1);
+    if (splits > ceil_div(m, 256)) splits = ceil_div(m, 256);
+    const size_t q_frags = (size_t)(ceil_div(m, 16) + 8 * splits) * cb * ns * 1024;
+    const size_t slabs = (size_t)q_slab_room(n, K) * r * n * sizeof(float);
     const size_t a = a256(p_frags), b = a256(q_frags) + a256(slabs);
     return (a > b ? a : b) + (mma == DLCX_MMA_F16 ? a256(kF16ScratchBytes) : 0);
 }
@@ -1661,30 +1701,36 @@ int launch_reconstruct_mfma(int mma, int64_t m, int64_t n, int r, const float *p
 // ---- fused round: workspace layout and launch ------------------------------------------------
 constexpr int kComputeUnits = 256;
 struct RoundPlan {
-    int chunks;        // column ranges per row block = slabs per worker
-    int64_t cols;      // columns per workgroup (multiple of 256)
-    int kc;            // workers per launch
+    int chunks;  // column ranges per row block = slabs per worker
+    int tiles;   // 256-column tiles of a row block; range x starts at tile ceil(x tiles / chunks)
+    int kc;      // workers per launch
 };
 
+// Column ranges per row block.  One workgroup fills a compute unit, so the launch takes as many
+// rounds as it has workgroups for each of the 256 units, and a round as long as its longest range
+// plus about 0.3 tiles of start-up and of slab: the cheapest count by that estimate.  Against the
+// counts measured (1 .. all tiles, us, chosen | rule before: 4 ranges from 2048 columns on, ranges of
+// 512 columns or more, at most 8): 5008 x 3376 three workers 3 ranges 274 | 4: 312; 8192 x 2048 1:
+// 205 | 4: 241; 8192 x 1024 1: 111 | 2: 125; 704 x 4160 9: 50 | 6: 61; 512 x 8192 16: 63 | 8: 79; 3008
+// x 6000 8: 309 | 6: 357; 512 x 512 2: 20 | 1: 23; 2048 x 8192 4: 194.  No ranges of more than 8 tiles
+// up to four ranges: one or two long ones are 13 % slower at 8192 columns whatever the number of rows
+// (the workgroups drift apart), and the count does not matter at 28672.
 static RoundPlan round_plan(int64_t m, int64_t n, int r) {
     RoundPlan p;
     (void)r;
     p.kc = 4;  // workers per launch: 4 x 2 basis blocks x 16 accumulator registers per wavefront
-    // Column ranges per row block, from sweeps of this kernel over the benchmark shapes (one
-    // workgroup occupies a compute unit): four ranges once the matrix is 2048 columns wide (at
-    // 8192 columns 13 % faster than one or two, whatever the number of rows; at 28672 columns
-    // the count does not matter), one for narrower matrices; more, up to eight, when that is
-    // what it takes to give every compute unit two workgroups, but never ranges under 512
-    // columns (two tiles per wavefront), where start-up and the slab sums cost more than a
-    // fuller machine gains.
-    const int64_t rows = ceil_div(m, 32);
-    int64_t chunks = n >= 2048 ? 4 : 1;
-    const int64_t need = ceil_div(2 * kComputeUnits, rows);
-    if (chunks < need) chunks = need < 8 ? need : 8;
-    const int64_t widest = n / 512 > 1 ? n / 512 : 1;
-    if (chunks > widest) chunks = widest;
-    p.cols = ceil_div(ceil_div(n, chunks), 256) * 256;
-    p.chunks = (int)ceil_div(n, p.cols);
+    const int64_t rows = ceil_div(m, 32), tiles = ceil_div(n, 256);
+    const int64_t lo = tiles > 24 ? 4 : ceil_div(tiles, 8), hi = tiles < 32 ? tiles : 32;
+    int64_t best = lo, best_cost = INT64_MAX;
+    for (int64_t c = lo; c <= hi; ++c) {
+        const int64_t cost = ceil_div(rows * c, kComputeUnits) * (10 * ceil_div(tiles, c) + 3);
+        if (cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    p.chunks = (int)best;
+    p.tiles = (int)tiles;
     return p;
 }
 
@@ -1715,7 +1761,7 @@ static int round_launch_t(const uint4 *pf, const uint4 *qf, int ks, const uint4 
     const dim3 grid((unsigned)pl.chunks, (unsigned)ceil_div(m, 32));
     Timed timed(KID_ROUND, st);
     hipLaunchKernelGGL((round_mfma_kernel<NS, CB, KC, TLBF16>), grid, dim3(kW), lds, st, pf, qf, ks,
-                       bf, ep, pslab, m, n, r, pl.cols, slab_stride);
+                       bf, ep, pslab, m, n, r, pl.tiles, slab_stride);
     return check_launch("round_mfma");
 }
 
