@@ -221,13 +221,8 @@ __global__ __launch_bounds__(kT) void sum_slabs_kernel(PtrPack<const float *> sl
                                                        int S, int64_t slab_stride) {
     const int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (v >= nvec) return;
-    const float *__restrict__ src = slabs.p[blockIdx.y];
-    float4 a = reinterpret_cast<const float4 *>(src)[v];
-    for (int s = 1; s < S; ++s) {
-        const float4 b = reinterpret_cast<const float4 *>(src + (int64_t)s * slab_stride)[v];
-        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-    }
-    reinterpret_cast<float4 *>(outs.p[blockIdx.y])[v] = a;
+    reinterpret_cast<float4 *>(outs.p[blockIdx.y])[v] =
+        sum_partials(slabs.p[blockIdx.y], slab_stride, S, v);
 }
 
 int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<float *> &outs,

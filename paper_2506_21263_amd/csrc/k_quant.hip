@@ -17,8 +17,8 @@ __device__ __forceinline__ float group_max(float a) {
     return a;
 }
 
-// kSum: the input is S partial sums, added in order and written to sums[k] on the way (a pass of its
-// own over them, 4 - 5 us behind every projection, cost as much as the quantiser itself).
+// kSum: the input is S partial sums, added and written to sums[k] on the way (a pass of its own over
+// them, 4 - 5 us behind every projection, cost as much as the quantiser itself).
 template <int kQbits, int kLanes, bool kSum>
 __global__ __launch_bounds__(kQThreads) void quantize_kernel(PtrPack<const float *> xs,
                                                              int64_t nvec,
@@ -30,15 +30,13 @@ __global__ __launch_bounds__(kQThreads) void quantize_kernel(PtrPack<const float
     const int64_t v = (int64_t)blockIdx.x * kQThreads + threadIdx.x;
     const bool live = v < nvec;  // whole groups are live or dead together
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live) a = reinterpret_cast<const float4 *>(x)[v];
     if constexpr (kSum) {
         if (live) {
-            for (int s = 1; s < S; ++s) {
-                const float4 b = reinterpret_cast<const float4 *>(x + (int64_t)s * stride)[v];
-                a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
-            }
+            a = sum_partials(x, stride, S, v);
             reinterpret_cast<float4 *>(sums.p[k])[v] = a;
         }
+    } else if (live) {
+        a = reinterpret_cast<const float4 *>(x)[v];
     }
     float amax = fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w)));
     amax = group_max<kLanes>(amax);
