@@ -114,11 +114,13 @@ int launch_traffic_probe(int K, const PtrPack<float *> &ef, const PtrPack<const 
 
 // ---- rank-r products ------------------------------------------------------------------
 // P_k = delta_k * Q_in   (delta m x n, q_in r x n, out r x m)
+// The reduction is split where the output alone does not fill the GPU: with `partial` the sums over
+// the splits are left to the caller, else they are formed here.
 int launch_project_p(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *q_in,
-                     const PtrPack<float *> &out, void *workspace, hipStream_t st);
-// Q_k = delta_k^T * P_hat (p_hat r x m, out r x n).  Rows are split where the columns alone do not
-// fill the GPU: with `partial` the sums over the splits are left to the caller, else formed here.
+                     const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                     hipStream_t st);
+// Q_k = delta_k^T * P_hat (p_hat r x m, out r x n); splits as above
 int launch_project_q(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *p_hat,
                      const PtrPack<float *> &out, void *workspace, PartialSums *partial,

@@ -71,7 +71,8 @@ int launch_reconstruct_fma(int64_t, int64_t, int, const float *, const float *,
 size_t fma_project_workspace_bytes(int64_t, int64_t, int, int);
 // k_gemm_mfma.hip
 int launch_project_p_mfma(int, int64_t, int64_t, int, int, const PtrPack<const float *> &,
-                          const float *, const PtrPack<float *> &, void *, hipStream_t);
+                          const float *, const PtrPack<float *> &, void *, PartialSums *,
+                          hipStream_t);
 int launch_project_q_mfma(int, int64_t, int64_t, int, int, const PtrPack<const float *> &,
                           const float *, const PtrPack<float *> &, void *, PartialSums *,
                           hipStream_t);
@@ -111,9 +112,10 @@ size_t project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K) {
 
 int launch_project_p(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<const float *> &delta, const float *q_in,
-                     const PtrPack<float *> &out, void *workspace, hipStream_t st) {
+                     const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                     hipStream_t st) {
     if (mma == DLCX_MMA_FMA) return launch_project_p_fma(m, n, r, K, delta, q_in, out, st);
-    return launch_project_p_mfma(mma, m, n, r, K, delta, q_in, out, workspace, st);
+    return launch_project_p_mfma(mma, m, n, r, K, delta, q_in, out, workspace, partial, st);
 }
 
 int launch_project_q(int mma, int64_t m, int64_t n, int r, int K,
@@ -421,7 +423,7 @@ int dlcx_plan_overlap(const dlcx_desc *descs_host, int n_matrices, double extra_
     return DLCX_OK;
 }
 
-// partial: the sums over row splits are left to the caller (nullptr: formed here)
+// partial: the sums over splits of the reduction are left to the caller (nullptr: formed here)
 static int project(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
                    const float *basis, float *const *factors_out_host, void *workspace,
                    PartialSums *partial, void *stream) {
@@ -443,7 +445,7 @@ static int project(const dlcx_desc *desc, int phase, int K, const float *const *
         return DLCX_EINVAL;
     if (phase == DLCX_PHASE_P)
         return launch_project_p(desc->mma, desc->m, desc->n, desc->r, K, d, basis, o, workspace,
-                                as_stream(stream));
+                                partial, as_stream(stream));
     return launch_project_q(desc->mma, desc->m, desc->n, desc->r, K, d, basis, o, workspace, partial,
                             as_stream(stream));
 }

@@ -23,10 +23,9 @@
 // Kernels in this file:
 //   pack_kcontig_kernel, pack_f16_kernel, pack_sweep_kernel   fragments of a basis, of both forms
 //                                                 of a basis, of all operands of a sweep
-//   project_p_mfma_kernel, project_q_mfma_kernel  projections, every wavefront does everything
-//                                                 (r <= 32, and P for matrices with few rows)
 //   project_p_ws_kernel, project_q_ws_kernel      projections with producer and consumer
-//                                                 wavefronts (r > 32)
+//                                                 wavefronts (Q: r > 32)
+//   project_q_mfma_kernel                         Q at r <= 32, every wavefront does everything
 //   reconstruct_mfma_kernel                       Delta_hat tile by tile with the elementwise
 //                                                 steps of Alg. 2 fused in (any rank)
 //   round_mfma_kernel                             the same plus the P phase of the next
@@ -115,6 +114,26 @@ __device__ __forceinline__ void mfma_split(const uint4 (&a)[NS], const uint4 (&b
         c = mfma(a[0], b[1], c);
     }
     c = mfma(a[0], b[0], c);
+}
+
+// The same with the products of the smaller pieces in an accumulator of their own (kApart), added to
+// `c` at the end of the sum by the caller.  They are 2^-8 of the others or less: c is rounded once per
+// 16 terms instead of NS (NS + 1) / 2 times, and in a long sum that rounding is the fp32 error.
+template <int NS, bool kApart>
+__device__ __forceinline__ void mfma_split_sum(const uint4 (&a)[NS], const uint4 (&b)[NS],
+                                               f32x16_t &c, f32x16_t &small) {
+    if constexpr (!kApart) {
+        mfma_split<NS>(a, b, c);
+    } else {
+        if (NS == 3) {
+            small = mfma(a[2], b[0], small);
+            small = mfma(a[0], b[2], small);
+            small = mfma(a[1], b[1], small);
+        }
+        small = mfma(a[1], b[0], small);
+        small = mfma(a[0], b[1], small);
+        c = mfma(a[0], b[0], c);
+    }
 }
 
 // row of D held in register v of lane `lane`
@@ -296,12 +315,20 @@ __global__ __launch_bounds__(kW) void pack_sweep_kernel(KContig basis, KStrided 
 
 // ---------------------------------------------------------------------------------------------
 // P phase:  P_k[i][c] = sum_j delta_k[i][j] Q_in[c][j].
-// Workgroup: RB row blocks (32 RB rows) of delta, swept along j in stages of 64 (4 k-steps).
-// The 4 wavefronts split the work as WC (groups of CBW basis blocks) x WK (halves of a stage) x
-// WR (groups of row blocks).  A = basis fragments (M = c), B = delta from LDS (N = i): D[c][i].
-// A basis fragment serves RB / WR row blocks once it is in registers, so the fragment traffic
-// per byte of delta falls with RB: at r = 256 it is 4 : 1 with 64 rows and 2 : 1 with 128, which
-// is what lets the matrix cores, not L2, set the pace there.
+// Workgroup: RB row blocks (32 RB rows) of delta, swept along its range of columns j in stages of 64
+// (4 k-steps); A = basis fragments (M = c), B = delta from LDS (N = i): D[c][i].  A basis fragment
+// serves RB / WR row blocks once it is in registers, so the fragment traffic per byte of delta
+// falls with RB: at r = 256 it is 4 : 1 with 64 rows and 2 : 1 with 128.  A stage of matrix-core work
+// is about as long as a round trip to HBM and a single wavefront per SIMD cannot hide one behind the
+// other, so the workgroup has 8 wavefronts with two roles.  Wavefronts 4..7 (producers) stream delta: stage s
+// lives in register set s & 1, is split into bf16 pieces and laid down in LDS buffer s & 1 one
+// stage before it is used, and its set is refilled at once with stage s + 2, so that every
+// request has two stages of time to come back.  Wavefronts 0..3 (consumers) own WC x WR blocks of
+// the output, fetch their basis fragments through L2 two or four k-steps ahead (their load
+// counter never waits for HBM) and keep the matrix cores busy on the buffer the producers filled
+// last.  One
+// LDS-only barrier per stage for all eight.  Loads past the matrix or past the last stage are
+// clamped to a valid address and zeroed / never read, which keeps both loops free of branches.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPPitch = 64 * 2 + 16;  // bytes per LDS row of one piece: 64 bf16 + pad
 
@@ -313,185 +340,23 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int NS, int CBW, int WC, int WK, int WR, int RB>
-constexpr int project_p_lds_bytes() {
-    constexpr int buf = 2 * NS * 32 * RB * kPPitch;
-    constexpr int red = (WK == 2) ? 2 * CBW * (RB / WR) * 16 * 64 * 4 : 0;
-    return buf > red ? buf : red;
-}
-
-template <int NS, int CBW, int WC, int WK, int WR, int RB>
-__global__ __launch_bounds__(kW) void project_p_mfma_kernel(PtrPack<const float *> deltas,
-                                                            const uint4 *__restrict__ afrags,
-                                                            PtrPack<float *> outs, int64_t m,
-                                                            int64_t n, int r) {
-    constexpr int CB = CBW * WC;
-    constexpr int RBW = RB / WR;
-    constexpr int KSW = 4 / WK;
-    constexpr int kRows = 32 * RB;
-    constexpr int kVec = kRows * 16 / kW;  // float4 per thread and stage
-    static_assert(WC * WK * WR == 4, "four wavefronts");
-    constexpr int kBuf = NS * kRows * kPPitch;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-
-    const float *__restrict__ delta = deltas.p[blockIdx.y];
-    float *__restrict__ out = outs.p[blockIdx.y];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wc = wave % WC, wk = (wave / WC) % WK, wr = wave / (WC * WK);
-    const int64_t i0 = (int64_t)blockIdx.x * kRows;
-    const int64_t nstages = (n + 63) / 64;
-
-    f32x16_t acc[CBW][RBW];
-#pragma unroll
-    for (int a = 0; a < CBW; ++a)
-#pragma unroll
-        for (int b = 0; b < RBW; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-    // this thread's float4 of a stage: (row, 4 columns)
-    float4 pre[kVec];
-    auto load_stage = [&](int64_t t) {
-#pragma unroll
-        for (int u = 0; u < kVec; ++u) {
-            const int idx = tid + kW * u;
-            const int row = idx >> 4, c4 = idx & 15;
-            const int64_t j = t * 64 + c4 * 4;
-            pre[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i0 + row < m && j < n)
-                pre[u] = stream_load4(delta + (i0 + row) * n + j);
-        }
-    };
-    // basis fragments of a stage: fetched one stage ahead, so that the matrix cores do not wait
-    // for L2 after every barrier -- except in the 4-block shape, where the second copy of the
-    // fragments costs a wavefront per SIMD and the kernel comes out slower
-    constexpr bool kAhead = !(CBW == 2 && WC == 2);
-    uint4 a[KSW][CBW][NS];
-    auto load_frags = [&](uint4 (&dst)[KSW][CBW][NS], int64_t t) {
-#pragma unroll
-        for (int ks = 0; ks < KSW; ++ks)
-#pragma unroll
-            for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-                for (int h = 0; h < NS; ++h) {
-                    const int64_t sg = t * 4 + wk * KSW + ks;
-                    dst[ks][cb][h] = afrags[((sg * CB + wc * CBW + cb) * NS + h) * 64 + lane];
-                }
-    };
-    if (kAhead && nstages > 0) load_frags(a, 0);
-    load_stage(0);
-    for (int64_t t = 0; t < nstages; ++t) {
-        unsigned char *buf = lds + (t & 1) * kBuf;
-#pragma unroll
-        for (int u = 0; u < kVec; ++u) {
-            const int idx = tid + kW * u;
-            const int row = idx >> 4, c4 = idx & 15;
-            uint32_t lo[NS], hi[NS];
-            split2<NS>(pre[u].x, pre[u].y, lo);
-            split2<NS>(pre[u].z, pre[u].w, hi);
-#pragma unroll
-            for (int h = 0; h < NS; ++h)
-                *reinterpret_cast<uint2 *>(buf + (h * kRows + row) * kPPitch + c4 * 8) =
-                    make_uint2(lo[h], hi[h]);
-        }
-        // the next stage's fragments are requested before the next stage of delta, so that
-        // waiting for them later does not wait for that stage as well
-        uint4 an[KSW][CBW][NS];  // unused (and removed by the compiler) unless kAhead
-        if (kAhead) {
-            if (t + 1 < nstages) load_frags(an, t + 1);
-        } else {
-            load_frags(a, t);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 1 < nstages) load_stage(t + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_barrier();
-#pragma unroll
-        for (int ks = 0; ks < KSW; ++ks) {
-            const int s = wk * KSW + ks;
-            uint4 b[RBW][NS];
-#pragma unroll
-            for (int rb = 0; rb < RBW; ++rb)
-#pragma unroll
-                for (int h = 0; h < NS; ++h) {
-                    const int row = (wr * RBW + rb) * 32 + (lane & 31);
-                    b[rb][h] = *reinterpret_cast<const uint4 *>(
-                        buf + (h * kRows + row) * kPPitch + s * 32 + (lane >> 5) * 16);
-                }
-#pragma unroll
-            for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-                for (int rb = 0; rb < RBW; ++rb) mfma_split<NS>(a[ks][cb], b[rb], acc[cb][rb]);
-        }
-        if (kAhead && t + 1 < nstages) {
-#pragma unroll
-            for (int ks = 0; ks < KSW; ++ks)
-#pragma unroll
-                for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-                    for (int h = 0; h < NS; ++h) a[ks][cb][h] = an[ks][cb][h];
-        }
-    }
-    if (WK == 2) {  // add the two halves of the reduction: wk = 1 hands over through LDS
-        __syncthreads();
-        float *red = reinterpret_cast<float *>(lds);
-        const int slot = wr * WC + wc;  // WK == 2 => WC * WR == 2
-        if (wk == 1) {
-#pragma unroll
-            for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-                for (int rb = 0; rb < RBW; ++rb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        red[((slot * CBW * RBW + cb * RBW + rb) * 16 + v) * 64 + lane] = acc[cb][rb][v];
-        }
-        __syncthreads();
-        if (wk == 1) return;
-#pragma unroll
-        for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-            for (int rb = 0; rb < RBW; ++rb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    acc[cb][rb][v] += red[((slot * CBW * RBW + cb * RBW + rb) * 16 + v) * 64 + lane];
-    }
-#pragma unroll
-    for (int cb = 0; cb < CBW; ++cb)
-#pragma unroll
-        for (int rb = 0; rb < RBW; ++rb) {
-            const int64_t i = i0 + (wr * RBW + rb) * 32 + (lane & 31);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int c = (wc * CBW + cb) * 32 + d_row(v, lane);
-                if (c < r && i < m) out[(int64_t)c * m + i] = acc[cb][rb][v];
-            }
-        }
-}
-
-// ---------------------------------------------------------------------------------------------
-// P phase at 8 basis blocks (128 < r <= 256), where a stage of matrix-core work is about as long
-// as a round trip to HBM and a single wavefront per SIMD cannot hide one behind the other.  The
-// workgroup has 8 wavefronts with two roles.  Wavefronts 4..7 (producers) stream delta: stage s
-// lives in register set s & 1, is split into bf16 pieces and laid down in LDS buffer s & 1 one
-// stage before it is used, and its set is refilled at once with stage s + 2, so that every
-// request has two stages of time to come back.  Wavefronts 0..3 (consumers) own WC x WR blocks of
-// the output, fetch their basis fragments through L2 two or four k-steps ahead (their load
-// counter never waits for HBM) and keep the matrix cores busy on the buffer the producers filled
-// last.  One
-// LDS-only barrier per stage for all eight.  Loads past the matrix or past the last stage are
-// clamped to a valid address and zeroed / never read, which keeps both loops free of branches.
-// ---------------------------------------------------------------------------------------------
 constexpr int kWs = 512;  // threads of the two-role workgroup
 
 // NS == 1 is the fp16 form (one product per block instead of three): the producers multiply
 // delta by 2^kF16DeltaShift and record its largest magnitude in *amax_record, the consumers undo
 // the scales through out_scale.  `guard` (NS >= 2) makes the launch a stand-by: it returns at
 // once if the fp16 launch before it saw its operands in range.
+// Accumulators of the small products (mfma_split_sum) at 1 and 2 basis blocks, where the registers are
+// there for the asking.  Error against fp64 of three pieces, 6528 x 5136 at r = 4: 4.5e-7, in one
+// accumulator 1.1e-6; 8192 x 8192 r = 20 193 us either way.
+template <int NS, int BLOCKS>
+constexpr bool kApartP = NS >= 2 && BLOCKS <= 2;
 template <int NS, int CBW, int WC, int WR, int RB>
 __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
                                                            PtrPack<float *> outs, int64_t m,
-                                                           int64_t n, int r,
+                                                           int64_t n, int r, int64_t stages_per_wg,
+                                                           int64_t slab_stride,
                                                            uint32_t *__restrict__ amax_record,
                                                            const float *__restrict__ out_scale,
                                                            const uint32_t *__restrict__ guard) {
@@ -505,10 +370,12 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
 
     if (guard != nullptr && f16_range_ok(*guard)) return;  // uniform over the launch
     const float *__restrict__ delta = deltas.p[blockIdx.y];
-    float *__restrict__ out = outs.p[blockIdx.y];
+    float *__restrict__ out = outs.p[blockIdx.y] + (int64_t)blockIdx.z * slab_stride;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t i0 = (int64_t)blockIdx.x * kRows;
-    const int64_t nstages = (n + 63) / 64;
+    const int64_t sfirst = (int64_t)blockIdx.z * stages_per_wg;  // of the matrix's stages of 64 columns
+    const int64_t sleft = (n + 63) / 64 - sfirst;
+    const int64_t nstages = stages_per_wg < sleft ? stages_per_wg : sleft;
 
     if (wave >= 4) {  // ---------------------------------------------------------- producers
         const int tid = threadIdx.x - kW;
@@ -519,7 +386,7 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int u = 0; u < kVec; ++u) {
                 const int idx = tid + kW * u;
                 const int row = idx >> 4, c4 = idx & 15;
-                const int64_t j = tc * 64 + c4 * 4;
+                const int64_t j = (sfirst + tc) * 64 + c4 * 4;
                 const bool ok = i0 + row < m && j < n;
                 // the value of a clamped load is discarded when the stage is laid down, not
                 // here: touching it now would wait for the request just made
@@ -531,7 +398,7 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int u = 0; u < kVec; ++u) {
                 const int idx = tid + kW * u;
                 const int row = idx >> 4, c4 = idx & 15;
-                const bool ok = i0 + row < m && t * 64 + c4 * 4 < n;
+                const bool ok = i0 + row < m && (sfirst + t) * 64 + c4 * 4 < n;
                 float4 x = make_float4(ok ? set[u].x : 0.f, ok ? set[u].y : 0.f,
                                        ok ? set[u].z : 0.f, ok ? set[u].w : 0.f);
                 if constexpr (NS == 1) {
@@ -578,13 +445,17 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
     }
     // -------------------------------------------------------------------------------- consumers
     const int wc = wave % WC, wr = wave / WC;
-    f32x16_t acc[CBW][RBW];
+    constexpr bool kApart = kApartP<NS, CBW * RBW>;
+    f32x16_t acc[CBW][RBW], small[kApart ? CBW : 1][kApart ? RBW : 1];
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
         for (int b = 0; b < RBW; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+            for (int v = 0; v < 16; ++v) {
+                acc[a][b][v] = 0.f;
+                if constexpr (kApart) small[a][b][v] = 0.f;
+            }
     // fragments of global k-step g (4 per stage) in ring position g % AD: requested two k-steps
     // ahead, or a whole stage ahead where that is at most 8 registers per position (one fp16
     // piece, or one basis block per wavefront).  There the matrix-core work of two k-steps is
@@ -595,7 +466,7 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
     uint4 a[AD][CBW][NS];
     const int64_t gmax = nstages * 4 - 1;
     auto load_frags = [&](int64_t g, int pos) {
-        const int64_t gc = g < gmax ? g : gmax;
+        const int64_t gc = sfirst * 4 + (g < gmax ? g : gmax);
 #pragma unroll
         for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
@@ -622,12 +493,21 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
                 for (int rb = 0; rb < RBW; ++rb)
-                    mfma_split<NS>(a[ks % AD][cb], b[rb], acc[cb][rb]);
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[rb], acc[cb][rb],
+                                               small[kApart ? cb : 0][kApart ? rb : 0]);
             // requested here and nowhere later: AD k-steps of matrix-core work to come back
             load_frags(t * 4 + ks + AD, ks % AD);
             __builtin_amdgcn_sched_barrier(0);
         }
         lds_barrier();
+    }
+    if constexpr (kApart) {
+#pragma unroll
+        for (int cb = 0; cb < CBW; ++cb)
+#pragma unroll
+            for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[cb][rb][v] += small[cb][rb][v];
     }
 #pragma unroll
     for (int cb = 0; cb < CBW; ++cb)
@@ -1108,6 +988,15 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
                     issue(tile_at(it + 1), 0, true, ep.apply && Kw == 1);
                 }
                 wave_lds_sync();
+                // NS == 3: the tile's products in accumulators of their own, added to the sum once
+                // (mfma_split_sum: the fp32 error of a long sum is the rounding of its large terms)
+                f32x16_t part[CB];
+                if constexpr (NS == 3) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) part[cb][v] = 0.f;
+                }
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     uint4 b[NS];
@@ -1121,8 +1010,14 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 #pragma unroll
                         for (int h = 0; h < NS; ++h)
                             a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
-                        mfma_split<NS>(a, b, acc[k][cb]);
+                        mfma_split<NS>(a, b, NS == 3 ? part[cb] : acc[k][cb]);
                     }
+                }
+                if constexpr (NS == 3) {
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[k][cb][v] += part[cb][v];
                 }
             }
         }
@@ -1181,6 +1076,10 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 // wavefront w owns the CBW basis blocks of group w % WCB and WCB of the four 32-column blocks.
 // Register sets, buffers, barriers and clamping as in the P kernel.
 // ---------------------------------------------------------------------------------------------
+// Accumulators of the small products as in the P kernel, with three pieces (one workgroup per unit, 256
+// registers) at 4 basis blocks too: 8192 x 8192 r = 100 4.0e-7 from fp64, 1.0e-6 in one accumulator.
+template <int NS, int BLOCKS>
+constexpr bool kApartQ = NS >= 2 && BLOCKS <= (NS == 3 ? 4 : 2);
 template <int NS, int CBW, int WCB>
 __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
@@ -1274,13 +1173,17 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
     }
     // -------------------------------------------------------------------------------- consumers
     const int wcb = wave % WCB, wq = wave / WCB;
-    f32x16_t acc[CBW][QW];
+    constexpr bool kApart = kApartQ<NS, CBW * QW>;
+    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1];
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
         for (int b = 0; b < QW; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+            for (int v = 0; v < 16; ++v) {
+                acc[a][b][v] = 0.f;
+                if constexpr (kApart) small[a][b][v] = 0.f;
+            }
     constexpr int AD = CBW * NS <= 2 ? 4 : 2;  // as in project_p_ws_kernel
     uint4 a[AD][CBW][NS];                      // fragments of k-step g in ring position g % AD
     const int64_t gmax = s_begin + ksteps_per_wg - 1;
@@ -1310,11 +1213,21 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
 #pragma unroll
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
-                for (int q = 0; q < QW; ++q) mfma_split<NS>(a[ks % AD][cb], b[q], acc[cb][q]);
+                for (int q = 0; q < QW; ++q)
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q], acc[cb][q],
+                                               small[kApart ? cb : 0][kApart ? q : 0]);
             load_frags(s_begin + t * 4 + ks + AD, ks % AD);
             __builtin_amdgcn_sched_barrier(0);
         }
         lds_barrier();
+    }
+    if constexpr (kApart) {
+#pragma unroll
+        for (int cb = 0; cb < CBW; ++cb)
+#pragma unroll
+            for (int q = 0; q < QW; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[cb][q][v] += small[cb][q][v];
     }
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
@@ -1342,59 +1255,104 @@ struct QPlan {
     int64_t ksteps_per_wave, KS;
 };
 
+// Splits of the reduction.  A projection has one workgroup per 128 rows (P; 64 in one case, p_plan) or
+// columns (Q) of the output and worker; where that leaves compute units without one, the reduction is
+// split and the partial sums, one slab per split and worker, are added afterwards (sum_partials).
 constexpr int64_t kQUnits = 256;  // compute units
-static int64_t q_cols(int64_t n) { return ceil_div(n, 128); }
-// Most row splits the plan may choose, whatever the rows and the rank.
-static int64_t q_most_splits(int64_t cols, int64_t K) {
-    const int64_t wgs = cols * K;
-    const int64_t s = wgs >= kQUnits ? ceil_div(2 * kQUnits, wgs) : 2 * kQUnits / wgs;
-    return s < 1 ? 1 : (s > 64 ? 64 : s);
+constexpr int64_t kPShort = 1024;  // columns up to which the P kernel may take 64 rows
+// Most splits a plan may choose for `wgs` workgroups per split, whatever the reduction's length and
+// the rank: no more than two workgroups per compute unit.
+static int64_t most_splits(int64_t wgs) {
+    const int64_t s = ceil_div(2 * kQUnits, wgs);
+    return s > 64 ? 64 : s;
 }
+static int64_t out_wgs(int64_t side) { return ceil_div(side, 128); }
 // Slabs a workspace for K workers has room for: enough for any smaller number of workers and any
 // smaller rank that is later run in it.
-static int64_t q_slab_room(int64_t n, int K) {
+static int64_t slab_room(int64_t side, int K) {
     int64_t room = 0;
     for (int k = 1; k <= K; ++k) {
-        const int64_t s = q_most_splits(q_cols(n), k);
+        const int64_t s = most_splits(out_wgs(side) * k);
         if (s > 1 && s * k > room) room = s * k;
     }
     return room;
 }
 
-static QPlan q_plan(int64_t m, int64_t n, int r, int K) {
+// The cheapest number of splits, up to smax, of a reduction over `length`: rounds of the launch x
+// length of a workgroup's share in whole `granule`s (and 128 more to start and drain), plus the slabs,
+// written and read, in the same unit (512 bytes of delta on one compute unit).  Two workgroups on some
+// units and one on the others is as slow as two everywhere.  Measured (us, chosen | two per unit, the
+// rule before): Q of 8192 x 1024 r = 64 8 splits 39 | 16: 47; 2048 x 2048 r = 32 4: 21 | 8: 28; r = 64
+// 4: 26 | 8: 33; 8192 x 3008 r = 32 5: 74 | 6: 101; 4096 x 4096 r = 64 2: 59 | 4: 68; 5008 x 3376 r = 56
+// three workers, three pieces 3: 66 | 7: 90.  P, 64 rows and no splits before: 2048 x 8192 r = 32 55 |
+// 125, r = 100 88 | 163; 2048 x 2048 r = 64 26 | 41; 3008 x 5008 r = 100 two workers 54 | 107; 256 x 8192
+// r = 16 one worker 21 | 102; 1120 x 6688 r = 210 one worker 34 | 170.
+static int64_t best_splits(int64_t wgs, int64_t length, int64_t granule, int64_t slab_elements,
+                           int64_t smax) {
+    int64_t best = INT64_MAX, S = 1;
+    for (int64_t s = 1; s <= smax; ++s) {
+        const int64_t share = ceil_div(ceil_div(length, s), granule) * granule;
+        const int64_t cost = ceil_div(wgs * s, kQUnits) * (share + 128) + s * slab_elements / 16384;
+        if (cost < best) {
+            best = cost;
+            S = s;
+        }
+    }
+    return S;
+}
+
+struct PPlan {
+    int rows;        // rows of delta per workgroup
+    int S;           // column splits
+    int64_t stages;  // stages of 64 columns of a split
+};
+// 64 rows per workgroup where the matrix cores set the pace (4 or 8 basis blocks), the rows then still
+// fit the units in one round and the reduction is short: a longer chain of stages is not what such a
+// launch waits for.  64 | 128 rows, us: 8192 x 512 r = 100 two workers 21 | 27, 2176 x 256 r = 145 16 |
+// 20, 7136 x 640 r = 74 22 | 25, 6000 x 1024 r = 100 21 | 23; 3008 x 2048 r = 200 41 | 39, 2048 x 3072 r =
+// 200 three pieces 81 | 76.
+static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
+    PPlan p;
+    const int64_t stages = ceil_div(n, 64);
+    p.rows = cb_of(r) >= 4 && n <= kPShort && ceil_div(m, 64) * K <= kQUnits ? 64 : 128;
+    const int64_t wgs = ceil_div(m, p.rows) * K;
+    int64_t smax = most_splits(wgs), S = 1;
+    if (smax > ceil_div(stages, 2)) smax = ceil_div(stages, 2);
+    // (a second workgroup on every unit does not pay here: 8192 x 8192 r = 64 271 us split in two, 240 not)
+    if (wgs < kQUnits) S = best_splits(wgs, n, 64, (int64_t)K * r * m, smax);
+    p.stages = ceil_div(stages, S);
+    p.S = (int)ceil_div(stages, p.stages);
+    return p;
+}
+
+static QPlan q_plan(int ns, int64_t m, int64_t n, int r, int K) {
     QPlan p;
     const int cb = cb_of(r);
     // 128 columns per workgroup in both Q kernels
     p.JB = 4;
     p.depth = 2;  // k-steps (16 rows) of delta in flight per wavefront
-    const int64_t cols = q_cols(n);
-    int64_t smax = q_most_splits(cols, K);
+    const int64_t wgs = out_wgs(n) * K;
+    int64_t smax = most_splits(wgs);
     const int64_t by_rows = ceil_div(m, 64 * p.depth * 2);  // at least 2 pipeline rounds per wave
     if (smax > by_rows) smax = by_rows;
     int64_t S = 1;
-    if (cols * K >= kQUnits) {
+    if (ns == 3 && cb == 1) {
+        // the one-role kernel: two workgroups for every unit, whatever remains.  (Fewer splits, with
+        // longer fp32 sums, are up to 1.7 times as far from fp64: 6112 x 6864 r = 4.)
+        S = smax;
+    } else if (wgs >= kQUnits) {
         // every compute unit has a workgroup: two, except at 8 basis blocks, where one fills it
         if (cb < 8) S = smax;
+    } else if (ns == 3 && cb == 8) {
+        // no room for accumulators of the small products (kApartQ): short sums instead, 5008 x 3376 r =
+        // 200 157 us; by the estimate 143 and 1.2 times as far from fp64; before 185
+        S = 2 * kQUnits / wgs < smax ? 2 * kQUnits / wgs : smax;
     } else {
-        // Fewer column blocks than units: rounds of the launch x rows of a workgroup (and 128 more to
-        // start and drain), plus the slabs, written and read, in the same unit (rows of one workgroup).
-        // Two workgroups on some units and one on the others is as slow as two everywhere.  Measured
-        // (us, chosen | two per unit, the rule before): 8192 x 1024 r = 64 8 splits 39.7 | 16: 47; 2048 x
-        // 2048 r = 32 4: 27 | 8: 31; r = 64 4: 26 | 8: 33; 8192 x 3008 r = 32 5: 74 | 6: 101; 4096 x 4096
-        // r = 64 2: 59 | 4: 68; 5008 x 3376 r = 56 three workers, three pieces 3: 71 | 7: 94.
-        int64_t best = INT64_MAX;
-        for (int64_t s = 1; s <= smax; ++s) {
-            const int64_t cost = ceil_div(cols * K * s, kQUnits) * (ceil_div(m, s) + 128) +
-                                 s * K * r * n / 16384;
-            if (cost < best) {
-                best = cost;
-                S = s;
-            }
-        }
+        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, smax);
     }
-    p.S = (int)S;
-    int64_t kpw = ceil_div(ceil_div(m, 16), (int64_t)p.S * 4);
+    const int64_t kpw = ceil_div(ceil_div(m, 16), S * 4);
     p.ksteps_per_wave = ceil_div(kpw, p.depth) * p.depth;
+    p.S = (int)ceil_div(ceil_div(m, 16), p.ksteps_per_wave * 4);  // none without rows
     p.KS = p.ksteps_per_wave * 4 * p.S;
     return p;
 }
@@ -1408,11 +1366,12 @@ size_t mfma_project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K)
     const size_t p_frags = (size_t)ceil_div(n, 64) * 4 * cb * ns * 1024;
     // k-steps are rounded up to `depth` per wavefront: 8 more for every split (most of them with one
     // worker, if the workspace is later used for fewer workers)
-    int64_t splits = q_most_splits(q_cols(n), 1);
+    int64_t splits = most_splits(out_wgs(n));
     if (splits > ceil_div(m, 256)) splits = ceil_div(m, 256);
     const size_t q_frags = (size_t)(ceil_div(m, 16) + 8 * splits) * cb * ns * 1024;
-    const size_t slabs = (size_t)q_slab_room(n, K) * r * n * sizeof(float);
-    const size_t a = a256(p_frags), b = a256(q_frags) + a256(slabs);
+    const size_t slabs = (size_t)slab_room(n, K) * r * n * sizeof(float);
+    const size_t p_slabs = (size_t)slab_room(m, K) * r * m * sizeof(float);
+    const size_t a = a256(p_frags) + a256(p_slabs), b = a256(q_frags) + a256(slabs);
     return (a > b ? a : b) + (mma == DLCX_MMA_F16 ? a256(kF16ScratchBytes) : 0);
 }
 
@@ -1457,36 +1416,21 @@ static int pack_f16(const KContig &p, uint4 *frags_f16, const F16Scratch &f, hip
     return check_launch("pack_f16");
 }
 
-template <int NS, int CBW, int WC, int WK, int WR, int RB>
-static int project_p_launch(const PtrPack<const float *> &delta, const uint4 *frags,
-                            const PtrPack<float *> &out, int64_t m, int64_t n, int r, int K,
-                            hipStream_t st) {
-    constexpr int lds = project_p_lds_bytes<NS, CBW, WC, WK, WR, RB>();
-    static size_t granted = 0;
-    int rc = grant_dynamic_lds(
-        reinterpret_cast<const void *>(project_p_mfma_kernel<NS, CBW, WC, WK, WR, RB>), lds,
-        &granted, "project_p attribute");
-    if (rc != DLCX_OK) return rc;
-    const dim3 grid((unsigned)ceil_div(m, 32 * RB), (unsigned)K);
-    hipLaunchKernelGGL((project_p_mfma_kernel<NS, CBW, WC, WK, WR, RB>), grid, dim3(kW), lds, st,
-                       delta, frags, out, m, n, r);
-    return DLCX_OK;
-}
-
-template <int NS, int CBW, int WC, int WR, int RB>
-static int project_p_ws_launch(const PtrPack<const float *> &delta, const uint4 *frags,
-                               const PtrPack<float *> &out, int64_t m, int64_t n, int r, int K,
-                               hipStream_t st, uint32_t *record = nullptr,
+template <int NS, int CBW, int WC, int WR, int RB = 4>
+static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &delta,
+                               const uint4 *frags, const PtrPack<float *> &out, int64_t m,
+                               int64_t n, int r, int K, hipStream_t st, uint32_t *record = nullptr,
                                const float *out_scale = nullptr, const uint32_t *guard = nullptr) {
     constexpr int lds = 2 * NS * 32 * RB * kPPitch;
     static size_t granted = 0;
     int rc = grant_dynamic_lds(
-        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB>), lds, &granted,
-        "project_p attribute");
+        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB>), lds,
+        &granted, "project_p attribute");
     if (rc != DLCX_OK) return rc;
-    const dim3 grid((unsigned)ceil_div(m, 32 * RB), (unsigned)K);
-    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB>), grid, dim3(kWs), lds, st, delta,
-                       frags, out, m, n, r, record, out_scale, guard);
+    const dim3 grid((unsigned)ceil_div(m, 32 * RB), (unsigned)K, (unsigned)pl.S);
+    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB>), grid, dim3(kWs), lds, st,
+                       delta, frags, out, m, n, r, pl.stages, (int64_t)r * m, record, out_scale,
+                       guard);
     return DLCX_OK;
 }
 
@@ -1494,12 +1438,14 @@ static int project_p_ws_launch(const PtrPack<const float *> &delta, const uint4 
 // and not the stream of delta set the pace: one fp16 product per block instead of three bf16
 // ones, followed by the bf16 kernel as a stand-by that returns at once unless the fp16 launch
 // recorded a largest |delta| outside the window in which fp16 is safe.  False: not applicable
-// (fewer basis blocks, or too few rows for the two-role kernel), the caller goes on as usual.
+// (fewer basis blocks, or rows for fewer than 256 workgroups: such a matrix has always had the bf16
+// form), the caller goes on as usual.
 static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                           const float *q_in, const PtrPack<float *> &out, void *workspace,
                           hipStream_t st, int *rc_out) {
     const int cb = cb_of(r);
-    if (cb < 4 || ceil_div(m, 128) * K < 256) return false;
+    if (cb < 4 || out_wgs(m) * K < kQUnits) return false;
+    const PPlan pl = p_plan(m, n, r, K);  // never split with that many workgroups
     const int64_t KS = ceil_div(n, 64) * 4;
     char *ws = reinterpret_cast<char *>(workspace);
     uint4 *frags2 = reinterpret_cast<uint4 *>(ws);                                // two bf16 pieces
@@ -1509,13 +1455,13 @@ static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<cons
     if (rc == DLCX_OK) {
         Timed timed(KID_PROJECT_P, st);
         if (cb == 4) {
-            rc = project_p_ws_launch<1, 2, 2, 2, 4>(delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
+            rc = project_p_ws_launch<1, 2, 2, 2>(pl, delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
             if (rc == DLCX_OK)
-                rc = project_p_ws_launch<2, 2, 2, 2, 4>(delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
+                rc = project_p_ws_launch<2, 2, 2, 2>(pl, delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
         } else {
-            rc = project_p_ws_launch<1, 2, 4, 1, 4>(delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
+            rc = project_p_ws_launch<1, 2, 4, 1>(pl, delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
             if (rc == DLCX_OK)
-                rc = project_p_ws_launch<2, 2, 4, 1, 4>(delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
+                rc = project_p_ws_launch<2, 2, 4, 1>(pl, delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
         }
         if (rc == DLCX_OK) rc = check_launch("project_p_f16");
     }
@@ -1523,40 +1469,55 @@ static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<cons
     return true;
 }
 
+// The sums over the splits of a reduction, left to the caller (partial) or formed here.
+static int finish_splits(int K, int S, int64_t slab, const PtrPack<float *> &dst,
+                         const PtrPack<float *> &out, PartialSums *partial, hipStream_t st) {
+    if (S == 1) return DLCX_OK;
+    PartialSums sums;
+    sums.S = S;
+    sums.stride = slab;
+    for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k];
+    if (partial) {
+        *partial = sums;
+        return DLCX_OK;
+    }
+    return launch_sum_slabs(K, sums.slabs, out, slab, S, slab, st);
+}
+
 template <int NS>
 static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                         const float *q_in, const PtrPack<float *> &out, void *workspace,
-                        hipStream_t st) {
+                        PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
-    const int64_t KS = ceil_div(n, 64) * 4;
-    uint4 *frags = reinterpret_cast<uint4 *>(workspace);
+    const PPlan pl = p_plan(m, n, r, K);
+    const int64_t KS = ceil_div(n, 64) * 4, slab = (int64_t)r * m;
+    char *wsb = reinterpret_cast<char *>(workspace);
+    uint4 *frags = reinterpret_cast<uint4 *>(wsb);
     int rc = pack_kcontig<NS>(KContig{q_in, r, n, cb, KS, frags}, st);
     if (rc != DLCX_OK) return rc;
-    Timed timed(KID_PROJECT_P, st);
-    switch (cb) {
-        case 1: rc = project_p_launch<NS, 1, 1, 2, 2, 2>(delta, frags, out, m, n, r, K, st); break;
-        case 2:
-            if (ceil_div(m, 128) * K >= 256)
-                rc = project_p_ws_launch<NS, 1, 2, 2, 4>(delta, frags, out, m, n, r, K, st);
-            else
-                rc = project_p_launch<NS, 2, 1, 2, 2, 2>(delta, frags, out, m, n, r, K, st);
-            break;
-        case 4:
-            if (ceil_div(m, 128) * K >= 256)
-                rc = project_p_ws_launch<NS, 2, 2, 2, 4>(delta, frags, out, m, n, r, K, st);
-            else
-                rc = project_p_launch<NS, 2, 2, 1, 2, 2>(delta, frags, out, m, n, r, K, st);
-            break;
-        default:
-            // 128 rows per workgroup once that still gives every compute unit a workgroup
-            if (ceil_div(m, 128) * K >= 256)
-                rc = project_p_ws_launch<NS, 2, 4, 1, 4>(delta, frags, out, m, n, r, K, st);
-            else
-                rc = project_p_launch<NS, 2, 4, 1, 1, 2>(delta, frags, out, m, n, r, K, st);
-            break;
+    PtrPack<float *> dst = out;
+    if (pl.S > 1) {
+        float *base = reinterpret_cast<float *>(wsb + a256((size_t)KS * cb * NS * 1024));
+        for (int k = 0; k < K; ++k) dst.p[k] = base + (int64_t)k * pl.S * slab;
+    }
+    {
+        Timed timed(KID_PROJECT_P, st);
+        switch (cb) {
+            case 1: rc = project_p_ws_launch<NS, 1, 1, 4>(pl, delta, frags, dst, m, n, r, K, st); break;
+            case 2: rc = project_p_ws_launch<NS, 1, 2, 2>(pl, delta, frags, dst, m, n, r, K, st); break;
+            case 4:
+                rc = pl.rows == 64 ? project_p_ws_launch<NS, 2, 2, 2, 2>(pl, delta, frags, dst, m, n, r, K, st)
+                                   : project_p_ws_launch<NS, 2, 2, 2>(pl, delta, frags, dst, m, n, r, K, st);
+                break;
+            default:
+                rc = pl.rows == 64 ? project_p_ws_launch<NS, 2, 4, 1, 2>(pl, delta, frags, dst, m, n, r, K, st)
+                                   : project_p_ws_launch<NS, 2, 4, 1>(pl, delta, frags, dst, m, n, r, K, st);
+                break;
+        }
+        if (rc == DLCX_OK) rc = check_launch("project_p_mfma");
     }
     if (rc != DLCX_OK) return rc;
-    return check_launch("project_p_mfma");
+    return finish_splits(K, pl.S, slab, dst, out, partial, st);
 }
 
 template <int NS, int CBW, int WCB>
@@ -1582,7 +1543,7 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
                         const float *p_hat, const PtrPack<float *> &out, void *workspace,
                         PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
-    const QPlan q = q_plan(m, n, r, K);
+    const QPlan q = q_plan(NS, m, n, r, K);
     const bool f16 = F16 && cb >= 4;
     const int pieces = F16 ? 3 : NS;  // as the workspace was sized
     char *wsb = reinterpret_cast<char *>(workspace);
@@ -1621,26 +1582,20 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     }
     if (rc == DLCX_OK) rc = check_launch("project_q_mfma");
     }
-    if (rc != DLCX_OK || q.S == 1) return rc;
-    PartialSums sums;
-    sums.S = q.S;
-    sums.stride = slab;
-    for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k];
-    if (partial) {
-        *partial = sums;
-        return DLCX_OK;
-    }
-    return launch_sum_slabs(K, sums.slabs, out, slab, q.S, slab, st);
+    if (rc != DLCX_OK) return rc;
+    return finish_splits(K, q.S, slab, dst, out, partial, st);
 }
 
 int launch_project_p_mfma(int mma, int64_t m, int64_t n, int r, int K,
                           const PtrPack<const float *> &delta, const float *q_in,
-                          const PtrPack<float *> &out, void *workspace, hipStream_t st) {
-    if (mma == DLCX_MMA_F32) return project_p_ns<3>(m, n, r, K, delta, q_in, out, workspace, st);
+                          const PtrPack<float *> &out, void *workspace, PartialSums *partial,
+                          hipStream_t st) {
+    if (mma == DLCX_MMA_F32)
+        return project_p_ns<3>(m, n, r, K, delta, q_in, out, workspace, partial, st);
     int rc = DLCX_OK;
     if (mma == DLCX_MMA_F16 && project_p_f16(m, n, r, K, delta, q_in, out, workspace, st, &rc))
         return rc;
-    return project_p_ns<2>(m, n, r, K, delta, q_in, out, workspace, st);
+    return project_p_ns<2>(m, n, r, K, delta, q_in, out, workspace, partial, st);
 }
 
 int launch_project_q_mfma(int mma, int64_t m, int64_t n, int r, int K,

@@ -159,6 +159,37 @@ def test_project_p_and_q(mma, m, n, r, K, group):
         assert close(to_np(outs[k]), want_q[k], TOL[mma]), ("Q", k)
 
 
+@pytest.mark.parametrize("mma", [dlcx.MMA_F32, dlcx.MMA_BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("m,n,r,K", [
+    (1040, 3184, 24, 1), (144, 4112, 48, 2), (1296, 2064, 100, 3), (528, 1808, 200, 1),  # P split by columns
+    (1040, 784, 100, 2), (336, 1008, 200, 3), (2096, 272, 145, 1),  # short rows: 64 per workgroup
+    (3184, 1040, 24, 1), (4112, 144, 48, 2), (2064, 1296, 100, 3), (1808, 528, 200, 1),  # Q split by rows
+])
+def test_projections_split_along_the_reduction(mma, m, n, r, K):
+    # Few rows (columns) of output: the reduction is split and the partial sums are added behind it, by
+    # the projection itself or by the quantiser.  Stages of 64 that do not divide into the splits, a
+    # last stage that is partial, every number of basis blocks.
+    inp, deltas = _lowrank_inputs(m, n, r, K, seed=7 * m + n + r)
+    d = dlcx.desc(m, n, r, 8, 16, mma)
+    ws = ws_for(d, K + 1)  # a workspace sized for more workers serves fewer
+    d_deltas = [to_dev(x) for x in deltas]
+    p_hat = ref.orthonormalize(rng(r).standard_normal((r, m)).astype(np.float32))
+    for phase, basis, L, want in ((dlcx.PHASE_P, inp.q_in, m, ref.project_p), (dlcx.PHASE_Q, p_hat, n, ref.project_q)):
+        ws.fill_(255)  # NaN in whatever is not written
+        outs = [torch.zeros(r, L, device=DEV) for _ in range(K)]
+        dlcx.dlcx_project(d, phase, d_deltas, to_dev(basis), outs, ws)
+        codes, scales = payload_buffers(d, phase, K)
+        ws.fill_(255)
+        dlcx.dlcx_compress_batched(d, phase, d_deltas, to_dev(basis), codes, scales, ws)
+        factors = ws[: K * r * L * 4].view(torch.float32).view(K, r, L)
+        for k in range(K):
+            assert close(to_np(outs[k]), want(deltas[k], basis), TOL[mma]), (phase, k)
+            assert torch.equal(factors[k], outs[k])  # the same additions in the same order
+            cw, sw = ref.quantize(to_np(outs[k]), 8, 16)
+            assert np.array_equal(to_np(codes[k]), cw)
+            assert np.array_equal(to_np(scales[k]).view(np.uint32), sw.view(np.uint32))
+
+
 @pytest.mark.parametrize("m,n,r,K", [
     (16, 16, 16, 1), (48, 272, 17, 3), (272, 80, 31, 2),      # fewer steps than wavefronts, ragged tiles
     (1040, 208, 65, 1), (320, 336, 128, 2), (272, 528, 129, 1), (512, 256, 256, 1),
