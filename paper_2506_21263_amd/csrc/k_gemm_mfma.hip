@@ -24,8 +24,9 @@
 //   pack_kcontig_kernel, pack_f16_kernel, pack_sweep_kernel   fragments of a basis, of both forms
 //                                                 of a basis, of all operands of a sweep
 //   project_p_ws_kernel, project_q_ws_kernel      projections with producer and consumer
-//                                                 wavefronts (Q: r > 32)
-//   project_q_mfma_kernel                         Q at r <= 32, every wavefront does everything
+//                                                 wavefronts
+//   project_q_mfma_kernel                         Q of three pieces at r <= 32, every wavefront
+//                                                 does everything
 //   reconstruct_mfma_kernel                       Delta_hat tile by tile with the elementwise
 //                                                 steps of Alg. 2 fused in (any rank)
 //   round_mfma_kernel                             the same plus the P phase of the next
@@ -551,9 +552,11 @@ __device__ __forceinline__ void vec_to_array<4>(const float4 &v, float (&out)[4]
     out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
 }
 
-// Used for one basis block (r <= 32); from two blocks on project_q_ws_kernel below (at two
-// blocks this kernel needs 326 registers, one wavefront per SIMD: 4.8 - 5.5 TB/s on the large
-// shapes against 4.9 - 6.0).
+// Used for three pieces and one basis block (r <= 32): there the two-role kernel below has one
+// workgroup per unit, 98 KB of LDS, and half of this one's requests in flight (8192 x 8192 r = 20 181 us
+// here, 206 there).  With two pieces it has two workgroups per unit and takes every rank: 170 us
+// against 178 here, 2048 x 2048 r = 32 21 | 25, 4352 x 7824 r = 6 three workers 87 | 108.  From two
+// blocks on this kernel needs 326 registers, one wavefront per SIMD.
 template <int JB>
 __device__ __forceinline__ typename VecOf<JB>::type stream_load_vec(const float *p);
 template <>
@@ -1080,6 +1083,8 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 // registers) at 4 basis blocks too: 8192 x 8192 r = 100 4.0e-7 from fp64, 1.0e-6 in one accumulator.
 template <int NS, int BLOCKS>
 constexpr bool kApartQ = NS >= 2 && BLOCKS <= (NS == 3 ? 4 : 2);
+template <int NS, int BLOCKS>
+constexpr int kChainsQ = NS >= 2 && BLOCKS == 1 ? 2 : 1;  // accumulators that take the k-steps in turn
 template <int NS, int CBW, int WCB>
 __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
@@ -1174,7 +1179,10 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
     // -------------------------------------------------------------------------------- consumers
     const int wcb = wave % WCB, wq = wave / WCB;
     constexpr bool kApart = kApartQ<NS, CBW * QW>;
-    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1];
+    constexpr int kChains = kChainsQ<NS, CBW * QW>;
+    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1], odd;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) odd[v] = 0.f;
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
@@ -1214,7 +1222,8 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
                 for (int q = 0; q < QW; ++q)
-                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q], acc[cb][q],
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q],
+                                               ks % kChains ? odd : acc[cb][q],
                                                small[kApart ? cb : 0][kApart ? q : 0]);
             load_frags(s_begin + t * 4 + ks + AD, ks % AD);
             __builtin_amdgcn_sched_barrier(0);
@@ -1228,6 +1237,10 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
             for (int q = 0; q < QW; ++q)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[cb][q][v] += small[cb][q][v];
+    }
+    if constexpr (kChains == 2) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][0][v] += odd[v];
     }
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
@@ -1575,7 +1588,10 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     }
     const uint32_t *guard = f16 ? f.record : nullptr;
     switch (cb) {
-        case 1: hipLaunchKernelGGL((project_q_mfma_kernel<NS, 1, 4, 2>), grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab); break;
+        case 1:
+            if constexpr (NS == 2) rc = project_q_ws_launch<NS, 1, 1>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
+            else hipLaunchKernelGGL((project_q_mfma_kernel<NS, 1, 4, 2>), grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab);
+            break;
         case 2: rc = project_q_ws_launch<NS, 1, 2>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab); break;
         case 4: rc = project_q_ws_launch<NS, 1, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard); break;
         default: rc = project_q_ws_launch<NS, 2, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard); break;
