@@ -14,7 +14,7 @@ kernel of libdlcx_hip.so.
 
 The matrices of a stage are independent, so consecutive runs of them are dealt to a few HIP
 streams (all at the default priority): the short, latency-bound kernels of one run (Cholesky,
-Jacobi, quantiser; batched over the run) then go beside the HBM-bound sweeps of another.
+effective rank, quantiser; batched over the run) then go beside the HBM-bound sweeps of another.
 """
 import ctypes as C
 
