@@ -100,9 +100,11 @@ __device__ __forceinline__ double2 sturm_fill() { return make_double2(4.0, 0.0);
 
 // Number of eigenvalues below x: sign changes of p_i = (d_i - x) p_{i-1} - e_i^2 p_{i-2}, where the
 // quotients p_i / p_{i-1} would need a division per term.  The sign bits are collected and compared
-// 16 at a time; every eight terms the pair is scaled back (a term is at most 5 x the larger of the
-// two before it and, over two steps, at least 2^-120 x, so nothing overflows or vanishes between).
-// Eight terms are read while the eight before are worked on.
+// 16 at a time; every eight terms the pair is scaled back by the larger of the two (one may be exactly
+// zero: x on the diagonal of decoupled rows).  A term is at most 5 x the larger of the two before it, and
+// the step from pair to pair has the determinant e^2 >= 2^-120: over eight the larger one grows at most
+// 2^19 x and shrinks to no less than 2^-979, so nothing overflows or vanishes between.  Eight terms are
+// read while the eight before are worked on.
 __device__ __forceinline__ int count_below(const double2 *t, int blocks, double x) {
     double p0 = 0.0, p1 = 1.0;  // t[0].y multiplies p0
     uint32_t signs = 0;
@@ -118,7 +120,7 @@ __device__ __forceinline__ int count_below(const double2 *t, int blocks, double 
             p0 = p1;
             p1 = p;
         }
-        const int ex = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+        const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
         p0 = ldexp(p0, ex);
         p1 = ldexp(p1, ex);
     };

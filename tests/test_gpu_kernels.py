@@ -473,6 +473,30 @@ def test_effective_rank_tile_edges_and_decoupled_rows(r, kind):
         assert int(out.item()) == ref.effective_rank(q, tau), tau
 
 
+@pytest.mark.parametrize("r,norms2", [
+    (32, [1] * 18 + [0] * 13 + [9]), (64, [1] * 18 + [0] * 45 + [5]), (64, [5] + [1] * 41 + [0] * 22),
+    (100, [1] * 18 + [65] + [0] * 81), (250, [1] * 101 + [65] + [0] * 148),
+])
+def test_effective_rank_on_runs_of_equal_decoupled_rows(r, norms2):
+    # S is diagonal, the largest element G + 1 times the others for the G points that a round of the
+    # multisection takes (4, 8, 64): the first point is the repeated eigenvalue to the last bit, and
+    # every other term of the Sturm sequence there is exactly zero.  (No share of the trace falls on a whole
+    # number of eigenvalues.)
+    n = 768
+    q = np.zeros((r, n), np.float32)
+    for c, x in enumerate(norms2):  # x = a^2 + b^2 + ..: small integers, squares and sums are exact
+        for k in range(3):
+            a = int(np.sqrt(x))
+            q[c, 3 * c + k] = a
+            x -= a * a
+        assert x == 0
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for tau in (0.3, 0.6, 0.9, 0.99):
+        dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
+        assert int(out.item()) == ref.effective_rank(q, tau), tau
+
+
 def test_select_rank_stage_value_and_window():
     # three matrices with known r' (3, 49, zero matrix -> rmin 4): mean 56/3 = 18.67 -> 19
     n, r = 512, 64
