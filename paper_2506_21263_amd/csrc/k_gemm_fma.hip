@@ -338,8 +338,14 @@ static int q_splits(int64_t m, int64_t n, int K) {
 }
 
 size_t fma_project_workspace_bytes(int64_t m, int64_t n, int r, int K) {
-    // Q phase: K * S slabs of r x n floats
-    return (size_t)K * (size_t)q_splits(m, n, K) * (size_t)r * (size_t)n * sizeof(float);
+    // Q phase: slabs of r x n floats, enough for any smaller number of workers that is later run in this
+    // workspace: fewer workers may be split further, 8 at 8256 columns not at all, 7 in two (14 slabs)
+    int64_t slabs = 0;
+    for (int k = 1; k <= K; ++k) {
+        const int64_t s = (int64_t)k * q_splits(m, n, k);
+        if (s > slabs) slabs = s;
+    }
+    return (size_t)slabs * (size_t)r * (size_t)n * sizeof(float);
 }
 
 int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,

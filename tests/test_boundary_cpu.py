@@ -3,6 +3,7 @@ header declares, sizes payloads as the paper's accounting implies, and rejects b
 before launching anything."""
 import ctypes as C
 import os
+import random
 import re
 
 import pytest
@@ -38,6 +39,24 @@ def test_payload_bytes_follow_the_layout():
     d0 = dlcx.desc(512, 512, 8, 4, 64)
     assert dlcx.dlcx_payload_bytes(d0, 0)[0] + dlcx.dlcx_payload_bytes(d0, 1)[0] == 4608
     assert dlcx.dlcx_workspace_bytes(d, 4) >= 4 * 64 * 8192 * 4
+
+
+@pytest.mark.parametrize("mma", range(4), ids=["fma", "f32", "bf16", "f16"])
+def test_a_workspace_serves_fewer_workers_and_lower_ranks(mma):
+    # dlcx_workspace_bytes promises room for UP TO K workers, and a stage keeps one workspace while
+    # its rank falls.  A call's own layout fits the size of its own (r, K), so it is enough that the
+    # size never grows when K or r gets smaller.
+    rng = random.Random(mma)
+    shapes = [(8944, 9248, 64), (512, 8256, 16), (8256, 512, 16), (256, 256, 256), (28672, 8192, 256)]
+    shapes += [(16 * round(2 ** rng.uniform(0, 10)), 16 * round(2 ** rng.uniform(0, 10)),
+                round(2 ** rng.uniform(0, 8))) for _ in range(400)]
+    for m, n, r in shapes:
+        r = min(r, m, n)
+        size = [dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, r, 4, 16, mma), K) for K in range(1, 17)]
+        assert all(a > 0 for a in size) and size == sorted(size), (m, n, r)
+        low = rng.randint(1, r)
+        for K in (1, 3, 8, 16):
+            assert dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, low, 4, 16, mma), K) <= size[K - 1], (m, n, r, low, K)
 
 
 @pytest.mark.parametrize("bad", [

@@ -190,6 +190,27 @@ def test_projections_split_along_the_reduction(mma, m, n, r, K):
             assert np.array_equal(to_np(scales[k]).view(np.uint32), sw.view(np.uint32))
 
 
+@pytest.mark.parametrize("mma", [dlcx.MMA_FMA, dlcx.MMA_F32, dlcx.MMA_BF16, dlcx.MMA_F16],
+                         ids=["fma", "f32", "bf16", "f16"])
+@pytest.mark.parametrize("m,n,r,K,k", [(512, 8256, 16, 8, 7), (1024, 8720, 96, 4, 3), (8720, 528, 96, 4, 3)])
+def test_fewer_workers_stay_inside_a_larger_workspace(mma, m, n, r, K, k):
+    # Fewer workers may be split further (8 workers at 8256 columns not at all, 7 in two): the
+    # bytes behind a workspace sized for K workers stay as they were when k of them are run.
+    guard = 1 << 20
+    size = dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, r, 4, 16, mma), K)
+    buf = torch.full((size + guard,), 165, device=DEV, dtype=torch.uint8)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(r)
+    delta = torch.randn(m, n, generator=g, device=DEV)
+    d = dlcx.desc(m, n, r, 4, 16, mma)
+    for phase, L in ((dlcx.PHASE_P, n), (dlcx.PHASE_Q, m)):
+        basis = torch.randn(r, L, generator=g, device=DEV)
+        codes, scales = payload_buffers(d, phase, k)
+        dlcx.dlcx_compress_batched(d, phase, [delta] * k, basis, codes, scales, buf[:size])
+        assert bool((buf[size:] == 165).all()), phase
+        assert all(torch.equal(c, codes[0]) for c in codes) and bool((codes[0] != 0).any())
+
+
 @pytest.mark.parametrize("m,n,r,K", [
     (16, 16, 16, 1), (48, 272, 17, 3), (272, 80, 31, 2),      # fewer steps than wavefronts, ragged tiles
     (1040, 208, 65, 1), (320, 336, 128, 2), (272, 528, 129, 1), (512, 256, 256, 1),
