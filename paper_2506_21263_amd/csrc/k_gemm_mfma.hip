@@ -1280,12 +1280,17 @@ static int64_t most_splits(int64_t wgs) {
     return s > 64 ? 64 : s;
 }
 static int64_t out_wgs(int64_t side) { return ceil_div(side, 128); }
+// Most splits of a reduction by its length: two stages of 64 columns (P), two pipeline rounds of every
+// wavefront (Q: 2 x 4 x 2 k-steps of 16 rows) each.
+static int64_t most_p_splits(int64_t n) { return ceil_div(ceil_div(n, 64), 2); }
+static int64_t most_q_splits(int64_t m) { return ceil_div(m, 256); }
 // Slabs a workspace for K workers has room for: enough for any smaller number of workers and any
 // smaller rank that is later run in it.
-static int64_t slab_room(int64_t side, int K) {
+static int64_t slab_room(int64_t side, int K, int64_t by_length) {
     int64_t room = 0;
     for (int k = 1; k <= K; ++k) {
-        const int64_t s = most_splits(out_wgs(side) * k);
+        int64_t s = most_splits(out_wgs(side) * k);
+        if (s > by_length) s = by_length;
         if (s > 1 && s * k > room) room = s * k;
     }
     return room;
@@ -1330,7 +1335,7 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     p.rows = cb_of(r) >= 4 && n <= kPShort && ceil_div(m, 64) * K <= kQUnits ? 64 : 128;
     const int64_t wgs = ceil_div(m, p.rows) * K;
     int64_t smax = most_splits(wgs), S = 1;
-    if (smax > ceil_div(stages, 2)) smax = ceil_div(stages, 2);
+    if (smax > most_p_splits(n)) smax = most_p_splits(n);
     // (a second workgroup on every unit does not pay here: 8192 x 8192 r = 64 271 us split in two, 240 not)
     if (wgs < kQUnits) S = best_splits(wgs, n, 64, (int64_t)K * r * m, smax);
     p.stages = ceil_div(stages, S);
@@ -1346,8 +1351,7 @@ static QPlan q_plan(int ns, int64_t m, int64_t n, int r, int K) {
     p.depth = 2;  // k-steps (16 rows) of delta in flight per wavefront
     const int64_t wgs = out_wgs(n) * K;
     int64_t smax = most_splits(wgs);
-    const int64_t by_rows = ceil_div(m, 64 * p.depth * 2);  // at least 2 pipeline rounds per wave
-    if (smax > by_rows) smax = by_rows;
+    if (smax > most_q_splits(m)) smax = most_q_splits(m);
     int64_t S = 1;
     if (ns == 3 && cb == 1) {
         // the one-role kernel: two workgroups for every unit, whatever remains.  (Fewer splits, with
@@ -1380,10 +1384,10 @@ size_t mfma_project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K)
     // k-steps are rounded up to `depth` per wavefront: 8 more for every split (most of them with one
     // worker, if the workspace is later used for fewer workers)
     int64_t splits = most_splits(out_wgs(n));
-    if (splits > ceil_div(m, 256)) splits = ceil_div(m, 256);
+    if (splits > most_q_splits(m)) splits = most_q_splits(m);
     const size_t q_frags = (size_t)(ceil_div(m, 16) + 8 * splits) * cb * ns * 1024;
-    const size_t slabs = (size_t)slab_room(n, K) * r * n * sizeof(float);
-    const size_t p_slabs = (size_t)slab_room(m, K) * r * m * sizeof(float);
+    const size_t slabs = (size_t)slab_room(n, K, most_q_splits(m)) * r * n * sizeof(float);
+    const size_t p_slabs = (size_t)slab_room(m, K, most_p_splits(n)) * r * m * sizeof(float);
     const size_t a = a256(p_frags) + a256(p_slabs), b = a256(q_frags) + a256(slabs);
     return (a > b ? a : b) + (mma == DLCX_MMA_F16 ? a256(kF16ScratchBytes) : 0);
 }

@@ -59,6 +59,21 @@ def test_a_workspace_serves_fewer_workers_and_lower_ranks(mma):
             assert dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, low, 4, 16, mma), K) <= size[K - 1], (m, n, r, low, K)
 
 
+@pytest.mark.parametrize("mma", range(1, 4), ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("m,n,r,K", [(256, 256, 256, 4), (512, 512, 256, 4), (512, 512, 8, 2), (16, 4096, 16, 8)])
+def test_workspaces_of_small_matrices_stay_small(mma, m, n, r, K):
+    # Room for partial sums only as far as the length of the reduction lets a plan split it: a share
+    # of at least 128 columns (P) or 256 rows (Q).  Besides them: the K factors, the fragments of both
+    # factors and the basis in up to three pieces of 2 bytes (sides and rank padded to 64 and to a
+    # power of two), or the fp64 sums of the orthonormalisation.
+    size = dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, r, 4, 16, mma), K)
+    slabs = K * r * (m * -(-n // 128) + n * -(-m // 256)) * 4
+    up = lambda x: -(-x // 64) * 64 + 256
+    frags = 3 * 2 * max(32, 2 * r) * (up(m) + up(n))
+    sums = (-(-max(m, n) // 512) + 3) * (r + 1) ** 2 * 8
+    assert size <= K * r * max(m, n) * 4 + slabs + frags + sums + 16384
+
+
 @pytest.mark.parametrize("bad", [
     dict(m=0), dict(n=-16), dict(r=0), dict(r=257), dict(r=600), dict(qbits=3), dict(qbits=16),
     dict(group=48), dict(group=0), dict(m=520), dict(mma=4), dict(mma=-1)])
