@@ -1343,7 +1343,7 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     return p;
 }
 
-static QPlan q_plan(int ns, int64_t m, int64_t n, int r, int K) {
+static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
     QPlan p;
     const int cb = cb_of(r);
     // 128 columns per workgroup in both Q kernels
@@ -1360,6 +1360,11 @@ static QPlan q_plan(int ns, int64_t m, int64_t n, int r, int K) {
     } else if (wgs >= kQUnits) {
         // every compute unit has a workgroup: two, except at 8 basis blocks, where one fills it
         if (cb < 8) S = smax;
+    } else if (ns == 2 && cb >= 4 && !f16) {
+        // one accumulator for all piece products: sums as short as a full launch makes them (two
+        // workgroups for every unit, one at 8 basis blocks, whatever remains)
+        S = ceil_div(cb == 8 ? kQUnits : 2 * kQUnits, wgs);
+        if (S > smax) S = smax;
     } else if (ns == 3 && cb == 8) {
         // no room for accumulators of the small products (kApartQ): short sums instead, 5008 x 3376 r =
         // 200 157 us; by the estimate 143 and 1.2 times as far from fp64; before 185
@@ -1560,8 +1565,8 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
                         const float *p_hat, const PtrPack<float *> &out, void *workspace,
                         PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
-    const QPlan q = q_plan(NS, m, n, r, K);
     const bool f16 = F16 && cb >= 4;
+    const QPlan q = q_plan(NS, f16, m, n, r, K);
     const int pieces = F16 ? 3 : NS;  // as the workspace was sized
     char *wsb = reinterpret_cast<char *>(workspace);
     uint4 *frags = reinterpret_cast<uint4 *>(wsb);
