@@ -991,36 +991,46 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
                     issue(tile_at(it + 1), 0, true, ep.apply && Kw == 1);
                 }
                 wave_lds_sync();
-                // NS == 3: the tile's products in accumulators of their own, added to the sum once
-                // (mfma_split_sum: the fp32 error of a long sum is the rounding of its large terms)
-                f32x16_t part[CB];
-                if constexpr (NS == 3) {
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) part[cb][v] = 0.f;
-                }
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    uint4 b[NS];
+                // NS == 3: the tile's products of a basis block in an accumulator of their own, added to
+                // the sum once (mfma_split_sum: the fp32 error of a long sum is the rounding of its
+                // large terms).  Block by block: for all of them at once the registers do not last.
+                auto load_b = [&](int s, uint4 (&b)[NS]) {
 #pragma unroll
                     for (int h = 0; h < NS; ++h)
                         b[h] = *reinterpret_cast<const uint4 *>(
                             btile + (h * 32 + (lane & 31)) * kPPitch + s * 32 + (lane >> 5) * 16);
+                };
+                auto product = [&](int cb, int s, const uint4 (&b)[NS], f32x16_t &sum) {
+                    uint4 a[NS];
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) {
-                        uint4 a[NS];
-#pragma unroll
-                        for (int h = 0; h < NS; ++h)
-                            a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
-                        mfma_split<NS>(a, b, NS == 3 ? part[cb] : acc[k][cb]);
-                    }
-                }
+                    for (int h = 0; h < NS; ++h)
+                        a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
+                    mfma_split<NS>(a, b, sum);
+                };
                 if constexpr (NS == 3) {
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
+                    for (int cb = 0; cb < CB; ++cb) {
+                        f32x16_t part;
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) acc[k][cb][v] += part[cb][v];
+                        for (int v = 0; v < 16; ++v) part[v] = 0.f;
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            uint4 b[NS];
+                            load_b(s, b);
+                            product(cb, s, b, part);
+                        }
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[k][cb][v] += part[v];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        uint4 b[NS];
+                        load_b(s, b);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) product(cb, s, b, acc[k][cb]);
+                    }
                 }
             }
         }
