@@ -352,6 +352,11 @@ constexpr int kWs = 512;  // threads of the two-role workgroup
 // accumulator 1.1e-6; 8192 x 8192 r = 20 193 us either way.
 template <int NS, int BLOCKS>
 constexpr bool kApartP = NS >= 2 && BLOCKS <= 2;
+// Accumulators that take the k-steps in turn, where a wavefront has one block: half as many roundings in
+// each.  Error against fp64, 8192 x 8192 r = 20 three pieces 2.4e-7 (in one accumulator 4.7e-7), 8192 x
+// 2048 r = 32 two pieces 4.2e-7 (4.7e-7); no difference in time.
+template <int NS, int BLOCKS>
+constexpr int kChainsP = NS >= 2 && BLOCKS == 1 ? 2 : 1;
 template <int NS, int CBW, int WC, int WR, int RB>
 __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
@@ -447,7 +452,10 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
     // -------------------------------------------------------------------------------- consumers
     const int wc = wave % WC, wr = wave / WC;
     constexpr bool kApart = kApartP<NS, CBW * RBW>;
-    f32x16_t acc[CBW][RBW], small[kApart ? CBW : 1][kApart ? RBW : 1];
+    constexpr int kTurns = kChainsP<NS, CBW * RBW>;
+    f32x16_t acc[CBW][RBW], small[kApart ? CBW : 1][kApart ? RBW : 1], odd;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) odd[v] = 0.f;
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
@@ -494,7 +502,8 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
                 for (int rb = 0; rb < RBW; ++rb)
-                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[rb], acc[cb][rb],
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[rb],
+                                               ks % kTurns ? odd : acc[cb][rb],
                                                small[kApart ? cb : 0][kApart ? rb : 0]);
             // requested here and nowhere later: AD k-steps of matrix-core work to come back
             load_frags(t * 4 + ks + AD, ks % AD);
@@ -509,6 +518,10 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int rb = 0; rb < RBW; ++rb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[cb][rb][v] += small[cb][rb][v];
+    }
+    if constexpr (kTurns == 2) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][0][v] += odd[v];
     }
 #pragma unroll
     for (int cb = 0; cb < CBW; ++cb)
@@ -991,9 +1004,10 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
                     issue(tile_at(it + 1), 0, true, ep.apply && Kw == 1);
                 }
                 wave_lds_sync();
-                // NS == 3: the tile's products of a basis block in an accumulator of their own, added to
-                // the sum once (mfma_split_sum: the fp32 error of a long sum is the rounding of its
-                // large terms).  Block by block: for all of them at once the registers do not last.
+                // NS == 3, or one basis block: the tile's products of a block in an accumulator of their
+                // own, added to the sum once (mfma_split_sum: the fp32 error of a long sum is the
+                // rounding of its large terms).  Block by block: for all of them at once the registers
+                // do not last.
                 auto load_b = [&](int s, uint4 (&b)[NS]) {
 #pragma unroll
                     for (int h = 0; h < NS; ++h)
@@ -1007,7 +1021,7 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
                         a[h] = basis_lds[((s * CB + cb) * NS + h) * 64 + lane];
                     mfma_split<NS>(a, b, sum);
                 };
-                if constexpr (NS == 3) {
+                if constexpr (NS == 3 || CB == 1) {
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb) {
                         f32x16_t part;
@@ -1094,9 +1108,9 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 template <int NS, int BLOCKS>
 constexpr bool kApartQ = NS >= 2 && BLOCKS <= (NS == 3 ? 4 : 2);
 template <int NS, int BLOCKS>
-constexpr int kChainsQ = NS >= 2 && BLOCKS == 1 ? 2 : 1;  // accumulators that take the k-steps in turn
+constexpr int kChainsQ = NS >= 2 && BLOCKS == 1 ? 4 : 1;  // accumulators that take the k-steps in turn
 template <int NS, int CBW, int WCB>
-__global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *> deltas,
+__global__ __launch_bounds__(kWs, NS == 2 && CBW * WCB == 1 ? 4 : 1) void project_q_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r, int64_t ksteps_per_wg,
@@ -1189,10 +1203,12 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
     // -------------------------------------------------------------------------------- consumers
     const int wcb = wave % WCB, wq = wave / WCB;
     constexpr bool kApart = kApartQ<NS, CBW * QW>;
-    constexpr int kChains = kChainsQ<NS, CBW * QW>;
-    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1], odd;
+    constexpr int kTurns = kChainsQ<NS, CBW * QW>;
+    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1], odd[3];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) odd[v] = 0.f;
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) odd[x][v] = 0.f;
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
@@ -1233,7 +1249,7 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
 #pragma unroll
                 for (int q = 0; q < QW; ++q)
                     mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q],
-                                               ks % kChains ? odd : acc[cb][q],
+                                               ks % kTurns ? odd[(ks + 3) % 4] : acc[cb][q],
                                                small[kApart ? cb : 0][kApart ? q : 0]);
             load_frags(s_begin + t * 4 + ks + AD, ks % AD);
             __builtin_amdgcn_sched_barrier(0);
@@ -1248,9 +1264,9 @@ __global__ __launch_bounds__(kWs) void project_q_ws_kernel(PtrPack<const float *
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[cb][q][v] += small[cb][q][v];
     }
-    if constexpr (kChains == 2) {
+    if constexpr (kTurns == 4) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] += odd[v];
+        for (int v = 0; v < 16; ++v) acc[0][0][v] = (acc[0][0][v] + odd[0][v]) + (odd[1][v] + odd[2][v]);
     }
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
