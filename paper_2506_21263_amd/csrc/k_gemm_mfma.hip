@@ -537,6 +537,104 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
         }
 }
 
+// The same product with every wavefront doing everything, 64 rows per workgroup: wavefront (wk, wr) takes
+// 32 rows and the k-steps 2 wk, 2 wk + 1 of every stage, the two halves are added at the end; basis
+// fragments are requested a stage ahead and before the next stage of delta.  For one basis block, where the
+// matrix cores have little to do: four such workgroups share a compute unit (two with three pieces) and
+// even out what 128 rows at a time leave over.  Where it is used: p_plan.
+constexpr int kOneRows = 64;
+template <int NS>
+__global__ __launch_bounds__(kW) void project_p_one_kernel(PtrPack<const float *> deltas,
+                                                           const uint4 *__restrict__ afrags,
+                                                           PtrPack<float *> outs, int64_t m,
+                                                           int64_t n, int r) {
+    constexpr int kVec = kOneRows * 16 / kW;  // float4 per thread and stage
+    constexpr int kBuf = NS * kOneRows * kPPitch;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kBuf];
+    const float *__restrict__ delta = deltas.p[blockIdx.y];
+    float *__restrict__ out = outs.p[blockIdx.y];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wk = wave & 1, wr = wave >> 1;
+    const int64_t i0 = (int64_t)blockIdx.x * kOneRows;
+    const int64_t nstages = (n + 63) / 64;
+    f32x16_t acc, small;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = small[v] = 0.f;
+
+    float4 pre[kVec];  // this thread's share of a stage: (row, 4 columns)
+    auto load_stage = [&](int64_t t) {
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) {
+            const int idx = tid + kW * u;
+            const int row = idx >> 4;
+            const int64_t j = t * 64 + (idx & 15) * 4;
+            pre[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (i0 + row < m && j < n) pre[u] = stream_load4(delta + (i0 + row) * n + j);
+        }
+    };
+    uint4 a[2][NS];
+    auto load_frags = [&](uint4 (&dst)[2][NS], int64_t t) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int h = 0; h < NS; ++h)
+                dst[ks][h] = afrags[((t * 4 + wk * 2 + ks) * NS + h) * 64 + lane];
+    };
+    load_frags(a, 0);
+    load_stage(0);
+    for (int64_t t = 0; t < nstages; ++t) {
+        unsigned char *buf = lds + (t & 1) * kBuf;
+#pragma unroll
+        for (int u = 0; u < kVec; ++u) {
+            const int idx = tid + kW * u;
+            uint32_t lo[NS], hi[NS];
+            split2<NS>(pre[u].x, pre[u].y, lo);
+            split2<NS>(pre[u].z, pre[u].w, hi);
+#pragma unroll
+            for (int h = 0; h < NS; ++h)
+                *reinterpret_cast<uint2 *>(buf + (h * kOneRows + (idx >> 4)) * kPPitch + (idx & 15) * 8) =
+                    make_uint2(lo[h], hi[h]);
+        }
+        // fragments before delta: waiting for them later does not wait for that stage as well
+        uint4 an[2][NS];
+        if (t + 1 < nstages) load_frags(an, t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < nstages) load_stage(t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            uint4 b[NS];
+#pragma unroll
+            for (int h = 0; h < NS; ++h)
+                b[h] = *reinterpret_cast<const uint4 *>(buf + (h * kOneRows + wr * 32 + (lane & 31)) * kPPitch +
+                                                        (wk * 2 + ks) * 32 + (lane >> 5) * 16);
+            mfma_split_sum<NS, true>(a[ks], b, acc, small);
+        }
+        if (t + 1 < nstages) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int h = 0; h < NS; ++h) a[ks][h] = an[ks][h];
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] += small[v];
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(lds);
+    if (wk == 1)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(wr * 16 + v) * 64 + lane] = acc[v];
+    __syncthreads();
+    const int64_t i = i0 + wr * 32 + (lane & 31);
+    if (wk == 1 || i >= m) return;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = d_row(v, lane);
+        if (c < r) out[(int64_t)c * m + i] = acc[v] + red[(wr * 16 + v) * 64 + lane];
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Q phase:  Q_k[j][c] = sum_i delta_k[i][j] P_hat[c][i].
 // Wavefront: 32 JB columns x all CB basis blocks over its own range of rows.  The B operand
@@ -1349,21 +1447,32 @@ struct PPlan {
     int rows;        // rows of delta per workgroup
     int S;           // column splits
     int64_t stages;  // stages of 64 columns of a split
+    bool one_role;   // project_p_one_kernel
 };
 // 64 rows per workgroup where the matrix cores set the pace (4 or 8 basis blocks), the rows then still
 // fit the units in one round and the reduction is short: a longer chain of stages is not what such a
 // launch waits for.  64 | 128 rows, us: 8192 x 512 r = 100 two workers 21 | 27, 2176 x 256 r = 145 16 |
 // 20, 7136 x 640 r = 74 22 | 25, 6000 x 1024 r = 100 21 | 23; 3008 x 2048 r = 200 41 | 39, 2048 x 3072 r =
 // 200 three pieces 81 | 76.
+// One basis block and a workgroup for nearly every unit: the one-role kernel, unless the reduction is long
+// and 128 rows deal evenly (one for every unit, or nearly two).  one-role | two-role, us, r = 20, two
+// workers, two pieces: 15360 x 512 18.4 | 19.2, x 2048 54.0 | 55.8; 16384 x 512 18.9 | 20.5, x 4096 126 |
+// 131, x 8192 221 | 216; 16896 x 512 21.7 | 27.2, x 4096 129 | 165, x 8192 250 | 279; 24576 x 4096 152 | 185,
+// x 8192 315 | 344; 32768 x 1024 64 | 71, x 4096 213 | 234, x 8192 411 | 350; 65536 x 1024 117 | 132, x 4096
+// 410 | 428, x 8192 791 | 699.  Three pieces: 16384 x 1024 36.5 | 40.3, x 8192 221 | 210; 16896 x 8192 340 |
+// 374; 32768 x 1024 67 | 76, x 4096 244 | 261, x 8192 459 | 420.  Errors against 64 bits are within 2 %.
+constexpr int64_t kPLong = 4096;
+constexpr int64_t kPOneFrom = 240;  // workgroups of 128 rows
 static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     PPlan p;
     const int64_t stages = ceil_div(n, 64);
     p.rows = cb_of(r) >= 4 && n <= kPShort && ceil_div(m, 64) * K <= kQUnits ? 64 : 128;
     const int64_t wgs = ceil_div(m, p.rows) * K;
+    p.one_role = cb_of(r) == 1 && wgs >= kPOneFrom && !(n > kPLong && (wgs <= kQUnits || 2 * wgs > 3 * kQUnits));
     int64_t smax = most_splits(wgs), S = 1;
     if (smax > most_p_splits(n)) smax = most_p_splits(n);
     // (a second workgroup on every unit does not pay here: 8192 x 8192 r = 64 271 us split in two, 240 not)
-    if (wgs < kQUnits) S = best_splits(wgs, n, 64, (int64_t)K * r * m, smax);
+    if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, (int64_t)K * r * m, smax);
     p.stages = ceil_div(stages, S);
     p.S = (int)ceil_div(stages, p.stages);
     return p;
@@ -1551,7 +1660,13 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     {
         Timed timed(KID_PROJECT_P, st);
         switch (cb) {
-            case 1: rc = project_p_ws_launch<NS, 1, 1, 4>(pl, delta, frags, dst, m, n, r, K, st); break;
+            case 1:
+                if (pl.one_role)
+                    hipLaunchKernelGGL(project_p_one_kernel<NS>, dim3((unsigned)ceil_div(m, kOneRows), (unsigned)K),
+                                       dim3(kW), 0, st, delta, frags, out, m, n, r);
+                else
+                    rc = project_p_ws_launch<NS, 1, 1, 4>(pl, delta, frags, dst, m, n, r, K, st);
+                break;
             case 2: rc = project_p_ws_launch<NS, 1, 2, 2>(pl, delta, frags, dst, m, n, r, K, st); break;
             case 4:
                 rc = pl.rows == 64 ? project_p_ws_launch<NS, 2, 2, 2, 2>(pl, delta, frags, dst, m, n, r, K, st)

@@ -190,6 +190,28 @@ def test_projections_split_along_the_reduction(mma, m, n, r, K):
             assert np.array_equal(to_np(scales[k]).view(np.uint32), sw.view(np.uint32))
 
 
+@pytest.mark.parametrize("mma", [dlcx.MMA_F32, dlcx.MMA_BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("m,n,r,K", [
+    (2064, 16, 16, 16), (2064, 80, 31, 16), (1920, 208, 12, 16), (4000, 144, 32, 9),  # one-role: 64 rows
+    (2048, 4112, 20, 16), (2048, 4096, 20, 16),  # one workgroup for every unit: two-role if long, one-role if not
+])
+def test_project_p_of_one_basis_block_with_a_workgroup_per_unit(mma, m, n, r, K):
+    # Ranks up to 32 and at least 240 workgroups of 128 rows: rows that do not divide into 64, one and
+    # two stages of 64 columns, a stage that is partial, both sides of the rule between the kernels.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + n)
+    deltas = [torch.randn(m, n, generator=g, device=DEV) for _ in range(2)]
+    basis = torch.randn(r, n, generator=g, device=DEV)
+    d = dlcx.desc(m, n, r, 8, 16, mma)
+    outs = [torch.full((r, m), float("nan"), device=DEV) for _ in range(K)]
+    dlcx.dlcx_project(d, dlcx.PHASE_P, [deltas[k % 2] for k in range(K)], basis, outs, ws_for(d, K))
+    for k in (0, 1):
+        want = to_np(basis).astype(np.float64) @ to_np(deltas[k]).astype(np.float64).T
+        assert close(to_np(outs[k]), want, TOL[mma]), k
+    for k in range(2, K):
+        assert torch.equal(outs[k], outs[k % 2]), k
+
+
 @pytest.mark.parametrize("mma", [dlcx.MMA_FMA, dlcx.MMA_F32, dlcx.MMA_BF16, dlcx.MMA_F16],
                          ids=["fma", "f32", "bf16", "f16"])
 @pytest.mark.parametrize("m,n,r,K,k", [(512, 8256, 16, 8, 7), (1024, 8720, 96, 4, 3), (8720, 528, 96, 4, 3)])
