@@ -1835,13 +1835,15 @@ struct RoundPlan {
 // 205 | 4: 241; 8192 x 1024 1: 111 | 2: 125; 704 x 4160 9: 50 | 6: 61; 512 x 8192 16: 63 | 8: 79; 3008
 // x 6000 8: 309 | 6: 357; 512 x 512 2: 20 | 1: 23; 2048 x 8192 4: 194.  No ranges of more than 8 tiles
 // up to four ranges: one or two long ones are 13 % slower at 8192 columns whatever the number of rows
-// (the workgroups drift apart), and the count does not matter at 28672.
+// (the workgroups drift apart), and the count does not matter at 28672.  At 4096 columns two ranges are
+// already too long: 4096 x 4096 r = 32 two workers 191, three 158, four 137; 11008 x 4096 467 | 366 | 355,
+// eight 338; 8192 x 4096 324 | 265 | 253.  (3840 and 4080 columns: two are as good as four.)
 static RoundPlan round_plan(int64_t m, int64_t n, int r) {
     RoundPlan p;
     (void)r;
     p.kc = 4;  // workers per launch: 4 x 2 basis blocks x 16 accumulator registers per wavefront
     const int64_t rows = ceil_div(m, 32), tiles = ceil_div(n, 256);
-    const int64_t lo = tiles > 24 ? 4 : ceil_div(tiles, 8), hi = tiles < 32 ? tiles : 32;
+    const int64_t lo = tiles > 24 ? 4 : n == 4096 ? 3 : ceil_div(tiles, 8), hi = tiles < 32 ? tiles : 32;
     int64_t best = lo, best_cost = INT64_MAX;
     for (int64_t c = lo; c <= hi; ++c) {
         const int64_t cost = ceil_div(rows * c, kComputeUnits) * (10 * ceil_div(tiles, c) + 3);
