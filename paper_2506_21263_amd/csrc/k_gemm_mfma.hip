@@ -1420,7 +1420,7 @@ static int64_t slab_room(int64_t side, int K, int64_t by_length) {
     return room;
 }
 
-// The cheapest number of splits, up to smax, of a reduction over `length`: rounds of the launch x
+// The cheapest number of splits, smin to smax, of a reduction over `length`: rounds of the launch x
 // length of a workgroup's share in whole `granule`s (and 128 more to start and drain), plus the slabs,
 // written and read, in the same unit (512 bytes of delta on one compute unit).  Two workgroups on some
 // units and one on the others is as slow as two everywhere.  Measured (us, chosen | two per unit, the
@@ -1430,9 +1430,9 @@ static int64_t slab_room(int64_t side, int K, int64_t by_length) {
 // 125, r = 100 88 | 163; 2048 x 2048 r = 64 26 | 41; 3008 x 5008 r = 100 two workers 54 | 107; 256 x 8192
 // r = 16 one worker 21 | 102; 1120 x 6688 r = 210 one worker 34 | 170.
 static int64_t best_splits(int64_t wgs, int64_t length, int64_t granule, int64_t slab_elements,
-                           int64_t smax) {
-    int64_t best = INT64_MAX, S = 1;
-    for (int64_t s = 1; s <= smax; ++s) {
+                           int64_t smin, int64_t smax) {
+    int64_t best = INT64_MAX, S = smin;
+    for (int64_t s = smin; s <= smax; ++s) {
         const int64_t share = ceil_div(ceil_div(length, s), granule) * granule;
         const int64_t cost = ceil_div(wgs * s, kQUnits) * (share + 128) + s * slab_elements / 16384;
         if (cost < best) {
@@ -1472,7 +1472,7 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     int64_t smax = most_splits(wgs), S = 1;
     if (smax > most_p_splits(n)) smax = most_p_splits(n);
     // (a second workgroup on every unit does not pay here: 8192 x 8192 r = 64 271 us split in two, 240 not)
-    if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, (int64_t)K * r * m, smax);
+    if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, (int64_t)K * r * m, 1, smax);
     p.stages = ceil_div(stages, S);
     p.S = (int)ceil_div(stages, p.stages);
     return p;
@@ -1501,11 +1501,13 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
         S = ceil_div(cb == 8 ? kQUnits : 2 * kQUnits, wgs);
         if (S > smax) S = smax;
     } else if (ns == 3 && cb == 8) {
-        // no room for accumulators of the small products (kApartQ): short sums instead, 5008 x 3376 r =
-        // 200 157 us; by the estimate 143 and 1.2 times as far from fp64; before 185
-        S = 2 * kQUnits / wgs < smax ? 2 * kQUnits / wgs : smax;
+        // no room for accumulators of the small products (kApartQ): at least a workgroup for every
+        // unit, as short sums as that makes.  5008 x 3376 r = 200 157 us; with fewer splits 143 and 1.2
+        // times as far from fp64
+        const int64_t fill = ceil_div(kQUnits, wgs);
+        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, fill < smax ? fill : smax, smax);
     } else {
-        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, smax);
+        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, 1, smax);
     }
     const int64_t kpw = ceil_div(ceil_div(m, 16), S * 4);
     p.ksteps_per_wave = ceil_div(kpw, p.depth) * p.depth;
