@@ -355,9 +355,10 @@ constexpr bool kApartP = NS >= 2 && BLOCKS <= 2;
 // Accumulators that take the k-steps in turn, where a wavefront has one block: half as many roundings in
 // each.  Error against fp64, 8192 x 8192 r = 20 three pieces 2.4e-7 (in one accumulator 4.7e-7), 8192 x
 // 2048 r = 32 two pieces 4.2e-7 (4.7e-7); no difference in time.
-template <int NS, int BLOCKS>
-constexpr int kChainsP = NS >= 2 && BLOCKS == 1 ? 2 : 1;
-template <int NS, int CBW, int WC, int WR, int RB>
+// LONE: as many where it has two, if there are no two workgroups to a compute unit (registers).
+template <int NS, int BLOCKS, bool LONE>
+constexpr int kChainsP = NS >= 2 && BLOCKS <= (LONE ? 2 : 1) ? 2 : 1;
+template <int NS, int CBW, int WC, int WR, int RB, bool LONE>
 __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
                                                            PtrPack<float *> outs, int64_t m,
@@ -452,17 +453,16 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
     // -------------------------------------------------------------------------------- consumers
     const int wc = wave % WC, wr = wave / WC;
     constexpr bool kApart = kApartP<NS, CBW * RBW>;
-    constexpr int kTurns = kChainsP<NS, CBW * RBW>;
-    f32x16_t acc[CBW][RBW], small[kApart ? CBW : 1][kApart ? RBW : 1], odd;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) odd[v] = 0.f;
+    constexpr int kTurns = kChainsP<NS, CBW * RBW, LONE>;
+    f32x16_t acc[kTurns][CBW][RBW], small[kApart ? CBW : 1][kApart ? RBW : 1];
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
         for (int b = 0; b < RBW; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                acc[a][b][v] = 0.f;
+#pragma unroll
+                for (int t = 0; t < kTurns; ++t) acc[t][a][b][v] = 0.f;
                 if constexpr (kApart) small[a][b][v] = 0.f;
             }
     // fragments of global k-step g (4 per stage) in ring position g % AD: requested two k-steps
@@ -502,8 +502,7 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
                 for (int rb = 0; rb < RBW; ++rb)
-                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[rb],
-                                               ks % kTurns ? odd : acc[cb][rb],
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[rb], acc[ks % kTurns][cb][rb],
                                                small[kApart ? cb : 0][kApart ? rb : 0]);
             // requested here and nowhere later: AD k-steps of matrix-core work to come back
             load_frags(t * 4 + ks + AD, ks % AD);
@@ -511,18 +510,15 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
         }
         lds_barrier();
     }
-    if constexpr (kApart) {
 #pragma unroll
-        for (int cb = 0; cb < CBW; ++cb)
+    for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
-            for (int rb = 0; rb < RBW; ++rb)
+        for (int rb = 0; rb < RBW; ++rb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[cb][rb][v] += small[cb][rb][v];
-    }
-    if constexpr (kTurns == 2) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] += odd[v];
-    }
+            for (int v = 0; v < 16; ++v) {
+                if constexpr (kApart) acc[0][cb][rb][v] += small[cb][rb][v];
+                if constexpr (kTurns == 2) acc[0][cb][rb][v] += acc[1][cb][rb][v];
+            }
 #pragma unroll
     for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
@@ -532,7 +528,7 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             for (int v = 0; v < 16; ++v) {
                 const int c = (wc * CBW + cb) * 32 + d_row(v, lane);
                 if (c < r && i < m)
-                    out[(int64_t)c * m + i] = NS == 1 ? acc[cb][rb][v] * out_scale[c] : acc[cb][rb][v];
+                    out[(int64_t)c * m + i] = NS == 1 ? acc[0][cb][rb][v] * out_scale[c] : acc[0][cb][rb][v];
             }
         }
 }
@@ -1201,13 +1197,17 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 // wavefront w owns the CBW basis blocks of group w % WCB and WCB of the four 32-column blocks.
 // Register sets, buffers, barriers and clamping as in the P kernel.
 // ---------------------------------------------------------------------------------------------
-// Accumulators of the small products as in the P kernel, with three pieces (one workgroup per unit, 256
-// registers) at 4 basis blocks too: 8192 x 8192 r = 100 4.0e-7 from fp64, 1.0e-6 in one accumulator.
-template <int NS, int BLOCKS>
-constexpr bool kApartQ = NS >= 2 && BLOCKS <= (NS == 3 ? 4 : 2);
-template <int NS, int BLOCKS>
-constexpr int kChainsQ = NS >= 2 && BLOCKS == 1 ? 4 : 1;  // accumulators that take the k-steps in turn
-template <int NS, int CBW, int WCB>
+// LONE: at most one workgroup per compute unit, which then has twice the registers: always with three
+// pieces (98 KB of LDS), with two where the plan says so.  Accumulators of the small products as in the P
+// kernel, LONE at 4 basis blocks too; accumulators that take the k-steps in turn: four for one block, LONE
+// two.  Error against fp64 of two pieces, 8192 x 8064 four workers: r = 64 5.9e-7 (one chain: 7.2e-7), r =
+// 100 7.0e-7 (one chain with all products in it: 1.06e-6); of three, 3056 x 6336 five workers r = 48 1.5e-7
+// (one chain: 2.9e-7); no difference in time.
+template <int NS, int BLOCKS, bool LONE>
+constexpr bool kApartQ = NS >= 2 && BLOCKS <= (LONE ? 4 : 2);
+template <int NS, int BLOCKS, bool LONE>
+constexpr int kChainsQ = NS < 2 ? 1 : BLOCKS == 1 ? 4 : LONE && BLOCKS <= 4 ? 2 : 1;
+template <int NS, int CBW, int WCB, bool LONE = NS == 3>
 __global__ __launch_bounds__(kWs, NS == 2 && CBW * WCB == 1 ? 4 : 1) void project_q_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
                                                            PtrPack<float *> outs, int64_t m,
@@ -1300,20 +1300,17 @@ __global__ __launch_bounds__(kWs, NS == 2 && CBW * WCB == 1 ? 4 : 1) void projec
     }
     // -------------------------------------------------------------------------------- consumers
     const int wcb = wave % WCB, wq = wave / WCB;
-    constexpr bool kApart = kApartQ<NS, CBW * QW>;
-    constexpr int kTurns = kChainsQ<NS, CBW * QW>;
-    f32x16_t acc[CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1], odd[3];
-#pragma unroll
-    for (int x = 0; x < 3; ++x)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) odd[x][v] = 0.f;
+    constexpr bool kApart = kApartQ<NS, CBW * QW, LONE>;
+    constexpr int kTurns = kChainsQ<NS, CBW * QW, LONE>;
+    f32x16_t acc[kTurns][CBW][QW], small[kApart ? CBW : 1][kApart ? QW : 1];
 #pragma unroll
     for (int a = 0; a < CBW; ++a)
 #pragma unroll
         for (int b = 0; b < QW; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                acc[a][b][v] = 0.f;
+#pragma unroll
+                for (int t = 0; t < kTurns; ++t) acc[t][a][b][v] = 0.f;
                 if constexpr (kApart) small[a][b][v] = 0.f;
             }
     constexpr int AD = CBW * NS <= 2 ? 4 : 2;  // as in project_p_ws_kernel
@@ -1346,26 +1343,23 @@ __global__ __launch_bounds__(kWs, NS == 2 && CBW * WCB == 1 ? 4 : 1) void projec
             for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
                 for (int q = 0; q < QW; ++q)
-                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q],
-                                               ks % kTurns ? odd[(ks + 3) % 4] : acc[cb][q],
+                    mfma_split_sum<NS, kApart>(a[ks % AD][cb], b[q], acc[ks % kTurns][cb][q],
                                                small[kApart ? cb : 0][kApart ? q : 0]);
             load_frags(s_begin + t * 4 + ks + AD, ks % AD);
             __builtin_amdgcn_sched_barrier(0);
         }
         lds_barrier();
     }
-    if constexpr (kApart) {
 #pragma unroll
-        for (int cb = 0; cb < CBW; ++cb)
+    for (int cb = 0; cb < CBW; ++cb)
 #pragma unroll
-            for (int q = 0; q < QW; ++q)
+        for (int q = 0; q < QW; ++q)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[cb][q][v] += small[cb][q][v];
-    }
-    if constexpr (kTurns == 4) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] = (acc[0][0][v] + odd[0][v]) + (odd[1][v] + odd[2][v]);
-    }
+            for (int v = 0; v < 16; ++v) {
+                if constexpr (kApart) acc[0][cb][q][v] += small[cb][q][v];
+                if constexpr (kTurns >= 2) acc[0][cb][q][v] += acc[1][cb][q][v];
+                if constexpr (kTurns == 4) acc[0][cb][q][v] += acc[2][cb][q][v] + acc[3][cb][q][v];
+            }
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
         const int64_t j = j0 + (wq * QW + q) * 32 + (lane & 31);
@@ -1375,7 +1369,7 @@ __global__ __launch_bounds__(kWs, NS == 2 && CBW * WCB == 1 ? 4 : 1) void projec
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int c = (wcb * CBW + cb) * 32 + d_row(v, lane);
-                if (c < r) out[(int64_t)c * n + j] = NS == 1 ? acc[cb][q][v] * out_scale[c] : acc[cb][q][v];
+                if (c < r) out[(int64_t)c * n + j] = NS == 1 ? acc[0][cb][q][v] * out_scale[c] : acc[0][cb][q][v];
             }
     }
 }
@@ -1390,6 +1384,7 @@ static inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 struct QPlan {
     int JB, S, depth;
     int64_t ksteps_per_wave, KS;
+    bool lone;  // at most one workgroup per compute unit, the kernel's form for that
 };
 
 // Splits of the reduction.  A projection has one workgroup per 128 rows (P; 64 in one case, p_plan) or
@@ -1429,17 +1424,16 @@ static int64_t slab_room(int64_t side, int K, int64_t by_length) {
 // three workers, three pieces 3: 66 | 7: 90.  P, 64 rows and no splits before: 2048 x 8192 r = 32 55 |
 // 125, r = 100 88 | 163; 2048 x 2048 r = 64 26 | 41; 3008 x 5008 r = 100 two workers 54 | 107; 256 x 8192
 // r = 16 one worker 21 | 102; 1120 x 6688 r = 210 one worker 34 | 170.
+static int64_t split_cost(int64_t wgs, int64_t length, int64_t granule, int64_t slab_elements, int64_t s) {
+    const int64_t share = ceil_div(ceil_div(length, s), granule) * granule;
+    return ceil_div(wgs * s, kQUnits) * (share + 128) + s * slab_elements / 16384;
+}
 static int64_t best_splits(int64_t wgs, int64_t length, int64_t granule, int64_t slab_elements,
                            int64_t smin, int64_t smax) {
-    int64_t best = INT64_MAX, S = smin;
-    for (int64_t s = smin; s <= smax; ++s) {
-        const int64_t share = ceil_div(ceil_div(length, s), granule) * granule;
-        const int64_t cost = ceil_div(wgs * s, kQUnits) * (share + 128) + s * slab_elements / 16384;
-        if (cost < best) {
-            best = cost;
+    int64_t S = smin;
+    for (int64_t s = smin + 1; s <= smax; ++s)
+        if (split_cost(wgs, length, granule, slab_elements, s) < split_cost(wgs, length, granule, slab_elements, S))
             S = s;
-        }
-    }
     return S;
 }
 
@@ -1448,6 +1442,7 @@ struct PPlan {
     int S;           // column splits
     int64_t stages;  // stages of 64 columns of a split
     bool one_role;   // project_p_one_kernel
+    bool lone;       // at most one workgroup per compute unit
 };
 // 64 rows per workgroup where the matrix cores set the pace (4 or 8 basis blocks), the rows then still
 // fit the units in one round and the reduction is short: a longer chain of stages is not what such a
@@ -1475,6 +1470,7 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, (int64_t)K * r * m, 1, smax);
     p.stages = ceil_div(stages, S);
     p.S = (int)ceil_div(stages, p.stages);
+    p.lone = wgs * p.S <= kQUnits;
     return p;
 }
 
@@ -1484,6 +1480,7 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
     // 128 columns per workgroup in both Q kernels
     p.JB = 4;
     p.depth = 2;  // k-steps (16 rows) of delta in flight per wavefront
+    p.lone = ns == 3;
     const int64_t wgs = out_wgs(n) * K;
     int64_t smax = most_splits(wgs);
     if (smax > most_q_splits(m)) smax = most_q_splits(m);
@@ -1495,17 +1492,22 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
     } else if (wgs >= kQUnits) {
         // every compute unit has a workgroup: two, except at 8 basis blocks, where one fills it
         if (cb < 8) S = smax;
-    } else if (ns == 2 && cb >= 4 && !f16) {
-        // one accumulator for all piece products: sums as short as a full launch makes them (two
-        // workgroups for every unit, one at 8 basis blocks, whatever remains)
-        S = ceil_div(cb == 8 ? kQUnits : 2 * kQUnits, wgs);
-        if (S > smax) S = smax;
-    } else if (ns == 3 && cb == 8) {
-        // no room for accumulators of the small products (kApartQ): at least a workgroup for every
-        // unit, as short sums as that makes.  5008 x 3376 r = 200 157 us; with fewer splits 143 and 1.2
-        // times as far from fp64
-        const int64_t fill = ceil_div(kQUnits, wgs);
-        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, fill < smax ? fill : smax, smax);
+    } else if (!f16 && (ns == 2 || cb == 8)) {
+        // Sums no less accurate than those of one accumulator for all piece products in s0 splits, two
+        // workgroups for every unit (one at 8 basis blocks), whatever remains: the squared error goes with
+        // the roundings of a sum over its splits, and again over the splits.  Where one accumulator takes
+        // them all (4, 8 blocks) that needs s0 splits, apart from the small products (2 blocks) s0 / sqrt(3),
+        // in two accumulators as well (lone) s0 / sqrt(12); one block has four for a workgroup, where the
+        // one-role kernel had one for each of four wavefronts: 0.45 s0 by measurement.
+        const int64_t full = ceil_div(cb == 8 ? kQUnits : 2 * kQUnits, wgs), s0 = full < smax ? full : smax;
+        const int64_t slab = (int64_t)K * r * n, granule = 64 * p.depth;
+        S = best_splits(wgs, m, granule, slab, cb == 1 ? ceil_div(s0 * 45, 100) : cb == 2 ? ceil_div(s0 * 58, 100) : s0, smax);
+        const int64_t fit = kQUnits / wgs < smax ? kQUnits / wgs : smax, least = ceil_div(s0 * 29, 100);
+        if (ns == 2 && (cb == 2 || cb == 4) && least <= fit) {
+            const int64_t one = best_splits(wgs, m, granule, slab, least, fit);
+            p.lone = split_cost(wgs, m, granule, slab, one) <= split_cost(wgs, m, granule, slab, S);
+            if (p.lone) S = one;
+        }
     } else {
         S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, 1, smax);
     }
@@ -1575,7 +1577,7 @@ static int pack_f16(const KContig &p, uint4 *frags_f16, const F16Scratch &f, hip
     return check_launch("pack_f16");
 }
 
-template <int NS, int CBW, int WC, int WR, int RB = 4>
+template <int NS, int CBW, int WC, int WR, int RB = 4, bool LONE = NS == 3>
 static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &delta,
                                const uint4 *frags, const PtrPack<float *> &out, int64_t m,
                                int64_t n, int r, int K, hipStream_t st, uint32_t *record = nullptr,
@@ -1583,11 +1585,11 @@ static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &de
     constexpr int lds = 2 * NS * 32 * RB * kPPitch;
     static size_t granted = 0;
     int rc = grant_dynamic_lds(
-        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB>), lds,
+        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE>), lds,
         &granted, "project_p attribute");
     if (rc != DLCX_OK) return rc;
     const dim3 grid((unsigned)ceil_div(m, 32 * RB), (unsigned)K, (unsigned)pl.S);
-    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB>), grid, dim3(kWs), lds, st,
+    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE>), grid, dim3(kWs), lds, st,
                        delta, frags, out, m, n, r, pl.stages, (int64_t)r * m, record, out_scale,
                        guard);
     return DLCX_OK;
@@ -1669,7 +1671,10 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
                 else
                     rc = project_p_ws_launch<NS, 1, 1, 4>(pl, delta, frags, dst, m, n, r, K, st);
                 break;
-            case 2: rc = project_p_ws_launch<NS, 1, 2, 2>(pl, delta, frags, dst, m, n, r, K, st); break;
+            case 2:
+                rc = pl.lone ? project_p_ws_launch<NS, 1, 2, 2, 4, true>(pl, delta, frags, dst, m, n, r, K, st)
+                             : project_p_ws_launch<NS, 1, 2, 2>(pl, delta, frags, dst, m, n, r, K, st);
+                break;
             case 4:
                 rc = pl.rows == 64 ? project_p_ws_launch<NS, 2, 2, 2, 2>(pl, delta, frags, dst, m, n, r, K, st)
                                    : project_p_ws_launch<NS, 2, 2, 2>(pl, delta, frags, dst, m, n, r, K, st);
@@ -1685,7 +1690,7 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     return finish_splits(K, pl.S, slab, dst, out, partial, st);
 }
 
-template <int NS, int CBW, int WCB>
+template <int NS, int CBW, int WCB, bool LONE = NS == 3>
 static int project_q_ws_launch(const dim3 &grid, hipStream_t st, const PtrPack<const float *> &delta,
                                const uint4 *frags, const PtrPack<float *> &dst, int64_t m,
                                int64_t n, int r, int64_t ksteps_per_wg, int64_t slab,
@@ -1693,10 +1698,10 @@ static int project_q_ws_launch(const dim3 &grid, hipStream_t st, const PtrPack<c
                                const uint32_t *guard = nullptr) {
     constexpr int lds = 2 * 16 * NS * 1024;
     static size_t granted = 0;
-    int rc = grant_dynamic_lds(reinterpret_cast<const void *>(project_q_ws_kernel<NS, CBW, WCB>),
+    int rc = grant_dynamic_lds(reinterpret_cast<const void *>(project_q_ws_kernel<NS, CBW, WCB, LONE>),
                                lds, &granted, "project_q attribute");
     if (rc != DLCX_OK) return rc;
-    hipLaunchKernelGGL((project_q_ws_kernel<NS, CBW, WCB>), grid, dim3(kWs), lds, st, delta, frags, dst,
+    hipLaunchKernelGGL((project_q_ws_kernel<NS, CBW, WCB, LONE>), grid, dim3(kWs), lds, st, delta, frags, dst,
                        m, n, r, ksteps_per_wg, slab, record, out_scale, guard);
     return DLCX_OK;
 }
@@ -1744,8 +1749,14 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
             if constexpr (NS == 2) rc = project_q_ws_launch<NS, 1, 1>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
             else hipLaunchKernelGGL((project_q_mfma_kernel<NS, 1, 4, 2>), grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab);
             break;
-        case 2: rc = project_q_ws_launch<NS, 1, 2>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab); break;
-        case 4: rc = project_q_ws_launch<NS, 1, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard); break;
+        case 2:
+            rc = q.lone ? project_q_ws_launch<NS, 1, 2, true>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab)
+                        : project_q_ws_launch<NS, 1, 2>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
+            break;
+        case 4:
+            if (q.lone) rc = project_q_ws_launch<NS, 1, 4, true>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
+            else rc = project_q_ws_launch<NS, 1, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard);
+            break;
         default: rc = project_q_ws_launch<NS, 2, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard); break;
     }
     if (rc == DLCX_OK) rc = check_launch("project_q_mfma");

@@ -164,6 +164,7 @@ def test_project_p_and_q(mma, m, n, r, K, group):
     (1040, 3184, 24, 1), (144, 4112, 48, 2), (1296, 2064, 100, 3), (528, 1808, 200, 1),  # P split by columns
     (1040, 784, 100, 2), (336, 1008, 200, 3), (2096, 272, 145, 1),  # short rows: 64 per workgroup
     (3184, 1040, 24, 1), (4112, 144, 48, 2), (2064, 1296, 100, 3), (1808, 528, 200, 1),  # Q split by rows
+    (1040, 1264, 48, 15), (1040, 1264, 100, 15), (1264, 1040, 48, 15),  # more than one workgroup per unit
 ])
 def test_projections_split_along_the_reduction(mma, m, n, r, K):
     # Few rows (columns) of output: the reduction is split and the partial sums are added behind it, by
