@@ -61,10 +61,23 @@ int launch_quantize(int K, const PtrPack<const float *> &x, int64_t count, int q
 // The same on sums that are still partial: x[k] = sum_s slabs[k][s] in slab order (S slabs `stride`
 // floats apart) is written to sums.p[k] and quantised in one pass.
 struct PartialSums {
-    int S = 1;  // 1: nothing to add, the sums are where they belong
+    int S = 1;  // 1 without a guard: nothing to add, the sums are where they belong
     int64_t stride = 0;
     PtrPack<const float *> slabs;
+    // Sums of an fp16 launch and its stand-by, which may have been split differently: there are S of
+    // them if the record that `guard` points to says that the fp16 launch counts, else S_alt.
+    const uint32_t *guard = nullptr;
+    int S_alt = 1;
 };
+// Did the fp16 form of a projection see its operands in range?  (largest |delta| as fp32 bits)
+__device__ __forceinline__ bool f16_range_ok(uint32_t amax_bits) {
+    const float a = __uint_as_float(amax_bits);
+    return a >= 0x1p-14f && a < 15.99f;
+}
+// (A kernel takes the members one by one: the whole struct, indexed by worker, would go to scratch.)
+__device__ __forceinline__ int split_count(int S, int S_alt, const uint32_t *guard) {
+    return guard != nullptr && !f16_range_ok(*guard) ? S_alt : S;
+}
 // The sum of S partial sums at float4 v.  Added in fp64: with up to 64 of them the fp32 additions were
 // a third of a projection's error.  Four requests go out together: one at a time a sum of 32 waits
 // for 32 trips to L2.
@@ -126,8 +139,8 @@ int launch_project_q(int mma, int64_t m, int64_t n, int r, int K,
                      const PtrPack<float *> &out, void *workspace, PartialSums *partial,
                      hipStream_t st);
 // out[k] = sum_s slabs[k][s], s in index order
-int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<float *> &outs,
-                     int64_t count, int S, int64_t slab_stride, hipStream_t st);
+int launch_sum_slabs(int K, const PartialSums &part, const PtrPack<float *> &outs, int64_t count,
+                     hipStream_t st);
 // What happens to each tile d of delta_hat = P_hat Q_bar^T, in this order:
 //   out            : d is written
 //   K > 0          : e_k <- e_k - d                     (error buffers of Alg. 2)

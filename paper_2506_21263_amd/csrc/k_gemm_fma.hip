@@ -218,19 +218,20 @@ __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *
 // out[k][x] = sum_s slabs[k][s][x], s in index order (fixed order: run-to-run identical)
 __global__ __launch_bounds__(kT) void sum_slabs_kernel(PtrPack<const float *> slabs,
                                                        PtrPack<float *> outs, int64_t nvec,
-                                                       int S, int64_t slab_stride) {
+                                                       int64_t slab_stride, int S, int S_alt,
+                                                       const uint32_t *guard) {
     const int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (v >= nvec) return;
     reinterpret_cast<float4 *>(outs.p[blockIdx.y])[v] =
-        sum_partials(slabs.p[blockIdx.y], slab_stride, S, v);
+        sum_partials(slabs.p[blockIdx.y], slab_stride, split_count(S, S_alt, guard), v);
 }
 
-int launch_sum_slabs(int K, const PtrPack<const float *> &slabs, const PtrPack<float *> &outs,
-                     int64_t count, int S, int64_t slab_stride, hipStream_t st) {
+int launch_sum_slabs(int K, const PartialSums &part, const PtrPack<float *> &outs, int64_t count,
+                     hipStream_t st) {
     const int64_t nvec = count >> 2;
     Timed timed(KID_SUM_SLABS, st);
     hipLaunchKernelGGL(sum_slabs_kernel, dim3((unsigned)ceil_div(nvec, kT), (unsigned)K), dim3(kT),
-                       0, st, slabs, outs, nvec, S, slab_stride);
+                       0, st, part.slabs, outs, nvec, part.stride, part.S, part.S_alt, part.guard);
     return check_launch("sum_slabs");
 }
 
@@ -403,7 +404,7 @@ int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
         *partial = sums;
         return DLCX_OK;
     }
-    return launch_sum_slabs(K, sums.slabs, out, slab, S, slab, st);
+    return launch_sum_slabs(K, sums, out, slab, st);
 }
 
 int launch_reconstruct_fma(int64_t m, int64_t n, int r, const float *p_hat, const float *q_bar,

@@ -256,12 +256,6 @@ __global__ __launch_bounds__(kW) void basis_scale_kernel(const float *__restrict
     }
 }
 
-// Did the fp16 form of the launch see its operands in range?  (largest |delta| as fp32 bits)
-__device__ __forceinline__ bool f16_range_ok(uint32_t amax_bits) {
-    const float a = __uint_as_float(amax_bits);
-    return a >= 0x1p-14f && a < 15.99f;
-}
-
 // largest |x| over a wavefront, then one atomic per wavefront (bit patterns of non-negative
 // floats order like the floats)
 __device__ __forceinline__ void record_amax(float a, uint32_t *record) {
@@ -1505,7 +1499,10 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
         const int64_t fit = kQUnits / wgs < smax ? kQUnits / wgs : smax, least = ceil_div(s0 * 29, 100);
         if (ns == 2 && (cb == 2 || cb == 4) && least <= fit) {
             const int64_t one = best_splits(wgs, m, granule, slab, least, fit);
-            p.lone = split_cost(wgs, m, granule, slab, one) <= split_cost(wgs, m, granule, slab, S);
+            // (at 4 blocks one workgroup streams 4 - 8 % slower than two: 8192 x 8192 r = 128 two workers
+            // 142 us in two splits, 137 in four; 4096 x 4096 four workers 78 and 83)
+            p.lone = split_cost(wgs, m, granule, slab, one) * 10 <=
+                     split_cost(wgs, m, granule, slab, S) * (cb == 4 ? 9 : 10);
             if (p.lone) S = one;
         }
     } else {
@@ -1631,18 +1628,13 @@ static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<cons
 }
 
 // The sums over the splits of a reduction, left to the caller (partial) or formed here.
-static int finish_splits(int K, int S, int64_t slab, const PtrPack<float *> &dst,
-                         const PtrPack<float *> &out, PartialSums *partial, hipStream_t st) {
-    if (S == 1) return DLCX_OK;
-    PartialSums sums;
-    sums.S = S;
-    sums.stride = slab;
-    for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k];
+static int finish_splits(int K, const PartialSums &sums, const PtrPack<float *> &out,
+                         PartialSums *partial, hipStream_t st) {
     if (partial) {
         *partial = sums;
         return DLCX_OK;
     }
-    return launch_sum_slabs(K, sums.slabs, out, slab, S, slab, st);
+    return launch_sum_slabs(K, sums, out, sums.stride, st);
 }
 
 template <int NS>
@@ -1657,9 +1649,12 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     int rc = pack_kcontig<NS>(KContig{q_in, r, n, cb, KS, frags}, st);
     if (rc != DLCX_OK) return rc;
     PtrPack<float *> dst = out;
+    PartialSums sums;
+    sums.S = pl.S;
+    sums.stride = slab;
     if (pl.S > 1) {
         float *base = reinterpret_cast<float *>(wsb + a256((size_t)KS * cb * NS * 1024));
-        for (int k = 0; k < K; ++k) dst.p[k] = base + (int64_t)k * pl.S * slab;
+        for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k] = base + (int64_t)k * pl.S * slab;
     }
     {
         Timed timed(KID_PROJECT_P, st);
@@ -1686,8 +1681,8 @@ static int project_p_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
         }
         if (rc == DLCX_OK) rc = check_launch("project_p_mfma");
     }
-    if (rc != DLCX_OK) return rc;
-    return finish_splits(K, pl.S, slab, dst, out, partial, st);
+    if (rc != DLCX_OK || pl.S == 1) return rc;
+    return finish_splits(K, sums, out, partial, st);
 }
 
 template <int NS, int CBW, int WCB, bool LONE = NS == 3>
@@ -1707,62 +1702,74 @@ static int project_q_ws_launch(const dim3 &grid, hipStream_t st, const PtrPack<c
 }
 
 // F16: the fp16 form for 4 or 8 basis blocks (see project_p_f16), with the bf16 kernel as its
-// stand-by; NS is then the stand-by's piece count (2) and the workspace holds three pieces.
+// stand-by; NS is then the stand-by's piece count (2) and the workspace holds three pieces.  The
+// stand-by keeps the splits of DLCX_MMA_BF16, so that its result is that mode's bit for bit; which of
+// the two numbers of partial sums counts is read from the record when they are added.
 template <int NS, bool F16>
 static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                         const float *p_hat, const PtrPack<float *> &out, void *workspace,
                         PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
     const bool f16 = F16 && cb >= 4;
-    const QPlan q = q_plan(NS, f16, m, n, r, K);
+    const QPlan q = q_plan(NS, false, m, n, r, K), h = f16 ? q_plan(NS, true, m, n, r, K) : q;
+    const int S = q.S > h.S ? q.S : h.S;  // slabs of a worker
+    const int64_t KS = q.KS > h.KS ? q.KS : h.KS, slab = (int64_t)r * n;
     const int pieces = F16 ? 3 : NS;  // as the workspace was sized
     char *wsb = reinterpret_cast<char *>(workspace);
     uint4 *frags = reinterpret_cast<uint4 *>(wsb);
-    uint4 *frags1 = reinterpret_cast<uint4 *>(wsb + (size_t)q.KS * cb * NS * 1024);
+    uint4 *frags1 = reinterpret_cast<uint4 *>(wsb + (size_t)KS * cb * NS * 1024);
     F16Scratch f = f16_scratch(nullptr);
     int rc = DLCX_OK;
     if (f16) {
-        const size_t slab_bytes = q.S > 1 ? a256((size_t)K * q.S * r * n * sizeof(float)) : 0;
-        f = f16_scratch(wsb + a256((size_t)q.KS * cb * pieces * 1024) + slab_bytes);
-        rc = pack_f16(KContig{p_hat, r, m, cb, q.KS, frags}, frags1, f, st);
+        const size_t slab_bytes = S > 1 ? a256((size_t)K * S * slab * sizeof(float)) : 0;
+        f = f16_scratch(wsb + a256((size_t)KS * cb * pieces * 1024) + slab_bytes);
+        rc = pack_f16(KContig{p_hat, r, m, cb, KS, frags}, frags1, f, st);
     } else {
-        rc = pack_kcontig<NS>(KContig{p_hat, r, m, cb, q.KS, frags}, st);
+        rc = pack_kcontig<NS>(KContig{p_hat, r, m, cb, KS, frags}, st);
     }
     if (rc != DLCX_OK) return rc;
-    const int64_t slab = (int64_t)r * n;
     PtrPack<float *> dst = out;
-    if (q.S > 1) {
-        float *base = reinterpret_cast<float *>(wsb + a256((size_t)q.KS * cb * pieces * 1024));
-        for (int k = 0; k < K; ++k) dst.p[k] = base + (int64_t)k * q.S * slab;
+    PartialSums sums;
+    sums.S = h.S;
+    sums.stride = slab;
+    if (q.S != h.S) {
+        sums.guard = f.record;
+        sums.S_alt = q.S;
+    }
+    if (S > 1) {
+        float *base = reinterpret_cast<float *>(wsb + a256((size_t)KS * cb * pieces * 1024));
+        for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k] = base + (int64_t)k * S * slab;
     }
     const dim3 grid((unsigned)ceil_div(n, 32 * q.JB), (unsigned)K, (unsigned)q.S);
+    const int64_t ksteps = q.ksteps_per_wave * 4;
     {
     Timed timed(KID_PROJECT_Q, st);
     if (f16) {  // the stand-by launches below then carry the record as their guard
-        if (cb == 4) rc = project_q_ws_launch<1, 1, 4>(grid, st, delta, frags1, dst, m, n, r, q.ksteps_per_wave * 4, slab, f.record, f.out_scale);
-        else rc = project_q_ws_launch<1, 2, 4>(grid, st, delta, frags1, dst, m, n, r, q.ksteps_per_wave * 4, slab, f.record, f.out_scale);
+        const dim3 hgrid(grid.x, grid.y, (unsigned)h.S);
+        if (cb == 4) rc = project_q_ws_launch<1, 1, 4>(hgrid, st, delta, frags1, dst, m, n, r, h.ksteps_per_wave * 4, slab, f.record, f.out_scale);
+        else rc = project_q_ws_launch<1, 2, 4>(hgrid, st, delta, frags1, dst, m, n, r, h.ksteps_per_wave * 4, slab, f.record, f.out_scale);
         if (rc != DLCX_OK) return rc;
     }
     const uint32_t *guard = f16 ? f.record : nullptr;
     switch (cb) {
         case 1:
-            if constexpr (NS == 2) rc = project_q_ws_launch<NS, 1, 1>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
+            if constexpr (NS == 2) rc = project_q_ws_launch<NS, 1, 1>(grid, st, delta, frags, dst, m, n, r, ksteps, slab);
             else hipLaunchKernelGGL((project_q_mfma_kernel<NS, 1, 4, 2>), grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab);
             break;
         case 2:
-            rc = q.lone ? project_q_ws_launch<NS, 1, 2, true>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab)
-                        : project_q_ws_launch<NS, 1, 2>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
+            rc = q.lone ? project_q_ws_launch<NS, 1, 2, true>(grid, st, delta, frags, dst, m, n, r, ksteps, slab)
+                        : project_q_ws_launch<NS, 1, 2>(grid, st, delta, frags, dst, m, n, r, ksteps, slab);
             break;
         case 4:
-            if (q.lone) rc = project_q_ws_launch<NS, 1, 4, true>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab);
-            else rc = project_q_ws_launch<NS, 1, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard);
+            rc = q.lone ? project_q_ws_launch<NS, 1, 4, true>(grid, st, delta, frags, dst, m, n, r, ksteps, slab, nullptr, nullptr, guard)
+                        : project_q_ws_launch<NS, 1, 4>(grid, st, delta, frags, dst, m, n, r, ksteps, slab, nullptr, nullptr, guard);
             break;
-        default: rc = project_q_ws_launch<NS, 2, 4>(grid, st, delta, frags, dst, m, n, r, q.ksteps_per_wave * 4, slab, nullptr, nullptr, guard); break;
+        default: rc = project_q_ws_launch<NS, 2, 4>(grid, st, delta, frags, dst, m, n, r, ksteps, slab, nullptr, nullptr, guard); break;
     }
     if (rc == DLCX_OK) rc = check_launch("project_q_mfma");
     }
-    if (rc != DLCX_OK) return rc;
-    return finish_splits(K, q.S, slab, dst, out, partial, st);
+    if (rc != DLCX_OK || S == 1) return rc;
+    return finish_splits(K, sums, out, partial, st);
 }
 
 int launch_project_p_mfma(int mma, int64_t m, int64_t n, int r, int K,

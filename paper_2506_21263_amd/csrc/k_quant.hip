@@ -23,8 +23,9 @@ template <int kQbits, int kLanes, bool kSum>
 __global__ __launch_bounds__(kQThreads) void quantize_kernel(PtrPack<const float *> xs,
                                                              int64_t nvec,
                                                              PtrPack<uint8_t *> codes,
-                                                             PtrPack<float *> scales, int S,
-                                                             int64_t stride, PtrPack<float *> sums) {
+                                                             PtrPack<float *> scales, int64_t stride,
+                                                             int S, int S_alt, const uint32_t *guard,
+                                                             PtrPack<float *> sums) {
     const int k = blockIdx.y;
     const float *__restrict__ x = xs.p[k];
     const int64_t v = (int64_t)blockIdx.x * kQThreads + threadIdx.x;
@@ -32,7 +33,7 @@ __global__ __launch_bounds__(kQThreads) void quantize_kernel(PtrPack<const float
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
     if constexpr (kSum) {
         if (live) {
-            a = sum_partials(x, stride, S, v);
+            a = sum_partials(x, stride, split_count(S, S_alt, guard), v);
             reinterpret_cast<float4 *>(sums.p[k])[v] = a;
         }
     } else if (live) {
@@ -106,16 +107,16 @@ __global__ __launch_bounds__(kQThreads) void dequant_average_kernel(
 template <int kQbits, bool kSum>
 static int quantize_dispatch(int K, const PtrPack<const float *> &x, int64_t nvec, int group,
                              const PtrPack<uint8_t *> &codes, const PtrPack<float *> &scales,
-                             int S, int64_t stride, const PtrPack<float *> &sums, hipStream_t st) {
+                             const PartialSums &part, const PtrPack<float *> &sums, hipStream_t st) {
     const dim3 grid((unsigned)ceil_div(nvec, kQThreads), (unsigned)K);
     const dim3 block(kQThreads);
     Timed timed(KID_QUANTIZE, st);
     switch (group) {
-        case 16: hipLaunchKernelGGL((quantize_kernel<kQbits, 4, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
-        case 32: hipLaunchKernelGGL((quantize_kernel<kQbits, 8, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
-        case 64: hipLaunchKernelGGL((quantize_kernel<kQbits, 16, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
-        case 128: hipLaunchKernelGGL((quantize_kernel<kQbits, 32, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
-        case 256: hipLaunchKernelGGL((quantize_kernel<kQbits, 64, kSum>), grid, block, 0, st, x, nvec, codes, scales, S, stride, sums); break;
+        case 16: hipLaunchKernelGGL((quantize_kernel<kQbits, 4, kSum>), grid, block, 0, st, x, nvec, codes, scales, part.stride, part.S, part.S_alt, part.guard, sums); break;
+        case 32: hipLaunchKernelGGL((quantize_kernel<kQbits, 8, kSum>), grid, block, 0, st, x, nvec, codes, scales, part.stride, part.S, part.S_alt, part.guard, sums); break;
+        case 64: hipLaunchKernelGGL((quantize_kernel<kQbits, 16, kSum>), grid, block, 0, st, x, nvec, codes, scales, part.stride, part.S, part.S_alt, part.guard, sums); break;
+        case 128: hipLaunchKernelGGL((quantize_kernel<kQbits, 32, kSum>), grid, block, 0, st, x, nvec, codes, scales, part.stride, part.S, part.S_alt, part.guard, sums); break;
+        case 256: hipLaunchKernelGGL((quantize_kernel<kQbits, 64, kSum>), grid, block, 0, st, x, nvec, codes, scales, part.stride, part.S, part.S_alt, part.guard, sums); break;
         default: return DLCX_EINVAL;
     }
     return check_launch("quantize");
@@ -128,8 +129,8 @@ int launch_quantize(int K, const PtrPack<const float *> &x, int64_t count, int q
     const int64_t nvec = count >> 2;
     const PtrPack<float *> none = {};
     if (qbits == 4)
-        return quantize_dispatch<4, false>(K, x, nvec, group, codes, scales, 1, 0, none, st);
-    return quantize_dispatch<8, false>(K, x, nvec, group, codes, scales, 1, 0, none, st);
+        return quantize_dispatch<4, false>(K, x, nvec, group, codes, scales, PartialSums(), none, st);
+    return quantize_dispatch<8, false>(K, x, nvec, group, codes, scales, PartialSums(), none, st);
 }
 
 int launch_sum_quantize(int K, const PartialSums &part, const PtrPack<float *> &sums,
@@ -137,16 +138,14 @@ int launch_sum_quantize(int K, const PartialSums &part, const PtrPack<float *> &
                         const PtrPack<float *> &scales, hipStream_t st) {
     if (count == 0 || K == 0) return DLCX_OK;
     const int64_t nvec = count >> 2;
-    if (part.S == 1) {
+    if (part.S == 1 && part.guard == nullptr) {
         PtrPack<const float *> x;
         for (int k = 0; k < K; ++k) x.p[k] = sums.p[k];
         return launch_quantize(K, x, count, qbits, group, codes, scales, st);
     }
     if (qbits == 4)
-        return quantize_dispatch<4, true>(K, part.slabs, nvec, group, codes, scales, part.S,
-                                          part.stride, sums, st);
-    return quantize_dispatch<8, true>(K, part.slabs, nvec, group, codes, scales, part.S, part.stride,
-                                      sums, st);
+        return quantize_dispatch<4, true>(K, part.slabs, nvec, group, codes, scales, part, sums, st);
+    return quantize_dispatch<8, true>(K, part.slabs, nvec, group, codes, scales, part, sums, st);
 }
 
 int launch_dequant_average(int K, const PtrPack<const uint8_t *> &codes,

@@ -327,6 +327,38 @@ def test_fp16_form_stands_by_outside_its_range(case):
             assert rel_l2(res[dlcx.MMA_F16][K + 3], want) <= TOL[dlcx.MMA_BF16]
 
 
+@pytest.mark.parametrize("m,n,r,K", [(4096, 320, 200, 8), (2064, 1296, 100, 3), (3072, 3072, 140, 1)])
+@pytest.mark.parametrize("huge", [False, True], ids=["in-range", "stand-by"])
+def test_fp16_form_and_its_stand_by_are_split_each_in_its_own_way(m, n, r, K, huge):
+    """The two launches leave different numbers of partial sums; the quantiser and the sum behind a
+    projection read from the record how many count."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m + r)
+    deltas = [0.1 * torch.randn(m, n, generator=g, device=DEV) for _ in range(K)]
+    if huge:
+        deltas[K - 1][m - 1, n - 1] = 1.0e3
+    for phase, L, lb in ((dlcx.PHASE_P, m, n), (dlcx.PHASE_Q, n, m)):
+        basis = torch.randn(r, lb, generator=g, device=DEV)
+        got = {}
+        for mma in (dlcx.MMA_BF16, dlcx.MMA_F16):
+            d = dlcx.desc(m, n, r, 8, 16, mma)
+            ws = ws_for(d, K)
+            outs = [torch.empty(r, L, device=DEV) for _ in range(K)]
+            ws.fill_(255)
+            dlcx.dlcx_project(d, phase, deltas, basis, outs, ws)
+            codes, scales = payload_buffers(d, phase, K)
+            ws.fill_(255)
+            dlcx.dlcx_compress_batched(d, phase, deltas, basis, codes, scales, ws)
+            factors = ws[: K * r * L * 4].view(torch.float32).view(K, r, L)
+            assert all(torch.equal(factors[k], outs[k]) for k in range(K)), (phase, mma)
+            got[mma] = outs, codes
+        for k in range(K):
+            want = to_np(basis.double() @ (deltas[k].double().T if phase == dlcx.PHASE_P else deltas[k].double()).contiguous())
+            assert close(to_np(got[dlcx.MMA_F16][0][k]), want, TOL[dlcx.MMA_BF16 if huge else dlcx.MMA_F16])
+            if huge:
+                assert all(torch.equal(a[k], b[k]) for a, b in zip(got[dlcx.MMA_BF16], got[dlcx.MMA_F16])), (phase, k)
+
+
 @pytest.mark.parametrize("mma", MODES, ids=MODE_IDS)
 @pytest.mark.parametrize("m,n,r,K,group", SHAPES)
 def test_decompress_and_error_buffer(mma, m, n, r, K, group):
