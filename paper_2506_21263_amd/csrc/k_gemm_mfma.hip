@@ -1461,7 +1461,10 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     int64_t smax = most_splits(wgs), S = 1;
     if (smax > most_p_splits(n)) smax = most_p_splits(n);
     // (a second workgroup on every unit does not pay here: 8192 x 8192 r = 64 271 us split in two, 240 not)
-    if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, (int64_t)K * r * m, 1, smax);
+    // (where a workgroup has little to stream the slabs cost two and a half times the estimate's: 3264 x 320
+    // r = 246 two workers 22.8 us split in two, 19.3 not, 8192 x 256 r = 200 21.5 | 17.7)
+    const int64_t slab = (int64_t)K * r * m * (n <= kPShort ? 5 : 2) / 2;
+    if (wgs < kQUnits && !p.one_role) S = best_splits(wgs, n, 64, slab, 1, smax);
     p.stages = ceil_div(stages, S);
     p.S = (int)ceil_div(stages, p.stages);
     p.lone = wgs * p.S <= kQUnits;
