@@ -140,12 +140,13 @@ __device__ __forceinline__ int count_below(const double2 *t, int blocks, double 
 }
 
 // The c-th largest eigenvalue (c from 0) by groups of G lanes, every lane of the wavefront calling;
-// lo, hi: an interval with all eigenvalues, narrowed to 2^-48 of its width, which is about the error
-// the reduction to tridiagonal form leaves (r 2^-53).
+// lo, hi: an interval with all eigenvalues, inside [-1, 1], narrowed to less than 2^-56.  The sums that
+// decide r' are at least 1/2 and rounded at 2^-54: an eigenvalue that is zero, or vanishes beside the
+// others, then adds nothing to them.
 template <int G>
 __device__ __forceinline__ double nth_largest(const double2 *t, int r, int c, double lo, double hi,
                                               int lane) {
-    constexpr int kRounds = G == 64 ? 8 : G == 32 ? 10 : G == 16 ? 12 : G == 8 ? 16 : 21;
+    constexpr int kRounds = G == 64 ? 10 : G == 32 ? 12 : G == 16 ? 14 : G == 8 ? 18 : 25;  // 2 (G + 1)^-n
     const int below = r - 1 - c;  // eigenvalues smaller than the one wanted
     const int sub = lane & (G - 1), base = lane - sub;
     constexpr uint64_t mask = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
@@ -163,30 +164,31 @@ __device__ __forceinline__ double nth_largest(const double2 *t, int r, int c, do
     return fmax(0.5 * (lo + hi), 0.0);
 }
 
-// smallest k whose k largest of the descending values hold at least tau of their sum (0: all zero),
-// by one wavefront, four values a lane
+// smallest k whose k largest of the descending values (in LDS, zeros behind them up to a multiple of 64)
+// hold at least tau of their sum (0: all zero), by one wavefront.  Every lane adds them all up one after the other, largest first, and keeps the
+// partial sums that fall to it: for tau = 1 it matters that the total is the last of those sums.
 __device__ __forceinline__ int32_t count_share(const double *eig, int r, double tau, int lane) {
-    double cum[4], sum = 0.0;
+    double keep[DLCX_MAX_RANK / 64] = {0.0, 0.0, 0.0, 0.0}, cum = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int c = 4 * lane + q;
-        sum += c < r ? eig[c] : 0.0;
-        cum[q] = sum;
-    }
-    double incl = sum;  // over this lane and those before it
+    for (int q = 0; q < DLCX_MAX_RANK / 64; ++q) {
+        for (int c = 0; c < 64 && 64 * q + c < r; c += 16) {  // sixteen read at a time
+            double e[16];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
+            for (int u = 0; u < 16; ++u) e[u] = eig[64 * q + c + u];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                cum += e[u];
+                keep[q] = lane == c + u ? cum : keep[q];
+            }
+        }
     }
-    const double before = incl - sum, total = __shfl(incl, 63, 64);
     int32_t k = r;
 #pragma unroll
-    for (int q = 3; q >= 0; --q)
-        if ((q < 3 ? before + cum[q] : incl) >= tau * total) k = 4 * lane + q + 1;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) k = min(k, __shfl_xor(k, off, 64));
-    return total > 0.0 ? min(k, r) : 0;
+    for (int q = DLCX_MAX_RANK / 64 - 1; q >= 0; --q) {
+        const uint64_t m = __ballot(keep[q] >= tau * cum && 64 * q + lane < r);
+        if (m) k = 64 * q + __builtin_ctzll(m) + 1;
+    }
+    return cum > 0.0 ? k : 0;
 }
 
 // The Householder reflection of a row whose first element right of the diagonal is x0 and whose
@@ -249,9 +251,11 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // What tridiag_kernel leaves in FactorItem::g above rank 64: (d_i, e_i^2) scaled, from double 0;
-// then lo, hi; then the eigenvalues (still scaled: r' does not depend on a power of two).
+// then lo, hi and the number of rows that are not zero; then the eigenvalues (still scaled: r' does not
+// depend on a power of two).
 __device__ __forceinline__ double2 *tri_of(const FactorItem &it) { return reinterpret_cast<double2 *>(it.g); }
 __device__ __forceinline__ double *bounds_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK; }
+__device__ __forceinline__ int live_of(const FactorItem &it) { return __builtin_amdgcn_readfirstlane((int)bounds_of(it)[2]); }
 __device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK + 8; }
 
 // Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
@@ -282,14 +286,34 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
     __shared__ double pbuf[R];
     __shared__ double red[4];
     __shared__ double2 tri[R];              // d_k and the off-diagonal element before it
+    __shared__ int order[R];                // the rows of S that are not zero
+    __shared__ int counts[4];
     const FactorItem it = batch.it[blockIdx.x];
-    const int r = it.r, nchunks = it.nchunks;
+    const int nchunks = it.nchunks;
     const double *__restrict__ part = it.part;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tj = lane & 15, g = lane >> 4, ti = wave * 4 + g;
-    const int64_t rr = (int64_t)r * r;
-    if (r <= kFusedRank) return;
+    const int64_t pitch = it.r, rr = pitch * pitch;
+    if (it.r <= kFusedRank) return;
+
+    // The zero columns of the factor: left out, their eigenvalues are zero.  (Reflected with the others
+    // they would come back as rounding, and count at tau = 1.)
+    bool on = false;
+    if (tid < it.r) {
+        double s = 0.0;
+        for (int c = 0; c < nchunks; ++c) s += part[tid * pitch + tid + c * rr];
+        on = s != 0.0;
+    }
+    const uint64_t mask = __ballot(on);
+    if (lane == 0) counts[wave] = __popcll(mask);
+    __syncthreads();
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) before += w < wave ? counts[w] : 0;
+    if (on) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
+    const int r = __builtin_amdgcn_readfirstlane((counts[0] + counts[1]) + (counts[2] + counts[3]));
+    __syncthreads();
 
     double t[NT][NT];  // t[x][y], x <= y
 #pragma unroll
@@ -298,8 +322,8 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
         for (int y = x; y < NT; ++y) {
             const int a = 16 * x + ti, b = 16 * y + tj;
             double s = 0.0;
-            if (a < r && b < r) {
-                const double *src = part + (int64_t)(a < b ? a : b) * r + (a < b ? b : a);
+            if (a < r && b < r) {  // order[] rises
+                const double *src = part + order[a < b ? a : b] * pitch + order[a < b ? b : a];
                 for (int c = 0; c < nchunks; ++c) s += src[c * rr];
             }
             t[x][y] = s;
@@ -422,6 +446,7 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
         if (lane == 0) {
             bounds_of(it)[0] = in.lo;
             bounds_of(it)[1] = in.hi;
+            bounds_of(it)[2] = r;
         }
     }
 }
@@ -436,20 +461,21 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     __shared__ double sm[RC][RC + 1];
     __shared__ __attribute__((aligned(16))) double vb[64 + 8], wb[64 + 8];
     __shared__ double2 tri[RC + kSturmPad];
-    __shared__ double eig[RC];
+    __shared__ double eig[64];
+    __shared__ int order[64];
     const FactorItem it = batch.it[blockIdx.x];
-    const int r = it.r, nchunks = it.nchunks;
+    const int nchunks = it.nchunks;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t rr = (int64_t)r * r;
-    if (r > RC || r <= RC / 2 * (RC > 32)) return;  // another kernel's
+    const int64_t rr = (int64_t)it.r * it.r;
+    if (it.r > RC || it.r <= RC / 2 * (RC > 32)) return;  // another kernel's
     constexpr int E = RC * RC / kTT;
     int from[E];
     double sum[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int x = (tid + kTT * e) / RC, y = (tid + kTT * e) % RC;
-        from[e] = x <= y && y < r ? x * r + y : -1;
+        from[e] = x <= y && y < it.r ? x * it.r + y : -1;
         sum[e] = 0.0;
     }
     for (int c = 0; c < nchunks; c += 2) {  // chunk by chunk in order, two requested at a time
@@ -474,12 +500,19 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
         }
     }
     __syncthreads();
+    // the rows that are not zero, as in tridiag_kernel (every wavefront writes the same)
+    const bool on = lane < it.r && sm[lane % RC][lane % RC] != 0.0;
+    const uint64_t mask = __ballot(on);
+    if (on) order[__popcll(mask & ((1ull << lane) - 1))] = lane;
+    const int r = __popcll(mask);
+    __syncthreads();
     if (wave == 0) {
         double t[RC];
+        const int row = lane < r ? order[lane] : 0;
 #pragma unroll
         for (int j = 0; j < RC; ++j) {
-            const double e = sm[lane % RC][j];
-            t[j] = lane < RC ? e : 0.0;
+            const double e = sm[row][j < r ? order[j] : 0];
+            t[j] = lane < r && j < r ? e : 0.0;
         }
         for (int k = 0; k + 1 < r; ++k) {
             const double x = t[0];
@@ -518,10 +551,16 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
                             t[8 * q + u - 1] = fma(-v, wb[8 * q + u], fma(-w, vb[8 * q + u], t[8 * q + u]));
                 }
         }
-        const double last = read_lane(t[0], r - 1);
-        if (lane == 0) tri[r - 1].x = last;
+        if (r > 0) {
+            const double last = read_lane(t[0], r - 1);
+            if (lane == 0) tri[r - 1].x = last;
+        }
     }
     __syncthreads();
+    if (r == 0) {  // nothing but zeros
+        if (tid == 0) *it.out = 0;
+        return;
+    }
     const Interval in = gershgorin(tri, r, lane);
     __syncthreads();  // every wavefront has its interval
     if (tid < r)
@@ -535,6 +574,7 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
         const int c = tid / G;
         const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, in.lo, in.hi, lane);
         if (c < r && (lane & (G - 1)) == 0) eig[c] = ev;
+        if (tid >= r && tid < 64) eig[tid] = 0.0;
     };
     if (r <= 4) find(std::integral_constant<int, 64>());
     else if (r <= 8) find(std::integral_constant<int, 32>());
@@ -552,8 +592,9 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
 __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
     __shared__ double2 tri[DLCX_MAX_RANK + kSturmPad];
     const FactorItem it = batch.it[blockIdx.y];
-    const int r = it.r;
-    if (r <= kFusedRank || (int)blockIdx.x * 4 >= r) return;
+    if (it.r <= kFusedRank) return;
+    const int r = live_of(it);
+    if ((int)blockIdx.x * 4 >= r) return;
     for (int i = threadIdx.x; i < 16 * sturm_blocks(r) + 8; i += 256)
         tri[i] = i < r ? tri_of(it)[i] : sturm_fill();
     __syncthreads();
@@ -565,9 +606,13 @@ __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {
+    __shared__ double eig[DLCX_MAX_RANK];
     const FactorItem it = batch.it[blockIdx.x];
     if (it.r <= kFusedRank) return;
-    const int32_t k = count_share(eig_of(it), it.r, tau, threadIdx.x);
+    const int r = live_of(it);
+    for (int c = threadIdx.x; c < DLCX_MAX_RANK; c += 64) eig[c] = c < r ? eig_of(it)[c] : 0.0;
+    __syncthreads();
+    const int32_t k = count_share(eig, r, tau, threadIdx.x);
     if (threadIdx.x == 0) *it.out = k;
 }
 

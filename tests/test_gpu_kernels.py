@@ -573,6 +573,38 @@ def test_effective_rank_on_runs_of_equal_decoupled_rows(r, norms2):
         assert int(out.item()) == ref.effective_rank(q, tau), tau
 
 
+@pytest.mark.parametrize("r", [1, 2, 5, 8, 17, 24, 31, 32, 33, 40, 55, 64, 65, 100, 129, 200, 256])
+def test_effective_rank_counts_no_zero_column_at_tau_one(r):
+    # Exactly zero columns (what the orthonormalisation makes of dead ones, and Q_bar inherits) hold
+    # no share of the trace: at tau = 1 r' is the number of the others, wherever they stand.
+    n = 512
+    g = rng(r)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for trial in range(12):
+        q = (g.standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.7)).astype(np.float32)
+        dead = g.permutation(r)[: g.integers(0, r + 1)] if trial else np.arange(1, r)
+        q[dead] = 0.0
+        dlcx.dlcx_effective_rank(n, r, to_dev(q), 1.0, out, ws)
+        assert int(out.item()) == r - len(dead), (trial, sorted(dead))
+        for tau in (0.9, 0.99):
+            dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
+            assert int(out.item()) == ref.effective_rank(q, tau), (trial, tau)
+
+
+@pytest.mark.parametrize("r", [16, 31, 60, 120, 250])
+def test_effective_rank_at_tau_one_stops_where_the_sum_does(r):
+    # Orthogonal columns with squared norms 4^-k: their sum in 64 bits, largest first, ends with
+    # 4^-26 (4^-27 = 2^-54 is less than half a unit in the last place of 4 / 3).
+    n = 256
+    q = np.zeros((r, n), np.float32)
+    q[np.arange(r), np.arange(r)] = 2.0 ** -np.minimum(np.arange(r), 60.0)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    dlcx.dlcx_effective_rank(n, r, to_dev(q), 1.0, out, ws)
+    assert int(out.item()) == min(r, 27) == ref.effective_rank(q, 1.0)
+
+
 def test_select_rank_stage_value_and_window():
     # three matrices with known r' (3, 49, zero matrix -> rmin 4): mean 56/3 = 18.67 -> 19
     n, r = 512, 64
