@@ -327,7 +327,8 @@ int dlcx_effective_rank_batched(const dlcx_desc *descs_host, const float *const 
                                 void *workspace, void *stream);
 /* Alg. 3's r'_t for one matrix (the paper gives no formula; see dlcx_select_rank for the
  * definition used): the smallest k whose k largest eigenvalues of Q_bar^T Q_bar hold at least
- * tau of the trace, written to a DEVICE int32 (0 when Q_bar is all zero); asynchronous. */
+ * tau of the trace, written to a DEVICE int32 (0 when Q_bar is all zero or holds a NaN);
+ * asynchronous. */
 int dlcx_effective_rank(int64_t L, int32_t r, const float *q_bar, double tau,
                         int32_t *rprime_out_dev, void *workspace, void *stream);
 

@@ -299,20 +299,23 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
 
     // The zero columns of the factor: left out, their eigenvalues are zero.  (Reflected with the others
     // they would come back as rounding, and count at tau = 1.)
-    bool on = false;
+    bool on = false, odd = false;
     if (tid < it.r) {
         double s = 0.0;
         for (int c = 0; c < nchunks; ++c) s += part[tid * pitch + tid + c * rr];
         on = s != 0.0;
+        odd = !(s < __builtin_inf());
     }
     const uint64_t mask = __ballot(on);
-    if (lane == 0) counts[wave] = __popcll(mask);
+    const bool wave_odd = __ballot(odd) != 0;  // a NaN or an infinity in the factor: no rows, r' = 0
+    if (lane == 0) counts[wave] = wave_odd ? -kTT : __popcll(mask);
     __syncthreads();
     int before = 0;
 #pragma unroll
     for (int w = 0; w < 4; ++w) before += w < wave ? counts[w] : 0;
-    if (on) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
-    const int r = __builtin_amdgcn_readfirstlane((counts[0] + counts[1]) + (counts[2] + counts[3]));
+    if (on && before >= 0) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
+    int r = __builtin_amdgcn_readfirstlane((counts[0] + counts[1]) + (counts[2] + counts[3]));
+    r = r < 0 ? 0 : r;
     __syncthreads();
 
     double t[NT][NT];  // t[x][y], x <= y
@@ -500,8 +503,18 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
         }
     }
     __syncthreads();
+    const double diag = lane < it.r ? sm[lane % RC][lane % RC] : 0.0;
+    if (__ballot(!(diag < __builtin_inf()))) {
+        // A NaN in S: r' = 0.  Infinities alone: every column of S is infinite and the first one holds
+        // every share, up to rank 31; at 32, as above, 0.
+        bool nan = false;
+        for (int j = 0; j < it.r; ++j) nan = nan || (lane < it.r && sm[lane % RC][j] != sm[lane % RC][j]);
+        const int32_t k = __ballot(nan) != 0 || it.r >= 32 ? 0 : 1;
+        if (tid == 0) *it.out = k;
+        return;
+    }
     // the rows that are not zero, as in tridiag_kernel (every wavefront writes the same)
-    const bool on = lane < it.r && sm[lane % RC][lane % RC] != 0.0;
+    const bool on = diag != 0.0;
     const uint64_t mask = __ballot(on);
     if (on) order[__popcll(mask & ((1ull << lane) - 1))] = lane;
     const int r = __popcll(mask);

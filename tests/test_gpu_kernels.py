@@ -605,6 +605,25 @@ def test_effective_rank_at_tau_one_stops_where_the_sum_does(r):
     assert int(out.item()) == min(r, 27) == ref.effective_rank(q, 1.0)
 
 
+@pytest.mark.parametrize("r", [1, 3, 16, 31, 32, 33, 64, 65, 130, 256])
+def test_effective_rank_of_a_factor_that_is_not_finite(r):
+    # A NaN anywhere: no eigenvalue is a number and no share is ever reached, r' = 0.  An infinity: up
+    # to rank 31 every column of S is infinite and the first one holds every share (where an element
+    # beside it is zero, S has a NaN); above that no eigenvalue is found, 0.
+    n = 512
+    g = rng(r)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for col in sorted({0, r // 2, r - 1}):
+        for value, beside, want in ((np.nan, 1.0, 0), (np.inf, 1.0, 1 if r < 32 else 0),
+                                    (-np.inf, 1.0, 1 if r < 32 else 0), (np.inf, 0.0, 1 if r == 1 else 0)):
+            q = g.standard_normal((r, n)).astype(np.float32)
+            q[:, n // 3] = beside
+            q[col, n // 3] = value
+            dlcx.dlcx_effective_rank(n, r, to_dev(q), 0.99, out, ws)
+            assert int(out.item()) == want, (col, value, beside)
+
+
 def test_select_rank_stage_value_and_window():
     # three matrices with known r' (3, 49, zero matrix -> rmin 4): mean 56/3 = 18.67 -> 19
     n, r = 512, 64
