@@ -171,7 +171,7 @@ struct FactorItem {
     int64_t L;
     int32_t r, nchunks;
     double *part;    // nchunks x r x r partial Gram sums (upper triangles)
-    double *g;       // r x (r + 1): g[0] is the mark of the orthonormalisation, or the Jacobi matrix
+    double *g;       // g[0]: the mark of the orthonormalisation; or the tridiagonal matrix (k_rank.hip)
     double *w;       // r x r: inverse factor (orthonormalisation only)
     int32_t *out;    // r' (effective rank only)
 };

@@ -629,9 +629,12 @@ __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau
     if (threadIdx.x == 0) *it.out = k;
 }
 
+// doubles of the partial sums, whole pairs: what follows them is read and written in pairs
+static size_t partial_doubles(int64_t L, int r) { return ((size_t)gram_chunks(L) * r * r + 1) & ~(size_t)1; }
+
 size_t effrank_workspace_bytes(int64_t L, int r) {
     const size_t re = (size_t)((r + 1) & ~1);
-    return a256x(((size_t)gram_chunks(L) * r * r + re * re) * sizeof(double));
+    return a256x((partial_doubles(L, r) + re * re) * sizeof(double));
 }
 
 void effrank_item(FactorItem *it, const float *q_bar, int64_t L, int r, int32_t *out,
@@ -641,7 +644,7 @@ void effrank_item(FactorItem *it, const float *q_bar, int64_t L, int r, int32_t 
     it->r = r;
     it->nchunks = gram_chunks(L);
     it->part = reinterpret_cast<double *>(workspace);
-    it->g = it->part + (size_t)it->nchunks * r * r;
+    it->g = it->part + partial_doubles(L, r);
     it->w = nullptr;
     it->out = out;
 }
