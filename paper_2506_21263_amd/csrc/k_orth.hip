@@ -40,6 +40,7 @@ __device__ __forceinline__ f64x4_t mfma64(double a, double b, f64x4_t c) {
 // close as two (2.5e-8, the rounding to fp32), at 1e9 it is at 3 - 7e-8; the line leaves a factor of 20.
 constexpr double kDone = 1.0;
 constexpr double kOneRoundNorm = 4e6;
+constexpr int kOdd = 1;  // it.g[kOdd]: the first column that is not finite, as a double (r: none)
 __device__ __forceinline__ bool second_round_idle(const FactorItem &it, int round) {
     return round == 1 && it.g[0] == kDone;
 }
@@ -333,15 +334,28 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
             for (int v = 0; v < 4; ++v)
                 if (4 * v + g == col) {
                     const double d = t[s][v];
-                    dscale[16 * (id[s] & 0xff) + col] = d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+                    dscale[16 * (id[s] & 0xff) + col] = !(d < __builtin_inf()) ? -1.0 : d > 0.0 ? 1.0 / sqrt(d) : 0.0;
                 }
     __syncthreads();
+    // The first column that is not finite (kOdd).  It and those after it come out as NaN, and must not
+    // reach those before it: their rows are zeros here, their columns of W NaN, and apply_w reads zeros
+    // for them.  (A product with a zero keeps a NaN: whole blocks of the matrix cores' operands would
+    // carry it.)
+    int odd = r;
+    for (int q = 0; q < r; q += 64) {
+        const uint64_t m = __ballot(q + lane < r && dscale[q + lane < r ? q + lane : 0] < 0.0);
+        if (m && odd == r) odd = q + __builtin_ctzll(m);
+    }
+    if (tid == 0) it.g[kOdd] = (double)odd;
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
         if (id[s] < 0) continue;
         const int I = id[s] >> 8, J = id[s] & 0xff;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) t[s][v] *= dscale[16 * J + 4 * v + g] * dscale[16 * I + col];
+        for (int v = 0; v < 4; ++v) {
+            const double scaled = t[s][v] * (dscale[16 * J + 4 * v + g] * dscale[16 * I + col]);
+            t[s][v] = 16 * I + col < odd && 16 * J + 4 * v + g < odd ? scaled : 0.0;
+        }
         if (I == 0) {  // block (0, 0)
 #pragma unroll
             for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
@@ -354,6 +368,9 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         asm volatile("" : "+s"(x));
         I = x >> 8;
         J = x & 0xff;
+    };
+    auto w_entry = [&](int row, int c, double x) {
+        return c >= odd ? __builtin_nan("") : row < odd ? dscale[row] * x : 0.0;
     };
     bool dead = false;
     double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
@@ -384,7 +401,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
                     for (int v = 0; v < 4; ++v) {
                         norm2 = fma(x[v], x[v], norm2);
                         const int c = 16 * k + 4 * v + g, kk = 16 * J + col;
-                        if (c < r) w[(int64_t)kk * r + c] = dscale[kk] * x[v];
+                        if (c < r) w[(int64_t)kk * r + c] = w_entry(kk, c, x[v]);
                     }
                 } else {
                     t[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
@@ -396,7 +413,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
                     panel[k][v][lane] = x;
                     norm2 = fma(x, x, norm2);
                     const int c = 16 * k + 4 * v + g, kk = 16 * k + col;
-                    if (c < r && kk < r) w[(int64_t)kk * r + c] = dscale[kk] * x;
+                    if (c < r && kk < r) w[(int64_t)kk * r + c] = w_entry(kk, c, x);
                 }
             }
         }
@@ -463,11 +480,11 @@ __global__ __launch_bounds__(kGT) void apply_w_kernel(FactorBatch batch, int rou
     if (second_round_idle(it, round)) return;
     float *__restrict__ p = it.f;
     const double *__restrict__ w = it.w;
-    const int r = it.r, nb = (r + 15) >> 4;
+    const int r = it.r, nb = (r + 15) >> 4, odd = __builtin_amdgcn_readfirstlane((int)it.g[kOdd]);
     for (int idx = threadIdx.x; idx < nb * 256; idx += kGT) {
         const int c = idx >> 4, c4 = idx & 15;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c < r && i0 + c4 * 4 < L)
+        if (c < odd && i0 + c4 * 4 < L)  // odd <= r
             v = *reinterpret_cast<const float4 *>(p + (int64_t)c * L + i0 + c4 * 4);
         *reinterpret_cast<float4 *>(fl + c * 64 + c4 * 4) = v;
     }

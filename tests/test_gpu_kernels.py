@@ -260,6 +260,39 @@ def test_fp64_products_at_tile_edges(m, n, r, K):
     assert close(to_np(out), p.astype(np.float64).T @ q.astype(np.float64), 2.0 ** -23)
 
 
+@pytest.mark.parametrize("mma", MODES, ids=MODE_IDS)
+@pytest.mark.parametrize("value", [np.nan, np.inf], ids=["nan", "inf"])
+@pytest.mark.parametrize("m,n,r", [(48, 80, 17), (272, 144, 100)])
+def test_what_is_not_finite_stays_in_its_row_and_column(mma, value, m, n, r):
+    # Padding of tiles and lanes past the matrix must not meet a NaN or an infinity, and a product
+    # with one reaches the outputs that contain it, no others.
+    g = rng(m)
+    delta = g.standard_normal((m, n)).astype(np.float32)
+    p, q = g.standard_normal((r, m)).astype(np.float32), g.standard_normal((r, n)).astype(np.float32)
+    i, j, c = m - 1, n - 1, r - 1
+    d = dlcx.desc(m, n, r, 8, 16, mma)
+    ws = ws_for(d, 1)
+
+    def products(delta, p, q):
+        P, Q, D = torch.zeros(r, m, device=DEV), torch.zeros(r, n, device=DEV), torch.zeros(m, n, device=DEV)
+        dlcx.dlcx_project(d, dlcx.PHASE_P, [to_dev(delta)], to_dev(q), [P], ws)
+        dlcx.dlcx_project(d, dlcx.PHASE_Q, [to_dev(delta)], to_dev(p), [Q], ws)
+        dlcx.dlcx_decompress(d, to_dev(p), to_dev(q), D, workspace=ws)
+        return to_np(P), to_np(Q), to_np(D)
+
+    clean = products(delta, p, q)
+    delta2, p2, q2 = delta.copy(), p.copy(), q.copy()
+    delta2[i, j] = p2[c, i] = q2[c, j] = value
+    hit = [np.zeros(x.shape, bool) for x in clean]
+    hit[0][:, i] = hit[0][c, :] = True   # P = delta q: row i of delta, column c of the basis
+    hit[1][:, j] = hit[1][c, :] = True
+    hit[2][i, :] = hit[2][:, j] = True
+    for got, want, h in zip(products(delta2, p2, q2), clean, hit):
+        assert not np.isfinite(got[h]).any()
+        assert np.isfinite(got[~h]).all()
+        assert np.array_equal(got[~h], want[~h])
+
+
 # ranks above 64 in the fp16 form: (Q only: few rows) / (P and Q: the two-role P kernel is used)
 SHAPES_F16 = [(640, 2048, 96, 2, 128), (2048, 512, 256, 1, 64), (4096, 320, 200, 8, 64),
               (4112, 336, 72, 8, 16), (4112, 336, 130, 8, 16)]
@@ -464,6 +497,27 @@ def test_orthonormalize_block_edges_both_rounds(L, r, cond):
     ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
     dlcx.dlcx_orthonormalize(L, r, d_A, ws)
     assert rel_l2(to_np(d_A), want) <= 2.4e-7
+
+
+@pytest.mark.parametrize("L,r", [(64, 1), (272, 20), (1040, 33), (528, 100), (1024, 256)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf], ids=["nan", "inf", "-inf"])
+def test_orthonormalize_leaves_the_columns_before_one_that_is_not_finite(L, r, value):
+    # Column c of a thin QR hangs on the columns up to c alone: those before the first column that is
+    # not finite are what they are without the rest, that column and those after it are NaN.
+    g = rng(L + r)
+    A = g.standard_normal((r, L)).astype(np.float32)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    for col in sorted({0, r // 3, 17 * r // 20, r - 1}):
+        B = A.copy()
+        B[col, L // 2] = value
+        B[r - 1, 0] = np.nan if col < r - 1 else B[r - 1, 0]
+        d_B = to_dev(B)
+        dlcx.dlcx_orthonormalize(L, r, d_B, ws)
+        got = to_np(d_B)
+        assert np.isnan(got[col:]).all(), col
+        if col:
+            q, t = np.linalg.qr(A[:col].T.astype(np.float64))
+            assert rel_l2(got[:col], (q * np.sign(np.diag(t))).T) <= 2.4e-7, col
 
 
 def test_orthonormalize_degenerate_columns():
