@@ -237,19 +237,21 @@ int launch_sum_slabs(int K, const PartialSums &part, const PtrPack<float *> &out
 
 // ---------------------------------------------------------------------------------------------
 // delta_hat = P_hat Q_bar^T:  D[i][j] = sum_c P_hat[c][i] Q_bar[c][j], 16 rows x 64 columns per
-// wavefront (256 columns per workgroup), so that a lane ends up with four consecutive columns of
-// four rows; the epilogue writes the tile (optional), subtracts it from the K error buffers (e_k <-
+// wavefront (WC wavefronts of a workgroup beside one another, 4 / WC below), so that a lane ends up
+// with four consecutive columns of four rows; the epilogue writes the tile (optional), subtracts it from the K error buffers (e_k <-
 // delta_k - delta_hat) and, when theta is given, forms the next pseudo-gradients and applies the
 // Nesterov outer update with the tile as the gradient.
 // ---------------------------------------------------------------------------------------------
+template <int WC>
 __global__ __launch_bounds__(kT) void reconstruct_f64_kernel(const float *__restrict__ p_hat,
                                                              const float *__restrict__ q_bar,
                                                              ReconEpilogue ep, int64_t m,
                                                              int64_t n, int r, int col_wgs) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, x = lane & 15;
-    const int64_t i0 = (int64_t)(blockIdx.x / col_wgs) * 16;
-    const int64_t j = (int64_t)(blockIdx.x % col_wgs) * 256 + wave * 64 + 4 * x;
+    const int64_t i0 = (int64_t)(blockIdx.x / col_wgs) * (64 / WC) + wave / WC * 16;
+    const int64_t j = (int64_t)(blockIdx.x % col_wgs) * (64 * WC) + wave % WC * 64 + 4 * x;
+    if (i0 >= m) return;
     const float *pa = p_hat + i0 + x, *pb = q_bar + (j < n ? j : 0);
     f64x4_t acc[4];
 #pragma unroll
@@ -409,11 +411,18 @@ int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
 
 int launch_reconstruct_fma(int64_t m, int64_t n, int r, const float *p_hat, const float *q_bar,
                            const ReconEpilogue &ep, hipStream_t st) {
-    const int64_t col_wgs = ceil_div(n, 256);  // in one dimension: m / 16 may exceed the others'
-    const dim3 grid((unsigned)(col_wgs * ceil_div(m, 16)));
     Timed timed(KID_RECONSTRUCT, st);
-    hipLaunchKernelGGL(reconstruct_f64_kernel, grid, dim3(kT), 0, st, p_hat, q_bar, ep, m, n, r,
-                       (int)col_wgs);
+    auto go = [&](auto wc) {  // the grid in one dimension: m / 16 may exceed the others'
+        constexpr int WC = decltype(wc)::value;
+        const int64_t col_wgs = ceil_div(n, 64 * WC);
+        const dim3 grid((unsigned)(col_wgs * ceil_div(m, 64 / WC)));
+        hipLaunchKernelGGL(reconstruct_f64_kernel<WC>, grid, dim3(kT), 0, st, p_hat, q_bar, ep, m, n, r,
+                           (int)col_wgs);
+    };
+    // no wavefront without columns: 8192 x 64 r = 64 11.1 us, four side by side 12.4
+    if (n <= 64) go(std::integral_constant<int, 1>());
+    else if (n <= 128) go(std::integral_constant<int, 2>());
+    else go(std::integral_constant<int, 4>());
     return check_launch("reconstruct_f64");
 }
 

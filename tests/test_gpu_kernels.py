@@ -237,12 +237,13 @@ def test_fewer_workers_stay_inside_a_larger_workspace(mma, m, n, r, K, k):
 @pytest.mark.parametrize("m,n,r,K", [
     (16, 16, 16, 1), (48, 272, 17, 3), (272, 80, 31, 2),      # fewer steps than wavefronts, ragged tiles
     (1040, 208, 65, 1), (320, 336, 128, 2), (272, 528, 129, 1), (512, 256, 256, 1),
-    (8208, 64, 20, 2), (8208, 80, 48, 2),                     # two row blocks per wavefront in P
+    (8208, 64, 20, 2), (8208, 80, 48, 2), (48, 128, 20, 1),   # two row blocks per wavefront in P; narrow
 ])
 def test_fp64_products_at_tile_edges(m, n, r, K):
     # The fp64-accumulating form: products of fp32 values are exact and their sums carry 2^-53 per
-    # addition, so P and the reconstruction are the 64-bit result rounded once (2^-24 relative);
-    # Q adds up to 16 partial sums in fp32: 2^-24 of the partial sums for each.
+    # addition, so P and the reconstruction are the 64-bit result rounded once (2^-24 relative).  Q is
+    # rounded to fp32 in every slab (up to 64 of them), added up in fp64 and rounded once more: errors
+    # of 2^-24 of each partial sum, which in norm are 2^-24 of the result for sums of random signs.
     g = rng(m + 3 * n + r)
     deltas = [g.standard_normal((m, n)).astype(np.float32) for _ in range(K)]
     p, q = g.standard_normal((r, m)).astype(np.float32), g.standard_normal((r, n)).astype(np.float32)
