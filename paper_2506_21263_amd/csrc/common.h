@@ -29,7 +29,7 @@ int grant_dynamic_lds(const void *kernel, size_t bytes, size_t *granted, const c
 // launch with two HIP events on the launch stream.  Off by default; costs nothing when off.
 enum KernelId {
     KID_DELTA_EF = 0, KID_NESTEROV, KID_QUANTIZE, KID_DEQUANT_AVG, KID_PACK, KID_PROJECT_P,
-    KID_PROJECT_Q, KID_SUM_SLABS, KID_RECONSTRUCT, KID_GRAM, KID_CHOL, KID_APPLY_W, KID_JACOBI,
+    KID_PROJECT_Q, KID_SUM_SLABS, KID_RECONSTRUCT, KID_GRAM, KID_CHOL, KID_APPLY_W, KID_EFF_RANK,
     KID_ROUND, KID_QUANT_ROUND, KID_REQUANT, KID_EF_UPDATE,
     KID_MFMA_PEAK, KID_TRAFFIC_PROBE, KID_COUNT
 };

@@ -161,7 +161,7 @@ const char *dlcx_last_hip_error(void) { return g_last_error.c_str(); }
 static const char *const kKernelNames[KID_COUNT] = {
     "delta_ef", "outer_nesterov", "quantize", "dequant_average", "pack_fragments", "project_p",
     "project_q", "sum_slabs", "reconstruct", "gram_partials", "chol_inverse", "apply_w",
-    "jacobi_rank", "round_fused", "quant_round", "requantize", "ef_update",
+    "effective_rank", "round_fused", "quant_round", "requantize", "ef_update",
     "mfma_peak", "traffic_probe"};
 
 int dlcx_profile_enable(int on) {

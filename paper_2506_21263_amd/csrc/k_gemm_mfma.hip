@@ -25,8 +25,9 @@
 //                                                 of a basis, of all operands of a sweep
 //   project_p_ws_kernel, project_q_ws_kernel      projections with producer and consumer
 //                                                 wavefronts
-//   project_q_mfma_kernel                         Q of three pieces at r <= 32, every wavefront
-//                                                 does everything
+//   project_p_one_kernel, project_q_one_kernel    projections at r <= 32 (P where it is the faster
+//                                                 one, Q of three pieces), every wavefront does
+//                                                 everything
 //   reconstruct_mfma_kernel                       Delta_hat tile by tile with the elementwise
 //                                                 steps of Alg. 2 fused in (any rank)
 //   round_mfma_kernel                             the same plus the P phase of the next
@@ -626,150 +627,100 @@ __global__ __launch_bounds__(kW) void project_p_one_kernel(PtrPack<const float *
 }
 
 // ---------------------------------------------------------------------------------------------
-// Q phase:  Q_k[j][c] = sum_i delta_k[i][j] P_hat[c][i].
-// Wavefront: 32 JB columns x all CB basis blocks over its own range of rows.  The B operand
-// (N = column, reduction down the column) is loaded straight from HBM into the operand layout:
-// lane (x, half) reads the JB consecutive columns j0 + JB x .. of the rows i0 + 8 half + e,
-// e = 0..7, and column JB x + q feeds MFMA block q (the column blocks are interleaved, which an
-// MFMA does not care about), so one load instruction covers 2 rows x 128 JB contiguous bytes.
-// The 4 wavefronts of a workgroup take consecutive quarters of the workgroup's rows and are added
-// in wavefront order at the end; blockIdx.z splits the rows further into slabs.
+// Q phase of one basis block (r <= 32) and three pieces:  Q_k[j][c] = sum_i delta_k[i][j] P_hat[c][i].
+// Wavefront: 128 columns over its own range of rows.  The B operand (N = column, reduction down the
+// column) is loaded straight from HBM into the operand layout: lane (x, half) reads the 4 consecutive
+// columns j0 + 4 x .. of the rows i0 + 8 half + e, e = 0..7, and column 4 x + q feeds MFMA block q (the
+// column blocks are interleaved, which an MFMA does not care about), so one load instruction covers 2
+// rows x 512 contiguous bytes.  The 4 wavefronts of a workgroup take consecutive quarters of the
+// workgroup's rows and are added in wavefront order at the end; blockIdx.z splits the rows further into
+// slabs.
+// The two-role kernel below has one workgroup per unit there, 98 KB of LDS, and half of this one's
+// requests in flight (8192 x 8192 r = 20 181 us here, 206 there).  With two pieces it has two workgroups
+// per unit and takes every rank: 170 us against 178 here, 2048 x 2048 r = 32 21 | 25, 4352 x 7824 r = 6
+// three workers 87 | 108.  From two blocks on this kernel needs 326 registers, one wavefront per SIMD.
 // ---------------------------------------------------------------------------------------------
-template <int JB> struct VecOf;
-template <> struct VecOf<1> { typedef float type; };
-template <> struct VecOf<2> { typedef float2 type; };
-template <> struct VecOf<4> { typedef float4 type; };
-
-template <int JB>
-__device__ __forceinline__ void vec_to_array(const typename VecOf<JB>::type &v, float (&out)[JB]);
-template <>
-__device__ __forceinline__ void vec_to_array<1>(const float &v, float (&out)[1]) { out[0] = v; }
-template <>
-__device__ __forceinline__ void vec_to_array<2>(const float2 &v, float (&out)[2]) {
-    out[0] = v.x; out[1] = v.y;
-}
-template <>
-__device__ __forceinline__ void vec_to_array<4>(const float4 &v, float (&out)[4]) {
-    out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-}
-
-// Used for three pieces and one basis block (r <= 32): there the two-role kernel below has one
-// workgroup per unit, 98 KB of LDS, and half of this one's requests in flight (8192 x 8192 r = 20 181 us
-// here, 206 there).  With two pieces it has two workgroups per unit and takes every rank: 170 us
-// against 178 here, 2048 x 2048 r = 32 21 | 25, 4352 x 7824 r = 6 three workers 87 | 108.  From two
-// blocks on this kernel needs 326 registers, one wavefront per SIMD.
-template <int JB>
-__device__ __forceinline__ typename VecOf<JB>::type stream_load_vec(const float *p);
-template <>
-__device__ __forceinline__ float stream_load_vec<1>(const float *p) {
-    return __builtin_nontemporal_load(p);
-}
-template <>
-__device__ __forceinline__ float2 stream_load_vec<2>(const float *p) {
-    typedef float nt_f32x2 __attribute__((ext_vector_type(2)));
-    const nt_f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f32x2 *>(p));
-    return make_float2(v.x, v.y);
-}
-template <>
-__device__ __forceinline__ float4 stream_load_vec<4>(const float *p) {
-    return stream_load4(p);
-}
-
-template <int NS, int CB, int JB, int DEPTH>
-__global__ __launch_bounds__(kW) void project_q_mfma_kernel(PtrPack<const float *> deltas,
-                                                            const uint4 *__restrict__ afrags,
-                                                            PtrPack<float *> outs, int64_t m,
-                                                            int64_t n, int r,
-                                                            int64_t ksteps_per_wave,
-                                                            int64_t slab_stride) {
-    __shared__ float red[CB * JB * 16 * 64];
+constexpr int kQDepth = 2;  // k-steps (16 rows) of delta in flight per wavefront
+__global__ __launch_bounds__(kW) void project_q_one_kernel(PtrPack<const float *> deltas,
+                                                           const uint4 *__restrict__ afrags,
+                                                           PtrPack<float *> outs, int64_t m,
+                                                           int64_t n, int r, int64_t ksteps_per_wave,
+                                                           int64_t slab_stride) {
+    constexpr int NS = 3;
+    __shared__ float red[4 * 16 * 64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y] + (int64_t)blockIdx.z * slab_stride;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t jcol = (int64_t)blockIdx.x * (32 * JB) + JB * (lane & 31);
-    const bool col_ok = jcol < n;  // n is a multiple of 16: the JB columns are in or out together
+    const int64_t jcol = (int64_t)blockIdx.x * 128 + 4 * (lane & 31);
+    const bool col_ok = jcol < n;  // n is a multiple of 16: the 4 columns are in or out together
     const int64_t s_begin = ((int64_t)blockIdx.z * 4 + wave) * ksteps_per_wave;
-    const int64_t s_end = s_begin + ksteps_per_wave;  // a multiple of DEPTH k-steps
+    const int64_t s_end = s_begin + ksteps_per_wave;  // a multiple of kQDepth k-steps
 
-    f32x16_t acc[CB][JB];
+    f32x16_t acc[4];
 #pragma unroll
-    for (int a = 0; a < CB; ++a)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int b = 0; b < JB; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
 
-    float breg[DEPTH][8][JB];
+    float4 breg[kQDepth][8];
     auto load_kstep = [&](int d, int64_t s) {
         const int64_t ibase = s * 16 + (lane >> 5) * 8;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-#pragma unroll
-            for (int q = 0; q < JB; ++q) breg[d][e][q] = 0.f;
-            if (ibase + e < m && col_ok)
-                vec_to_array<JB>(stream_load_vec<JB>(delta + (ibase + e) * n + jcol), breg[d][e]);
+            breg[d][e] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (ibase + e < m && col_ok) breg[d][e] = stream_load4(delta + (ibase + e) * n + jcol);
         }
     };
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load_kstep(d, s_begin + d);
-    for (int64_t s = s_begin; s < s_end; s += DEPTH) {
+    for (int d = 0; d < kQDepth; ++d) load_kstep(d, s_begin + d);
+    for (int64_t s = s_begin; s < s_end; s += kQDepth) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            uint4 a[CB][NS];
+        for (int d = 0; d < kQDepth; ++d) {
+            uint4 a[NS];
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int h = 0; h < NS; ++h) a[h] = afrags[((s + d) * NS + h) * 64 + lane];
+            uint4 b[4][NS];
 #pragma unroll
-                for (int h = 0; h < NS; ++h)
-                    a[cb][h] = afrags[(((s + d) * CB + cb) * NS + h) * 64 + lane];
-            uint4 b[JB][NS];
-#pragma unroll
-            for (int q = 0; q < JB; ++q) {
+            for (int q = 0; q < 4; ++q) {
                 float x[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = breg[d][e][q];
+                for (int e = 0; e < 8; ++e) {
+                    const float4 y = breg[d][e];
+                    x[e] = q == 0 ? y.x : q == 1 ? y.y : q == 2 ? y.z : y.w;
+                }
                 split8<NS>(x, b[q]);
             }
-            if (s + d + DEPTH < s_end) load_kstep(d, s + d + DEPTH);
+            if (s + d + kQDepth < s_end) load_kstep(d, s + d + kQDepth);
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int q = 0; q < JB; ++q) mfma_split<NS>(a[cb], b[q], acc[cb][q]);
+            for (int q = 0; q < 4; ++q) mfma_split<NS>(a, b[q], acc[q]);
         }
     }
     // wavefronts 3, 2, 1 hand their sums to wavefront 0, in that order
     for (int w = 3; w >= 1; --w) {
         if (wave == w) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int q = 0; q < JB; ++q)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        red[((cb * JB + q) * 16 + v) * 64 + lane] = acc[cb][q][v];
+                for (int v = 0; v < 16; ++v) red[(q * 16 + v) * 64 + lane] = acc[q][v];
         }
         __syncthreads();
         if (wave == 0) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int q = 0; q < JB; ++q)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        acc[cb][q][v] += red[((cb * JB + q) * 16 + v) * 64 + lane];
+                for (int v = 0; v < 16; ++v) acc[q][v] += red[(q * 16 + v) * 64 + lane];
         }
         __syncthreads();
     }
     if (wave != 0 || !col_ok) return;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+    for (int v = 0; v < 16; ++v) {
+        const int c = d_row(v, lane);
+        if (c < r) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int c = cb * 32 + d_row(v, lane);
-            if (c < r) {
-#pragma unroll
-                for (int q = 0; q < JB; ++q) out[(int64_t)c * n + jcol + q] = acc[cb][q][v];
-            }
+            for (int q = 0; q < 4; ++q) out[(int64_t)c * n + jcol + q] = acc[q][v];
         }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1181,7 +1132,8 @@ __global__ __launch_bounds__(kW) void round_mfma_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// Q phase for 4 or 8 basis blocks in the two-role form of project_p_ws_kernel.  A workgroup owns
+// Q phase in the two-role form of project_p_ws_kernel, for any number of basis blocks (one: with two
+// pieces only).  A workgroup owns
 // 128 columns and a range of rows, swept in stages of 64 rows (4 k-steps).  Producer thread
 // (column quad c4, row group rg) requests 8 rows x 4 columns per stage -- one instruction of a
 // wavefront covers 2 rows x 512 bytes -- and holds, for each of its 4 columns, exactly the 8
@@ -1376,7 +1328,7 @@ static inline int cb_of(int r) { return r <= 32 ? 1 : r <= 64 ? 2 : r <= 128 ? 4
 static inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct QPlan {
-    int JB, S, depth;
+    int S;
     int64_t ksteps_per_wave, KS;
     bool lone;  // at most one workgroup per compute unit, the kernel's form for that
 };
@@ -1474,9 +1426,6 @@ static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
 static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
     QPlan p;
     const int cb = cb_of(r);
-    // 128 columns per workgroup in both Q kernels
-    p.JB = 4;
-    p.depth = 2;  // k-steps (16 rows) of delta in flight per wavefront
     p.lone = ns == 3;
     const int64_t wgs = out_wgs(n) * K;
     int64_t smax = most_splits(wgs);
@@ -1497,7 +1446,7 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
         // in two accumulators as well (lone) s0 / sqrt(12); one block has four for a workgroup, where the
         // one-role kernel had one for each of four wavefronts: 0.45 s0 by measurement.
         const int64_t full = ceil_div(cb == 8 ? kQUnits : 2 * kQUnits, wgs), s0 = full < smax ? full : smax;
-        const int64_t slab = (int64_t)K * r * n, granule = 64 * p.depth;
+        const int64_t slab = (int64_t)K * r * n, granule = 64 * kQDepth;
         S = best_splits(wgs, m, granule, slab, cb == 1 ? ceil_div(s0 * 45, 100) : cb == 2 ? ceil_div(s0 * 58, 100) : s0, smax);
         const int64_t fit = kQUnits / wgs < smax ? kQUnits / wgs : smax, least = ceil_div(s0 * 29, 100);
         if (ns == 2 && (cb == 2 || cb == 4) && least <= fit) {
@@ -1509,10 +1458,10 @@ static QPlan q_plan(int ns, bool f16, int64_t m, int64_t n, int r, int K) {
             if (p.lone) S = one;
         }
     } else {
-        S = best_splits(wgs, m, 64 * p.depth, (int64_t)K * r * n, 1, smax);
+        S = best_splits(wgs, m, 64 * kQDepth, (int64_t)K * r * n, 1, smax);
     }
     const int64_t kpw = ceil_div(ceil_div(m, 16), S * 4);
-    p.ksteps_per_wave = ceil_div(kpw, p.depth) * p.depth;
+    p.ksteps_per_wave = ceil_div(kpw, kQDepth) * kQDepth;
     p.S = (int)ceil_div(ceil_div(m, 16), p.ksteps_per_wave * 4);  // none without rows
     p.KS = p.ksteps_per_wave * 4 * p.S;
     return p;
@@ -1525,7 +1474,7 @@ size_t mfma_project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K)
     // DLCX_MMA_F16: one fp16 piece beside the two bf16 pieces of the stand-by launch
     const int ns = mma == DLCX_MMA_F16 ? 3 : ns_of(mma), cb = cb_of(r);
     const size_t p_frags = (size_t)ceil_div(n, 64) * 4 * cb * ns * 1024;
-    // k-steps are rounded up to `depth` per wavefront: 8 more for every split (most of them with one
+    // k-steps are rounded up to kQDepth per wavefront: 8 more for every split (most of them with one
     // worker, if the workspace is later used for fewer workers)
     int64_t splits = most_splits(out_wgs(n));
     if (splits > most_q_splits(m)) splits = most_q_splits(m);
@@ -1743,7 +1692,7 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
         float *base = reinterpret_cast<float *>(wsb + a256((size_t)KS * cb * pieces * 1024));
         for (int k = 0; k < K; ++k) sums.slabs.p[k] = dst.p[k] = base + (int64_t)k * S * slab;
     }
-    const dim3 grid((unsigned)ceil_div(n, 32 * q.JB), (unsigned)K, (unsigned)q.S);
+    const dim3 grid((unsigned)out_wgs(n), (unsigned)K, (unsigned)q.S);
     const int64_t ksteps = q.ksteps_per_wave * 4;
     {
     Timed timed(KID_PROJECT_Q, st);
@@ -1757,7 +1706,7 @@ static int project_q_ns(int64_t m, int64_t n, int r, int K, const PtrPack<const 
     switch (cb) {
         case 1:
             if constexpr (NS == 2) rc = project_q_ws_launch<NS, 1, 1>(grid, st, delta, frags, dst, m, n, r, ksteps, slab);
-            else hipLaunchKernelGGL((project_q_mfma_kernel<NS, 1, 4, 2>), grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab);
+            else hipLaunchKernelGGL(project_q_one_kernel, grid, dim3(kW), 0, st, delta, frags, dst, m, n, r, q.ksteps_per_wave, slab);
             break;
         case 2:
             rc = q.lone ? project_q_ws_launch<NS, 1, 2, true>(grid, st, delta, frags, dst, m, n, r, ksteps, slab)
@@ -1861,9 +1810,8 @@ struct RoundPlan {
 // (the workgroups drift apart), and the count does not matter at 28672.  At 4096 columns two ranges are
 // already too long: 4096 x 4096 r = 32 two workers 191, three 158, four 137; 11008 x 4096 467 | 366 | 355,
 // eight 338; 8192 x 4096 324 | 265 | 253.  (3840 and 4080 columns: two are as good as four.)
-static RoundPlan round_plan(int64_t m, int64_t n, int r) {
+static RoundPlan round_plan(int64_t m, int64_t n) {
     RoundPlan p;
-    (void)r;
     p.kc = 4;  // workers per launch: 4 x 2 basis blocks x 16 accumulator registers per wavefront
     const int64_t rows = ceil_div(m, 32), tiles = ceil_div(n, 256);
     const int64_t lo = tiles > 24 ? 4 : n == 4096 ? 3 : ceil_div(tiles, 8), hi = tiles < 32 ? tiles : 32;
@@ -1883,7 +1831,7 @@ static RoundPlan round_plan(int64_t m, int64_t n, int r) {
 // [basis fragments | P_hat_prev fragments | Q_bar_prev fragments | slabs (K x chunks x r x m)]
 size_t mfma_round_workspace_bytes(int mma, int64_t m, int64_t n, int r, int r_prev, int K) {
     const int ns = ns_of(mma);
-    const RoundPlan pl = round_plan(m, n, r);
+    const RoundPlan pl = round_plan(m, n);
     const size_t ksp = (size_t)(r_prev + 15) / 16;
     size_t total = a256((size_t)ceil_div(n, 64) * 4 * cb_of(r) * ns * 1024);
     total += a256((size_t)ceil_div(m, 32) * ksp * ns * 1024);
@@ -1926,7 +1874,7 @@ static int round_ns(int64_t m, int64_t n, int r, int r_prev, const float *p_hat,
                     const float *basis, const ReconEpilogue &ep_all, const PtrPack<float *> &factors,
                     void *workspace, PartialSums *partial, hipStream_t st) {
     const int cb = cb_of(r);
-    const RoundPlan pl = round_plan(m, n, r);
+    const RoundPlan pl = round_plan(m, n);
     const int ks = (r_prev + 15) / 16;
     const int64_t xbm = ceil_div(m, 32), xbn = ceil_div(n, 32);
     char *ws = reinterpret_cast<char *>(workspace);

@@ -20,7 +20,9 @@
 // Every kernel here takes a batch of factors (one descriptor per matrix, passed by value): the
 // work per matrix is small and latency-bound, so the matrices of a stage go through each step
 // together, one workgroup (or one slice of the grid) per matrix.  What a factor's result is made of
-// does not depend on the batch it comes in.
+// does not depend on the batch it comes in, but for the rounding of the norm behind the mark (added
+// up per wavefront, of which there are as many as the largest rank of the batch asks for): whether the
+// second round runs is the batch's where that norm is within rounding of kOneRoundNorm.
 #include "common.h"
 
 namespace dlcx {

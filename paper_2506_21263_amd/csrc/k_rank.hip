@@ -662,7 +662,7 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
         rmin = r < rmin ? r : rmin;
         rmid = rmid || (r > 32 && r <= kFusedRank);
     }
-    Timed timed(KID_JACOBI, st);
+    Timed timed(KID_EFF_RANK, st);
     const dim3 grid((unsigned)batch.n), threads(kTT);
     // each kernel leaves the factors of another rank class alone
     if (rmin <= 32) hipLaunchKernelGGL(tridiag_small_kernel<32>, grid, threads, 0, st, summed, tau);
