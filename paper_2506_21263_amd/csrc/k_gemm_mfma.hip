@@ -1397,13 +1397,14 @@ struct PPlan {
 // 200 three pieces 81 | 76.
 // One basis block and a workgroup for nearly every unit: the one-role kernel, unless the reduction is long
 // and 128 rows deal evenly (one for every unit, or nearly two).  one-role | two-role, us, r = 20, two
-// workers, two pieces: 15360 x 512 18.4 | 19.2, x 2048 54.0 | 55.8; 16384 x 512 18.9 | 20.5, x 4096 126 |
-// 131, x 8192 221 | 216; 16896 x 512 21.7 | 27.2, x 4096 129 | 165, x 8192 250 | 279; 24576 x 4096 152 | 185,
-// x 8192 315 | 344; 32768 x 1024 64 | 71, x 4096 213 | 234, x 8192 411 | 350; 65536 x 1024 117 | 132, x 4096
-// 410 | 428, x 8192 791 | 699.  Three pieces: 16384 x 1024 36.5 | 40.3, x 8192 221 | 210; 16896 x 8192 340 |
-// 374; 32768 x 1024 67 | 76, x 4096 244 | 261, x 8192 459 | 420.  Errors against 64 bits are within 2 %.
+// workers, two pieces: 14336 x 512 18.3 | 18.3; 15360 x 512 18.4 | 19.2, x 2048 54.0 | 55.8; 16384 x 512
+// 18.9 | 20.5, x 4096 126 | 131, x 8192 221 | 216; 16896 x 512 21.7 | 27.2, x 4096 129 | 165, x 8192 250 |
+// 279; 24576 x 4096 152 | 185, x 8192 315 | 344; 32768 x 1024 64 | 71, x 4096 213 | 234, x 8192 411 | 350;
+// 65536 x 1024 117 | 132, x 4096 410 | 428, x 8192 791 | 699.  Three pieces: 16384 x 1024 36.5 | 40.3, x
+// 8192 221 | 210; 16896 x 8192 340 | 374; 32768 x 1024 67 | 76, x 4096 244 | 261, x 8192 459 | 420; 7232 x
+// 704 r = 6 four workers 23.5 | 25.0.  Errors against 64 bits are within 2 %.
 constexpr int64_t kPLong = 4096;
-constexpr int64_t kPOneFrom = 240;  // workgroups of 128 rows
+constexpr int64_t kPOneFrom = 224;  // workgroups of 128 rows
 static PPlan p_plan(int64_t m, int64_t n, int r, int K) {
     PPlan p;
     const int64_t stages = ceil_div(n, 64);

@@ -219,7 +219,7 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 //          operands from LDS in accumulator layout, no transposition anywhere.
 // The wavefront that owns block (k + 1, k + 1) updates it first and factors it while the others
 // are still updating.  r^3 2/3 fp64 operations on one compute unit's matrix cores: r = 256 takes
-// 144 us and r = 32 13 us (row by row with the matrix in L2 / LDS: 2530 and 49 us).
+// 151 us and r = 32 13 us (row by row with the matrix in L2 / LDS: 2530 and 49 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;

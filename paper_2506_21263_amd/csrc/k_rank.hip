@@ -272,7 +272,7 @@ __device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 
 // SIMD (eight wavefronts that each formed v and beta for themselves took 1.45 us a step at r = 64,
 // this form 1.05), and the registers of a whole SIMD for one wavefront (136 tiles at r = 256 are 272
 // of its 512; with eight wavefronts spilled registers made 16 us a step,
-// now 3.0).  Seven factors at r = 256: 784 us, and the eigenvalues 54 us after it (one thread per
+// now 3.0).  Seven factors at r = 256: 783 us, and the eigenvalues 63 us after it (one thread per
 // eigenvalue and a division per term, after a reduction that walked S in L2: 4400 us together).
 template <int NT>
 __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
@@ -457,8 +457,8 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
 // Ranks up to kFusedRank: the whole matrix in one wavefront, row i in lane i, and no barrier until
 // the eigenvalues.  Every lane sums its own row of S v; v and w go round through LDS.  The columns
 // are renumbered as they go: step k reflects register column 0 and the update writes column j into
-// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 40 us (50 with four
-// wavefronts and three barriers a step, 246 at 1024 threads), r = 64: 93 us (510).
+// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 41 us (246 at 1024
+// threads, a division per term and bisection), r = 64: 98 us (510).
 template <int RC>  // columns held: 32 or 64
 __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, double tau) {
     __shared__ double sm[RC][RC + 1];

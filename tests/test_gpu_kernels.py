@@ -193,11 +193,11 @@ def test_projections_split_along_the_reduction(mma, m, n, r, K):
 
 @pytest.mark.parametrize("mma", [dlcx.MMA_F32, dlcx.MMA_BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("m,n,r,K", [
-    (2064, 16, 16, 16), (2064, 80, 31, 16), (1920, 208, 12, 16), (4000, 144, 32, 9),  # one-role: 64 rows
+    (2064, 16, 16, 16), (2064, 80, 31, 16), (1776, 208, 12, 16), (4000, 144, 32, 9),  # one-role: 64 rows
     (2048, 4112, 20, 16), (2048, 4096, 20, 16),  # one workgroup for every unit: two-role if long, one-role if not
 ])
 def test_project_p_of_one_basis_block_with_a_workgroup_per_unit(mma, m, n, r, K):
-    # Ranks up to 32 and at least 240 workgroups of 128 rows: rows that do not divide into 64, one and
+    # Ranks up to 32 and at least 224 workgroups of 128 rows: rows that do not divide into 64, one and
     # two stages of 64 columns, a stage that is partial, both sides of the rule between the kernels.
     g = torch.Generator(device=DEV)
     g.manual_seed(m + n)
