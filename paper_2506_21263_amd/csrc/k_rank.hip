@@ -14,7 +14,8 @@
 
 namespace dlcx {
 
-constexpr int kTT = 256;             // threads of the tridiagonal reduction
+constexpr int kTT = 256;             // threads of the reduction up to kFusedRank
+constexpr int kTri = 512;            // and above
 constexpr int kFusedRank = 64;       // ranks up to here finish in the same workgroup
 
 // the fp64 value of the lane that DPP control `kCtrl` pairs this lane with (inside rows of 16)
@@ -24,6 +25,12 @@ __device__ __forceinline__ double dpp(double x) {
     const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, 0xf, 0xf, true);
     const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, 0xf, 0xf, true);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// the value of lane X of the lane's row of 16
+template <int X>
+__device__ __forceinline__ double row_bcast(double x) {
+    const long long u = __double_as_longlong(x);
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, u, 0x150 + X, 0xf, 0xf, true));
 }
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor15 = 0x140;
 
@@ -259,41 +266,48 @@ __device__ __forceinline__ int live_of(const FactorItem &it) { return __builtin_
 __device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK + 8; }
 
 // Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
-// S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (ti, tj) holds element
-// (ti, tj) of every tile.  An off-diagonal tile serves S v twice, along its rows and its columns.
-// Per step k, with v and beta of row k in LDS:
-//   S v         row parts added over the 16 lanes of tj, column parts over ti: four rows of lanes
-//               in a wavefront and the four wavefronts (LDS)                        | barrier
-//   p = S v, v . p   one entry per thread                                           | barrier
-//   S -= v w^T + w v^T  with w = beta p - (beta^2 v.p / 2) v; the 16 lanes that hold row k + 1, in
-//               the first tile row still in use, turn it into the next v and beta   | barrier
-// Rows that are done have zeros in v and w; tile rows that are done are skipped.  What counts is
-// the number of instructions: four wavefronts, one per SIMD, so that nothing is done twice on a
-// SIMD (eight wavefronts that each formed v and beta for themselves took 1.45 us a step at r = 64,
-// this form 1.05), and the registers of a whole SIMD for one wavefront (136 tiles at r = 256 are 272
-// of its 512; with eight wavefronts spilled registers made 16 us a step,
-// now 3.0).  Seven factors at r = 256: 783 us, and the eigenvalues 63 us after it (one thread per
-// eigenvalue and a division per term, after a reduction that walked S in L2: 4400 us together).
+// S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (h, ti, tj) holds element
+// (ti, tj) of the tiles whose column y has parity h.  An off-diagonal tile serves S v twice, along its
+// rows and its columns.  Step k, with v of row k in LDS:
+//   S v      row parts added over the 16 lanes of tj, column parts over ti: four rows of lanes in a
+//            wavefront, four wavefronts and two parities in LDS                              | barrier
+//   p = S v  the parts added up, two lanes per entry                                         | barrier
+//   S -= v w^T + w v^T  with w = beta p - (beta^2 v.p / 2) v, formed where it is used; before its own
+//            share one wavefront works out the next v and beta from row k + 1, which the update before
+//            has left in LDS                                                                 | barrier
+// Rows that are done have zeros in v and w; groups of four tile rows that are done are skipped (a branch for
+// every row took as long as the work it saved).
+// Bound by the instructions of a step, two wavefronts to a SIMD, and by the chain of the reflection, 255
+// steps in a row.  Eight wavefronts of 256 registers, 144 of them tiles at r = 256: with one wavefront per
+// SIMD half of the tiles sat in the accumulator file, which vector instructions cannot name, two moves for
+// every use.  v and w along the rows come from one lane of each row of 16 (row_bcast): read from LDS row by
+// row they kept the LDS busy for a third of a step.  Seven factors at r = 256: 545 us, 2.1 us a step, of which
+// S v 0.75, sums and barriers 0.45, the reflection 0.5 and the update behind it 0.4 (one wavefront per SIMD:
+// 783 us; whole tile rows dealt to the wavefronts, which need fewer sums across lanes but differ in work and
+// branch at every tile: 725 us).
 template <int NT>
-__global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
-    constexpr int RS = NT <= 8 ? 8 : 16;
-    constexpr int CG = NT / 4;              // column sums per lane after four rows of lanes are added
+__global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
     constexpr int R = 16 * NT;
-    __shared__ double vrow[2][R];           // v of row k, zeros up to the diagonal
-    __shared__ double betas[2];             // 0: the row is tridiagonal already
-    __shared__ double rowpart[R];
+    constexpr int N = NT / 2;   // tile columns of one parity
+    constexpr int Q = R / 64;   // entries per lane where one wavefront has a whole row
+    constexpr int W = kTri / 64;
+    __shared__ double vbuf[2][R + 1];   // v of even and odd steps, zeros up to the diagonal
+    __shared__ double betas[2];         // 0: the row is tridiagonal already
+    __shared__ double arow[2][R + 1];   // row k + 1 of S before the update of step k, from the diagonal on
+    __shared__ double pbuf[R + 1];
+    __shared__ double rowpart[2][R];
     __shared__ double colpart[4][R];
-    __shared__ double pbuf[R];
-    __shared__ double red[4];
-    __shared__ double2 tri[R];              // d_k and the off-diagonal element before it
-    __shared__ int order[R];                // the rows of S that are not zero
-    __shared__ int counts[4];
+    __shared__ double2 tri[R];          // d_k and the off-diagonal element before it
+    __shared__ int order[R];            // the rows of S that are not zero
+    __shared__ int counts[W];
     const FactorItem it = batch.it[blockIdx.x];
     const int nchunks = it.nchunks;
     const double *__restrict__ part = it.part;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tj = lane & 15, g = lane >> 4, ti = wave * 4 + g;
+    const int par = wave & 1, quarter = wave >> 1;  // parity h; ti / 4
+    const int tj = lane & 15, g = lane >> 4, ti = quarter * 4 + g;
+    const int row_lane = tj < NT ? tj : 0;
     const int64_t pitch = it.r, rr = pitch * pitch;
     if (it.r <= kFusedRank) return;
 
@@ -308,138 +322,168 @@ __global__ __launch_bounds__(kTT, 1) void tridiag_kernel(FactorBatch batch) {
     }
     const uint64_t mask = __ballot(on);
     const bool wave_odd = __ballot(odd) != 0;  // a NaN or an infinity in the factor: no rows, r' = 0
-    if (lane == 0) counts[wave] = wave_odd ? -kTT : __popcll(mask);
+    if (lane == 0) counts[wave] = wave_odd ? -kTri : __popcll(mask);
+    if (tid < 2) {
+        vbuf[tid][R] = 0.0;
+        arow[tid][R] = 0.0;
+        pbuf[R] = 0.0;
+    }
     __syncthreads();
-    int before = 0;
+    int before = 0, r = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) before += w < wave ? counts[w] : 0;
+    for (int q = 0; q < W; ++q) {
+        before += q < wave ? counts[q] : 0;
+        r += counts[q];
+    }
     if (on && before >= 0) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
-    int r = __builtin_amdgcn_readfirstlane((counts[0] + counts[1]) + (counts[2] + counts[3]));
-    r = r < 0 ? 0 : r;
+    r = __builtin_amdgcn_readfirstlane(r < 0 ? 0 : r);
     __syncthreads();
 
-    double t[NT][NT];  // t[x][y], x <= y
+    // t[x][i]: tile (x, 2 i + h).  Where x is odd, i starts with the diagonal tile of h = 1; beside it
+    // h = 0 has the tile left of the diagonal, which takes no part in S v.
+    double t[NT][N];
 #pragma unroll
-    for (int x = 0; x < NT; ++x)
+    for (int x = 0; x < NT; ++x) {
+        const int a = 16 * x + ti, oa = a < r ? order[a] : 0;
 #pragma unroll
-        for (int y = x; y < NT; ++y) {
-            const int a = 16 * x + ti, b = 16 * y + tj;
-            double s = 0.0;
-            if (a < r && b < r) {  // order[] rises
-                const double *src = part + order[a < b ? a : b] * pitch + order[a < b ? b : a];
-                for (int c = 0; c < nchunks; ++c) s += src[c * rr];
-            }
-            t[x][y] = s;
+        for (int i = x / 2; i < N; ++i) {
+            const int b = 16 * (2 * i + par) + tj, ob = b < r ? order[b] : 0;
+            const bool in = a < r && b < r;  // order[] rises
+            const double *src = part + (in ? (oa < ob ? oa * pitch + ob : ob * pitch + oa) : 0);
+            double s = src[0];
+            for (int c = 1; c < nchunks; ++c) s += src[c * rr];
+            t[x][i] = in ? s : 0.0;
         }
-    // Row `row`, whose tile row is x: its v, beta and elements of the result, by the lanes that
-    // hold it.
-    auto publish = [&](auto xc, int row, int buf) {
+    }
+    // Row `row`, whose tile row is x, from its tile on.
+    auto keep_row = [&](auto xc, int row) {
         constexpr int x = decltype(xc)::value;
-        if (((row & 15) >> 2) != wave || g != (row & 3)) return;
-        const int d = row - 16 * x;  // the diagonal in tile column x
-        double *dst = &vrow[buf][tj];
-        double tail = 0.0;           // beyond the first element right of the diagonal
-        if (tj > d + 1) tail = t[x][x] * t[x][x];
-        double x0 = t[x][x];
-        int at = d + 1;
-        if constexpr (x + 1 < NT) {
-            const double e = t[x][x + 1];
-            if (d < 15 || tj > 0) tail = fma(e, e, tail);
-            if (d == 15) {
-                x0 = e;
-                at = 0;
-            }
+        if (((row & 15) >> 2) != quarter || g != (row & 3)) return;
+        double *dst = &arow[row & 1][tj];
 #pragma unroll
-            for (int y = x + 2; y < NT; ++y) tail = fma(t[x][y], t[x][y], tail);
+        for (int i = x / 2; i < N; ++i)
+            if (i > x / 2 || x % 2 == 0 || par == 1) dst[16 * (2 * i + par)] = t[x][i];
+    };
+    // The reflection of row c, by one wavefront, R / 64 entries per lane (lv, lw: v and w there; vc, v1, wc,
+    // w1: at c and c + 1; all zero for the first).  c + 1 may be R: nothing is right of the last row.
+    auto reflect = [&](int c, const double (&lv)[Q], const double (&lw)[Q], double vc,
+                       double wc, double v1, double w1) {
+        const double *ar = arow[c & 1];
+        double a[Q], tail = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const double x = fma(-lv[q], wc, fma(-lw[q], vc, ar[lane + 64 * q]));
+            a[q] = lane + 64 * q > c + 1 ? x : 0.0;  // arow has nothing left of the diagonal tile
+            tail = fma(a[q], a[q], tail);
         }
-        tail += dpp<kXor1>(tail);
-        tail += dpp<kXor2>(tail);
-        tail += dpp<kXor7>(tail);
-        tail += dpp<kXor15>(tail);
-        const uint64_t u = (uint64_t)__double_as_longlong(x0);
-        const int from = ((row & 3) * 16 + (at & 15)) * 4;
-        x0 = from_halves((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)u),
-                         (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(u >> 32)));
-        const Reflection f = reflection(x0, tail);
-        const double v0 = x0 - f.alpha;
-        if (tj == d) tri[row].x = t[x][x];
-        if (tj == 0) {
-            if (row + 1 < R) tri[row + 1].y = f.alpha;
-            betas[buf] = f.beta;
+        const double x0 = fma(-v1, wc, fma(-w1, vc, ar[c + 1])), d = fma(-vc, wc, fma(-wc, vc, ar[c]));
+        const Reflection f = reflection(x0, wave_sum(tail));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int e = lane + 64 * q;
+            const double y = e == c + 1 ? x0 - f.alpha : a[q];
+            vbuf[c & 1][e] = f.beta == 0.0 ? 0.0 : y;
         }
-#pragma unroll
-        for (int y2 = 0; y2 < x; ++y2) dst[16 * y2] = 0.0;
-        dst[16 * x] = tj > d + 1 ? t[x][x] : tj == d + 1 ? v0 : 0.0;
-        if constexpr (x + 1 < NT) {
-            dst[16 * (x + 1)] = d == 15 && tj == 0 ? v0 : t[x][x + 1];
-#pragma unroll
-            for (int y2 = x + 2; y2 < NT; ++y2) dst[16 * y2] = t[x][y2];
+        if (lane == 0) {
+            betas[c & 1] = f.beta;
+            tri[c].x = d;
+            if (c + 1 < R) tri[c + 1].y = f.alpha;
         }
     };
-    publish(std::integral_constant<int, 0>(), 0, 0);
+    keep_row(std::integral_constant<int, 0>(), 0);
+    keep_row(std::integral_constant<int, 0>(), 1);
+    __syncthreads();
+    if (wave == 0) {
+        const double zero[Q] = {};
+        reflect(0, zero, zero, 0.0, 0.0, 0.0, 0.0);
+    }
     __syncthreads();
     for (int k = 0; k + 1 < r; ++k) {
-        const int cur = k & 1;
-        const double beta = betas[cur];  // 0, with v = 0: nothing happens to S
-        const int live = (k + 1) >> 4;   // tile rows and columns before it are done
-        double cv[NT], rv[NT];
+        const double *v = vbuf[k & 1];
+        // v along the columns of this thread's tiles and, from lane x of its row, along their rows
+        double cv[N];
 #pragma unroll
-        for (int y = 0; y < NT; ++y) {
-            cv[y] = vrow[cur][16 * y + tj];
-            rv[y] = vrow[cur][16 * y + ti];
+        for (int i = 0; i < N; ++i) cv[i] = v[16 * (2 * i + par) + tj];
+        const double rv = v[16 * row_lane + ti];
+        {
+            const int live = (k + 1) >> 4;  // tile rows and columns before it are done
+            double cp[(N + 3) / 4 * 4] = {};
+            unrolled<NT / 4>([&](auto bc) {
+                constexpr int x0 = 4 * decltype(bc)::value;
+                if (x0 + 3 < live) return;
+                double rp[4];
+                unrolled<4>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value, x = x0 + u, i0 = x / 2;
+                    const double rx = row_bcast<x>(rv);
+                    // the first tile: on the diagonal (row part only) for h = x % 2; none for x odd and h = 0
+                    rp[u] = t[x][i0] * (x % 2 == 0 || par == 1 ? cv[i0] : 0.0);
+                    if (x % 2 == 0) cp[i0] = fma(t[x][i0], par == 1 ? rx : 0.0, cp[i0]);
+#pragma unroll
+                    for (int i = i0 + 1; i < N; ++i) {
+                        rp[u] = fma(t[x][i], cv[i], rp[u]);
+                        cp[i] = fma(t[x][i], rx, cp[i]);
+                    }
+                });
+                const double rs = row_sums<4>(rp, tj);
+                if ((tj & 3) == 0) rowpart[par][16 * (x0 + (tj >> 2)) + ti] = rs;
+            });
+#pragma unroll
+            for (int i = 0; i < N; i += 4) {
+                if (2 * i + 7 < live) continue;
+                const double cs = add_rows(add_halves(cp[i], cp[i + 2]), add_halves(cp[i + 1], cp[i + 3]));
+                if (i + g < N) colpart[quarter][16 * (2 * (i + g) + par) + tj] = cs;
+            }
+        }
+        __syncthreads();
+        if (wave < NT / 2) {
+            const int e = 32 * wave + (lane & 31), hh = lane >> 5;
+            const double s = (colpart[2 * hh][e] + colpart[2 * hh + 1][e]) + rowpart[hh][e];
+            const double p = add_halves(s, s);
+            if (hh == 0) pbuf[e] = e > k ? p : 0.0;  // rows that are done
+        }
+        __syncthreads();
+        const double beta = betas[k & 1];
+        double kk, cw[N], rw = pbuf[16 * row_lane + ti];
+#pragma unroll
+        for (int i = 0; i < N; ++i) cw[i] = pbuf[16 * (2 * i + par) + tj];
+        {
+            double lv[Q], lp[Q], dot = 0.0;
+            const double vc = v[k + 1], pc = pbuf[k + 1], v1 = v[k + 2], p1 = pbuf[k + 2];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                lv[q] = v[lane + 64 * q];
+                lp[q] = pbuf[lane + 64 * q];
+                dot = fma(lp[q], lv[q], dot);
+            }
+            kk = 0.5 * beta * (beta * wave_sum(dot));  // (beta^2 may overflow)
+            if (wave == 0) {  // the others wait for it: ahead of the wavefront beside it on the SIMD
+                __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) lp[q] = fma(beta, lp[q], -kk * lv[q]);
+                reflect(k + 1, lv, lp, vc, fma(beta, pc, -kk * vc), v1, fma(beta, p1, -kk * v1));
+            }
         }
         {
-            double cp[NT], rp[RS];
+            const int live = (k + 2) >> 4;
 #pragma unroll
-            for (int y = 0; y < NT; ++y) cp[y] = 0.0;
+            for (int i = 0; i < N; ++i) cw[i] = fma(beta, cw[i], -kk * cv[i]);
+            rw = fma(beta, rw, -kk * rv);
+            unrolled<NT / 4>([&](auto bc) {
+                constexpr int x0 = 4 * decltype(bc)::value;
+                if (x0 + 3 < live) return;
+                unrolled<4>([&](auto uc) {
+                    constexpr int x = x0 + decltype(uc)::value;
+                    const double rx = row_bcast<x>(rv), wx = row_bcast<x>(rw);
 #pragma unroll
-            for (int x = 0; x < RS; ++x) rp[x] = 0.0;
-#pragma unroll
-            for (int x = 0; x < NT; ++x)
-                if (x >= live) {
-                    double s = t[x][x] * cv[x];
-#pragma unroll
-                    for (int y = x + 1; y < NT; ++y) {
-                        s = fma(t[x][y], cv[y], s);
-                        cp[y] = fma(t[x][y], rv[x], cp[y]);
-                    }
-                    rp[x] = s;
-                }
-            double cs[NT / 2];
-#pragma unroll
-            for (int y = 0; y < NT / 2; ++y) cs[y] = add_halves(cp[y], cp[y + NT / 2]);
-#pragma unroll
-            for (int y = 0; y < CG; ++y)
-                colpart[wave][16 * (CG * g + y) + tj] = add_rows(cs[y], cs[y + CG]);
-            const double rsum = row_sums<RS>(rp, tj);
-            if (tj % (16 / RS) == 0 && tj / (16 / RS) < NT) rowpart[16 * (tj / (16 / RS)) + ti] = rsum;
+                    for (int i = x / 2; i < N; ++i) t[x][i] = fma(-rx, cw[i], fma(-wx, cv[i], t[x][i]));
+                });
+                unrolled<4>([&](auto uc) {
+                    if (x0 + decltype(uc)::value == live)
+                        keep_row(std::integral_constant<int, x0 + decltype(uc)::value>(), k + 2);
+                });
+            });
         }
-        __syncthreads();
-        if (tid < R) {
-            double p = rowpart[tid] + ((colpart[0][tid] + colpart[1][tid]) + (colpart[2][tid] + colpart[3][tid]));
-            if (tid <= k) p = 0.0;  // rows that are done
-            pbuf[tid] = p;
-            const double dot = wave_sum(p * vrow[cur][tid]);
-            if (lane == 0) red[wave] = dot;
-        }
-        __syncthreads();
-        double vp = red[0];
-#pragma unroll
-        for (int w = 1; w < R / 64; ++w) vp += red[w];
-        const double kk = 0.5 * beta * (beta * vp);  // (beta^2 may overflow)
-        double cw[NT], rw[NT];
-#pragma unroll
-        for (int y = 0; y < NT; ++y) {
-            cw[y] = fma(beta, pbuf[16 * y + tj], -kk * cv[y]);
-            rw[y] = fma(beta, pbuf[16 * y + ti], -kk * rv[y]);
-        }
-        unrolled<NT>([&](auto xc) {
-            constexpr int x = decltype(xc)::value;
-            if (x < live) return;
-#pragma unroll
-            for (int y = x; y < NT; ++y) t[x][y] = fma(-rv[x], cw[y], fma(-rw[x], cv[y], t[x][y]));
-            if (x == live) publish(xc, k + 1, cur ^ 1);
-        });
+        __builtin_amdgcn_s_setprio(0);
         __syncthreads();
     }
     if (wave == 0) {
@@ -669,11 +713,11 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
     if (rmid) hipLaunchKernelGGL(tridiag_small_kernel<64>, grid, threads, 0, st, summed, tau);
     if (rmax > kFusedRank) {
         if (rmax <= 128)
-            hipLaunchKernelGGL(tridiag_kernel<8>, grid, threads, 0, st, summed);
+            hipLaunchKernelGGL(tridiag_kernel<8>, grid, dim3(kTri), 0, st, summed);
         else if (rmax <= 192)
-            hipLaunchKernelGGL(tridiag_kernel<12>, grid, threads, 0, st, summed);
+            hipLaunchKernelGGL(tridiag_kernel<12>, grid, dim3(kTri), 0, st, summed);
         else
-            hipLaunchKernelGGL(tridiag_kernel<16>, grid, threads, 0, st, summed);
+            hipLaunchKernelGGL(tridiag_kernel<16>, grid, dim3(kTri), 0, st, summed);
         hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
                            dim3(256), 0, st, summed);
         hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
