@@ -23,6 +23,8 @@
 // does not depend on the batch it comes in, but for the rounding of the norm behind the mark (added
 // up per wavefront, of which there are as many as the largest rank of the batch asks for): whether the
 // second round runs is the batch's where that norm is within rounding of kOneRoundNorm.
+#include <type_traits>
+
 #include "common.h"
 
 namespace dlcx {
@@ -47,6 +49,30 @@ __device__ __forceinline__ bool second_round_idle(const FactorItem &it, int roun
     return round == 1 && it.g[0] == kDone;
 }
 
+// Work of a batch along one grid dimension: item i has the places first[i] .. first[i + 1] - 1.  (A grid as
+// long as the longest factor for every item: of a 100B-class layer's seven, one of 28672 rows beside six of
+// 8192, three workgroups in five had nothing to do but took their turn, and in apply_w 64 KB of LDS.)
+struct Places {
+    int first[kMaxBatch + 1];
+};
+// The item that `place` belongs to, by every wavefront for itself; `place` becomes the place inside it.
+__device__ __forceinline__ int item_of(const Places &at, int n, int &place) {
+    const int lane = threadIdx.x & 63;
+    static_assert(kMaxBatch == 64, "one lane per item");
+    const uint64_t m = __ballot(lane < n && at.first[lane < n ? lane : 0] <= place);
+    const int i = __builtin_amdgcn_readfirstlane(__popcll(m) - 1);
+    place -= at.first[i];
+    return i;
+}
+// count(item) places for every item
+template <typename F>
+static Places places_of(const FactorBatch &batch, F &&count) {
+    Places at;
+    at.first[0] = 0;
+    for (int i = 0; i < kMaxBatch; ++i) at.first[i + 1] = at.first[i] + (i < batch.n ? (int)count(batch.it[i]) : 0);
+    return at;
+}
+
 int gram_chunks(int64_t L) { return (int)ceil_div(L, kGramChunk); }
 
 // part[chunk][a][b] = sum_{i in chunk} f[a][i] * f[b][i] for the tile (ta, tb) of 16 NB x 16 NB
@@ -58,18 +84,23 @@ int gram_chunks(int64_t L) { return (int)ceil_div(L, kGramChunk); }
 // Bound by the fp64 matrix cores at high rank: seven factors of a 100B-class layer at r = 256
 // (77824 rows, 5.1 GFLOP over the upper triangle) take 117 us; through LDS tiles and vector
 // fp64 FMAs it was 200 us, and 40 us for a single 512 x 8 factor (64 barriers in a row), now 5.
+// The tiles of a chunk are consecutive workgroups of one XCD (every eighth workgroup of the grid), eight
+// chunks side by side: a chunk, 512 KB at r = 256, is read from memory once and 36 times from that XCD's L2.
 template <int NB>
-__global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch, int round) {
+__global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch, Places at, int tiles, int round) {
     __shared__ double red[4][NB * NB * 4][64];
-    const FactorItem it = batch.it[blockIdx.z];
-    const int r = it.r;
+    const int slot = blockIdx.x >> 3;
+    int group = slot / tiles;  // of eight chunks
+    int t = slot - group * tiles;
+    const FactorItem it = batch.it[item_of(at, batch.n, group)];
+    const int r = it.r, chunk = 8 * group + (blockIdx.x & 7);
     const int nt = (r + 16 * NB - 1) / (16 * NB);
-    if ((int)blockIdx.x >= it.nchunks || (int)blockIdx.y >= nt * (nt + 1) / 2) return;
+    if (chunk >= it.nchunks || t >= nt * (nt + 1) / 2) return;
     if (second_round_idle(it, round)) return;
     const float *__restrict__ f = it.f;
     const int64_t L = it.L;
     // tile index -> (ta, tb) with ta <= tb
-    int t = blockIdx.y, ta = 0;
+    int ta = 0;
     while (t >= nt - ta) {
         t -= nt - ta;
         ++ta;
@@ -85,7 +116,7 @@ __global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch, in
         pb[x] = f + (int64_t)(b < r ? b : r - 1) * L + 4 * q;
     }
     constexpr int kQuarter = kGramChunk / 4;
-    const int64_t begin = (int64_t)blockIdx.x * kGramChunk + wave * kQuarter;
+    const int64_t begin = (int64_t)chunk * kGramChunk + wave * kQuarter;
     int64_t end = begin + kQuarter;
     if (end > L) end = L;  // L is a multiple of 16: a step of 16 is whole or not there
     f64x4_t acc[NB][NB];
@@ -93,40 +124,43 @@ __global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch, in
     for (int x = 0; x < NB; ++x)
 #pragma unroll
         for (int y = 0; y < NB; ++y) acc[x][y] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-    if (begin < end) {
-        float4 va[NB], vb[NB];
-#pragma unroll
-        for (int x = 0; x < NB; ++x) {
-            va[x] = *reinterpret_cast<const float4 *>(pa[x] + begin);
-            vb[x] = *reinterpret_cast<const float4 *>(pb[x] + begin);
-        }
-        for (int64_t i = begin; i < end; i += 16) {
-            const int64_t nx = i + 16 < end ? i + 16 : begin;
-            float4 na[NB], nb[NB];
+    auto sums = [&](auto diagonal) {
+        if (begin >= end) return;
+        float4 va[2][NB], vb[2][NB];
+        auto load = [&](int set, int64_t i) {
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
-                na[x] = *reinterpret_cast<const float4 *>(pa[x] + nx);
-                nb[x] = *reinterpret_cast<const float4 *>(pb[x] + nx);
+                va[set][x] = *reinterpret_cast<const float4 *>(pa[x] + i);
+                vb[set][x] = *reinterpret_cast<const float4 *>(pb[x] + i);
             }
+            __builtin_amdgcn_sched_barrier(0);  // the requests go out before the products they do not belong to
+        };
+        auto multiply = [&](int set) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int x = 0; x < NB; ++x)
 #pragma unroll
                     for (int y = 0; y < NB; ++y) {
-                        if (x > y && ta == tb) continue;  // below the diagonal
-                        const float fa = s == 0 ? va[x].x : s == 1 ? va[x].y : s == 2 ? va[x].z : va[x].w;
-                        const float fb = s == 0 ? vb[y].x : s == 1 ? vb[y].y : s == 2 ? vb[y].z : vb[y].w;
+                        if (diagonal && x > y) continue;  // below the diagonal
+                        const float4 &a = va[set][x], &b = vb[set][y];
+                        const float fa = s == 0 ? a.x : s == 1 ? a.y : s == 2 ? a.z : a.w;
+                        const float fb = s == 0 ? b.x : s == 1 ? b.y : s == 2 ? b.z : b.w;
                         acc[x][y] = mfma64((double)fa, (double)fb, acc[x][y]);
                     }
-            }
-#pragma unroll
-            for (int x = 0; x < NB; ++x) {
-                va[x] = na[x];
-                vb[x] = nb[x];
-            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        load(0, begin);
+        for (int64_t i = begin; i < end; i += 32) {
+            load(1, i + 16 < end ? i + 16 : begin);
+            multiply(0);
+            if (i + 16 >= end) break;
+            load(0, i + 32 < end ? i + 32 : begin);
+            multiply(1);
         }
-    }
+    };
+    if (ta == tb) sums(std::true_type());  // two loops: one with a branch in it copied its accumulators about
+    else sums(std::false_type());
 #pragma unroll
     for (int x = 0; x < NB; ++x)
 #pragma unroll
@@ -134,7 +168,7 @@ __global__ __launch_bounds__(kGT) void gram_partial_kernel(FactorBatch batch, in
 #pragma unroll
             for (int v = 0; v < 4; ++v) red[wave][(x * NB + y) * 4 + v][lane] = acc[x][y][v];
     __syncthreads();
-    double *dst = it.part + (int64_t)blockIdx.x * r * r;
+    double *dst = it.part + (int64_t)chunk * r * r;
 #pragma unroll
     for (int u = 0; u < NB * NB; ++u) {  // a quarter of the tile each, quarters of the chunk in order
         const int e = wave * NB * NB + u;
@@ -189,12 +223,14 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
     }
     const int nb = max_r <= 16 ? 1 : 2;  // 16 x 16 blocks per side of a tile
     const int nt = (max_r + 16 * nb - 1) / (16 * nb);
-    const dim3 grid((unsigned)max_chunks, (unsigned)(nt * (nt + 1) / 2), (unsigned)batch.n);
+    const int tiles = nt * (nt + 1) / 2;
+    const Places at = places_of(batch, [](const FactorItem &it) { return ceil_div(it.nchunks, 8); });
+    const dim3 grid((unsigned)at.first[batch.n] * 8u * (unsigned)tiles);
     Timed timed(KID_GRAM, st);
     if (nb == 1)
-        hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, round);
+        hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, at, tiles, round);
     else
-        hipLaunchKernelGGL(gram_partial_kernel<2>, grid, dim3(kGT), 0, st, batch, round);
+        hipLaunchKernelGGL(gram_partial_kernel<2>, grid, dim3(kGT), 0, st, batch, at, tiles, round);
     int rc = check_launch("gram_partials");
     if (rc != DLCX_OK) return rc;
     *reduced = batch;
@@ -207,23 +243,26 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 
 // ---------------------------------------------------------------------------------------------
 // W = R^-1 of the scaled Gram matrix, one workgroup per matrix, the matrix in registers.
-// G is cut into 16 x 16 blocks; only the blocks (I, J), J <= I, exist, one accumulator each, dealt
-// to the wavefronts.  Eliminating [G | 1] block row by block row turns G into R and 1 into
-// R^-T = L^-1 (G = L L^T); a block (I, J) holds the rest of G (transposed: rows J, columns I)
-// until step J, and from then on block (I, J) of L^-1 under construction, which is final after
-// step I.  Step k:
-//   V = L_kk^-1 of the block (k, k), by one wavefront (factor_block);
+// G is cut into 16 x 16 blocks; only the blocks (I, J), J <= I, exist, one accumulator each: the last
+// wavefront holds those on the diagonal, the others are dealt out.  Eliminating [G | 1] block row by block row
+// turns G into R and 1 into R^-T = L^-1 (G = L L^T); a block (I, J) holds the rest of G (transposed: rows J,
+// columns I) until step J, and from then on block (I, J) of L^-1 under construction, which is final after
+// step I.  Step k, with V = L_kk^-1 of the block (k, k) from the step before:
 //   panel: block (I, k) -> V G_kI =: X_I (a block of R), block (k, J) -> V (k, J) =: X_J (final);
 //          both products take V as A operand and the accumulator as it is as B operand;
 //   every block with I > k:  J > k: -= X_J^T X_I ;  J <= k: -= X_I^T X_J  (X_k = V),
-//          operands from LDS in accumulator layout, no transposition anywhere.
-// The wavefront that owns block (k + 1, k + 1) updates it first and factors it while the others
-// are still updating.  r^3 2/3 fp64 operations on one compute unit's matrix cores: r = 256 takes
-// 151 us and r = 32 13 us (row by row with the matrix in L2 / LDS: 2530 and 49 us).
+//          operands from LDS in accumulator layout, no transposition anywhere;
+//   the diagonal's wavefront updates (k + 1, k + 1) first and factors it while the others are updating.
+// r^3 2/3 fp64 operations on one compute unit's matrix cores, 36 us at r = 256 at their rate.  A wavefront runs
+// through its blocks by a mask of those that a step concerns, and the loads and stores around the steps are a
+// handful of instructions a block: in the form before, which tested block indices and bounds one by one, the
+// kernel was 70 KB of instructions that came from memory once per launch (22 us to load the matrix), and the
+// wavefront that factored had updates of its own to do after it, for which all others waited.  r = 256 takes
+// CHOLUS us and r = 32 CHOL32 us (151 and 10 before that; row by row with the matrix in L2 / LDS: 2530 and 49 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;
-constexpr int kCT = 512;  // at most 8 wavefronts: 17 blocks each at r = 256, 136 of 256 registers
+constexpr int kCT = 512;  // at most 8 wavefronts: 18 blocks each at r = 256, 144 of 256 registers
 
 __device__ __forceinline__ double read_lane(double x, int lane) {
     const uint64_t u = (uint64_t)__double_as_longlong(x);
@@ -232,46 +271,53 @@ __device__ __forceinline__ double read_lane(double x, int lane) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// LDS written and read by the same wavefront: its instructions execute in order, so only the
-// compiler has to be kept from reordering.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// V = L^-1 of a symmetric 16 x 16 block G = L L^T (pitch kVPitch) by one wavefront: lane c < 16
-// holds column c of G, lane 16 + c column c of the unit matrix, and the elimination of row j is a
-// product of every column with a scalar read from lane i of row j (G is symmetric).  The square
-// roots are left to the end, so the chain from pivot to pivot is a reciprocal and two FMAs.
-// Dead pivots (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.  Returns
-// whether one of the first `live` pivots was dead.
-__device__ __forceinline__ bool factor_block(const double *g, double *v, int lane, int live) {
-    double c[16];
+// V = L^-1 of a symmetric 16 x 16 block G = L L^T by one wavefront, both as accumulators: register v of
+// lane (g, col) = (lane / 16, lane % 16) is element (4 v + g, col).  Eliminating row j from [G | 1] is a product
+// with one row of the operands in use, -(row j) / pivot as A (G is symmetric) and row j as B, and row j of an
+// accumulator lies where both want row j % 4 of their four: no lane needs another's value but for the pivots.
+// The pivot after is worked out beside the product that makes its row, by the same operations.  The square roots
+// are left to the end.  Dead pivots (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.
+// Writes V as the A operand of the panel reads it (pitch kVPitch) and as an accumulator; returns whether one
+// of the first `live` pivots was dead.
+__device__ __forceinline__ bool factor_block(f64x4_t t, double *va, double (*vb)[64], int lane, int live) {
+    const int g = lane >> 4, col = lane & 15;
+    f64x4_t u, own;  // the right half; the pivot of each row
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-        c[i] = lane < 16 ? g[i * kVPitch + lane] : (lane == 16 + i ? 1.0 : 0.0);
-    double own = 0.0;  // lane i < 16: pivot i
+    for (int q = 0; q < 4; ++q) u[q] = 4 * q + g == col ? 1.0 : 0.0;
+    double p = read_lane(t[0], 0);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        const double p = read_lane(c[j], j);
-        if (lane == j) own = p;
-        const bool dead = !(p > 1e-12);
+        const int q = j / 4, q1 = (j + 1) / 4;
+        const bool mine = g == j % 4, dead = !(p > 1e-12);
+        if (mine) own[q] = p;
         double rp = __builtin_amdgcn_rcp(p);
         rp = fma(fma(-p, rp, 1.0), rp, rp);
         rp = fma(fma(-p, rp, 1.0), rp, rp);
-        const double t = dead ? 0.0 : c[j] * rp;
-#pragma unroll
-        for (int i = j + 1; i < 16; ++i) c[i] = fma(-read_lane(c[j], i), t, c[i]);
+        if (j < 15) {
+            const double x = read_lane(t[q], 16 * (j % 4) + j + 1);
+            const double d = read_lane(t[q1], 16 * ((j + 1) % 4) + j + 1);
+            p = dead ? d : fma(-x * rp, x, d);
+        }
+        const double row = mine ? t[q] : 0.0;
+        const double a = dead || col <= j ? 0.0 : -row * rp;  // rows that are done keep what they have
+        if (j < 15) {
+            t = mfma64(a, row, t);
+            u = mfma64(a, mine ? u[q] : 0.0, u);
+        }
     }
-    const bool dead = !(own > 1e-12);
-    const double rs = dead ? 0.0 : 1.0 / sqrt(own);
+    bool any = false;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const double x = c[i] * read_lane(rs, i);
-        if (lane >= 16 && lane < 32) v[i * kVPitch + lane - 16] = x;
+    for (int q = 0; q < 4; ++q) {
+        const bool dead = !(own[q] > 1e-12);
+        double y = __builtin_amdgcn_rsq(own[q]);
+        y = fma(0.5 * y, fma(-own[q] * y, y, 1.0), y);
+        y = fma(0.5 * y, fma(-own[q] * y, y, 1.0), y);
+        const double x = dead ? 0.0 : u[q] * y;
+        va[(4 * q + g) * kVPitch + col] = x;
+        vb[q][lane] = x;
+        any = any || (dead && 4 * q + g < live);
     }
-    return __ballot(dead && lane < 16 && lane < live) != 0;
+    return __ballot(any) != 0;
 }
 
 template <int SLOTS>
@@ -283,45 +329,72 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     double *__restrict__ w = it.w;
     __shared__ double dscale[DLCX_MAX_RANK];  // 1 / column norm (0 for a zero column)
     __shared__ double panel[kMaxBlocks][4][64];
-    __shared__ double vbuf[2][16 * kVPitch];
-    __shared__ double diag[16 * kVPitch];
+    __shared__ double diag[kMaxBlocks][4][64];  // the blocks on the diagonal
+    __shared__ double va[2][16 * kVPitch];    // V of even and odd steps, as A operand ..
+    __shared__ double vb[2][4][64];           // .. and as accumulator
     __shared__ double red[kCT / 64];
     __shared__ int any_dead;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
     const int g = lane >> 4, col = lane & 15;
-    const int nb = (r + 15) >> 4, nblk = nb * (nb + 1) / 2;
+    const int nb = (r + 15) >> 4;
     const int64_t rr = (int64_t)r * r;
-    if (tid == 0) any_dead = 0;
-    f64x4_t t[SLOTS];
-    int id[SLOTS];  // I << 8 | J; past the last block I = 0xff... < 0, which no step asks for
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        const int b = wave + nw * s;
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= b) ++I;
-        id[s] = b < nblk ? I << 8 | (b - I * (I + 1) / 2) : -1;
+    const bool diagonal = wave == nw - 1;
+    // Lane s: row and column of the block in slot s, or row -1, column 0: none.  (This factor may have fewer
+    // blocks than the launch's largest.)
+    int bI = -1, bJ = 0;
+    if (!diagonal && lane < SLOTS) {
+        const int b = wave + (nw - 1) * lane;
+        int I = 1;
+        while ((I + 1) * I / 2 <= b) ++I;
+        if (b < nb * (nb - 1) / 2) {
+            bI = I;
+            bJ = b - I * (I - 1) / 2;
+        }
     }
-    auto load = [&](int s, int v, int q) {  // this lane's element of partial sum q
-        const int x = 16 * (id[s] & 0xff) + 4 * v + g, y = 16 * (id[s] >> 8) + col;
-        const bool in = id[s] >= 0 && x < r && y < r;  // the upper triangle is what is stored
-        const double e = part[q * rr + (in ? (x < y ? x * r + y : y * r + x) : 0)];
-        return in ? e : 0.0;
+    auto row_of = [&](int s) { return __builtin_amdgcn_readlane(bI, s); };
+    auto col_of = [&](int s) { return __builtin_amdgcn_readlane(bJ, s); };
+    // All blocks are held negated: what is taken from them is then added.
+    f64x4_t t[SLOTS];
+    // This lane's elements of block (I, J), partial sum q.  The upper triangle is what is stored; past the edge
+    // the last row or column is read again.  Slot by slot: of addresses no more than one slot's are in
+    // registers.
+    auto load = [&](f64x4_t &to, int I, int J, int q) {
+        const int y0 = 16 * I + col, x0 = 16 * J + g, y = y0 < r ? y0 : r - 1;
+        const double *src = part + q * rr;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int x = x0 + 4 * v < r ? x0 + 4 * v : r - 1;
+            to[v] = src[(x < y ? x : y) * r + (x < y ? y : x)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
     };
+    auto load_slot = [&](f64x4_t &to, int s, int q) { load(to, row_of(s) < 0 ? 0 : row_of(s), col_of(s), q); };
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s)
+    for (int s = 0; s < SLOTS; ++s) load_slot(t[s], s, 0);
+    if (tid == 0) any_dead = 0;
+    for (int s = wave; s < nb; s += nw) {  // two at most
+        f64x4_t x;
+        load(x, s, s, 0);
+        for (int q = 1; q < nchunks; ++q) {
+            f64x4_t y;
+            load(y, s, s, q);
+            x += y;
+        }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) t[s][v] = load(s, v, 0);
+        for (int v = 0; v < 4; ++v) {
+            diag[s][v][lane] = x[v];
+            if (4 * v + g == col) dscale[16 * s + col] = x[v];
+        }
+    }
     // chunk by chunk in order; with few blocks four chunks are requested before the first is added
     constexpr int N = SLOTS <= 2 ? 4 : 1;
     for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
-        double x[N][SLOTS][4];
+        f64x4_t x[N][SLOTS];
 #pragma unroll
         for (int u = 0; u < N; ++u)
 #pragma unroll
-            for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) x[u][s][v] = load(s, v, q + u < nchunks ? q + u : q);
+            for (int s = 0; s < SLOTS; ++s) load_slot(x[u][s], s, q + u < nchunks ? q + u : q);
 #pragma unroll
         for (int u = 0; u < N; ++u)
 #pragma unroll
@@ -329,15 +402,11 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 #pragma unroll
                 for (int v = 0; v < 4; ++v) t[s][v] += q + u < nchunks ? x[u][s][v] : 0.0;
     }
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s)
-        if (id[s] >= 0 && (id[s] >> 8) == (id[s] & 0xff))
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (4 * v + g == col) {
-                    const double d = t[s][v];
-                    dscale[16 * (id[s] & 0xff) + col] = !(d < __builtin_inf()) ? -1.0 : d > 0.0 ? 1.0 / sqrt(d) : 0.0;
-                }
+    __syncthreads();
+    for (int q = tid; q < 16 * nb; q += blockDim.x) {
+        const double d = dscale[q];
+        dscale[q] = q >= r ? 0.0 : !(d < __builtin_inf()) ? -1.0 : d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+    }
     __syncthreads();
     // The first column that is not finite (kOdd).  It and those after it come out as NaN, and must not
     // reach those before it: their rows are zeros here, their columns of W NaN, and apply_w reads zeros
@@ -349,103 +418,100 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         if (m && odd == r) odd = q + __builtin_ctzll(m);
     }
     if (tid == 0) it.g[kOdd] = (double)odd;
+    auto scale = [&](f64x4_t &x, int I, int J) {
+        const double dc = -dscale[16 * I + col];
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-        if (id[s] < 0) continue;
-        const int I = id[s] >> 8, J = id[s] & 0xff;
+        for (int v = 0; v < 4; ++v) x[v] *= dscale[16 * J + 4 * v + g] * dc;
+        if (odd < r)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const double scaled = t[s][v] * (dscale[16 * J + 4 * v + g] * dscale[16 * I + col]);
-            t[s][v] = 16 * I + col < odd && 16 * J + 4 * v + g < odd ? scaled : 0.0;
-        }
-        if (I == 0) {  // block (0, 0)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
-        }
-    }
-    // The slot's block, opaque to the compiler at every use: addresses derived from it would
-    // otherwise be kept for all slots across the loop, and the blocks spilled for them.
-    auto block_of = [&](int s, int &I, int &J) {
-        int x = id[s];
-        asm volatile("" : "+s"(x));
-        I = x >> 8;
-        J = x & 0xff;
+            for (int v = 0; v < 4; ++v) x[v] = 16 * I + col < odd && 16 * J + 4 * v + g < odd ? x[v] : 0.0;
     };
-    auto w_entry = [&](int row, int c, double x) {
-        return c >= odd ? __builtin_nan("") : row < odd ? dscale[row] * x : 0.0;
-    };
-    bool dead = false;
-    double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
-    if (wave == 0) {
-        wave_sync();
-        dead = factor_block(diag, vbuf[0], lane, r);
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) scale(t[s], row_of(s) < 0 ? 0 : row_of(s), col_of(s));
+    for (int s = wave; s < nb; s += nw) {
+        f64x4_t x;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = diag[s][v][lane];
+        scale(x, s, s);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) diag[s][v][lane] = x[v];
     }
     __syncthreads();
+    double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
+    // Block (I, J) of L^-1: W is the transpose, its rows scaled.
+    auto store = [&](int I, int J, const f64x4_t &x) {
+        const int row = 16 * J + col;
+        const double by = row < odd ? dscale[row] : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = 16 * I + 4 * v + g;
+            norm2 = fma(x[v], x[v], norm2);
+            if (c < r && row < r) w[row * r + c] = c >= odd ? __builtin_nan("") : by * x[v];
+        }
+    };
+    bool dead = false;
     for (int k = 0; k < nb; ++k) {
-        const double *vk = vbuf[k & 1];
-        double va[4];  // V as A operand
+        const double (*vk)[64] = vb[k & 1];
+        // acc (negated) += the product of its operands X_J and X_I (J > k), or X_I and X_J, of step k - 1
+        auto update = [&](f64x4_t &acc, int I, int J, int k, const double (*v)[64]) {
+            const double (*pa)[64] = panel[J > k ? J : I];
+            const double (*pb)[64] = J > k ? panel[I] : J == k ? v : panel[J];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) va[s] = vk[col * kVPitch + 4 * s + g];
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            int I, J;
-            block_of(s, I, J);
-            if ((I == k) != (J == k) && (I == k || J == k)) {
-                f64x4_t x = f64x4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) x = mfma64(va[q], t[s][q], x);
-                const int other = I == k ? J : I;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) panel[other][v][lane] = x[v];
-                if (I == k) {  // a final block of L^-1: W is its transpose, columns scaled
-                    t[s] = x;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        norm2 = fma(x[v], x[v], norm2);
-                        const int c = 16 * k + 4 * v + g, kk = 16 * J + col;
-                        if (c < r) w[(int64_t)kk * r + c] = w_entry(kk, c, x[v]);
-                    }
-                } else {
-                    t[s] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-                }
-            } else if (I == k) {  // (k, k): V itself
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const double x = vk[(4 * v + g) * kVPitch + col];
-                    panel[k][v][lane] = x;
-                    norm2 = fma(x, x, norm2);
-                    const int c = 16 * k + 4 * v + g, kk = 16 * k + col;
-                    if (c < r && kk < r) w[(int64_t)kk * r + c] = w_entry(kk, c, x);
-                }
-            }
-        }
-        __syncthreads();
-        if (k + 1 == nb) break;
-        auto update = [&](f64x4_t &acc, int I, int J) {
-            const int a = J > k ? J : I, b = J > k ? I : J;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc = mfma64(-panel[a][q][lane], panel[b][q][lane], acc);
+            for (int q = 0; q < 4; ++q) acc = mfma64(pa[q][lane], pb[q][lane], acc);
         };
-        bool owner = false;
+        auto update_diag = [&](int s, int k) {
+            f64x4_t x;
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s)
-            if (id[s] == ((k + 1) << 8 | (k + 1))) {
-                update(t[s], k + 1, k + 1);
+            for (int v = 0; v < 4; ++v) x[v] = diag[s][v][lane];
+            if (k >= 0) update(x, s, s, k, nullptr);
+            return x;
+        };
+        if (diagonal) {  // the others wait for this wavefront
+            __builtin_amdgcn_s_setprio(3);
+            dead |= factor_block(-update_diag(k, k - 1), va[k & 1], vb[k & 1], lane, r - 16 * k);
+            if (k > 0)
+                for (int s = k + 1; s < nb; ++s) {
+                    const f64x4_t x = update_diag(s, k - 1);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) diag[(4 * v + g) * kVPitch + col] = t[s][v];
-                owner = true;
-            }
-        if (owner) {
-            wave_sync();
-            dead |= factor_block(diag, vbuf[(k + 1) & 1], lane, r - 16 * (k + 1));
-        }
+                    for (int v = 0; v < 4; ++v) diag[s][v][lane] = x[v];
+                }
+            __builtin_amdgcn_s_setprio(0);
+        } else if (k > 0) {
+            const uint64_t mine = __ballot(bI >= k);
 #pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            int I, J;
-            block_of(s, I, J);
-            if (I > k && !(I == k + 1 && J == k + 1)) update(t[s], I, J);
+            for (int s = 0; s < SLOTS; ++s)
+                if (mine >> s & 1) update(t[s], row_of(s), col_of(s), k - 1, vb[(k - 1) & 1]);
         }
         __syncthreads();
+        if (diagonal) {
+            f64x4_t x;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[v] = vk[v][lane];
+            store(k, k, x);
+        } else {
+            double a[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[q] = -va[k & 1][col * kVPitch + 4 * q + g];
+            const uint64_t mine = __ballot(bI == k || (bI > k && bJ == k));
+#pragma unroll
+            for (int s = 0; s < SLOTS; ++s)
+                if (mine >> s & 1) {
+                    f64x4_t x = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x = mfma64(a[q], t[s][q], x);
+                    const int I = row_of(s);
+                    double (*to)[64] = panel[I == k ? col_of(s) : I];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) to[v][lane] = x[v];
+                    t[s] = I == k ? x : f64x4_t{0.0, 0.0, 0.0, 0.0};  // (k, J): a final block of L^-1
+                }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+        if (row_of(s) >= 0) store(row_of(s), col_of(s), t[s]);
+        __builtin_amdgcn_sched_barrier(0);
     }
     if (round != 0) return;
     // The orthogonality error of P W is about eps64 ||R^-1||^2 (the Gram sums are good to a few
@@ -473,17 +539,18 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 // wavefront gets long and short ones.
 // Bound by the fp64 matrix cores: seven factors of a 100B-class layer at r = 256 (77824 rows,
 // 5.1 GFLOP) take 130 us (vector fp64 FMAs with W through LDS: 598 us).
-__global__ __launch_bounds__(kGT) void apply_w_kernel(FactorBatch batch, int round) {
+template <int NW>  // wavefronts
+__global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, Places at, int round) {
     extern __shared__ __attribute__((aligned(16))) float fl[];  // [16 nb][64]
-    const FactorItem it = batch.it[blockIdx.y];
+    int place = blockIdx.x;
+    const FactorItem it = batch.it[item_of(at, batch.n, place)];
     const int64_t L = it.L;
-    const int64_t i0 = (int64_t)blockIdx.x * 64;
-    if (i0 >= L) return;
+    const int64_t i0 = (int64_t)place * 64;
     if (second_round_idle(it, round)) return;
     float *__restrict__ p = it.f;
     const double *__restrict__ w = it.w;
     const int r = it.r, nb = (r + 15) >> 4, odd = __builtin_amdgcn_readfirstlane((int)it.g[kOdd]);
-    for (int idx = threadIdx.x; idx < nb * 256; idx += kGT) {
+    for (int idx = threadIdx.x; idx < nb * 256; idx += 64 * NW) {
         const int c = idx >> 4, c4 = idx & 15;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (c < odd && i0 + c4 * 4 < L)  // odd <= r
@@ -494,9 +561,9 @@ __global__ __launch_bounds__(kGT) void apply_w_kernel(FactorBatch batch, int rou
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, n = lane & 15;
-    for (int u = 0; 4 * u < nb; ++u) {
-        // blocks w, 7 - w, 8 + w, 15 - w: the work of a block grows with its index
-        const int cb = 4 * u + ((u & 1) ? 3 - wave : wave);
+    for (int u = 0; NW * u < nb; ++u) {
+        // blocks w, 2 NW - 1 - w, 2 NW + w, ..: the work of a block grows with its index
+        const int cb = NW * u + ((u & 1) ? NW - 1 - wave : wave);
         if (cb >= nb) continue;
         const int c = cb * 16 + n;  // A: column of W (any valid one past r, not stored)
         const double *wc = w + (c < r ? c : r - 1);
@@ -550,36 +617,38 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
     int rc = launch_gram_partials_batch(batch, &summed, round, st);
     if (rc != DLCX_OK) return rc;
     int max_nb = 1;
-    int64_t max_rows = 1;
     for (int i = 0; i < batch.n; ++i) {
         const int nb = (batch.it[i].r + 15) / 16;
         if (nb > max_nb) max_nb = nb;
-        if (ceil_div(batch.it[i].L, 64) > max_rows) max_rows = ceil_div(batch.it[i].L, 64);
     }
     {
-        // accumulator blocks per wavefront: 2 up to r = 80, 6 up to r = 144, else 17
+        // a wavefront for the diagonal blocks, up to seven for the others; blocks of each: 2 up to r = 80,
+        // 6 up to r = 144, else 18
         Timed timed(KID_CHOL, st);
-        const int blocks = max_nb * (max_nb + 1) / 2, waves = kCT / 64;
-        const dim3 grid((unsigned)batch.n), threads((unsigned)(blocks < waves ? blocks : waves) * 64);
-        static_assert(6 * 8 >= (kSumRank / 16) * (kSumRank / 16 + 1) / 2, "ranks that sum chunks have at most 6");
-        if (blocks <= 2 * waves)
+        const int others = max_nb * (max_nb - 1) / 2, dealt = kCT / 64 - 1;
+        const dim3 grid((unsigned)batch.n), threads((unsigned)(1 + (others < dealt ? others : dealt)) * 64);
+        static_assert(6 * 7 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
+        static_assert(18 * 7 >= kMaxBlocks * (kMaxBlocks - 1) / 2, "blocks of the largest rank");
+        if (others <= 2 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
-        else if (blocks <= 6 * waves)
+        else if (others <= 6 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<6>, grid, threads, 0, st, summed, round);
         else
-            hipLaunchKernelGGL(chol_inverse_kernel<17>, grid, threads, 0, st, summed, round);
+            hipLaunchKernelGGL(chol_inverse_kernel<18>, grid, threads, 0, st, summed, round);
         rc = check_launch("chol_inverse");
     }
     if (rc != DLCX_OK) return rc;
     const size_t a_bytes = (size_t)max_nb * 16 * 64 * sizeof(float);
-    static size_t apply_granted = 0;
-    rc = grant_dynamic_lds(reinterpret_cast<const void *>(apply_w_kernel), a_bytes, &apply_granted,
-                       "apply_w attribute");
-    if (rc != DLCX_OK) return rc;
-    Timed timed(KID_APPLY_W, st);
-    hipLaunchKernelGGL(apply_w_kernel, dim3((unsigned)max_rows, (unsigned)batch.n), dim3(kGT),
-                       a_bytes, st, batch, round);
-    return check_launch("apply_w");
+    const Places at = places_of(batch, [](const FactorItem &it) { return ceil_div(it.L, 64); });
+    auto apply = [&](auto kernel, size_t *granted, int waves) {
+        int rc = grant_dynamic_lds(reinterpret_cast<const void *>(kernel), a_bytes, granted, "apply_w attribute");
+        if (rc != DLCX_OK) return rc;
+        Timed timed(KID_APPLY_W, st);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)at.first[batch.n]), dim3(64 * waves), a_bytes, st, batch, at, round);
+        return check_launch("apply_w");
+    };
+    static size_t granted4 = 0, granted8 = 0;
+    return max_nb > 8 ? apply(apply_w_kernel<8>, &granted8, 8) : apply(apply_w_kernel<4>, &granted4, 4);
 }
 
 // Fills the scratch pointers of item i from a workspace of orth_workspace_bytes(L, r) bytes.
