@@ -4,6 +4,8 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <type_traits>
+
 #include "../../include/dlcx.h"
 
 namespace dlcx {
@@ -163,6 +165,27 @@ size_t project_workspace_bytes(int mma, int64_t m, int64_t n, int r, int K);
 size_t reconstruct_workspace_bytes(int mma, int64_t m, int64_t n, int r);
 
 // ---- orthonormalisation and effective rank (k_orth.hip, k_rank.hip) ---------------------
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// the value of lane X of the lane's row of 16
+template <int X>
+__device__ __forceinline__ double row_bcast(double x) {
+    const long long u = __double_as_longlong(x);
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, u, 0x150 + X, 0xf, 0xf, true));
+}
+// f(0), f(1), .. f(N - 1) with the index as a compile-time constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        unrolled<N, I + 1>(f);
+    }
+}
+
 inline size_t a256x(size_t x) { return (x + 255) & ~(size_t)255; }
 // One r x L factor and its fp64 scratch; a batch of them is passed to a kernel by value.
 constexpr int kMaxBatch = 64;

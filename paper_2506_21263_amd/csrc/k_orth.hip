@@ -264,47 +264,54 @@ constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;
 constexpr int kCT = 512;  // at most 8 wavefronts: 18 blocks each at r = 256, 144 of 256 registers
 
-__device__ __forceinline__ double read_lane(double x, int lane) {
+// the values of the kG-th row of 16 lanes, in every row
+template <int kG>
+__device__ __forceinline__ double spread_row(double x) {
     const uint64_t u = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, lane);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    uint32_t w[2] = {(uint32_t)u, (uint32_t)(u >> 32)};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        w[i] = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false)[kG >> 1];
+        w[i] = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false)[kG & 1];
+    }
+    return __longlong_as_double((long long)(((uint64_t)w[1] << 32) | w[0]));
 }
 
-// V = L^-1 of a symmetric 16 x 16 block G = L L^T by one wavefront, both as accumulators: register v of
-// lane (g, col) = (lane / 16, lane % 16) is element (4 v + g, col).  Eliminating row j from [G | 1] is a product
-// with one row of the operands in use, -(row j) / pivot as A (G is symmetric) and row j as B, and row j of an
-// accumulator lies where both want row j % 4 of their four: no lane needs another's value but for the pivots.
-// The pivot after is worked out beside the product that makes its row, by the same operations.  The square roots
-// are left to the end.  Dead pivots (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.
-// Writes V as the A operand of the panel reads it (pitch kVPitch) and as an accumulator; returns whether one
-// of the first `live` pivots was dead.
+// V = L^-1 of a symmetric 16 x 16 block G = L L^T by one wavefront, both as accumulators: register q of
+// lane (g, col) = (lane / 16, lane % 16) is element (4 q + g, col).  Row j of [G | 1] is spread over the four
+// rows of lanes, a row's factor comes from its element in column j (row_bcast), and the pivot after is worked
+// out beside the updates that make it, by the same operations.  The square roots are left to the end.  Dead pivots
+// (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.  Writes V as the A operand of
+// the panel reads it (pitch kVPitch) and as an accumulator; returns whether one of the first `live` pivots was dead.
+// Bound by the chain from pivot to pivot, FACTORNEW clocks each beside a wavefront that keeps the matrix cores busy
+// (as products with one row of their operands in use: 480, a turn on the matrix cores after every pivot).
 __device__ __forceinline__ bool factor_block(f64x4_t t, double *va, double (*vb)[64], int lane, int live) {
     const int g = lane >> 4, col = lane & 15;
     f64x4_t u, own;  // the right half; the pivot of each row
 #pragma unroll
     for (int q = 0; q < 4; ++q) u[q] = 4 * q + g == col ? 1.0 : 0.0;
     double p = read_lane(t[0], 0);
+    unrolled<16>([&](auto jc) {
+        constexpr int j = decltype(jc)::value, q0 = j / 4, g0 = j % 4;
+        if (g == g0) own[q0] = p;
+        if constexpr (j < 15) {
+            constexpr int q1 = (j + 1) / 4, g1 = (j + 1) % 4;
+            const double row = spread_row<g0>(t[q0]), right = spread_row<g0>(u[q0]);
+            const double below = read_lane(t[q1], 16 * g1 + j), across = read_lane(row, j + 1);
+            const double next = read_lane(t[q1], 16 * g1 + j + 1);
+            double rp = __builtin_amdgcn_rcp(p);
+            rp = fma(fma(-p, rp, 1.0), rp, rp);
+            rp = fma(fma(-p, rp, 1.0), rp, rp);
+            rp = p > 1e-12 ? rp : 0.0;
+            p = fma(-(below * rp), across, next);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int q = j / 4, q1 = (j + 1) / 4;
-        const bool mine = g == j % 4, dead = !(p > 1e-12);
-        if (mine) own[q] = p;
-        double rp = __builtin_amdgcn_rcp(p);
-        rp = fma(fma(-p, rp, 1.0), rp, rp);
-        rp = fma(fma(-p, rp, 1.0), rp, rp);
-        if (j < 15) {
-            const double x = read_lane(t[q], 16 * (j % 4) + j + 1);
-            const double d = read_lane(t[q1], 16 * ((j + 1) % 4) + j + 1);
-            p = dead ? d : fma(-x * rp, x, d);
+            for (int q = q0; q < 4; ++q) {
+                const double f = row_bcast<j>(t[q]) * (q > q0 || g > g0 ? rp : 0.0);  // rows that are done: none
+                t[q] = fma(-f, row, t[q]);
+                u[q] = fma(-f, right, u[q]);
+            }
         }
-        const double row = mine ? t[q] : 0.0;
-        const double a = dead || col <= j ? 0.0 : -row * rp;  // rows that are done keep what they have
-        if (j < 15) {
-            t = mfma64(a, row, t);
-            u = mfma64(a, mine ? u[q] : 0.0, u);
-        }
-    }
+    });
     bool any = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -334,6 +341,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     __shared__ double vb[2][4][64];           // .. and as accumulator
     __shared__ double red[kCT / 64];
     __shared__ int any_dead;
+    __shared__ int factored;  // blocks on the diagonal that are
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
     const int g = lane >> 4, col = lane & 15;
@@ -342,12 +350,18 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     const bool diagonal = wave == nw - 1;
     // Lane s: row and column of the block in slot s, or row -1, column 0: none.  (This factor may have fewer
     // blocks than the launch's largest.)
+    // A block each in turn, but `beside`, the wavefront on the SIMD of the diagonal's, is left out every third
+    // time: fp64 products hold up the fp64 arithmetic of the other wavefront of a SIMD, so it starts on its
+    // updates when the factorisation is done.
+    const int beside = nw > 4 ? nw - 5 : -1;
     int bI = -1, bJ = 0;
     if (!diagonal && lane < SLOTS) {
-        const int b = wave + (nw - 1) * lane;
+        const int others = nw - 1;
+        int b = wave + others * lane;
+        if (beside >= 0) b -= lane / 3 + (lane % 3 == 2 && wave > beside ? 1 : 0);
         int I = 1;
         while ((I + 1) * I / 2 <= b) ++I;
-        if (b < nb * (nb - 1) / 2) {
+        if (b < nb * (nb - 1) / 2 && !(wave == beside && lane % 3 == 2)) {
             bI = I;
             bJ = b - I * (I - 1) / 2;
         }
@@ -372,7 +386,10 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     auto load_slot = [&](f64x4_t &to, int s, int q) { load(to, row_of(s) < 0 ? 0 : row_of(s), col_of(s), q); };
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) load_slot(t[s], s, 0);
-    if (tid == 0) any_dead = 0;
+    if (tid == 0) {
+        any_dead = 0;
+        factored = 0;
+    }
     for (int s = wave; s < nb; s += nw) {  // two at most
         f64x4_t x;
         load(x, s, s, 0);
@@ -438,7 +455,8 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     }
     __syncthreads();
     double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
-    // Block (I, J) of L^-1: W is the transpose, its rows scaled.
+    // Block (I, J) of L^-1, columns scaled: W^T, whose rows it stores (W itself went out in single numbers, each
+    // to a line of its own: 8 - 13 us at r = 256).
     auto store = [&](int I, int J, const f64x4_t &x) {
         const int row = 16 * J + col;
         const double by = row < odd ? dscale[row] : 0.0;
@@ -446,7 +464,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         for (int v = 0; v < 4; ++v) {
             const int c = 16 * I + 4 * v + g;
             norm2 = fma(x[v], x[v], norm2);
-            if (c < r && row < r) w[row * r + c] = c >= odd ? __builtin_nan("") : by * x[v];
+            if (c < r && row < r) w[c * r + row] = c >= odd ? __builtin_nan("") : by * x[v];
         }
     };
     bool dead = false;
@@ -469,6 +487,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         if (diagonal) {  // the others wait for this wavefront
             __builtin_amdgcn_s_setprio(3);
             dead |= factor_block(-update_diag(k, k - 1), va[k & 1], vb[k & 1], lane, r - 16 * k);
+            if (lane == 0) __hip_atomic_store(&factored, k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (k > 0)
                 for (int s = k + 1; s < nb; ++s) {
                     const f64x4_t x = update_diag(s, k - 1);
@@ -477,6 +496,9 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
                 }
             __builtin_amdgcn_s_setprio(0);
         } else if (k > 0) {
+            if (wave == beside)  // a matter of speed only: what is read is there since the last barrier
+                while (__hip_atomic_load(&factored, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= k)
+                    __builtin_amdgcn_s_sleep(1);
             const uint64_t mine = __ballot(bI >= k);
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s)
@@ -532,10 +554,10 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 
 // P <- P W in place, fp64 accumulation.  Workgroup: 64 consecutive elements of every factor column,
 // staged in LDS in fp32 (they are all read before the first is overwritten).  W is upper
-// triangular; a wavefront produces 16 columns at a time over the 64 elements: A = W^T (one double
-// per lane and step, 16 consecutive columns of four rows, straight from L2, four steps ahead),
-// B = P from LDS (16 bytes per lane: lane n holds elements 4 n .. 4 n + 3, element q feeds product
-// q), so one element of W serves four products.  The column blocks are dealt so that every
+// triangular; a wavefront produces 16 columns at a time over the 64 elements: A = W^T (four doubles
+// per lane and 16 rows of W, consecutive in W^T, straight from L2 a step ahead; the s-th of them feeds the s-th
+// product, and B agrees on that order of the reduction index), B = P from LDS (16 bytes per lane: lane n holds
+// elements 4 n .. 4 n + 3, element q feeds product q), so one element of W serves four products.  The column blocks are dealt so that every
 // wavefront gets long and short ones.
 // Bound by the fp64 matrix cores: seven factors of a 100B-class layer at r = 256 (77824 rows,
 // 5.1 GFLOP) take 130 us (vector fp64 FMAs with W through LDS: 598 us).
@@ -566,33 +588,39 @@ __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, 
         const int cb = NW * u + ((u & 1) ? NW - 1 - wave : wave);
         if (cb >= nb) continue;
         const int c = cb * 16 + n;  // A: column of W (any valid one past r, not stored)
-        const double *wc = w + (c < r ? c : r - 1);
+        const double *wc = w + (int64_t)(c < r ? c : r - 1) * r + 4 * g;
         auto load_w = [&](double (&dst)[4], int kb) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int k = kb * 16 + 4 * s + g;
-                dst[s] = wc[(int64_t)(k < r ? k : r - 1) * r];
-            }
+            for (int s = 0; s < 4; ++s) dst[s] = wc[kb * 16 + s];
         };
         f64x4_t acc[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[q] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-        double a[4];
-        load_w(a, 0);
-        for (int kb = 0; kb <= cb; ++kb) {
-            double an[4];
-            load_w(an, kb < cb ? kb + 1 : cb);
+        auto multiply = [&](const double (&a)[4], int kb) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const float4 b = *reinterpret_cast<const float4 *>(fl + (kb * 16 + 4 * s + g) * 64 + n * 4);
+                const float4 b = *reinterpret_cast<const float4 *>(fl + (kb * 16 + 4 * g + s) * 64 + n * 4);
                 acc[0] = mfma64(a[s], (double)b.x, acc[0]);
                 acc[1] = mfma64(a[s], (double)b.y, acc[1]);
                 acc[2] = mfma64(a[s], (double)b.z, acc[2]);
                 acc[3] = mfma64(a[s], (double)b.w, acc[3]);
             }
+        };
+        double a[4], last[4];
+        if (cb > 0) load_w(a, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {  // the block on the diagonal: rows past r are not there
+            const int k = cb * 16 + 4 * g + s;
+            last[s] = k < r ? wc[cb * 16 + s] : 0.0;
+        }
+        for (int kb = 0; kb < cb; ++kb) {
+            double an[4];
+            load_w(an, kb + 1 < cb ? kb + 1 : kb);
+            multiply(a, kb);
 #pragma unroll
             for (int s = 0; s < 4; ++s) a[s] = an[s];
         }
+        multiply(last, cb);
         if (i0 + n * 4 < L) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -627,11 +655,11 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
         Timed timed(KID_CHOL, st);
         const int others = max_nb * (max_nb - 1) / 2, dealt = kCT / 64 - 1;
         const dim3 grid((unsigned)batch.n), threads((unsigned)(1 + (others < dealt ? others : dealt)) * 64);
-        static_assert(6 * 7 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
-        static_assert(18 * 7 >= kMaxBlocks * (kMaxBlocks - 1) / 2, "blocks of the largest rank");
+        static_assert(6 / 3 * 20 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
+        static_assert(18 / 3 * 20 >= kMaxBlocks * (kMaxBlocks - 1) / 2, "blocks of the largest rank");
         if (others <= 2 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
-        else if (others <= 6 * dealt)
+        else if (others <= 6 / 3 * 20)
             hipLaunchKernelGGL(chol_inverse_kernel<6>, grid, threads, 0, st, summed, round);
         else
             hipLaunchKernelGGL(chol_inverse_kernel<18>, grid, threads, 0, st, summed, round);

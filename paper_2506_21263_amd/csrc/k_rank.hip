@@ -26,12 +26,6 @@ __device__ __forceinline__ double dpp(double x) {
     const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, 0xf, 0xf, true);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
-// the value of lane X of the lane's row of 16
-template <int X>
-__device__ __forceinline__ double row_bcast(double x) {
-    const long long u = __double_as_longlong(x);
-    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, u, 0x150 + X, 0xf, 0xf, true));
-}
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor15 = 0x140;
 
 __device__ __forceinline__ double from_halves(uint32_t lo, uint32_t hi) {
@@ -80,15 +74,6 @@ __device__ __forceinline__ double row_sums(double (&v)[N], int t) {
     if constexpr (N >= 16) halve<kXor1, 1>(v, t & 1);
     else v[0] += dpp<kXor1>(v[0]);
     return v[0];
-}
-
-// f(0), f(1), .. f(N - 1) with the index as a compile-time constant
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>());
-        unrolled<N, I + 1>(f);
-    }
 }
 
 // The tridiagonal matrix as the Sturm sequence reads it: t[i] = (d_i, -e_i^2), e_i between i - 1
@@ -241,12 +226,6 @@ __device__ __forceinline__ Interval gershgorin(const double2 *tri, int r, int la
     const double big = fmax(fabs(lo), fabs(hi));
     const int ex = big > 0.0 && big < 1e300 ? -__builtin_amdgcn_frexp_exp(big) : 0;
     return Interval{ldexp(lo, ex), ldexp(hi, ex), ex};
-}
-
-__device__ __forceinline__ double read_lane(double x, int lane) {
-    const uint64_t u = (uint64_t)__double_as_longlong(x);
-    return from_halves(__builtin_amdgcn_readlane((uint32_t)u, lane),
-                       __builtin_amdgcn_readlane((uint32_t)(u >> 32), lane));
 }
 
 // LDS written and read by the same wavefront: its instructions execute in order, so only the
