@@ -30,6 +30,7 @@
 namespace dlcx {
 
 constexpr int kGramChunk = 512;  // elements of L per partial sum
+constexpr int kQuarter = kGramChunk / 4;  // of a wavefront
 constexpr int kGT = 256;
 
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
@@ -115,7 +116,6 @@ __global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch,
         pa[x] = f + (int64_t)(a < r ? a : r - 1) * L + 4 * q;
         pb[x] = f + (int64_t)(b < r ? b : r - 1) * L + 4 * q;
     }
-    constexpr int kQuarter = kGramChunk / 4;
     const int64_t begin = (int64_t)chunk * kGramChunk + wave * kQuarter;
     int64_t end = begin + kQuarter;
     if (end > L) end = L;  // L is a multiple of 16: a step of 16 is whole or not there
@@ -261,8 +261,16 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 // CHOLUS us and r = 32 CHOL32 us (151 and 10 before that; row by row with the matrix in L2 / LDS: 2530 and 49 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
-constexpr int kVPitch = 17;
+constexpr int kVPitch = 17;  // of a 16 x 16 block in LDS
 constexpr int kCT = 512;  // at most 8 wavefronts: 18 blocks each at r = 256, 144 of 256 registers
+
+// LDS written and read by the same wavefront: its instructions execute in order, so only the
+// compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // the values of the kG-th row of 16 lanes, in every row
 template <int kG>
@@ -634,6 +642,106 @@ __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, 
     }
 }
 
+// The whole orthonormalisation of small factors, a workgroup each, which holds its factor in LDS: the sums, the
+// factorisation and P W as above for a single block, and the second round where the first asks for one.  All
+// sums are in the order of the kernels above: a batch takes this form if all of its factors are small, and what a
+// factor's result is does not hang on that.
+// Bound by latency.  One factor of 512 x 8: SMALLUS us instead of a chain of six launches, 27 us with the gaps
+// between them, of which the last three only read a mark; at the limits below it is still the shorter one
+// (512 .. 3072 x 8 .. 16, one to seven factors: SMALLRANGE).
+constexpr int kSmallRank = 16;
+constexpr int kSmallLength = 3072;
+constexpr int kSmallFloats = 24 * 1024;  // with the rows' padding, 96 KB
+constexpr int kSmallThreads = 512;
+static inline size_t small_bytes(int64_t L, int r) { return (size_t)r * (size_t)(L + 4) * sizeof(float); }
+__global__ __launch_bounds__(kSmallThreads) void orth_small_kernel(FactorBatch batch) {
+    constexpr int NW = kSmallThreads / 64;
+    extern __shared__ __attribute__((aligned(16))) float fl[];  // [r][L + 4]: 16 rows start in 64 banks
+    __shared__ double red[kSmallLength / kQuarter][4][64];
+    __shared__ double dscale[16];
+    __shared__ double va[16 * kVPitch], wt[16 * kVPitch], vb[4][64];
+    __shared__ int state;  // the first column that is not finite, 16 more: a second round is needed
+    const FactorItem it = batch.it[blockIdx.x];
+    const int r = it.r, L = (int)it.L, pitch = L + 4, quads = L / 4, quarters = 4 * it.nchunks;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *__restrict__ p = it.f;
+    for (int c = wave; c < r; c += NW)
+        for (int i = lane; i < quads; i += 64)
+            *reinterpret_cast<float4 *>(fl + c * pitch + 4 * i) = reinterpret_cast<const float4 *>(p + (int64_t)c * L)[i];
+    for (int round = 0; round < 2; ++round) {
+        __syncthreads();
+        const float *row = fl + (col < r ? col : r - 1) * pitch + 4 * g;  // rows past r: any valid one
+        for (int q = wave; q < quarters; q += NW) {  // quarters of the 512-element sums
+            f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+            for (int i = q * kQuarter; i < (q + 1) * kQuarter && i < L; i += 16) {
+                const float4 x = *reinterpret_cast<const float4 *>(row + i);
+                acc = mfma64((double)x.x, (double)x.x, acc);
+                acc = mfma64((double)x.y, (double)x.y, acc);
+                acc = mfma64((double)x.z, (double)x.z, acc);
+                acc = mfma64((double)x.w, (double)x.w, acc);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[q][v][lane] = acc[v];
+        }
+        __syncthreads();
+        if (wave == 0) {
+            f64x4_t x;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                x[v] = 0.0;
+                for (int q = 0; q < quarters; q += 4)
+                    x[v] += ((red[q][v][lane] + red[q + 1][v][lane]) + red[q + 2][v][lane]) + red[q + 3][v][lane];
+                if (4 * v + g == col)
+                    dscale[col] = col >= r ? 0.0 : !(x[v] < __builtin_inf()) ? -1.0 : x[v] > 0.0 ? 1.0 / sqrt(x[v]) : 0.0;
+            }
+            wave_sync();
+            const double dc = dscale[col];
+            const uint64_t m = __ballot(lane < 16 && dc < 0.0);  // columns that are not finite: as in chol_inverse_kernel
+            const int odd = m ? __builtin_ctzll(m) : r;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = col < odd && 4 * v + g < odd ? x[v] * (dscale[4 * v + g] * dc) : 0.0;
+            const bool dead = factor_block(x, va, vb, lane, r);
+            wave_sync();
+            double norm2 = 0.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double y = vb[v][lane];
+                const int c = 4 * v + g;
+                norm2 = fma(y, y, norm2);
+                wt[c * kVPitch + col] = c >= odd ? __builtin_nan("") : col < odd ? dc * y : 0.0;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) norm2 += __shfl_xor(norm2, off, 64);
+            if (lane == 0) state = odd + (dead || !(norm2 <= kOneRoundNorm) ? 32 : 0);
+        }
+        __syncthreads();
+        const int odd = state & 31;
+        const bool again = state >= 32;
+        double a[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[s] = wt[col * kVPitch + 4 * g + s];
+        for (int i = 16 * wave; i < L; i += 16 * NW) {  // 16 elements of every column, read before they are written
+            f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = 4 * g + s;
+                const float x = fl[(k < r ? k : 0) * pitch + i + col];
+                acc = mfma64(a[s], k < odd ? (double)x : 0.0, acc);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (4 * v + g < r) fl[(4 * v + g) * pitch + i + col] = (float)acc[v];
+        }
+        if (!again) break;
+    }
+    __syncthreads();
+    for (int c = wave; c < r; c += NW)
+        for (int i = lane; i < quads; i += 64)
+            reinterpret_cast<float4 *>(p + (int64_t)c * L)[i] = *reinterpret_cast<const float4 *>(fl + c * pitch + 4 * i);
+}
+
 size_t orth_workspace_bytes(int64_t L, int r) {
     // partials + g (pitch r + 1) + w
     return a256x(((size_t)gram_chunks(L) * r * r + (size_t)r * (r + 1) + (size_t)r * r) *
@@ -693,6 +801,21 @@ void orth_item(FactorItem *it, float *p, int64_t L, int r, void *workspace) {
 
 int launch_orthonormalize_batch(const FactorBatch &batch, hipStream_t st) {
     if (batch.n == 0) return DLCX_OK;
+    size_t bytes = 0;
+    bool small = true;
+    for (int i = 0; i < batch.n; ++i) {
+        const FactorItem &it = batch.it[i];
+        small = small && it.r <= kSmallRank && it.L <= kSmallLength && small_bytes(it.L, it.r) <= kSmallFloats * sizeof(float);
+        if (small && small_bytes(it.L, it.r) > bytes) bytes = small_bytes(it.L, it.r);
+    }
+    if (small) {
+        static size_t granted = 0;
+        int rc = grant_dynamic_lds(reinterpret_cast<const void *>(orth_small_kernel), bytes, &granted, "orth_small attribute");
+        if (rc != DLCX_OK) return rc;
+        Timed timed(KID_CHOL, st);
+        hipLaunchKernelGGL(orth_small_kernel, dim3((unsigned)batch.n), dim3(kSmallThreads), bytes, st, batch);
+        return check_launch("orth_small");
+    }
     int rc = cholqr_round(batch, 0, st);
     if (rc != DLCX_OK) return rc;
     return cholqr_round(batch, 1, st);

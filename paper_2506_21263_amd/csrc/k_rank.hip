@@ -477,6 +477,35 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
     }
 }
 
+// The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
+// a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
+// sums come from there depends on the batch).  Up to kSmallLength rows that is shorter than a launch before
+// this one: RANKSMALL
+constexpr int kSmallGram = 16;
+constexpr int kSmallLength = 2048;
+constexpr int kGramQuarter = 128;
+__device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGram][kSmallGram + 1]) {
+    typedef double f64x4_t __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, g = lane >> 4, L = (int)it.L, begin = (4 * c + wave) * kGramQuarter;
+    const float *row = it.f + (int64_t)(col < it.r ? col : it.r - 1) * L + 4 * g;
+    float4 x[kGramQuarter / 16];
+#pragma unroll
+    for (int u = 0; u < kGramQuarter / 16; ++u)
+        x[u] = *reinterpret_cast<const float4 *>(row + (begin + 16 * u < L ? begin + 16 * u : 0));
+    f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < kGramQuarter / 16; ++u) {
+        if (begin + 16 * u >= L) break;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].x, (double)x[u].x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].y, (double)x[u].y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].z, (double)x[u].z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].w, (double)x[u].w, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gram[wave][4 * v + g][col] = acc[v];
+}
+
 // Ranks up to kFusedRank: the whole matrix in one wavefront, row i in lane i, and no barrier until
 // the eigenvalues.  Every lane sums its own row of S v; v and w go round through LDS.  The columns
 // are renumbered as they go: step k reflects register column 0 and the update writes column j into
@@ -504,6 +533,20 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
         from[e] = x <= y && y < it.r ? x * it.r + y : -1;
         sum[e] = 0.0;
     }
+    if constexpr (RC <= 32)
+        if (nchunks == 0) {  // the sums are left to this kernel
+            __shared__ double gram[4][kSmallGram][kSmallGram + 1];
+            for (int c = 0; 4 * kGramQuarter * c < it.L; ++c) {
+                small_gram(it, c, gram);
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int x = (tid + kTT * e) / RC % kSmallGram, y = (tid + kTT * e) % RC % kSmallGram;
+                    sum[e] += ((gram[0][x][y] + gram[1][x][y]) + gram[2][x][y]) + gram[3][x][y];
+                }
+                __syncthreads();
+            }
+        }
     for (int c = 0; c < nchunks; c += 2) {  // chunk by chunk in order, two requested at a time
         double p[2][E];
 #pragma unroll
@@ -674,9 +717,16 @@ void effrank_item(FactorItem *it, const float *q_bar, int64_t L, int r, int32_t 
 
 int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_t st) {
     if (batch.n == 0) return DLCX_OK;
-    FactorBatch summed;  // the same factors with their Gram sums in one chunk where that pays
-    int rc = launch_gram_partials_batch(batch, &summed, 0, st);
-    if (rc != DLCX_OK) return rc;
+    FactorBatch summed = batch;  // the same factors with their Gram sums in one chunk where that pays, or none
+    bool small = true;
+    for (int i = 0; i < batch.n; ++i)
+        small = small && batch.it[i].r <= kSmallGram && batch.it[i].L <= kSmallLength;
+    if (small) {
+        for (int i = 0; i < batch.n; ++i) summed.it[i].nchunks = 0;
+    } else {
+        int rc = launch_gram_partials_batch(batch, &summed, 0, st);
+        if (rc != DLCX_OK) return rc;
+    }
     int rmax = 0, rmin = DLCX_MAX_RANK;
     bool rmid = false;
     for (int i = 0; i < batch.n; ++i) {

@@ -521,6 +521,51 @@ def test_orthonormalize_leaves_the_columns_before_one_that_is_not_finite(L, r, v
             assert rel_l2(got[:col], (q * np.sign(np.diag(t))).T) <= 2.4e-7, col
 
 
+@pytest.mark.parametrize("L,r", [(16, 1), (16, 16), (48, 3), (512, 8), (528, 15), (1520, 16), (1536, 16), (3056, 8),
+                                 (3072, 7), (3088, 2)])
+@pytest.mark.parametrize("cond", [3.0, 1e5])
+def test_small_factors_alone_and_in_a_batch_with_large_ones(L, r, cond):
+    # A batch of factors of at most 16 columns that fit in LDS is orthonormalised, and measured, by one launch; in
+    # a batch with a larger one they take the general kernels.  Same sums in the same order: the same bits; and
+    # against a 64-bit QR what is left is the rounding to fp32 after each round, as above.
+    g = rng(L * 5 + r)
+    U, W = synth.orthonormal_columns(g, L, r), synth.orthonormal_columns(g, r, r)
+    A = np.ascontiguousarray(((U * np.logspace(0, -np.log10(cond), r)) @ W.T).T.astype(np.float32))
+    big = g.standard_normal((20, 64)).astype(np.float32)
+    descs = [dlcx.desc(L, L, r, 4, 16), dlcx.desc(64, 64, 20, 4, 16)]
+    ws = torch.empty(dlcx.dlcx_batched_workspace_bytes(descs), device=DEV, dtype=torch.uint8)
+    got, ranks = [], []
+    for n in (1, 2):
+        f, out = [to_dev(A), to_dev(big)][:n], torch.full((2,), -1, device=DEV, dtype=torch.int32)
+        dlcx.dlcx_effective_rank_batched(descs[:n], f, 0.999, out, ws)
+        dlcx.dlcx_orthonormalize_batched(descs[:n], f, ws)
+        got.append(to_np(f[0]))
+        ranks.append(int(out[0].item()))
+    assert np.array_equal(got[0].view(np.uint32), got[1].view(np.uint32))
+    assert ranks[0] == ranks[1] == ref.effective_rank(A, 0.999)
+    q, t = np.linalg.qr(A.T.astype(np.float64))
+    assert rel_l2(got[0], (q * np.sign(np.diag(t))).T) <= 2.4e-7
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_small_factor_that_is_not_finite_or_has_no_rank(value):
+    L, r = 528, 12
+    A = rng(77).standard_normal((r, L)).astype(np.float32)
+    A[3] = 0.0
+    A[6] = 2.0 * A[1]
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    d_A = to_dev(A)
+    dlcx.dlcx_orthonormalize(L, r, d_A, ws)
+    want = to_np(d_A)
+    assert not want[3].any() and not want[6].any()
+    assert rel_l2(want, ref.orthonormalize(A)) <= 1e-5
+    A[9, 100] = value
+    d_A = to_dev(A)
+    dlcx.dlcx_orthonormalize(L, r, d_A, ws)
+    got = to_np(d_A)
+    assert np.isnan(got[9:]).all() and rel_l2(got[:9], want[:9]) <= 2.4e-7
+
+
 def test_orthonormalize_degenerate_columns():
     L, r = 256, 6
     g = rng(3)
