@@ -353,7 +353,7 @@ constexpr bool kApartP = NS >= 2 && BLOCKS <= 2;
 // LONE: as many where it has two, if there are no two workgroups to a compute unit (registers).
 template <int NS, int BLOCKS, bool LONE>
 constexpr int kChainsP = NS >= 2 && BLOCKS <= (LONE ? 2 : 1) ? 2 : 1;
-template <int NS, int CBW, int WC, int WR, int RB, bool LONE>
+template <int NS, int CBW, int WC, int WR, int RB, bool LONE, int kSets = 2>
 __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *> deltas,
                                                            const uint4 *__restrict__ afrags,
                                                            PtrPack<float *> outs, int64_t m,
@@ -419,29 +419,30 @@ __global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *
             }
         };
         // one step: lay down stage `stage` (held in `set`) for the consumers' next iteration
-        // while they work on the stage before it, then refill the set two stages further on
+        // while they work on the stage before it, then refill the set kSets stages further on
+        // (four sets measured no faster than three at best)
         auto step = [&](float4 (&set)[kVec], int64_t stage, bool refill) {
             store_stage(set, lds + (stage & 1) * kBuf, stage);
-            if (refill) load_stage(set, stage + 2);
+            if (refill) load_stage(set, stage + kSets);
             lds_barrier();
             // nothing of the next step moves above the barrier: splitting its set earlier would
             // wait for requests that are younger than they should be
             __builtin_amdgcn_sched_barrier(0);
         };
-        float4 set0[kVec], set1[kVec];
-        load_stage(set0, 0);
-        load_stage(set1, 1);
-        step(set0, 0, true);
-        // two stages per trip, no way round the second inside the loop: the compiler's wait
-        // counts at the loop head then see one order of outstanding requests only.  (Four sets
-        // and four stages of distance measured no faster.)
+        float4 set[kSets][kVec];
+#pragma unroll
+        for (int s = 0; s < kSets; ++s) load_stage(set[s], s);
+        step(set[0], 0, true);
+        // kSets stages per trip, no way round the later ones inside the loop: the compiler's wait
+        // counts at the loop head then see one order of outstanding requests only.
         int64_t t = 0;
-        for (; t + 1 < nstages; t += 2) {
-            step(set1, t + 1, true);
-            step(set0, t + 2, true);
-        }
-        // an odd number of stages: the consumers' last iteration needs its barrier
-        if (t < nstages) step(set1, t + 1, false);
+        for (; t + kSets - 1 < nstages; t += kSets)
+#pragma unroll
+            for (int s = 1; s <= kSets; ++s) step(set[s % kSets], t + s, true);
+        // what is left: the consumers' last iteration needs its barrier
+#pragma unroll
+        for (int s = 1; s < kSets; ++s)
+            if (t + s <= nstages) step(set[s], t + s, false);
         if constexpr (NS == 1) record_amax(amax, amax_record);
         return;
     }
@@ -1527,7 +1528,7 @@ static int pack_f16(const KContig &p, uint4 *frags_f16, const F16Scratch &f, hip
     return check_launch("pack_f16");
 }
 
-template <int NS, int CBW, int WC, int WR, int RB = 4, bool LONE = NS == 3>
+template <int NS, int CBW, int WC, int WR, int RB = 4, bool LONE = NS == 3, int kSets = 2>
 static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &delta,
                                const uint4 *frags, const PtrPack<float *> &out, int64_t m,
                                int64_t n, int r, int K, hipStream_t st, uint32_t *record = nullptr,
@@ -1535,11 +1536,11 @@ static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &de
     constexpr int lds = 2 * NS * 32 * RB * kPPitch;
     static size_t granted = 0;
     int rc = grant_dynamic_lds(
-        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE>), lds,
+        reinterpret_cast<const void *>(project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE, kSets>), lds,
         &granted, "project_p attribute");
     if (rc != DLCX_OK) return rc;
     const dim3 grid((unsigned)ceil_div(m, 32 * RB), (unsigned)K, (unsigned)pl.S);
-    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE>), grid, dim3(kWs), lds, st,
+    hipLaunchKernelGGL((project_p_ws_kernel<NS, CBW, WC, WR, RB, LONE, kSets>), grid, dim3(kWs), lds, st,
                        delta, frags, out, m, n, r, pl.stages, (int64_t)r * m, record, out_scale,
                        guard);
     return DLCX_OK;
@@ -1551,6 +1552,11 @@ static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &de
 // recorded a largest |delta| outside the window in which fp16 is safe.  False: not applicable
 // (fewer basis blocks, or rows for fewer than 256 workgroups: such a matrix has always had the bf16
 // form), the caller goes on as usual.
+// Columns from which that kernel's producers hold three register sets, stages requested ahead, where a workgroup
+// has a unit to itself (8 basis blocks; two sets are 64 KB in flight there): 8192 x 8192 r = 256 four workers
+// 259 us, two sets 266; 8192 x 28672 751 | 780, 28672 x 8192 r = 190 820 | 837, but 8192 x 1024 78 | 77.  At 4
+// blocks it gained nothing (8192 x 4096 r = 100 147 | 145, 8192 x 8192 r = 66 195 | 194).
+constexpr int64_t kPDeep = 4096;
 static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                           const float *q_in, const PtrPack<float *> &out, void *workspace,
                           hipStream_t st, int *rc_out) {
@@ -1570,7 +1576,8 @@ static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<cons
             if (rc == DLCX_OK)
                 rc = project_p_ws_launch<2, 2, 2, 2>(pl, delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
         } else {
-            rc = project_p_ws_launch<1, 2, 4, 1>(pl, delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
+            rc = n >= kPDeep ? project_p_ws_launch<1, 2, 4, 1, 4, false, 3>(pl, delta, frags1, out, m, n, r, K, st, f.record, f.out_scale)
+                             : project_p_ws_launch<1, 2, 4, 1>(pl, delta, frags1, out, m, n, r, K, st, f.record, f.out_scale);
             if (rc == DLCX_OK)
                 rc = project_p_ws_launch<2, 2, 4, 1>(pl, delta, frags2, out, m, n, r, K, st, nullptr, nullptr, f.record);
         }

@@ -401,10 +401,14 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     for (int s = wave; s < nb; s += nw) {  // two at most
         f64x4_t x;
         load(x, s, s, 0);
-        for (int q = 1; q < nchunks; ++q) {
-            f64x4_t y;
-            load(y, s, s, q);
-            x += y;
+        for (int q = 1; q < nchunks; q += 8) {
+            f64x4_t y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) load(y[u], s, s, q + u < nchunks ? q + u : q);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) x[v] += q + u < nchunks ? y[u][v] : 0.0;
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -412,8 +416,8 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
             if (4 * v + g == col) dscale[16 * s + col] = x[v];
         }
     }
-    // chunk by chunk in order; with few blocks four chunks are requested before the first is added
-    constexpr int N = SLOTS <= 2 ? 4 : 1;
+    // chunk by chunk in order; with few blocks eight chunks are requested before the first is added
+    constexpr int N = SLOTS <= 2 ? 8 : 1;
     for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
         f64x4_t x[N][SLOTS];
 #pragma unroll

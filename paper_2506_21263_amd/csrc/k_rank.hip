@@ -467,8 +467,9 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
     }
     if (wave == 0) {
         const Interval in = gershgorin(tri, r, lane);
-        for (int i = lane; i < r; i += 64)  // filled up to whole blocks by the reader
-            tri_of(it)[i] = sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0);
+        for (int i = lane; i < 16 * sturm_blocks(r); i += 64)
+            tri_of(it)[i] = i < r ? sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0)
+                                  : sturm_fill();
         if (lane == 0) {
             bounds_of(it)[0] = in.lo;
             bounds_of(it)[1] = in.hi;
@@ -547,15 +548,17 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
                 __syncthreads();
             }
         }
-    for (int c = 0; c < nchunks; c += 2) {  // chunk by chunk in order, two requested at a time
-        double p[2][E];
+    // chunk by chunk in order, kAhead requested at a time (r = 32, 16 chunks: 5 us less than two at a time)
+    constexpr int kAhead = RC <= 32 ? 8 : 4;
+    for (int c = 0; c < nchunks; c += kAhead) {
+        double p[kAhead][E];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < kAhead; ++u)
 #pragma unroll
             for (int e = 0; e < E; ++e)
                 p[u][e] = it.part[(c + u < nchunks ? c + u : c) * rr + (from[e] < 0 ? 0 : from[e])];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < kAhead; ++u)
 #pragma unroll
             for (int e = 0; e < E; ++e) sum[e] += c + u < nchunks ? p[u][e] : 0.0;
     }
@@ -667,21 +670,22 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     }
 }
 
-// Ranks above kFusedRank: one wavefront per eigenvalue, 64 points a round.
+// Ranks above kFusedRank: G lanes per eigenvalue.  More lanes mean fewer rounds but more points in all (64 x 10,
+// 32 x 12, 16 x 14 per eigenvalue): as many as leave one wavefront to a SIMD, which two share at the price of
+// both (launch_effective_rank_batch).  All lanes of a wavefront read the same terms, through the scalar
+// cache.  Seven matrices at r = 256: EIGUS us at G = 32, 64 at G = 64.
+template <int G>
 __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
-    __shared__ double2 tri[DLCX_MAX_RANK + kSturmPad];
     const FactorItem it = batch.it[blockIdx.y];
     if (it.r <= kFusedRank) return;
     const int r = live_of(it);
-    if ((int)blockIdx.x * 4 >= r) return;
-    for (int i = threadIdx.x; i < 16 * sturm_blocks(r) + 8; i += 256)
-        tri[i] = i < r ? tri_of(it)[i] : sturm_fill();
-    __syncthreads();
+    const double2 *__restrict__ tri = tri_of(it);
     const int lane = threadIdx.x & 63;
-    const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (c >= r) return;
-    const double ev = nth_largest<64>(tri, r, c, bounds_of(it)[0], bounds_of(it)[1], lane);
-    if (lane == 0) eig_of(it)[c] = ev;
+    const int first = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * (64 / G);
+    if (first >= r) return;
+    const int c = first + lane / G;
+    const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, bounds_of(it)[0], bounds_of(it)[1], lane);
+    if (c < r && (lane & (G - 1)) == 0) eig_of(it)[c] = ev;
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {
@@ -728,9 +732,11 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
         if (rc != DLCX_OK) return rc;
     }
     int rmax = 0, rmin = DLCX_MAX_RANK;
+    int64_t values = 0;  // eigenvalues of ranks above kFusedRank
     bool rmid = false;
     for (int i = 0; i < batch.n; ++i) {
         const int r = batch.it[i].r;
+        values += r > kFusedRank ? r : 0;
         rmax = r > rmax ? r : rmax;
         rmin = r < rmin ? r : rmin;
         rmid = rmid || (r > 32 && r <= kFusedRank);
@@ -747,8 +753,14 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
             hipLaunchKernelGGL(tridiag_kernel<12>, grid, dim3(kTri), 0, st, summed);
         else
             hipLaunchKernelGGL(tridiag_kernel<16>, grid, dim3(kTri), 0, st, summed);
-        hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
-                           dim3(256), 0, st, summed);
+        auto eigenvalues = [&](auto kernel, int g) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(rmax * g, 256), (unsigned)batch.n), dim3(256), 0, st, summed);
+        };
+        constexpr int64_t kSimds = 1024;
+        if (values <= kSimds) eigenvalues(eigenvalues_kernel<64>, 64);
+        else if (values <= 2 * kSimds) eigenvalues(eigenvalues_kernel<32>, 32);
+        else if (values <= 4 * kSimds) eigenvalues(eigenvalues_kernel<16>, 16);
+        else eigenvalues(eigenvalues_kernel<8>, 8);
         hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
     }
     return check_launch("effective_rank");
