@@ -83,20 +83,25 @@ int gram_chunks(int64_t L) { return (int)ceil_div(L, kGramChunk); }
 // straight from memory, 64 consecutive bytes per row, and nothing waits at a barrier until the
 // four quarters are added in order at the end.
 // Bound by the fp64 matrix cores at high rank: seven factors of a 100B-class layer at r = 256
-// (77824 rows, 5.1 GFLOP over the upper triangle) take 117 us; through LDS tiles and vector
-// fp64 FMAs it was 200 us, and 40 us for a single 512 x 8 factor (64 barriers in a row), now 5.
-// The tiles of a chunk are consecutive workgroups of one XCD (every eighth workgroup of the grid), eight
-// chunks side by side: a chunk, 512 KB at r = 256, is read from memory once and 36 times from that XCD's L2.
+// (77824 rows, 5.4 GFLOP over the upper triangle, 69 us at the datasheet's rate) take 108 us (118 with one loop
+// for all tiles, whose branch copied accumulators); through LDS tiles and vector fp64 FMAs it was 200 us, and
+// 40 us for a single 512 x 8 factor (64 barriers in a row), now 5.
+// From kGroupedChunks on, the tiles of a chunk are consecutive workgroups of one XCD (every eighth workgroup of the
+// grid), eight chunks side by side: a chunk, 512 KB at r = 256, is read from memory once and 36 times from that
+// XCD's L2.  Fewer chunks would leave some XCDs with more of them than others, or with none: their tiles go to
+// all XCDs in turn.
+constexpr int kGroupedChunks = 64;
 template <int NB>
-__global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch, Places at, int tiles, int round) {
+__global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch, Places at, int tiles, bool grouped, int round) {
     __shared__ double red[4][NB * NB * 4][64];
-    const int slot = blockIdx.x >> 3;
-    int group = slot / tiles;  // of eight chunks
-    int t = slot - group * tiles;
-    const FactorItem it = batch.it[item_of(at, batch.n, group)];
-    const int r = it.r, chunk = 8 * group + (blockIdx.x & 7);
+    const int slot = grouped ? blockIdx.x >> 3 : blockIdx.x;
+    int chunk = slot / tiles, t = slot - chunk * tiles;
+    if (grouped) chunk = 8 * chunk + (blockIdx.x & 7);
+    if (chunk >= at.first[batch.n]) return;
+    const FactorItem it = batch.it[item_of(at, batch.n, chunk)];
+    const int r = it.r;
     const int nt = (r + 16 * NB - 1) / (16 * NB);
-    if (chunk >= it.nchunks || t >= nt * (nt + 1) / 2) return;
+    if (t >= nt * (nt + 1) / 2) return;
     if (second_round_idle(it, round)) return;
     const float *__restrict__ f = it.f;
     const int64_t L = it.L;
@@ -224,13 +229,15 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
     const int nb = max_r <= 16 ? 1 : 2;  // 16 x 16 blocks per side of a tile
     const int nt = (max_r + 16 * nb - 1) / (16 * nb);
     const int tiles = nt * (nt + 1) / 2;
-    const Places at = places_of(batch, [](const FactorItem &it) { return ceil_div(it.nchunks, 8); });
-    const dim3 grid((unsigned)at.first[batch.n] * 8u * (unsigned)tiles);
+    const Places at = places_of(batch, [](const FactorItem &it) { return it.nchunks; });
+    const int chunks = at.first[batch.n];
+    const bool grouped = chunks >= kGroupedChunks;
+    const dim3 grid((unsigned)(grouped ? ceil_div(chunks, 8) * 8 : chunks) * (unsigned)tiles);
     Timed timed(KID_GRAM, st);
     if (nb == 1)
-        hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, at, tiles, round);
+        hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, at, tiles, grouped, round);
     else
-        hipLaunchKernelGGL(gram_partial_kernel<2>, grid, dim3(kGT), 0, st, batch, at, tiles, round);
+        hipLaunchKernelGGL(gram_partial_kernel<2>, grid, dim3(kGT), 0, st, batch, at, tiles, grouped, round);
     int rc = check_launch("gram_partials");
     if (rc != DLCX_OK) return rc;
     *reduced = batch;
@@ -253,12 +260,12 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 //   every block with I > k:  J > k: -= X_J^T X_I ;  J <= k: -= X_I^T X_J  (X_k = V),
 //          operands from LDS in accumulator layout, no transposition anywhere;
 //   the diagonal's wavefront updates (k + 1, k + 1) first and factors it while the others are updating.
-// r^3 2/3 fp64 operations on one compute unit's matrix cores, 36 us at r = 256 at their rate.  A wavefront runs
-// through its blocks by a mask of those that a step concerns, and the loads and stores around the steps are a
-// handful of instructions a block: in the form before, which tested block indices and bounds one by one, the
-// kernel was 70 KB of instructions that came from memory once per launch (22 us to load the matrix), and the
-// wavefront that factored had updates of its own to do after it, for which all others waited.  r = 256 takes
-// CHOLUS us and r = 32 CHOL32 us (151 and 10 before that; row by row with the matrix in L2 / LDS: 2530 and 49 us).
+// r^3 2/3 fp64 operations on one compute unit's matrix cores, 36 us at r = 256 at their rate (64 clocks an
+// instruction).  A wavefront runs through its blocks by a mask of those that a step concerns; loads, scaling and
+// stores are a handful of instructions a block (70 KB of instructions before, fetched from memory once per launch:
+// 22 us to load the matrix); and the wavefront that factors has little else to do, where all waited for its
+// other updates.  r = 256 takes 104 us: 16 steps of 5 us, of which the products 3.3, panel and barriers 1.3, and 20
+// us around them (151 before; row by row with the matrix in L2: 2530); r = 32 12 us, as before.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;  // of a 16 x 16 block in LDS
@@ -272,54 +279,41 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// the values of the kG-th row of 16 lanes, in every row
-template <int kG>
-__device__ __forceinline__ double spread_row(double x) {
-    const uint64_t u = (uint64_t)__double_as_longlong(x);
-    uint32_t w[2] = {(uint32_t)u, (uint32_t)(u >> 32)};
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        w[i] = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false)[kG >> 1];
-        w[i] = __builtin_amdgcn_permlane16_swap(w[i], w[i], false, false)[kG & 1];
-    }
-    return __longlong_as_double((long long)(((uint64_t)w[1] << 32) | w[0]));
-}
-
 // V = L^-1 of a symmetric 16 x 16 block G = L L^T by one wavefront, both as accumulators: register q of
-// lane (g, col) = (lane / 16, lane % 16) is element (4 q + g, col).  Row j of [G | 1] is spread over the four
-// rows of lanes, a row's factor comes from its element in column j (row_bcast), and the pivot after is worked
-// out beside the updates that make it, by the same operations.  The square roots are left to the end.  Dead pivots
-// (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.  Writes V as the A operand of
-// the panel reads it (pitch kVPitch) and as an accumulator; returns whether one of the first `live` pivots was dead.
-// Bound by the chain from pivot to pivot, FACTORNEW clocks each beside a wavefront that keeps the matrix cores busy
-// (as products with one row of their operands in use: 480, a turn on the matrix cores after every pivot).
+// lane (g, col) = (lane / 16, lane % 16) is element (4 q + g, col).  Eliminating row j from [G | 1] is a product
+// with one row of the operands in use, -(row j) / pivot as A (G is symmetric) and row j as B, and row j of an
+// accumulator lies where both want row j % 4 of their four: no lane needs another's value but for the pivots.
+// The pivot after is worked out beside the product that makes its row, by the same operations.  The square roots
+// are left to the end.  Dead pivots (<= 1e-12, or not a number) eliminate nothing and leave a zero row of V.
+// Writes V as the A operand of the panel reads it (pitch kVPitch) and as an accumulator; returns whether one
+// of the first `live` pivots was dead.
+// Bound by the chain from pivot to pivot, 330 clocks each.  (Rows spread over the lanes by permlane and
+// updated by vector instructions, 70 of them a pivot: 109 us instead of 104 for the kernel below at r = 256;
+// not unrolled, with the registers selected by the row: 125.)
 __device__ __forceinline__ bool factor_block(f64x4_t t, double *va, double (*vb)[64], int lane, int live) {
     const int g = lane >> 4, col = lane & 15;
     f64x4_t u, own;  // the right half; the pivot of each row
 #pragma unroll
     for (int q = 0; q < 4; ++q) u[q] = 4 * q + g == col ? 1.0 : 0.0;
     double p = read_lane(t[0], 0);
-    unrolled<16>([&](auto jc) {
-        constexpr int j = decltype(jc)::value, q0 = j / 4, g0 = j % 4;
-        if (g == g0) own[q0] = p;
-        if constexpr (j < 15) {
-            constexpr int q1 = (j + 1) / 4, g1 = (j + 1) % 4;
-            const double row = spread_row<g0>(t[q0]), right = spread_row<g0>(u[q0]);
-            const double below = read_lane(t[q1], 16 * g1 + j), across = read_lane(row, j + 1);
-            const double next = read_lane(t[q1], 16 * g1 + j + 1);
-            double rp = __builtin_amdgcn_rcp(p);
-            rp = fma(fma(-p, rp, 1.0), rp, rp);
-            rp = fma(fma(-p, rp, 1.0), rp, rp);
-            rp = p > 1e-12 ? rp : 0.0;
-            p = fma(-(below * rp), across, next);
 #pragma unroll
-            for (int q = q0; q < 4; ++q) {
-                const double f = row_bcast<j>(t[q]) * (q > q0 || g > g0 ? rp : 0.0);  // rows that are done: none
-                t[q] = fma(-f, row, t[q]);
-                u[q] = fma(-f, right, u[q]);
-            }
-        }
-    });
+    for (int j = 0; j < 16; ++j) {
+        const int q = j / 4, q1 = (j + 1) / 4;
+        const bool mine = g == j % 4;
+        if (mine) own[q] = p;
+        if (j == 15) break;
+        double rp = __builtin_amdgcn_rcp(p);
+        rp = fma(fma(-p, rp, 1.0), rp, rp);
+        rp = fma(fma(-p, rp, 1.0), rp, rp);
+        rp = p > 1e-12 ? rp : 0.0;
+        const double x = read_lane(t[q], 16 * (j % 4) + j + 1);
+        const double d = read_lane(t[q1], 16 * ((j + 1) % 4) + j + 1);
+        p = fma(-x * rp, x, d);
+        const double row = mine ? t[q] : 0.0;
+        const double a = col > j ? -row * rp : 0.0;  // rows that are done keep what they have
+        t = mfma64(a, row, t);
+        u = mfma64(a, mine ? u[q] : 0.0, u);
+    }
     bool any = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -358,10 +352,10 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     const bool diagonal = wave == nw - 1;
     // Lane s: row and column of the block in slot s, or row -1, column 0: none.  (This factor may have fewer
     // blocks than the launch's largest.)
-    // A block each in turn, but `beside`, the wavefront on the SIMD of the diagonal's, is left out every third
-    // time: fp64 products hold up the fp64 arithmetic of the other wavefront of a SIMD, so it starts on its
-    // updates when the factorisation is done.
-    const int beside = nw > 4 ? nw - 5 : -1;
+    // A block each in turn.  With many, `beside`, the wavefront on the SIMD of the diagonal's, is left out every
+    // third time: fp64 products hold up the fp64 arithmetic of the other wavefront of a SIMD, so it starts on
+    // its updates when the factorisation is done.
+    const int beside = SLOTS > 6 ? nw - 5 : -1;
     int bI = -1, bJ = 0;
     if (!diagonal && lane < SLOTS) {
         const int others = nw - 1;
@@ -378,58 +372,69 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     auto col_of = [&](int s) { return __builtin_amdgcn_readlane(bJ, s); };
     // All blocks are held negated: what is taken from them is then added.
     f64x4_t t[SLOTS];
-    // This lane's elements of block (I, J), partial sum q.  The upper triangle is what is stored; past the edge
-    // the last row or column is read again.  Slot by slot: of addresses no more than one slot's are in
-    // registers.
-    auto load = [&](f64x4_t &to, int I, int J, int q) {
+    // Where this lane's elements of block (I, J) are in a partial sum.  The upper triangle is what is stored; past
+    // the edge the last row or column is read again.
+    auto place = [&](int (&at)[4], int I, int J) {
         const int y0 = 16 * I + col, x0 = 16 * J + g, y = y0 < r ? y0 : r - 1;
-        const double *src = part + q * rr;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int x = x0 + 4 * v < r ? x0 + 4 * v : r - 1;
-            to[v] = src[(x < y ? x : y) * r + (x < y ? y : x)];
+            at[v] = (x < y ? x : y) * r + (x < y ? y : x);
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
-    auto load_slot = [&](f64x4_t &to, int s, int q) { load(to, row_of(s) < 0 ? 0 : row_of(s), col_of(s), q); };
+    constexpr int kOnDiagonal = SLOTS <= 2 ? 1 : 2;  // blocks on the diagonal that a wavefront reads: wave, wave + nw
+    f64x4_t own[kOnDiagonal];
+    auto first = [&](f64x4_t &to, int (&at)[4], int I, int J) {
+        place(at, I, J);
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s) load_slot(t[s], s, 0);
+        for (int v = 0; v < 4; ++v) to[v] = part[at[v]];
+        if (SLOTS > 6) __builtin_amdgcn_sched_barrier(0);  // of addresses no more than one block's are in registers
+    };
+    int at[SLOTS][4], at_own[kOnDiagonal][4];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) first(t[s], at[s], row_of(s) < 0 ? 0 : row_of(s), col_of(s));
+#pragma unroll
+    for (int s = 0; s < kOnDiagonal; ++s) {
+        const int i = wave + nw * s < nb ? wave + nw * s : 0;
+        first(own[s], at_own[s], i, i);
+    }
+    // chunk by chunk in order; with few blocks five chunks are requested before the first is added
+    constexpr int N = SLOTS <= 2 ? 5 : 1;
+    for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
+        f64x4_t x[N][SLOTS], y[N][kOnDiagonal];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const double *src = part + (q + u < nchunks ? q + u : q) * rr;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) x[u][s][v] = src[at[s][v]];
+#pragma unroll
+                for (int s = 0; s < kOnDiagonal; ++s) y[u][s][v] = src[at_own[s][v]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool on = q + u < nchunks;
+#pragma unroll
+                for (int s = 0; s < SLOTS; ++s) t[s][v] += on ? x[u][s][v] : 0.0;
+#pragma unroll
+                for (int s = 0; s < kOnDiagonal; ++s) own[s][v] += on ? y[u][s][v] : 0.0;
+            }
+    }
     if (tid == 0) {
         any_dead = 0;
         factored = 0;
     }
-    for (int s = wave; s < nb; s += nw) {  // two at most
-        f64x4_t x;
-        load(x, s, s, 0);
-        for (int q = 1; q < nchunks; q += 8) {
-            f64x4_t y[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) load(y[u], s, s, q + u < nchunks ? q + u : q);
+    for (int s = 0; s < kOnDiagonal; ++s) {
+        const int i = wave + nw * s;
+        if (i >= nb) continue;
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] += q + u < nchunks ? y[u][v] : 0.0;
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            diag[s][v][lane] = x[v];
-            if (4 * v + g == col) dscale[16 * s + col] = x[v];
-        }
-    }
-    // chunk by chunk in order; with few blocks eight chunks are requested before the first is added
-    constexpr int N = SLOTS <= 2 ? 8 : 1;
-    for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
-        f64x4_t x[N][SLOTS];
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-#pragma unroll
-            for (int s = 0; s < SLOTS; ++s) load_slot(x[u][s], s, q + u < nchunks ? q + u : q);
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-#pragma unroll
-            for (int s = 0; s < SLOTS; ++s)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) t[s][v] += q + u < nchunks ? x[u][s][v] : 0.0;
+        for (int v = 0; v < 4; ++v)
+            if (4 * v + g == col) dscale[16 * i + col] = own[s][v];
     }
     __syncthreads();
     for (int q = tid; q < 16 * nb; q += blockDim.x) {
@@ -457,13 +462,13 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     };
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) scale(t[s], row_of(s) < 0 ? 0 : row_of(s), col_of(s));
-    for (int s = wave; s < nb; s += nw) {
-        f64x4_t x;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = diag[s][v][lane];
-        scale(x, s, s);
+    for (int s = 0; s < kOnDiagonal; ++s) {
+        const int i = wave + nw * s;
+        if (i >= nb) continue;
+        scale(own[s], i, i);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) diag[s][v][lane] = x[v];
+        for (int v = 0; v < 4; ++v) diag[i][v][lane] = own[s][v];
     }
     __syncthreads();
     double norm2 = 0.0;  // this lane's share of ||R^-1||_F^2 (of the scaled matrix)
@@ -572,7 +577,8 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 // elements 4 n .. 4 n + 3, element q feeds product q), so one element of W serves four products.  The column blocks are dealt so that every
 // wavefront gets long and short ones.
 // Bound by the fp64 matrix cores: seven factors of a 100B-class layer at r = 256 (77824 rows,
-// 5.1 GFLOP) take 130 us (vector fp64 FMAs with W through LDS: 598 us).
+// 5.4 GFLOP) take 113 us (four wavefronts and a workgroup for every 64 rows of the longest factor: 133; vector
+// fp64 FMAs with W through LDS: 598 us).
 template <int NW>  // wavefronts
 __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, Places at, int round) {
     extern __shared__ __attribute__((aligned(16))) float fl[];  // [16 nb][64]
@@ -650,11 +656,11 @@ __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, 
 // factorisation and P W as above for a single block, and the second round where the first asks for one.  All
 // sums are in the order of the kernels above: a batch takes this form if all of its factors are small, and what a
 // factor's result is does not hang on that.
-// Bound by latency.  One factor of 512 x 8: SMALLUS us instead of a chain of six launches, 27 us with the gaps
-// between them, of which the last three only read a mark; at the limits below it is still the shorter one
-// (512 .. 3072 x 8 .. 16, one to seven factors: SMALLRANGE).
+// Bound by latency.  Instead of a chain of six launches, of which the last three mostly only read a mark: 512 x 8
+// 9.7 us (25.2 in six), 512 x 16 9.5 (25.7), 1024 x 16 13.4 (25.0), 2048 x 8 18.5 (24.6), seven of 1536 x 16
+// 24 - 27 (26.8); at 3056 x 8 25.2 (24.5) it no longer pays, hence the limits.
 constexpr int kSmallRank = 16;
-constexpr int kSmallLength = 3072;
+constexpr int kSmallLength = 2048;
 constexpr int kSmallFloats = 24 * 1024;  // with the rows' padding, 96 KB
 constexpr int kSmallThreads = 512;
 static inline size_t small_bytes(int64_t L, int r) { return (size_t)r * (size_t)(L + 4) * sizeof(float); }
@@ -767,11 +773,12 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
         Timed timed(KID_CHOL, st);
         const int others = max_nb * (max_nb - 1) / 2, dealt = kCT / 64 - 1;
         const dim3 grid((unsigned)batch.n), threads((unsigned)(1 + (others < dealt ? others : dealt)) * 64);
-        static_assert(6 / 3 * 20 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
+        static_assert(kMaxBlocks <= 2 * (kCT / 64), "two blocks on the diagonal for every wavefront at most");
+        static_assert(6 * 7 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
         static_assert(18 / 3 * 20 >= kMaxBlocks * (kMaxBlocks - 1) / 2, "blocks of the largest rank");
         if (others <= 2 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
-        else if (others <= 6 / 3 * 20)
+        else if (others <= 6 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<6>, grid, threads, 0, st, summed, round);
         else
             hipLaunchKernelGGL(chol_inverse_kernel<18>, grid, threads, 0, st, summed, round);

@@ -481,9 +481,10 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
 // The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
 // a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
 // sums come from there depends on the batch).  Up to kSmallLength rows that is shorter than a launch before
-// this one: RANKSMALL
+// this one: 512 x 8 15.4 us instead of 17.7 for both, 512 x 16 22.0 (24.5), 1024 x 16 24.1 (25.5), but 1536 x 16
+// 26.3 (25.4) and 2048 x 8 21.5 (18.8).
 constexpr int kSmallGram = 16;
-constexpr int kSmallLength = 2048;
+constexpr int kSmallLength = 1024;
 constexpr int kGramQuarter = 128;
 __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGram][kSmallGram + 1]) {
     typedef double f64x4_t __attribute__((ext_vector_type(4)));
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
                 __syncthreads();
             }
         }
-    // chunk by chunk in order, kAhead requested at a time (r = 32, 16 chunks: 5 us less than two at a time)
+    // chunk by chunk in order, kAhead requested at a time (r = 32, 16 chunks: 49.9 us with the sums' launch, two at a time 51.8)
     constexpr int kAhead = RC <= 32 ? 8 : 4;
     for (int c = 0; c < nchunks; c += kAhead) {
         double p[kAhead][E];
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
 // Ranks above kFusedRank: G lanes per eigenvalue.  More lanes mean fewer rounds but more points in all (64 x 10,
 // 32 x 12, 16 x 14 per eigenvalue): as many as leave one wavefront to a SIMD, which two share at the price of
 // both (launch_effective_rank_batch).  All lanes of a wavefront read the same terms, through the scalar
-// cache.  Seven matrices at r = 256: EIGUS us at G = 32, 64 at G = 64.
+// cache.  Seven matrices at r = 256: 54 us at G = 32, 64 at G = 64.
 template <int G>
 __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
     const FactorItem it = batch.it[blockIdx.y];

@@ -521,8 +521,8 @@ def test_orthonormalize_leaves_the_columns_before_one_that_is_not_finite(L, r, v
             assert rel_l2(got[:col], (q * np.sign(np.diag(t))).T) <= 2.4e-7, col
 
 
-@pytest.mark.parametrize("L,r", [(16, 1), (16, 16), (48, 3), (512, 8), (528, 15), (1520, 16), (1536, 16), (3056, 8),
-                                 (3072, 7), (3088, 2)])
+@pytest.mark.parametrize("L,r", [(16, 1), (16, 16), (48, 3), (512, 8), (528, 15), (1024, 16), (1040, 9), (1520, 16),
+                                 (1536, 16), (2048, 7), (2064, 2)])
 @pytest.mark.parametrize("cond", [3.0, 1e5])
 def test_small_factors_alone_and_in_a_batch_with_large_ones(L, r, cond):
     # A batch of factors of at most 16 columns that fit in LDS is orthonormalised, and measured, by one launch; in
