@@ -671,22 +671,21 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     }
 }
 
-// Ranks above kFusedRank: G lanes per eigenvalue.  More lanes mean fewer rounds but more points in all (64 x 10,
-// 32 x 12, 16 x 14 per eigenvalue): as many as leave one wavefront to a SIMD, which two share at the price of
-// both (launch_effective_rank_batch).  All lanes of a wavefront read the same terms, through the scalar
-// cache.  Seven matrices at r = 256: 54 us at G = 32, 64 at G = 64.
-template <int G>
+// Ranks above kFusedRank: one wavefront per eigenvalue, 64 points a round.  All lanes read the same terms, through
+// the scalar cache.  Bound by the instructions of the sequence, four a term, two wavefronts to some SIMDs: 64 us
+// for seven matrices at r = 256.  (32 lanes per eigenvalue, one wavefront to a SIMD: 54 us, but how many lanes there
+// are for one would then depend on the batch, and with it the last bit of an eigenvalue, which decides where tau
+// falls on a whole number of equal ones.)
 __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
     const FactorItem it = batch.it[blockIdx.y];
     if (it.r <= kFusedRank) return;
     const int r = live_of(it);
     const double2 *__restrict__ tri = tri_of(it);
     const int lane = threadIdx.x & 63;
-    const int first = (blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * (64 / G);
-    if (first >= r) return;
-    const int c = first + lane / G;
-    const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, bounds_of(it)[0], bounds_of(it)[1], lane);
-    if (c < r && (lane & (G - 1)) == 0) eig_of(it)[c] = ev;
+    const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (c >= r) return;
+    const double ev = nth_largest<64>(tri, r, c, bounds_of(it)[0], bounds_of(it)[1], lane);
+    if (lane == 0) eig_of(it)[c] = ev;
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {
@@ -733,11 +732,9 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
         if (rc != DLCX_OK) return rc;
     }
     int rmax = 0, rmin = DLCX_MAX_RANK;
-    int64_t values = 0;  // eigenvalues of ranks above kFusedRank
     bool rmid = false;
     for (int i = 0; i < batch.n; ++i) {
         const int r = batch.it[i].r;
-        values += r > kFusedRank ? r : 0;
         rmax = r > rmax ? r : rmax;
         rmin = r < rmin ? r : rmin;
         rmid = rmid || (r > 32 && r <= kFusedRank);
@@ -754,14 +751,8 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
             hipLaunchKernelGGL(tridiag_kernel<12>, grid, dim3(kTri), 0, st, summed);
         else
             hipLaunchKernelGGL(tridiag_kernel<16>, grid, dim3(kTri), 0, st, summed);
-        auto eigenvalues = [&](auto kernel, int g) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(rmax * g, 256), (unsigned)batch.n), dim3(256), 0, st, summed);
-        };
-        constexpr int64_t kSimds = 1024;
-        if (values <= kSimds) eigenvalues(eigenvalues_kernel<64>, 64);
-        else if (values <= 2 * kSimds) eigenvalues(eigenvalues_kernel<32>, 32);
-        else if (values <= 4 * kSimds) eigenvalues(eigenvalues_kernel<16>, 16);
-        else eigenvalues(eigenvalues_kernel<8>, 8);
+        hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
+                           dim3(256), 0, st, summed);
         hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
     }
     return check_launch("effective_rank");
