@@ -195,7 +195,7 @@ struct FactorItem {
     int32_t r, nchunks;
     double *part;    // nchunks x r x r partial Gram sums (upper triangles)
     double *g;       // g[0]: the mark of the orthonormalisation; or the tridiagonal matrix (k_rank.hip)
-    double *w;       // r x r: inverse factor (orthonormalisation only)
+    double *w;       // r x r: transpose of the inverse factor (orthonormalisation only)
     int32_t *out;    // r' (effective rank only)
 };
 struct FactorBatch {

@@ -1,7 +1,7 @@
 // Orthonormalisation of the averaged factor P_bar (L x r, stored r x L): the thin-QR Q-factor
 // with positive diagonal of R, as CholeskyQR with all small-matrix work in fp64:
 //   1. G = P^T P as fp64 partial sums over chunks of L (fixed chunking, summed in chunk order)
-//   2. one workgroup: scale G to unit diagonal, Cholesky G = R^T R, W = R^-1  (r x r, fp64)
+//   2. one workgroup: scale G to unit diagonal, Cholesky G = R^T R, W = R^-1  (r x r, fp64, kept as W^T)
 //   3. P <- P W, in place, fp64 accumulation
 // Scaling the columns of P does not change the Q-factor, and makes the Cholesky factorisation
 // insensitive to the very different column norms a warm-started basis produces.  A pivot of the
@@ -21,7 +21,7 @@
 // work per matrix is small and latency-bound, so the matrices of a stage go through each step
 // together, one workgroup (or one slice of the grid) per matrix.  What a factor's result is made of
 // does not depend on the batch it comes in, but for the rounding of the norm behind the mark (added
-// up per wavefront, of which there are as many as the largest rank of the batch asks for): whether the
+// up per wavefront, of which there are as many as the largest rank of the batch asks for, or by one): whether the
 // second round runs is the batch's where that norm is within rounding of kOneRoundNorm.
 #include <type_traits>
 

@@ -304,6 +304,26 @@ def test_project_p_and_q_fp16_form(m, n, r, K, group):
     test_project_p_and_q(dlcx.MMA_F16, m, n, r, K, group)
 
 
+@pytest.mark.parametrize("n", [4080, 4096, 4112, 4160, 4224])
+def test_project_p_fp16_form_with_three_stages_ahead(n):
+    # From 4096 columns on the producers of the fp16 P projection at 8 basis blocks hold three stages: numbers of
+    # stages of 64 columns that leave 0, 1 and 2 over, a ragged one, and the size before the line.  Operands
+    # rounded to 11 bits once, sums in random order: 2^-12 x sqrt(2) of the result, twice that is allowed.
+    m, r, K = 4096, 130, 8
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    deltas = [1e-2 * torch.randn(m, n, generator=g, device=DEV) for _ in range(K)]
+    basis = torch.randn(r, n, generator=g, device=DEV)
+    out = [torch.zeros(r, m, device=DEV) for _ in range(K)]
+    d = dlcx.desc(m, n, r, 4, 16, dlcx.MMA_F16)
+    dlcx.dlcx_project(d, dlcx.PHASE_P, deltas, basis, out, ws_for(d, K))
+    for x, y in zip(deltas, out):
+        want = basis.double() @ x.double().T.contiguous()
+        rms = want.square().mean().sqrt()
+        assert float((y.double() - want).norm() / want.norm()) <= 7e-4
+        assert float(((y.double() - want).abs() / torch.maximum(want.abs(), rms)).max()) <= 8 * 7e-4
+
+
 def test_fp16_form_is_the_bf16_form_up_to_rank_64():
     m, n, r, K, group = 1024, 768, 64, 4, 128
     inp, deltas = _lowrank_inputs(m, n, r, K, seed=5)
