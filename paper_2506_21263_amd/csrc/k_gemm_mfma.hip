@@ -353,15 +353,19 @@ constexpr bool kApartP = NS >= 2 && BLOCKS <= 2;
 // LONE: as many where it has two, if there are no two workgroups to a compute unit (registers).
 template <int NS, int BLOCKS, bool LONE>
 constexpr int kChainsP = NS >= 2 && BLOCKS <= (LONE ? 2 : 1) ? 2 : 1;
+// Wavefronts to a SIMD that the registers have to leave room for: two workgroups to a compute unit at up to 4
+// basis blocks, that is 128 registers.  Left to itself the compiler takes 130 for three of these kernels, and a
+// workgroup has its unit to itself.  Two pieces, us with one | two to a unit: 28672 x 8192 four workers r = 100
+// 943 | 884, r = 24 656 | 632; 8192 x 8192 r = 100 five workers 410 | 386, eight 503 | 483.  At ranks 33 .. 64
+// it goes either way: 8192 x 2048 six workers r = 64 102 | 95, 28672 x 2048 two workers r = 40 105 | 99, but
+// where few units get a second workgroup 8192 x 8192 five workers 283 | 313, 16384 x 4096 three 173 | 192.
+template <int NS, int BLOCKS, bool LONE>
+constexpr int kWavesP = NS <= 2 && BLOCKS <= 4 && !LONE ? 4 : 1;
 template <int NS, int CBW, int WC, int WR, int RB, bool LONE, int kSets = 2>
-__global__ __launch_bounds__(kWs) void project_p_ws_kernel(PtrPack<const float *> deltas,
-                                                           const uint4 *__restrict__ afrags,
-                                                           PtrPack<float *> outs, int64_t m,
-                                                           int64_t n, int r, int64_t stages_per_wg,
-                                                           int64_t slab_stride,
-                                                           uint32_t *__restrict__ amax_record,
-                                                           const float *__restrict__ out_scale,
-                                                           const uint32_t *__restrict__ guard) {
+__global__ __launch_bounds__(kWs, (kWavesP<NS, CBW * WC, LONE>)) void project_p_ws_kernel(
+    PtrPack<const float *> deltas, const uint4 *__restrict__ afrags, PtrPack<float *> outs, int64_t m, int64_t n,
+    int r, int64_t stages_per_wg, int64_t slab_stride, uint32_t *__restrict__ amax_record,
+    const float *__restrict__ out_scale, const uint32_t *__restrict__ guard) {
     constexpr int CB = CBW * WC;
     constexpr int RBW = RB / WR;
     constexpr int kRows = 32 * RB;

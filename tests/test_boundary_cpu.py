@@ -5,7 +5,10 @@ import ctypes as C
 import os
 import random
 import re
+import struct
+import subprocess
 
+import msgpack
 import pytest
 
 import paper_2506_21263_amd as dlcx
@@ -231,3 +234,42 @@ def test_static_scratch_entry_point_limits_and_argument_errors():
     bad = (C.c_void_p * 2)(fake, None)
     assert L.dlcx_average_static(C.byref(ok), 0, 2, bad, arr, fake, None) == dlcx.EINVAL
     assert L.dlcx_strerror(dlcx.ETOOBIG) == b"larger than the fixed scratch of this entry point"
+
+
+def kernel_metadata():
+    """What the compiler noted for every kernel in the library: demangled name -> its entry."""
+    blob, found = open(dlcx.LIB_PATH, "rb").read(), {}
+    for at in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
+        entries, pos = struct.unpack_from("<Q", blob, at.start() + 24)[0], at.start() + 32
+        for _ in range(entries):
+            offset, size, length = struct.unpack_from("<QQQ", blob, pos)
+            target, pos = blob[pos + 24:pos + 24 + length], pos + 24 + length
+            if b"gfx950" not in target:
+                continue
+            elf = blob[at.start() + offset:at.start() + offset + size]
+            phoff, = struct.unpack_from("<Q", elf, 32)
+            phsize, phnum = struct.unpack_from("<HH", elf, 54)
+            for i in range(phnum):
+                kind, _, start, _, _, filesz = struct.unpack_from("<IIQQQQ", elf, phoff + i * phsize)
+                if kind != 4:  # PT_NOTE
+                    continue
+                namesz, descsz, _ = struct.unpack_from("<III", elf, start)
+                desc = start + 12 + (namesz + 3) // 4 * 4
+                for k in msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]:
+                    found[k[".name"]] = k
+    names = subprocess.run(["c++filt"], input="\n".join(found), capture_output=True, text=True, check=True)
+    return dict(zip(names.stdout.split("\n"), found.values()))
+
+
+def test_two_workgroups_of_the_short_p_projections_share_a_unit():
+    # A workgroup has two wavefronts for every SIMD and 512 registers there are: where the plans count
+    # on two workgroups to a compute unit (at most two pieces, at most 4 basis blocks, not the form for
+    # a workgroup alone), a wavefront may have 128, none of them spilled.
+    seen = 0
+    for name, k in kernel_metadata().items():
+        m = re.search(r"project_p_ws_kernel<(\d+), (\d+), (\d+), \d+, \d+, (true|false), \d+>", name)
+        if not m or int(m[1]) > 2 or int(m[2]) * int(m[3]) > 4 or m[4] == "true":
+            continue
+        seen += 1
+        assert k[".vgpr_count"] <= 128 and k[".vgpr_spill_count"] == 0, (name, k)
+    assert seen == 5
