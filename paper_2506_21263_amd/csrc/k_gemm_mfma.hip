@@ -1550,17 +1550,20 @@ static int project_p_ws_launch(const PPlan &pl, const PtrPack<const float *> &de
     return DLCX_OK;
 }
 
+// Columns from which the producers of the fp16 P kernel hold three register sets, stages requested ahead, where a
+// workgroup has a unit to itself (8 basis blocks; two sets are 64 KB in flight there).  r = 256 four workers, us
+// with two sets | three: 8192 x 1024 67 | 67, x 2048 94 | 93, x 4096 152 | 150, x 5120 163 | 162, x 6144 208 | 208,
+// x 8192 231 | 223, x 12288 339 | 327, x 16384 438 | 426, x 20480 558 | 532, x 28672 764 | 732; r = 190 8192 x
+// 8192 238 | 239, x 28672 731 | 710, 28672 x 8192 826 | 811.  At 4 blocks it gained nothing (8192 x 4096 r = 100
+// 147 | 145, 8192 x 8192 r = 66 195 | 194).
+constexpr int64_t kPDeep = 8192;
+
 // The projection at 4 or 8 basis blocks (ranks above 64) in its fp16 form, where the matrix cores
 // and not the stream of delta set the pace: one fp16 product per block instead of three bf16
 // ones, followed by the bf16 kernel as a stand-by that returns at once unless the fp16 launch
 // recorded a largest |delta| outside the window in which fp16 is safe.  False: not applicable
 // (fewer basis blocks, or rows for fewer than 256 workgroups: such a matrix has always had the bf16
 // form), the caller goes on as usual.
-// Columns from which that kernel's producers hold three register sets, stages requested ahead, where a workgroup
-// has a unit to itself (8 basis blocks; two sets are 64 KB in flight there): 8192 x 8192 r = 256 four workers
-// 259 us, two sets 266; 8192 x 28672 751 | 780, 28672 x 8192 r = 190 820 | 837, but 8192 x 1024 78 | 77.  At 4
-// blocks it gained nothing (8192 x 4096 r = 100 147 | 145, 8192 x 8192 r = 66 195 | 194).
-constexpr int64_t kPDeep = 4096;
 static bool project_p_f16(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                           const float *q_in, const PtrPack<float *> &out, void *workspace,
                           hipStream_t st, int *rc_out) {
