@@ -236,13 +236,16 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// What tridiag_kernel leaves in FactorItem::g above rank 64: (d_i, e_i^2) scaled, from double 0;
-// then lo, hi and the number of rows that are not zero; then the eigenvalues (still scaled: r' does not
-// depend on a power of two).
+// What tridiag_kernel leaves in FactorItem::g above rank 64: the Sturm table with all that count_below reads,
+// from double 0; then lo, hi and the number of rows that are not zero; then the eigenvalues (still scaled: r'
+// does not depend on a power of two), which eigenvalues_kernel writes while it reads the table.
+constexpr int kTableTerms = DLCX_MAX_RANK + 8;
+static_assert(kTableTerms >= (DLCX_MAX_RANK + 15) / 16 * 16 + 8, "whole blocks and the half block after them");
+static_assert(2 * kTableTerms + 8 + DLCX_MAX_RANK <= (kFusedRank + 2) * (kFusedRank + 2), "room in the smallest g");
 __device__ __forceinline__ double2 *tri_of(const FactorItem &it) { return reinterpret_cast<double2 *>(it.g); }
-__device__ __forceinline__ double *bounds_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK; }
+__device__ __forceinline__ double *bounds_of(const FactorItem &it) { return it.g + 2 * kTableTerms; }
 __device__ __forceinline__ int live_of(const FactorItem &it) { return __builtin_amdgcn_readfirstlane((int)bounds_of(it)[2]); }
-__device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * DLCX_MAX_RANK + 8; }
+__device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * kTableTerms + 8; }
 
 // Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
 // S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (h, ti, tj) holds element
@@ -467,7 +470,7 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
     }
     if (wave == 0) {
         const Interval in = gershgorin(tri, r, lane);
-        for (int i = lane; i < 16 * sturm_blocks(r); i += 64)
+        for (int i = lane; i < 16 * sturm_blocks(r) + 8; i += 64)
             tri_of(it)[i] = i < r ? sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0)
                                   : sturm_fill();
         if (lane == 0) {

@@ -594,6 +594,24 @@ def test_small_factor_that_is_not_finite_or_has_no_rank(value):
     assert np.isnan(got[9:]).all() and rel_l2(got[:9], want[:9]) <= 2.4e-7
 
 
+@pytest.mark.parametrize("r", [65, 240, 241, 256])
+def test_sturm_table_ends_behind_all_that_is_read_of_it(r):
+    # Above rank 64 the eigenvalues are found from a table in the workspace, read in whole blocks of 16 terms and
+    # half a block further while other wavefronts write their eigenvalues there: all that is read has to be terms,
+    # those past the matrix (4, 0), and none of them an eigenvalue.
+    L = 256
+    A = rng(r).standard_normal((r, L)).astype(np.float32)
+    ws = torch.full((dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1),), 165, device=DEV, dtype=torch.uint8)
+    out = torch.zeros(1, device=DEV, dtype=torch.int32)
+    dlcx.dlcx_effective_rank(L, r, to_dev(A), 1.0, out, ws)
+    g = to_np(ws)[(r * r + 1) // 2 * 16:].view(np.float64)  # behind the partial sums, one chunk
+    last = (r + 15) // 16 * 16 + 8
+    table = g[:2 * last].reshape(last, 2)
+    assert (np.abs(table[:r, 0]) <= 1).all() and (table[:r, 1] <= 0).all()
+    assert (table[r:] == (4.0, 0.0)).all()
+    assert int(out.item()) == r
+
+
 def test_orthonormalize_degenerate_columns():
     L, r = 256, 6
     g = rng(3)
