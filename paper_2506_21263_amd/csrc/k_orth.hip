@@ -56,6 +56,10 @@ __device__ __forceinline__ bool second_round_idle(const FactorItem &it, int roun
 struct Places {
     int first[kMaxBatch + 1];
 };
+// A launch has less than 2^32 threads along x: longer rows of chunks (36 tiles of 256 threads each at most) and
+// of apply_w's workgroups (512 threads at most) go on along y.
+constexpr int kMostChunks = 1 << 18;
+constexpr int kMostRows = 1 << 22;
 // The item that `place` belongs to, by every wavefront for itself; `place` becomes the place inside it.
 __device__ __forceinline__ int item_of(const Places &at, int n, int &place) {
     const int lane = threadIdx.x & 63;
@@ -97,6 +101,7 @@ __global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch,
     const int slot = grouped ? blockIdx.x >> 3 : blockIdx.x;
     int chunk = slot / tiles, t = slot - chunk * tiles;
     if (grouped) chunk = 8 * chunk + (blockIdx.x & 7);
+    chunk += blockIdx.y * kMostChunks;
     if (chunk >= at.first[batch.n]) return;
     const FactorItem it = batch.it[item_of(at, batch.n, chunk)];
     const int r = it.r;
@@ -232,7 +237,9 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
     const Places at = places_of(batch, [](const FactorItem &it) { return it.nchunks; });
     const int chunks = at.first[batch.n];
     const bool grouped = chunks >= kGroupedChunks;
-    const dim3 grid((unsigned)(grouped ? ceil_div(chunks, 8) * 8 : chunks) * (unsigned)tiles);
+    static_assert(kMostChunks % 8 == 0, "whole groups");
+    const int row = chunks < kMostChunks ? chunks : kMostChunks;
+    const dim3 grid((unsigned)(grouped ? ceil_div(row, 8) * 8 : row) * (unsigned)tiles, (unsigned)ceil_div(chunks, kMostChunks));
     Timed timed(KID_GRAM, st);
     if (nb == 1)
         hipLaunchKernelGGL(gram_partial_kernel<1>, grid, dim3(kGT), 0, st, batch, at, tiles, grouped, round);
@@ -582,7 +589,8 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 template <int NW>  // wavefronts
 __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, Places at, int round) {
     extern __shared__ __attribute__((aligned(16))) float fl[];  // [16 nb][64]
-    int place = blockIdx.x;
+    int place = blockIdx.y * kMostRows + blockIdx.x;
+    if (place >= at.first[batch.n]) return;
     const FactorItem it = batch.it[item_of(at, batch.n, place)];
     const int64_t L = it.L;
     const int64_t i0 = (int64_t)place * 64;
@@ -791,7 +799,8 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
         int rc = grant_dynamic_lds(reinterpret_cast<const void *>(kernel), a_bytes, granted, "apply_w attribute");
         if (rc != DLCX_OK) return rc;
         Timed timed(KID_APPLY_W, st);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)at.first[batch.n]), dim3(64 * waves), a_bytes, st, batch, at, round);
+        const int rows = at.first[batch.n], row = rows < kMostRows ? rows : kMostRows;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)row, (unsigned)ceil_div(rows, kMostRows)), dim3(64 * waves), a_bytes, st, batch, at, round);
         return check_launch("apply_w");
     };
     static size_t granted4 = 0, granted8 = 0;

@@ -612,6 +612,26 @@ def test_sturm_table_ends_behind_all_that_is_read_of_it(r):
     assert int(out.item()) == r
 
 
+def test_a_very_long_factor_in_a_batch_with_one_of_large_rank():
+    # The launches have as many workgroups as the long factor has chunks, each as many threads as the high rank
+    # asks for, more than 2^32 threads together: the Gram sums of r' and of the orthonormalisation, and P W.
+    L = (1 << 29) + 16
+    descs = [dlcx.desc(L, L, 1, 4, 16), dlcx.desc(256, 256, 256, 4, 16)]
+    ws = torch.empty(dlcx.dlcx_batched_workspace_bytes(descs), device=DEV, dtype=torch.uint8)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(29)
+    f = [torch.randn(1, L, generator=g, device=DEV), torch.randn(256, 256, generator=g, device=DEV)]
+    want = f[0] / torch.linalg.vector_norm(f[0], dtype=torch.float64)
+    small = f[1].clone()
+    out = torch.zeros(2, device=DEV, dtype=torch.int32)
+    dlcx.dlcx_effective_rank_batched(descs, f, 1.0, out, ws)
+    dlcx.dlcx_orthonormalize_batched(descs, f, ws)
+    dlcx.dlcx_orthonormalize_batched(descs[1:], [small], ws)
+    assert out.tolist() == [1, 256]
+    assert float(torch.linalg.vector_norm(f[0] - want)) <= 2.4e-7  # the rounding to fp32, as above
+    assert torch.equal(f[1], small)
+
+
 def test_orthonormalize_degenerate_columns():
     L, r = 256, 6
     g = rng(3)
