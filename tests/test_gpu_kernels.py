@@ -612,6 +612,30 @@ def test_sturm_table_ends_behind_all_that_is_read_of_it(r):
     assert int(out.item()) == r
 
 
+@pytest.mark.parametrize("L,ranks", [
+    (1040, [20, 3, 33]),                  # equal lengths: a row of the grid each
+    (4096, [33, 20, 64, 7, 40, 33, 33, 33]),    # .. of whole groups of eight chunks
+    (5120, [33, 40, 17, 64, 33, 33, 130]),      # 70 chunks, not in groups of eight: looked up
+    (36880, [17]),                        # a row that ends within a group
+])
+def test_batches_of_equal_lengths_are_their_factors_one_by_one(L, ranks):
+    g = rng(L)
+    descs = [dlcx.desc(L, L, r, 4, 16) for r in ranks]
+    ws = torch.empty(dlcx.dlcx_batched_workspace_bytes(descs), device=DEV, dtype=torch.uint8)
+    A = [g.standard_normal((r, L)).astype(np.float32) for r in ranks]
+    f, out = [to_dev(a) for a in A], torch.zeros(len(ranks), device=DEV, dtype=torch.int32)
+    dlcx.dlcx_effective_rank_batched(descs, f, 0.9, out, ws)
+    dlcx.dlcx_orthonormalize_batched(descs, f, ws)
+    for i, r in enumerate(ranks):
+        one, alone = torch.zeros(1, device=DEV, dtype=torch.int32), to_dev(A[i])
+        dlcx.dlcx_effective_rank(L, r, alone, 0.9, one, ws)
+        dlcx.dlcx_orthonormalize(L, r, alone, ws)
+        assert torch.equal(alone, f[i]) and int(one.item()) == int(out[i].item()), i
+        q, t = np.linalg.qr(A[i].T.astype(np.float64))
+        assert rel_l2(to_np(f[i]), (q * np.sign(np.diag(t))).T) <= 2.4e-7, i
+        assert int(out[i].item()) == ref.effective_rank(A[i], 0.9), i
+
+
 def test_a_very_long_factor_in_a_batch_with_one_of_large_rank():
     # The launches have as many workgroups as the long factor has chunks, each as many threads as the high rank
     # asks for, more than 2^32 threads together: the Gram sums of r' and of the orthonormalisation, and P W.
