@@ -357,6 +357,14 @@ __device__ __forceinline__ bool factor_block(f64x4_t t, double *va, double (*vb)
     return __ballot(any) != 0;
 }
 
+// Blocks of a side that SLOTS of every wavefront but the diagonal's have room for.  What a workgroup takes of LDS
+// hangs on it: 25 KB up to r = 64, 29 to 80, 45 to 144, else 74.
+constexpr int most_blocks(int slots) {
+    int nb = 1;
+    while (nb < kMaxBlocks && (nb + 1) * nb / 2 <= slots * (kCT / 64 - 1)) ++nb;
+    return slots > 6 ? kMaxBlocks : nb;
+}
+
 template <int SLOTS>
 __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, int round) {
     const FactorItem it = batch.it[blockIdx.x];
@@ -364,9 +372,10 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
     const int r = it.r, nchunks = it.nchunks;
     const double *__restrict__ part = it.part;
     double *__restrict__ w = it.w;
-    __shared__ double dscale[DLCX_MAX_RANK];  // 1 / column norm (0 for a zero column)
-    __shared__ double panel[kMaxBlocks][4][64];
-    __shared__ double diag[kMaxBlocks][4][64];  // the blocks on the diagonal
+    constexpr int kBlocks = most_blocks(SLOTS);  // of a side
+    __shared__ double dscale[16 * kBlocks];   // 1 / column norm (0 for a zero column)
+    __shared__ double panel[kBlocks][4][64];
+    __shared__ double diag[kBlocks][4][64];   // the blocks on the diagonal
     __shared__ double va[2][16 * kVPitch];    // V of even and odd steps, as A operand ..
     __shared__ double vb[2][4][64];           // .. and as accumulator
     __shared__ double red[kCT / 64];
@@ -426,8 +435,10 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
         const int i = wave + nw * s < nb ? wave + nw * s : 0;
         first(own[s], at_own[s], i, i);
     }
-    // chunk by chunk in order; with few blocks five chunks are requested before the first is added
-    constexpr int N = SLOTS <= 2 ? 5 : 1;
+    // Chunk by chunk in order; with few blocks three chunks are requested before the first is added.  Of what is
+    // requested and not there nothing is added, but it takes as long: with five, 2048 x 64 37.1 us and 8192 x 32
+    // 29.3, with three 35.3 and 28.2, the whole orthonormalisation.
+    constexpr int N = SLOTS <= 2 ? 3 : 1;
     for (int q = 1; SLOTS <= 6 && q < nchunks; q += N) {  // above there is one: kSumRank
         f64x4_t x[N][SLOTS], y[N][kOnDiagonal];
 #pragma unroll
@@ -809,15 +820,18 @@ static int cholqr_round(const FactorBatch &batch, int round, hipStream_t st) {
         if (nb > max_nb) max_nb = nb;
     }
     {
-        // a wavefront for the diagonal blocks, up to seven for the others; blocks of each: 2 up to r = 80,
-        // 6 up to r = 144, else 18
+        // A wavefront for the diagonal blocks, up to seven for the others; blocks of each: 1 up to r = 64, 2 up to
+        // r = 80, 6 up to r = 144, else 18.  (Slots without a block load and add like the others: at r = 48 two to
+        // a wavefront took 31.0 us, one 29.5.)
         Timed timed(KID_CHOL, st);
         const int others = max_nb * (max_nb - 1) / 2, dealt = kCT / 64 - 1;
         const dim3 grid((unsigned)batch.n), threads((unsigned)(1 + (others < dealt ? others : dealt)) * 64);
         static_assert(kMaxBlocks <= 2 * (kCT / 64), "two blocks on the diagonal for every wavefront at most");
         static_assert(6 * 7 >= (kSumRank / 16) * (kSumRank / 16 - 1) / 2, "ranks that sum chunks have at most 6");
         static_assert(18 / 3 * 20 >= kMaxBlocks * (kMaxBlocks - 1) / 2, "blocks of the largest rank");
-        if (others <= 2 * dealt)
+        if (others <= dealt)
+            hipLaunchKernelGGL(chol_inverse_kernel<1>, grid, threads, 0, st, summed, round);
+        else if (others <= 2 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<2>, grid, threads, 0, st, summed, round);
         else if (others <= 6 * dealt)
             hipLaunchKernelGGL(chol_inverse_kernel<6>, grid, threads, 0, st, summed, round);

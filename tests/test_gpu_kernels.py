@@ -612,6 +612,31 @@ def test_sturm_table_ends_behind_all_that_is_read_of_it(r):
     assert int(out.item()) == r
 
 
+@pytest.mark.parametrize("L,r", [
+    (8192, 8), (7696, 16), (3600, 17), (4112, 24), (8192, 32), (3088, 33), (2048, 64), (1024, 90),  # 16 .. 2 chunks,
+    (8208, 32), (2064, 64), (1040, 90),  # .. added up by the kernels that use them; past the lines: beforehand
+])
+def test_sums_over_many_chunks(L, r):
+    # The partial sums of 512 elements each are requested several at a time.  Most of row k lies in chunk k modulo
+    # their number: a sum that is left out or counted twice takes or doubles whole rows.
+    g = rng(L + 11 * r)
+    chunks = -(-L // 512)
+    A = 0.1 * g.standard_normal((r, L))
+    for k in range(r):
+        c = k % chunks
+        A[k, 512 * c: 512 * c + 512] += g.standard_normal(min(512, L - 512 * c))
+    A = np.ascontiguousarray((A * np.arange(1, r + 1)[:, None] ** -0.3).astype(np.float32))
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(L, L, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    d_A = to_dev(A)
+    for tau in np.arange(0.05, 1.0, 0.1):
+        dlcx.dlcx_effective_rank(L, r, d_A, tau, out, ws)
+        assert int(out.item()) == ref.effective_rank(A, tau), tau
+    dlcx.dlcx_orthonormalize(L, r, d_A, ws)
+    q, t = np.linalg.qr(A.T.astype(np.float64))
+    assert rel_l2(to_np(d_A), (q * np.sign(np.diag(t))).T) <= 2.4e-7
+
+
 @pytest.mark.parametrize("L,ranks", [
     (1040, [20, 3, 33]),                  # equal lengths: a row of the grid each
     (4096, [33, 20, 64, 7, 40, 33, 33, 33]),    # .. of whole groups of eight chunks
