@@ -552,8 +552,10 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
                 __syncthreads();
             }
         }
-    // chunk by chunk in order, kAhead requested at a time (r = 32, 16 chunks: 49.9 us with the sums' launch, two at a time 51.8)
-    constexpr int kAhead = RC <= 32 ? 8 : 4;
+    // Chunk by chunk in order, kAhead requested at a time, with the sums' launch, us at two | four | eight:
+    // 8192 x 32 49.3 | 48.6 | 48.9, 2048 x 8 17.6 | 17.3 | 18.3, 512 x 32 45.9 | 46.1 | 46.9; with 64 columns two |
+    // four: 512 x 48 78.2 | 79.5, 2048 x 64 106.4 | 106.7.
+    constexpr int kAhead = RC <= 32 ? 4 : 2;
     for (int c = 0; c < nchunks; c += kAhead) {
         double p[kAhead][E];
 #pragma unroll
