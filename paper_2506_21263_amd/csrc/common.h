@@ -186,6 +186,33 @@ __device__ __forceinline__ void unrolled(F &&f) {
     }
 }
 
+// LDS written and read by the same wavefront: its instructions execute in order, so only the
+// compiler has to be kept from reordering.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f64x4_t mfma64(double a, double b, f64x4_t c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// Partial sums of the Gram matrix: elements of the long side in each, and of each quarter of one, which a
+// wavefront adds up by itself.
+constexpr int kGramChunk = 512;
+constexpr int kGramQuarter = kGramChunk / 4;
+// Sixteen elements of a quarter: lane (row, q) has elements 4 q .. 4 q + 3 of its row, and the s-th of them
+// feeds the s-th product, here and in gram_partial_kernel: the bits of a sum hang on that order.
+__device__ __forceinline__ f64x4_t gram_step(const float4 &x, f64x4_t acc) {
+    acc = mfma64((double)x.x, (double)x.x, acc);
+    acc = mfma64((double)x.y, (double)x.y, acc);
+    acc = mfma64((double)x.z, (double)x.z, acc);
+    return mfma64((double)x.w, (double)x.w, acc);
+}
+
 inline size_t a256x(size_t x) { return (x + 255) & ~(size_t)255; }
 // One r x L factor and its fp64 scratch; a batch of them is passed to a kernel by value.
 constexpr int kMaxBatch = 64;

@@ -18,11 +18,7 @@ namespace dlcx {
 
 constexpr int kT = 256;  // threads per workgroup (4 wavefronts)
 
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f64x4_t mfma64(float a, float b, f64x4_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64((double)a, (double)b, c, 0, 0, 0);
-}
+__device__ __forceinline__ f64x4_t mfma64(float a, float b, f64x4_t c) { return mfma64((double)a, (double)b, c); }
 __device__ __forceinline__ float part_of(const float4 &v, int s) {
     return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
 }

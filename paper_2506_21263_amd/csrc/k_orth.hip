@@ -29,15 +29,7 @@
 
 namespace dlcx {
 
-constexpr int kGramChunk = 512;  // elements of L per partial sum
-constexpr int kQuarter = kGramChunk / 4;  // of a wavefront
 constexpr int kGT = 256;
-
-typedef double f64x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ f64x4_t mfma64(double a, double b, f64x4_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
 
 // it.g[0] after the first round's step 2: a second round would change nothing that fp32 shows
 // (||R^-1||_F^2 of the unit-diagonal Gram matrix up to which that holds).  Measured against a 64-bit
@@ -145,8 +137,8 @@ __global__ __launch_bounds__(kGT, 4) void gram_partial_kernel(FactorBatch batch,
         pa[x] = f + (int64_t)(a < r ? a : r - 1) * L + 4 * q;
         pb[x] = f + (int64_t)(b < r ? b : r - 1) * L + 4 * q;
     }
-    const int64_t begin = (int64_t)chunk * kGramChunk + wave * kQuarter;
-    int64_t end = begin + kQuarter;
+    const int64_t begin = (int64_t)chunk * kGramChunk + wave * kGramQuarter;
+    int64_t end = begin + kGramQuarter;
     if (end > L) end = L;  // L is a multiple of 16: a step of 16 is whole or not there
     f64x4_t acc[NB][NB];
 #pragma unroll
@@ -298,14 +290,6 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;  // of a 16 x 16 block in LDS
 constexpr int kCT = 512;  // at most 8 wavefronts: 18 blocks each at r = 256, 144 of 256 registers
-
-// LDS written and read by the same wavefront: its instructions execute in order, so only the
-// compiler has to be kept from reordering.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // V = L^-1 of a symmetric 16 x 16 block G = L L^T by one wavefront, both as accumulators: register q of
 // lane (g, col) = (lane / 16, lane % 16) is element (4 q + g, col).  Eliminating row j from [G | 1] is a product
@@ -700,15 +684,15 @@ __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, 
 // Bound by latency.  Instead of a chain of six launches, of which the last three mostly only read a mark: 512 x 8
 // 9.7 us (25.2 in six), 512 x 16 9.5 (25.7), 1024 x 16 13.4 (25.0), 2048 x 8 18.5 (24.6), seven of 1536 x 16
 // 24 - 27 (26.8); at 3056 x 8 25.2 (24.5) it no longer pays, hence the limits.
-constexpr int kSmallRank = 16;
-constexpr int kSmallLength = 2048;
+constexpr int kSmallOrthRank = 16;
+constexpr int kSmallOrthLength = 2048;
 constexpr int kSmallFloats = 24 * 1024;  // with the rows' padding, 96 KB
 constexpr int kSmallThreads = 512;
 static inline size_t small_bytes(int64_t L, int r) { return (size_t)r * (size_t)(L + 4) * sizeof(float); }
 __global__ __launch_bounds__(kSmallThreads) void orth_small_kernel(FactorBatch batch) {
     constexpr int NW = kSmallThreads / 64;
     extern __shared__ __attribute__((aligned(16))) float fl[];  // [r][L + 4]: 16 rows start in 64 banks
-    __shared__ double red[kSmallLength / kQuarter][4][64];
+    __shared__ double red[kSmallOrthLength / kGramQuarter][4][64];
     __shared__ double dscale[16];
     __shared__ double va[16 * kVPitch], wt[16 * kVPitch], vb[4][64];
     __shared__ int state;  // the first column that is not finite, 16 more: a second round is needed
@@ -725,12 +709,8 @@ __global__ __launch_bounds__(kSmallThreads) void orth_small_kernel(FactorBatch b
         const float *row = fl + (col < r ? col : r - 1) * pitch + 4 * g;  // rows past r: any valid one
         for (int q = wave; q < quarters; q += NW) {  // quarters of the 512-element sums
             f64x4_t acc = f64x4_t{0.0, 0.0, 0.0, 0.0};
-            for (int i = q * kQuarter; i < (q + 1) * kQuarter && i < L; i += 16) {
-                const float4 x = *reinterpret_cast<const float4 *>(row + i);
-                acc = mfma64((double)x.x, (double)x.x, acc);
-                acc = mfma64((double)x.y, (double)x.y, acc);
-                acc = mfma64((double)x.z, (double)x.z, acc);
-                acc = mfma64((double)x.w, (double)x.w, acc);
+            for (int i = q * kGramQuarter; i < (q + 1) * kGramQuarter && i < L; i += 16) {
+                acc = gram_step(*reinterpret_cast<const float4 *>(row + i), acc);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) red[q][v][lane] = acc[v];
@@ -867,7 +847,7 @@ int launch_orthonormalize_batch(const FactorBatch &batch, hipStream_t st) {
     bool small = true;
     for (int i = 0; i < batch.n; ++i) {
         const FactorItem &it = batch.it[i];
-        small = small && it.r <= kSmallRank && it.L <= kSmallLength && small_bytes(it.L, it.r) <= kSmallFloats * sizeof(float);
+        small = small && it.r <= kSmallOrthRank && it.L <= kSmallOrthLength && small_bytes(it.L, it.r) <= kSmallFloats * sizeof(float);
         if (small && small_bytes(it.L, it.r) > bytes) bytes = small_bytes(it.L, it.r);
     }
     if (small) {

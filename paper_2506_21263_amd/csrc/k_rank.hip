@@ -55,24 +55,21 @@ __device__ __forceinline__ double wave_sum(double x) {
     return add_halves(x, x);
 }
 
-// N sums over the 16 lanes of a row at once (N = 4, 8 or 16): the lanes halve the values among
-// themselves as they add, lane t ends up with the sum of value t * N / 16.
-template <int kCtrl, int M, int N>
-__device__ __forceinline__ void halve(double (&v)[N], bool up) {
+// Four sums over the 16 lanes of a row at once: the lanes halve the values among themselves as they add, lane t
+// ends up with the sum of value t / 4.
+template <int kCtrl, int M>
+__device__ __forceinline__ void halve(double (&v)[4], bool up) {
 #pragma unroll
     for (int i = 0; i < M; ++i) {
         const double keep = up ? v[i + M] : v[i], send = up ? v[i] : v[i + M];
         v[i] = keep + dpp<kCtrl>(send);
     }
 }
-template <int N>
-__device__ __forceinline__ double row_sums(double (&v)[N], int t) {
-    halve<kXor15, N / 2>(v, t & 8);
-    halve<kXor7, N / 4>(v, t & 4);
-    if constexpr (N >= 8) halve<kXor2, N / 8>(v, t & 2);
-    else v[0] += dpp<kXor2>(v[0]);
-    if constexpr (N >= 16) halve<kXor1, 1>(v, t & 1);
-    else v[0] += dpp<kXor1>(v[0]);
+__device__ __forceinline__ double row_sums(double (&v)[4], int t) {
+    halve<kXor15, 2>(v, t & 8);
+    halve<kXor7, 1>(v, t & 4);
+    v[0] += dpp<kXor2>(v[0]);
+    v[0] += dpp<kXor1>(v[0]);
     return v[0];
 }
 
@@ -226,14 +223,6 @@ __device__ __forceinline__ Interval gershgorin(const double2 *tri, int r, int la
     const double big = fmax(fabs(lo), fabs(hi));
     const int ex = big > 0.0 && big < 1e300 ? -__builtin_amdgcn_frexp_exp(big) : 0;
     return Interval{ldexp(lo, ex), ldexp(hi, ex), ex};
-}
-
-// LDS written and read by the same wavefront: its instructions execute in order, so only the
-// compiler has to be kept from reordering.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // What tridiag_kernel leaves in FactorItem::g above rank 64: the Sturm table with all that count_below reads,
@@ -406,7 +395,7 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
                         cp[i] = fma(t[x][i], rx, cp[i]);
                     }
                 });
-                const double rs = row_sums<4>(rp, tj);
+                const double rs = row_sums(rp, tj);
                 if ((tj & 3) == 0) rowpart[par][16 * (x0 + (tj >> 2)) + ti] = rs;
             });
 #pragma unroll
@@ -483,14 +472,12 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
 
 // The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
 // a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
-// sums come from there depends on the batch).  Up to kSmallLength rows that is shorter than a launch before
+// sums come from there depends on the batch).  Up to kSmallGramLength rows that is shorter than a launch before
 // this one: 512 x 8 15.4 us instead of 17.7 for both, 512 x 16 22.0 (24.5), 1024 x 16 24.1 (25.5), but 1536 x 16
 // 26.3 (25.4) and 2048 x 8 21.5 (18.8).
-constexpr int kSmallGram = 16;
-constexpr int kSmallLength = 1024;
-constexpr int kGramQuarter = 128;
-__device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGram][kSmallGram + 1]) {
-    typedef double f64x4_t __attribute__((ext_vector_type(4)));
+constexpr int kSmallGramRank = 16;
+constexpr int kSmallGramLength = 1024;
+__device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGramRank][kSmallGramRank + 1]) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, g = lane >> 4, L = (int)it.L, begin = (4 * c + wave) * kGramQuarter;
     const float *row = it.f + (int64_t)(col < it.r ? col : it.r - 1) * L + 4 * g;
@@ -502,10 +489,7 @@ __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (
 #pragma unroll
     for (int u = 0; u < kGramQuarter / 16; ++u) {
         if (begin + 16 * u >= L) break;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].x, (double)x[u].x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].y, (double)x[u].y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].z, (double)x[u].z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].w, (double)x[u].w, acc, 0, 0, 0);
+        acc = gram_step(x[u], acc);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) gram[wave][4 * v + g][col] = acc[v];
@@ -540,13 +524,13 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     }
     if constexpr (RC <= 32)
         if (nchunks == 0) {  // the sums are left to this kernel
-            __shared__ double gram[4][kSmallGram][kSmallGram + 1];
-            for (int c = 0; 4 * kGramQuarter * c < it.L; ++c) {
+            __shared__ double gram[4][kSmallGramRank][kSmallGramRank + 1];
+            for (int c = 0; kGramChunk * c < it.L; ++c) {
                 small_gram(it, c, gram);
                 __syncthreads();
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    const int x = (tid + kTT * e) / RC % kSmallGram, y = (tid + kTT * e) % RC % kSmallGram;
+                    const int x = (tid + kTT * e) / RC % kSmallGramRank, y = (tid + kTT * e) % RC % kSmallGramRank;
                     sum[e] += ((gram[0][x][y] + gram[1][x][y]) + gram[2][x][y]) + gram[3][x][y];
                 }
                 __syncthreads();
@@ -729,7 +713,7 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
     FactorBatch summed = batch;  // the same factors with their Gram sums in one chunk where that pays, or none
     bool small = true;
     for (int i = 0; i < batch.n; ++i)
-        small = small && batch.it[i].r <= kSmallGram && batch.it[i].L <= kSmallLength;
+        small = small && batch.it[i].r <= kSmallGramRank && batch.it[i].L <= kSmallGramLength;
     if (small) {
         for (int i = 0; i < batch.n; ++i) summed.it[i].nchunks = 0;
     } else {
