@@ -358,7 +358,7 @@ constexpr int kChainsP = NS >= 2 && BLOCKS <= (LONE ? 2 : 1) ? 2 : 1;
 // workgroup has its unit to itself.  Two pieces, us with one | two to a unit: 28672 x 8192 four workers r = 100
 // 943 | 884, r = 24 656 | 632; 8192 x 8192 r = 100 five workers 410 | 386, eight 503 | 483.  At ranks 33 .. 64
 // it goes either way: 8192 x 2048 six workers r = 64 102 | 95, 28672 x 2048 two workers r = 40 105 | 99, but
-// where few units get a second workgroup 8192 x 8192 five workers 283 | 313, 16384 x 4096 three 173 | 192.
+// where few units get a second workgroup 8192 x 8192 five workers 283 | 313, 40960 x 8192 one 284 | 313.
 template <int NS, int BLOCKS, bool LONE>
 constexpr int kWavesP = NS <= 2 && BLOCKS <= 4 && !LONE ? 4 : 1;
 template <int NS, int CBW, int WC, int WR, int RB, bool LONE, int kSets = 2>

@@ -20,9 +20,9 @@
 // Every kernel here takes a batch of factors (one descriptor per matrix, passed by value): the
 // work per matrix is small and latency-bound, so the matrices of a stage go through each step
 // together, one workgroup (or one slice of the grid) per matrix.  What a factor's result is made of
-// does not depend on the batch it comes in, but for the rounding of the norm behind the mark (added
-// up per wavefront, of which there are as many as the largest rank of the batch asks for, or by one): whether the
-// second round runs is the batch's where that norm is within rounding of kOneRoundNorm.
+// does not depend on the batch it comes in, but above rank 16 for the rounding of the norm behind the
+// mark (added up per wavefront, of which there are as many as the largest rank of the batch asks
+// for): whether the second round runs is the batch's where that norm is within rounding of kOneRoundNorm.
 #include <type_traits>
 
 #include "common.h"
@@ -98,7 +98,7 @@ int gram_chunks(int64_t L) { return (int)ceil_div(L, kGramChunk); }
 // straight from memory, 64 consecutive bytes per row, and nothing waits at a barrier until the
 // four quarters are added in order at the end.
 // Bound by the fp64 matrix cores at high rank: seven factors of a 100B-class layer at r = 256
-// (77824 rows, 5.4 GFLOP over the upper triangle, 69 us at the datasheet's rate) take 108 us (118 with one loop
+// (77824 rows, 5.4 GFLOP over the upper triangle, 69 us at the datasheet's rate) take 110 us (118 with one loop
 // for all tiles, whose branch copied accumulators); through LDS tiles and vector fp64 FMAs it was 200 us, and
 // 40 us for a single 512 x 8 factor (64 barriers in a row), now 5.
 // From kGroupedChunks on, the tiles of a chunk are consecutive workgroups of one XCD (every eighth workgroup of the
@@ -285,7 +285,7 @@ int launch_gram_partials_batch(const FactorBatch &batch, FactorBatch *reduced, i
 // stores are a handful of instructions a block (70 KB of instructions before, fetched from memory once per launch:
 // 22 us to load the matrix); and the wavefront that factors has little else to do, where all waited for its
 // other updates.  r = 256 takes 104 us: 16 steps of 5 us, of which the products 3.3, panel and barriers 1.3, and 20
-// us around them (151 before; row by row with the matrix in L2: 2530); r = 32 12 us, as before.
+// us around them (151 before; row by row with the matrix in L2: 2530); r = 32 with up to 16 sums 9 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxBlocks = DLCX_MAX_RANK / 16;
 constexpr int kVPitch = 17;  // of a 16 x 16 block in LDS
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(kCT) void chol_inverse_kernel(FactorBatch batch, in
 // elements 4 n .. 4 n + 3, element q feeds product q), so one element of W serves four products.  The column blocks are dealt so that every
 // wavefront gets long and short ones.
 // Bound by the fp64 matrix cores: seven factors of a 100B-class layer at r = 256 (77824 rows,
-// 5.4 GFLOP) take 113 us (four wavefronts and a workgroup for every 64 rows of the longest factor: 133; vector
+// 5.4 GFLOP) take 112 us (four wavefronts and a workgroup for every 64 rows of the longest factor: 133; vector
 // fp64 FMAs with W through LDS: 598 us).
 template <int NW, typename At>  // wavefronts
 __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, At at, int round) {
@@ -679,11 +679,14 @@ __global__ __launch_bounds__(64 * NW, 2) void apply_w_kernel(FactorBatch batch, 
 
 // The whole orthonormalisation of small factors, a workgroup each, which holds its factor in LDS: the sums, the
 // factorisation and P W as above for a single block, and the second round where the first asks for one.  All
-// sums are in the order of the kernels above: a batch takes this form if all of its factors are small, and what a
-// factor's result is does not hang on that.
-// Bound by latency.  Instead of a chain of six launches, of which the last three mostly only read a mark: 512 x 8
-// 9.7 us (25.2 in six), 512 x 16 9.5 (25.7), 1024 x 16 13.4 (25.0), 2048 x 8 18.5 (24.6), seven of 1536 x 16
-// 24 - 27 (26.8); at 3056 x 8 25.2 (24.5) it no longer pays, hence the limits.
+// sums are in the order of the kernels above, that of the norm behind the mark among them (a single block's is
+// one wavefront's there too): a batch takes this form if all of its factors are small, and what a factor's result
+// is does not hang on that.
+// Bound by latency, one workgroup's.  Instead of a chain of six launches, of which the last three mostly only read
+// a mark, us in a graph, one launch | six: 512 x 8 8.4 | 16.3, 512 x 16 9.4 | 16.5, 1024 x 16 13.4 | 17.4, 1536 x 8
+// 15.2 | 16.8, 1520 x 16 17.5 | 17.5, 2048 x 8 18.4 | 17.2, 2032 x 12 20.5 | 17.3, seven of them 20.8 | 18.0.  From
+// the host, which takes longer for six launches than they run: 512 x 8 10.6 | 24.0, 1520 x 16 17.5 | 23.5, 2048 x
+// 8 18.4 | 23.4, 2032 x 12 20.5 | 24.1, hence the limits.
 constexpr int kSmallOrthRank = 16;
 constexpr int kSmallOrthLength = 2048;
 constexpr int kSmallFloats = 24 * 1024;  // with the rows' padding, 96 KB

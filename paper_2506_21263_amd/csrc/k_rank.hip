@@ -472,9 +472,10 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
 
 // The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
 // a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
-// sums come from there depends on the batch).  Up to kSmallGramLength rows that is shorter than a launch before
-// this one: 512 x 8 15.4 us instead of 17.7 for both, 512 x 16 22.0 (24.5), 1024 x 16 24.1 (25.5), but 1536 x 16
-// 26.3 (25.4) and 2048 x 8 21.5 (18.8).
+// sums come from there depends on the batch).  Up to kSmallGramLength rows that is no longer than a launch before
+// this one, us without | with it, in a graph: 512 x 8 14.9 | 16.5, 512 x 16 21.4 | 23.3, 1024 x 8 17.0 | 16.7, 1024
+// x 16 23.7 | 23.8; from the host 1024 x 8 17.2 | 17.8.  Above it is longer, as a chunk takes 2 us: 1040 x 8 17.7 |
+// 17.0, 1536 x 8 19.1 | 17.0, 1536 x 16 25.7 | 23.9, 2048 x 16 27.9 | 23.9.
 constexpr int kSmallGramRank = 16;
 constexpr int kSmallGramLength = 1024;
 __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGramRank][kSmallGramRank + 1]) {
@@ -498,8 +499,8 @@ __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (
 // Ranks up to kFusedRank: the whole matrix in one wavefront, row i in lane i, and no barrier until
 // the eigenvalues.  Every lane sums its own row of S v; v and w go round through LDS.  The columns
 // are renumbered as they go: step k reflects register column 0 and the update writes column j into
-// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 41 us (246 at 1024
-// threads, a division per term and bisection), r = 64: 98 us (510).
+// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 40 - 42 us (246 at
+// 1024 threads, a division per term and bisection), r = 64: 98 us (510).
 template <int RC>  // columns held: 32 or 64
 __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, double tau) {
     __shared__ double sm[RC][RC + 1];
