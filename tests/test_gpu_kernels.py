@@ -575,6 +575,28 @@ def test_small_factors_alone_and_in_a_batch_with_large_ones(L, r, cond):
     assert rel_l2(got[0], (q * np.sign(np.diag(t))).T) <= 2.4e-7
 
 
+@pytest.mark.parametrize("r", [2, 9, 16])
+def test_small_factors_take_the_second_round_alone_or_in_a_batch(r):
+    # Whether the second round runs hangs on ||R^-1||_F^2 of the unit-diagonal Gram matrix (4e6 is the line): two
+    # columns at an angle of e put 2 / e^2 there.  Up to rank 16 it is one wavefront's sum in every form, so factors
+    # on either side of the line, and as close to it as fp32 inputs get, have the same bits alone and in a batch.
+    L, n = 512, 24
+    g = rng(r)
+    Q = synth.orthonormal_columns(g, L, r + 1).T
+    big = g.standard_normal((20, 64)).astype(np.float32)
+    angles = np.sqrt(2.0 / 4e6) * (1 + 2.0 ** -np.arange(2, n + 2) * np.where(np.arange(n) % 2, 1, -1))
+    for e in angles:
+        A = Q[:r].copy()
+        A[r - 1] = Q[0] * np.cos(e) + Q[r] * np.sin(e)
+        A = A.astype(np.float32)
+        descs = [dlcx.desc(L, L, r, 4, 16), dlcx.desc(64, 64, 20, 4, 16)]
+        ws = torch.empty(dlcx.dlcx_batched_workspace_bytes(descs), device=DEV, dtype=torch.uint8)
+        alone, batch = [to_dev(A)], [to_dev(A), to_dev(big)]
+        dlcx.dlcx_orthonormalize_batched(descs[:1], alone, ws)
+        dlcx.dlcx_orthonormalize_batched(descs, batch, ws)
+        assert torch.equal(alone[0], batch[0]), e
+
+
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 def test_small_factor_that_is_not_finite_or_has_no_rank(value):
     L, r = 528, 12
