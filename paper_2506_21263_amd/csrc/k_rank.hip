@@ -4,7 +4,8 @@
 // orthonormalisation).  Everything after it is fp64 too:
 //   tridiag_kernel       Householder reduction to tridiagonal form, one workgroup per matrix
 //   eigenvalues          every eigenvalue by multisection on the Sturm sequence: G lanes evaluate
-//                        G points of an interval at once, so a round narrows it G + 1 times
+//                        G points of an interval at once, so a round narrows it G + 1 times; up to
+//                        rank 64 only as far as it takes to tell which sums hold the share
 //   count                prefix sum over the eigenvalues (they come out in order) and count
 // Up to rank 64 the last two follow in the same workgroup; above, eigenvalues_kernel spreads them
 // over the GPU (one wavefront per eigenvalue) and count_kernel finishes.
@@ -27,6 +28,7 @@ __device__ __forceinline__ double dpp(double x) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor7 = 0x141, kXor15 = 0x140;
+constexpr int kRowShl1 = 0x101;  // from the lane after it, the last of a row of 16: zero
 
 __device__ __forceinline__ double from_halves(uint32_t lo, uint32_t hi) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
@@ -128,18 +130,14 @@ __device__ __forceinline__ int count_below(const double2 *t, int blocks, double 
     return cnt;
 }
 
-// The c-th largest eigenvalue (c from 0) by groups of G lanes, every lane of the wavefront calling;
-// lo, hi: an interval with all eigenvalues, inside [-1, 1], narrowed to less than 2^-56.  The sums that
-// decide r' are at least 1/2 and rounded at 2^-54: an eigenvalue that is zero, or vanishes beside the
-// others, then adds nothing to them.
+// Bounds lo, hi of the c-th largest eigenvalue (c from 0), inside [-1, 1], narrowed `rounds` times by groups of G
+// lanes, every lane of the wavefront calling: G points of the interval at once, so a round narrows it G + 1 times.
 template <int G>
-__device__ __forceinline__ double nth_largest(const double2 *t, int r, int c, double lo, double hi,
-                                              int lane) {
-    constexpr int kRounds = G == 64 ? 10 : G == 32 ? 12 : G == 16 ? 14 : G == 8 ? 18 : 25;  // 2 (G + 1)^-n
+__device__ __forceinline__ void narrow(const double2 *t, int r, int c, double &lo, double &hi, int lane, int rounds) {
     const int below = r - 1 - c;  // eigenvalues smaller than the one wanted
     const int sub = lane & (G - 1), base = lane - sub;
     constexpr uint64_t mask = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
-    for (int itn = 0; itn < kRounds; ++itn) {
+    for (int itn = 0; itn < rounds; ++itn) {
         const double step = (hi - lo) * (1.0 / (double)(G + 1));
         const double x = fma((double)(sub + 1), step, lo);
         const bool above = count_below(t, sturm_blocks(r), x) > below;  // x is above the eigenvalue
@@ -150,7 +148,53 @@ __device__ __forceinline__ double nth_largest(const double2 *t, int r, int c, do
         lo = nlo;
         hi = nhi;
     }
-    return fmax(0.5 * (lo + hi), 0.0);
+}
+// Rounds to an interval of less than 2^-56, 2 (G + 1)^-n: the sums that decide r' are at least 1/2 and rounded at
+// 2^-54, so an eigenvalue that is zero, or vanishes beside the others, then adds nothing to them.  After the first
+// kEarly of them, at 2^-19 .. 2^-23, the bounds nearly always tell already which sums hold the share (decided()).
+template <int G>
+struct Rounds {
+    static constexpr int kAll = G == 64 ? 10 : G == 32 ? 12 : G == 16 ? 14 : G == 8 ? 18 : 25;
+    static constexpr int kEarly = G == 64 ? 4 : G == 32 ? 4 : G == 16 ? 5 : G == 8 ? 7 : 9;
+};
+__device__ __forceinline__ double eigenvalue(double lo, double hi) { return fmax(0.5 * (lo + hi), 0.0); }
+
+// r' from bounds of the r eigenvalues in descending order, N a lane: value 64 q + lane is between lo[q] and hi[q].
+// Returns -1 where the bounds leave open whether one of the sums holds tau of the total: what count_share
+// makes of values inside the bounds it then returns, whatever they are.  The k largest hold the share if
+// (1 - tau) of their sum is at least tau of the sum of the others; 2^-40 of the total is beyond all roundings.
+template <int N>
+__device__ __forceinline__ int decided(const double (&lo)[N], const double (&hi)[N], int r, double tau, int lane) {
+    double ls[N], hs[N], lt = 0.0, ht = 0.0;  // the sums up to a value, the totals
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const bool on = 64 * q + lane < r;
+        ls[q] = on ? fmax(lo[q], 0.0) : 0.0;
+        hs[q] = on ? fmax(hi[q], 0.0) : 0.0;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double l = __shfl_up(ls[q], off, 64), h = __shfl_up(hs[q], off, 64);
+            ls[q] += lane >= off ? l : 0.0;
+            hs[q] += lane >= off ? h : 0.0;
+        }
+        ls[q] += lt;
+        hs[q] += ht;
+        lt = read_lane(ls[q], 63);
+        ht = read_lane(hs[q], 63);
+    }
+    const double slack = 0x1p-40 * ht;
+    int k = 0;
+    bool open = false;
+#pragma unroll
+    for (int q = N - 1; q >= 0; --q) {
+        const bool on = 64 * q + lane < r;
+        const bool yes = (1.0 - tau) * ls[q] >= tau * (ht - hs[q]) + slack;
+        const bool no = (1.0 - tau) * hs[q] + slack < tau * (lt - ls[q]);
+        open = open || __ballot(on && !yes && !no) != 0;
+        const uint64_t m = __ballot(on && yes);
+        if (m) k = 64 * q + __builtin_ctzll(m) + 1;
+    }
+    return open || k == 0 ? -1 : k;
 }
 
 // smallest k whose k largest of the descending values (in LDS, zeros behind them up to a multiple of 64)
@@ -496,17 +540,186 @@ __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (
     for (int v = 0; v < 4; ++v) gram[wave][4 * v + g][col] = acc[v];
 }
 
-// Ranks up to kFusedRank: the whole matrix in one wavefront, row i in lane i, and no barrier until
-// the eigenvalues.  Every lane sums its own row of S v; v and w go round through LDS.  The columns
-// are renumbered as they go: step k reflects register column 0 and the update writes column j into
-// j - 1, so that no register is ever indexed by k.  r = 32 with its eigenvalues: 40 - 42 us (246 at
-// 1024 threads, a division per term and bisection), r = 64: 98 us (510).
+// ---------------------------------------------------------------------------------------------
+// Householder reduction by one wavefront, rows in lanes, columns in registers, no barrier and no LDS but for the
+// result.  A step, with x the column that is reflected (v: x below the diagonal, its first element moved by c):
+//   u = S x_tail and the sums over |x_tail|^2 and x_tail . u do not wait for the reflection, they run beside it:
+//   S v = u + c S_1 and v . S v = x_tail . u + c (2 u_1 + c S_11), with S_1 the next column and u_1 = S_1 . x_tail;
+//   S -= v w^T + w v^T, the next column first.
+// An element of x, v, w along the columns comes from one lane of each row of 16 as the operand of the product
+// (row_newbcast); the rows are dealt to the lanes so that such a register is a copy of rows of lanes of the
+// vector itself.  After four steps rows and columns are renumbered: register and lane indices are constants.
+// ---------------------------------------------------------------------------------------------
+// acc[i % 2] += element C + i of src (one lane of each row of 16) * by[i], i = 0 .. 3.  A DPP operand has to be two
+// wait states behind the vector instruction that wrote it.
+template <int C>
+__device__ __forceinline__ void dot_bcast4(double (&acc)[2], double src, const double *by) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc[0]), "+v"(acc[1])
+        : "v"(src), "v"(by[0]), "v"(by[1]), "v"(by[2]), "v"(by[3]), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+}
+// t[i] += (element C + i of w) * a + (element C + i of v) * b, i = 0 .. 3
+template <int C>
+__device__ __forceinline__ void update_bcast4(double *t, double w, double a, double v, double b) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %5 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %4, %5 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %6, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %6, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %6, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %6, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3])
+        : "v"(w), "v"(a), "v"(v), "v"(b), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+}
+struct Two {
+    double a, b;
+};
+// .a: the lower half of the wavefront in both halves, .b: the upper
+__device__ __forceinline__ Two halves_of(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return Two{from_halves(lo[0], hi[0]), from_halves(lo[1], hi[1])};
+}
+// .a: the even row of each pair of rows of 16 lanes in both, .b: the odd one
+__device__ __forceinline__ Two rows_of(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return Two{from_halves(lo[0], hi[0]), from_halves(lo[1], hi[1])};
+}
+
+// Up to 32 rows: row 2 m + b in lanes 16 b + m and 32 + 16 b + m, the lower half of the wavefront with the even
+// columns, the upper with the odd ones: t[c] is column 2 c + h.
+struct Rows32 {
+    static __device__ __forceinline__ int row(int lane) { return 2 * (lane & 15) + ((lane >> 4) & 1); }
+    static constexpr int lane(int row) { return (row >> 1) + 16 * (row & 1); }
+    static __device__ __forceinline__ double sum(double x) {
+        x += dpp<kXor1>(x);
+        x += dpp<kXor2>(x);
+        x += dpp<kXor7>(x);
+        x += dpp<kXor15>(x);
+        return add_rows(x, x);
+    }
+    static __device__ __forceinline__ double gather(double x) { return add_halves(x, x); }
+    template <int J>
+    static __device__ __forceinline__ double column(const double *t) {
+        const Two x = halves_of(t[J >> 1]);
+        return (J & 1) ? x.b : x.a;
+    }
+    static __device__ __forceinline__ void spread(double x, int lane, double (&to)[1]) {
+        const Two r = rows_of(x);
+        to[0] = lane < 32 ? r.a : r.b;
+    }
+    // the lane that holds element `row` of a spread vector
+    static __device__ __forceinline__ bool holds(int lane, int q, int row) { return (lane >> 5) == (row & 1) && (lane & 15) == (row >> 1); }
+    static constexpr int kSpread = 1;
+    static constexpr int kSteps = 2;  // to a register of columns
+};
+// Up to 64 rows: row 4 m + b in lane 16 b + m, t[16 q + c] is column 4 c + q.
+struct Rows64 {
+    static __device__ __forceinline__ int row(int lane) { return 4 * (lane & 15) + (lane >> 4); }
+    static constexpr int lane(int row) { return (row >> 2) + 16 * (row & 3); }
+    static __device__ __forceinline__ double sum(double x) { return wave_sum(x); }
+    static __device__ __forceinline__ double gather(double x) { return x; }
+    template <int J>
+    static __device__ __forceinline__ double column(const double *t) { return t[16 * (J & 3) + (J >> 2)]; }
+    static __device__ __forceinline__ void spread(double x, int, double (&to)[4]) {
+        const Two r = rows_of(x), even = halves_of(r.a), odd = halves_of(r.b);
+        to[0] = even.a;
+        to[1] = odd.a;
+        to[2] = even.b;
+        to[3] = odd.b;
+    }
+    static __device__ __forceinline__ bool holds(int lane, int q, int row) { return q == (row & 3) && (lane & 15) == (row >> 2); }
+    static constexpr int kSpread = 4;
+    static constexpr int kSteps = 4;
+};
+
+// Steps k, k + 1, .. up to `stop`, a multiple of Rows::kSteps away, or until row r - 1 is reached; C registers of
+// each spread vector's columns are in use (the others are done).  x: the column of step k.  tri: the result's place
+// for lane 0, places of no use for the others.
+template <typename Rows, int C>
+__device__ __forceinline__ void reduce_steps(double *t, double &x, int &k, int stop, int r, double2 *tri, int lane) {
+    constexpr int Q = Rows::kSpread;
+    const int row = Rows::row(lane);
+    for (; k < stop && k < r; k += Rows::kSteps) {
+        unrolled<Rows::kSteps>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            const double dk = read_lane(x, Rows::lane(s));
+            tri[k + s].x = dk;
+            if (k + s + 1 >= r) return;
+            const double x0 = read_lane(x, Rows::lane(s + 1)), xt = row > s + 1 ? x : 0.0;
+            double xb[Q];
+            Rows::spread(xt, lane, xb);
+            double acc[2] = {0.0, 0.0};
+            unrolled<Q>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                unrolled<C / 4>([&](auto cc) { dot_bcast4<4 * decltype(cc)::value>(acc, xb[q], t + 16 * q + 4 * decltype(cc)::value); });
+            });
+            const double tail = Rows::sum(xt * xt);
+            const double u = Rows::gather(acc[0] + acc[1]);
+            const double s1 = Rows::template column<s + 1>(t);
+            const double xu = Rows::sum(xt * u);
+            const Reflection f = reflection(x0, tail);
+            const double c = x0 - f.alpha;
+            tri[k + s + 1].y = f.alpha;
+            const double vp = fma(c, fma(c, read_lane(s1, Rows::lane(s + 1)), 2.0 * read_lane(u, Rows::lane(s + 1))), xu);
+            const double kk = 0.5 * f.beta * (f.beta * vp);  // (beta^2 may overflow)
+            const double v = row == s + 1 ? c : xt, p = fma(c, s1, u);
+            const double w = row > s ? fma(f.beta, p, -kk * v) : 0.0;
+            double wb[Q];
+            Rows::spread(w, lane, wb);
+#pragma unroll
+            for (int q = 0; q < Q; ++q) xb[q] = Rows::holds(lane, q, s + 1) ? c : xb[q];  // v
+            unrolled<Q>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                unrolled<C / 4>([&](auto cc) {
+                    update_bcast4<4 * decltype(cc)::value>(t + 16 * q + 4 * decltype(cc)::value, wb[q], -v, xb[q], -w);
+                });
+            });
+            x = fma(c, -w, fma(read_lane(w, Rows::lane(s + 1)), -v, s1));  // as the same element of t
+        });
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int c = 0; c < C; ++c) t[16 * q + c] = c + 1 < C ? dpp<kRowShl1>(t[16 * q + c + 1]) : 0.0;
+        x = dpp<kRowShl1>(x);
+    }
+}
+// The reduction of the r x r matrix element(i, j), r <= 32: d_i and the off-diagonal before it to tri[i]
+template <typename F>
+__device__ __forceinline__ void reduce32(F &&element, int r, double2 *tri, int lane) {
+    double t[16];
+    const int row = Rows32::row(lane), h = lane >> 5;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+        const int j = 2 * c + h;
+        const double e = element(row < r ? row : 0, j < r ? j : 0);
+        t[c] = row < r && j < r ? e : 0.0;
+    }
+    double x = Rows32::column<0>(t);
+    int k = 0;
+    if (r > 16) reduce_steps<Rows32, 16>(t, x, k, (r - 15) & ~1, r, tri, lane);  // to 16 rows or fewer
+    reduce_steps<Rows32, 8>(t, x, k, r, r, tri, lane);
+}
+
+// Ranks up to kFusedRank: the reduction in one wavefront, then the eigenvalues in all four, in bounds first: the
+// share is nearly always decided after a third of their rounds.  Bound by latency: at r = 32 the reduction 32 K
+// clocks (1040 a step), the eigenvalues 12 K, 5 K around them (one lane to a row, v and w through the LDS and
+// the sums one after the other: 74 K and 22 K).  Whole calls, us before | after: 512 x 8 14.9 | 9.7, 512 x 16 21.4 |
+// 13.1, 2048 x 32 46.5 | 27.9, 2048 x 48 79.0 | 48.9, 2048 x 64 105.8 | 64.0.
 template <int RC>  // columns held: 32 or 64
 __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, double tau) {
     __shared__ double sm[RC][RC + 1];
-    __shared__ __attribute__((aligned(16))) double vb[64 + 8], wb[64 + 8];
-    __shared__ double2 tri[RC + kSturmPad];
-    __shared__ double eig[64];
+    __shared__ double2 tri[RC + kSturmPad], unused[64 + RC + kSturmPad];
+    __shared__ double eig[64], eig_hi[64];
     __shared__ int order[64];
     const FactorItem it = batch.it[blockIdx.x];
     const int nchunks = it.nchunks;
@@ -579,54 +792,28 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     if (on) order[__popcll(mask & ((1ull << lane) - 1))] = lane;
     const int r = __popcll(mask);
     __syncthreads();
-    if (wave == 0) {
-        double t[RC];
-        const int row = lane < r ? order[lane] : 0;
+    if (wave == 0 && r > 0) {
+        double2 *to = lane == 0 ? tri : unused + lane;
+        auto element = [&](int i, int j) { return sm[order[i]][order[j]]; };
+        if constexpr (RC <= 32) {
+            reduce32(element, r, to, lane);
+        } else {
+            double t[64];
+            const int row = Rows64::row(lane);
 #pragma unroll
-        for (int j = 0; j < RC; ++j) {
-            const double e = sm[row][j < r ? order[j] : 0];
-            t[j] = lane < r && j < r ? e : 0.0;
-        }
-        for (int k = 0; k + 1 < r; ++k) {
-            const double x = t[0];
-            const double dk = read_lane(x, k), x0 = read_lane(x, k + 1);
-            const Reflection f = reflection(x0, wave_sum(lane > k + 1 ? x * x : 0.0));
-            const double v = f.beta == 0.0 ? 0.0 : lane > k + 1 ? x : lane == k + 1 ? x0 - f.alpha : 0.0;
-            if (lane == 0) {
-                tri[k].x = dk;
-                tri[k + 1].y = f.alpha;
+            for (int j = 0; j < 64; ++j) {
+                const double e = element(row < r ? row : 0, j < r ? j : 0);
+                t[16 * (j & 3) + (j >> 2)] = row < r && j < r ? e : 0.0;
             }
-            // past the last row: zeros, as far as a group of eight columns may reach
-            if (lane >= k) vb[lane - k] = v;
-            if (lane < 8) vb[64 - k + lane] = 0.0;
+            double x = t[0];
+            int k = 0;
+            if (r > 32) reduce_steps<Rows64, 16>(t, x, k, (r - 29) & ~3, r, to, lane);
+            // 32 rows or fewer are left
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                if (row < 32) sm[row][j] = t[16 * (j & 3) + (j >> 2)];
             wave_sync();
-            const int live = r - k;
-            double p[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int q = 0; q < RC / 8; ++q)
-                if (8 * q < live) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (8 * q + u > 0) p[u & 3] = fma(t[8 * q + u], vb[8 * q + u], p[u & 3]);
-                }
-            const double pv = lane > k ? (p[0] + p[1]) + (p[2] + p[3]) : 0.0;
-            const double kk = 0.5 * f.beta * (f.beta * wave_sum(v * pv));  // (beta^2 may overflow)
-            const double w = fma(f.beta, pv, -kk * v);
-            if (lane >= k) wb[lane - k] = w;
-            if (lane < 8) wb[64 - k + lane] = 0.0;
-            wave_sync();
-#pragma unroll
-            for (int q = 0; q < RC / 8; ++q)
-                if (8 * q < live) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (8 * q + u > 0)
-                            t[8 * q + u - 1] = fma(-v, wb[8 * q + u], fma(-w, vb[8 * q + u], t[8 * q + u]));
-                }
-        }
-        if (r > 0) {
-            const double last = read_lane(t[0], r - 1);
-            if (lane == 0) tri[r - 1].x = last;
+            reduce32([&](int i, int j) { return sm[i][j]; }, r - k, to + k, lane);
         }
     }
     __syncthreads();
@@ -645,15 +832,35 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     auto find = [&](auto gc) {
         constexpr int G = decltype(gc)::value;
         const int c = tid / G;
-        const double ev = nth_largest<G>(tri, r, c < r ? c : r - 1, in.lo, in.hi, lane);
-        if (c < r && (lane & (G - 1)) == 0) eig[c] = ev;
+        using R = Rounds<G>;
+        double lo = in.lo, hi = in.hi;
+        const int nth = c < r ? c : r - 1;
+        const bool mine = c < r && (lane & (G - 1)) == 0;
+        narrow<G>(tri, r, nth, lo, hi, lane, R::kEarly);
+        if (mine) {
+            eig[c] = lo;
+            eig_hi[c] = hi;
+        }
+        __syncthreads();
+        const double l[1] = {eig[lane]}, h[1] = {eig_hi[lane]};
+        const int k = decided(l, h, r, tau, lane);  // by every wavefront, from the same
+        if (k >= 0) {
+            if (tid == 0) *it.out = k;
+            return true;
+        }
+        narrow<G>(tri, r, nth, lo, hi, lane, R::kAll - R::kEarly);
+        __syncthreads();
+        if (mine) eig[c] = eigenvalue(lo, hi);
         if (tid >= r && tid < 64) eig[tid] = 0.0;
+        return false;
     };
-    if (r <= 4) find(std::integral_constant<int, 64>());
-    else if (r <= 8) find(std::integral_constant<int, 32>());
-    else if (r <= 16) find(std::integral_constant<int, 16>());
-    else if (RC <= 32 || r <= 32) find(std::integral_constant<int, 8>());
-    else find(std::integral_constant<int, 4>());
+    bool done;
+    if (r <= 4) done = find(std::integral_constant<int, 64>());
+    else if (r <= 8) done = find(std::integral_constant<int, 32>());
+    else if (r <= 16) done = find(std::integral_constant<int, 16>());
+    else if (RC <= 32 || r <= 32) done = find(std::integral_constant<int, 8>());
+    else done = find(std::integral_constant<int, 4>());
+    if (done) return;
     __syncthreads();
     if (wave == 0) {
         const int32_t k = count_share(eig, r, tau, lane);
@@ -674,8 +881,9 @@ __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
     const int lane = threadIdx.x & 63;
     const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (c >= r) return;
-    const double ev = nth_largest<64>(tri, r, c, bounds_of(it)[0], bounds_of(it)[1], lane);
-    if (lane == 0) eig_of(it)[c] = ev;
+    double lo = bounds_of(it)[0], hi = bounds_of(it)[1];
+    narrow<64>(tri, r, c, lo, hi, lane, Rounds<64>::kAll);
+    if (lane == 0) eig_of(it)[c] = eigenvalue(lo, hi);
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {

@@ -842,6 +842,25 @@ def test_effective_rank_at_tau_one_stops_where_the_sum_does(r):
     assert int(out.item()) == min(r, 27) == ref.effective_rank(q, 1.0)
 
 
+@pytest.mark.parametrize("r", [3, 4, 7, 8, 14, 16, 18, 30, 32, 34, 47, 62, 64, 66, 128, 190, 256])
+@pytest.mark.parametrize("kind", ["dense", "equal"])
+def test_effective_rank_where_a_share_is_reached_by_a_hair(r, kind):
+    # tau 1e-9 below and above the share of the j largest eigenvalues: bounds of 2^-19 .. 2^-23 cannot
+    # tell on which side it falls, eigenvalues to 2^-56 (of sums of at most 256) can.
+    n = 512
+    q = (rng(7 * r).standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.6)).astype(np.float32)
+    if kind == "equal":
+        q = np.zeros((r, n), np.float32)
+        q[np.arange(r), np.arange(r)] = 1.0
+    s = np.cumsum(np.linalg.eigvalsh(q.astype(np.float64) @ q.T.astype(np.float64))[::-1])
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for j in sorted({1, r // 3, r // 2, r - 1}):
+        for tau, want in ((s[j - 1] / s[-1] - 1e-9, j), (s[j - 1] / s[-1] + 1e-9, j + 1)):
+            dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
+            assert int(out.item()) == want == ref.effective_rank(q, tau), (j, tau)
+
+
 @pytest.mark.parametrize("r", [1, 3, 16, 31, 32, 33, 64, 65, 130, 256])
 def test_effective_rank_of_a_factor_that_is_not_finite(r):
     # A NaN anywhere: no eigenvalue is a number and no share is ever reached, r' = 0.  An infinity: up
