@@ -4,11 +4,11 @@
 // orthonormalisation).  Everything after it is fp64 too:
 //   tridiag_kernel       Householder reduction to tridiagonal form, one workgroup per matrix
 //   eigenvalues          every eigenvalue by multisection on the Sturm sequence: G lanes evaluate
-//                        G points of an interval at once, so a round narrows it G + 1 times; up to
-//                        rank 64 only as far as it takes to tell which sums hold the share
+//                        G points of an interval at once, so a round narrows it G + 1 times; only
+//                        as far as it takes to tell which sums hold the share
 //   count                prefix sum over the eigenvalues (they come out in order) and count
-// Up to rank 64 the last two follow in the same workgroup; above, eigenvalues_kernel spreads them
-// over the GPU (one wavefront per eigenvalue) and count_kernel finishes.
+// Up to rank 64 the last two follow in the same workgroup; above, eigenvalue_bounds_kernel and, where those leave
+// it open, eigenvalues_kernel spread them over the GPU (one wavefront per eigenvalue) and count_kernel finishes.
 #include <type_traits>
 
 #include "common.h"
@@ -18,6 +18,7 @@ namespace dlcx {
 constexpr int kTT = 256;             // threads of the reduction up to kFusedRank
 constexpr int kTri = 512;            // and above
 constexpr int kFusedRank = 64;       // ranks up to here finish in the same workgroup
+constexpr int kTail = 64;            // rows that one wavefront reduces at most
 
 // the fp64 value of the lane that DPP control `kCtrl` pairs this lane with (inside rows of 16)
 template <int kCtrl>
@@ -270,249 +271,19 @@ __device__ __forceinline__ Interval gershgorin(const double2 *tri, int r, int la
 }
 
 // What tridiag_kernel leaves in FactorItem::g above rank 64: the Sturm table with all that count_below reads,
-// from double 0; then lo, hi and the number of rows that are not zero; then the eigenvalues (still scaled: r'
-// does not depend on a power of two), which eigenvalues_kernel writes while it reads the table.
+// from double 0; then lo, hi and the number of rows that are not zero.  Behind them the other kernels' part, written
+// while the table is read: whether r' is open, bounds of every eigenvalue, the eigenvalues (still scaled: r' does
+// not depend on a power of two).
 constexpr int kTableTerms = DLCX_MAX_RANK + 8;
 static_assert(kTableTerms >= (DLCX_MAX_RANK + 15) / 16 * 16 + 8, "whole blocks and the half block after them");
-static_assert(2 * kTableTerms + 8 + DLCX_MAX_RANK <= (kFusedRank + 2) * (kFusedRank + 2), "room in the smallest g");
+static_assert(2 * kTableTerms + 8 + 3 * DLCX_MAX_RANK <= (kFusedRank + 2) * (kFusedRank + 2), "room in the smallest g");
 __device__ __forceinline__ double2 *tri_of(const FactorItem &it) { return reinterpret_cast<double2 *>(it.g); }
 __device__ __forceinline__ double *bounds_of(const FactorItem &it) { return it.g + 2 * kTableTerms; }
 __device__ __forceinline__ int live_of(const FactorItem &it) { return __builtin_amdgcn_readfirstlane((int)bounds_of(it)[2]); }
+__device__ __forceinline__ double *open_of(const FactorItem &it) { return it.g + 2 * kTableTerms + 7; }
 __device__ __forceinline__ double *eig_of(const FactorItem &it) { return it.g + 2 * kTableTerms + 8; }
-
-// Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
-// S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (h, ti, tj) holds element
-// (ti, tj) of the tiles whose column y has parity h.  An off-diagonal tile serves S v twice, along its
-// rows and its columns.  Step k, with v of row k in LDS:
-//   S v      row parts added over the 16 lanes of tj, column parts over ti: four rows of lanes in a
-//            wavefront, four wavefronts and two parities in LDS                              | barrier
-//   p = S v  the parts added up, two lanes per entry                                         | barrier
-//   S -= v w^T + w v^T  with w = beta p - (beta^2 v.p / 2) v, formed where it is used; before its own
-//            share one wavefront works out the next v and beta from row k + 1, which the update before
-//            has left in LDS                                                                 | barrier
-// Rows that are done have zeros in v and w; groups of four tile rows that are done are skipped (a branch for
-// every row took as long as the work it saved).
-// Bound by the instructions of a step, two wavefronts to a SIMD, and by the chain of the reflection, 255
-// steps in a row.  Eight wavefronts of 256 registers, 144 of them tiles at r = 256: with one wavefront per
-// SIMD half of the tiles sat in the accumulator file, which vector instructions cannot name, two moves for
-// every use.  v and w along the rows come from one lane of each row of 16 (row_bcast): read from LDS row by
-// row they kept the LDS busy for a third of a step.  Seven factors at r = 256: 545 us, 2.1 us a step, of which
-// S v 0.75, sums and barriers 0.45, the reflection 0.5 and the update behind it 0.4 (one wavefront per SIMD:
-// 783 us; whole tile rows dealt to the wavefronts, which need fewer sums across lanes but differ in work and
-// branch at every tile: 725 us).
-template <int NT>
-__global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
-    constexpr int R = 16 * NT;
-    constexpr int N = NT / 2;   // tile columns of one parity
-    constexpr int Q = R / 64;   // entries per lane where one wavefront has a whole row
-    constexpr int W = kTri / 64;
-    __shared__ double vbuf[2][R + 1];   // v of even and odd steps, zeros up to the diagonal
-    __shared__ double betas[2];         // 0: the row is tridiagonal already
-    __shared__ double arow[2][R + 1];   // row k + 1 of S before the update of step k, from the diagonal on
-    __shared__ double pbuf[R + 1];
-    __shared__ double rowpart[2][R];
-    __shared__ double colpart[4][R];
-    __shared__ double2 tri[R];          // d_k and the off-diagonal element before it
-    __shared__ int order[R];            // the rows of S that are not zero
-    __shared__ int counts[W];
-    const FactorItem it = batch.it[blockIdx.x];
-    const int nchunks = it.nchunks;
-    const double *__restrict__ part = it.part;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int par = wave & 1, quarter = wave >> 1;  // parity h; ti / 4
-    const int tj = lane & 15, g = lane >> 4, ti = quarter * 4 + g;
-    const int row_lane = tj < NT ? tj : 0;
-    const int64_t pitch = it.r, rr = pitch * pitch;
-    if (it.r <= kFusedRank) return;
-
-    // The zero columns of the factor: left out, their eigenvalues are zero.  (Reflected with the others
-    // they would come back as rounding, and count at tau = 1.)
-    bool on = false, odd = false;
-    if (tid < it.r) {
-        double s = 0.0;
-        for (int c = 0; c < nchunks; ++c) s += part[tid * pitch + tid + c * rr];
-        on = s != 0.0;
-        odd = !(s < __builtin_inf());
-    }
-    const uint64_t mask = __ballot(on);
-    const bool wave_odd = __ballot(odd) != 0;  // a NaN or an infinity in the factor: no rows, r' = 0
-    if (lane == 0) counts[wave] = wave_odd ? -kTri : __popcll(mask);
-    if (tid < 2) {
-        vbuf[tid][R] = 0.0;
-        arow[tid][R] = 0.0;
-        pbuf[R] = 0.0;
-    }
-    __syncthreads();
-    int before = 0, r = 0;
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-        before += q < wave ? counts[q] : 0;
-        r += counts[q];
-    }
-    if (on && before >= 0) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
-    r = __builtin_amdgcn_readfirstlane(r < 0 ? 0 : r);
-    __syncthreads();
-
-    // t[x][i]: tile (x, 2 i + h).  Where x is odd, i starts with the diagonal tile of h = 1; beside it
-    // h = 0 has the tile left of the diagonal, which takes no part in S v.
-    double t[NT][N];
-#pragma unroll
-    for (int x = 0; x < NT; ++x) {
-        const int a = 16 * x + ti, oa = a < r ? order[a] : 0;
-#pragma unroll
-        for (int i = x / 2; i < N; ++i) {
-            const int b = 16 * (2 * i + par) + tj, ob = b < r ? order[b] : 0;
-            const bool in = a < r && b < r;  // order[] rises
-            const double *src = part + (in ? (oa < ob ? oa * pitch + ob : ob * pitch + oa) : 0);
-            double s = src[0];
-            for (int c = 1; c < nchunks; ++c) s += src[c * rr];
-            t[x][i] = in ? s : 0.0;
-        }
-    }
-    // Row `row`, whose tile row is x, from its tile on.
-    auto keep_row = [&](auto xc, int row) {
-        constexpr int x = decltype(xc)::value;
-        if (((row & 15) >> 2) != quarter || g != (row & 3)) return;
-        double *dst = &arow[row & 1][tj];
-#pragma unroll
-        for (int i = x / 2; i < N; ++i)
-            if (i > x / 2 || x % 2 == 0 || par == 1) dst[16 * (2 * i + par)] = t[x][i];
-    };
-    // The reflection of row c, by one wavefront, R / 64 entries per lane (lv, lw: v and w there; vc, v1, wc,
-    // w1: at c and c + 1; all zero for the first).  c + 1 may be R: nothing is right of the last row.
-    auto reflect = [&](int c, const double (&lv)[Q], const double (&lw)[Q], double vc,
-                       double wc, double v1, double w1) {
-        const double *ar = arow[c & 1];
-        double a[Q], tail = 0.0;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const double x = fma(-lv[q], wc, fma(-lw[q], vc, ar[lane + 64 * q]));
-            a[q] = lane + 64 * q > c + 1 ? x : 0.0;  // arow has nothing left of the diagonal tile
-            tail = fma(a[q], a[q], tail);
-        }
-        const double x0 = fma(-v1, wc, fma(-w1, vc, ar[c + 1])), d = fma(-vc, wc, fma(-wc, vc, ar[c]));
-        const Reflection f = reflection(x0, wave_sum(tail));
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int e = lane + 64 * q;
-            const double y = e == c + 1 ? x0 - f.alpha : a[q];
-            vbuf[c & 1][e] = f.beta == 0.0 ? 0.0 : y;
-        }
-        if (lane == 0) {
-            betas[c & 1] = f.beta;
-            tri[c].x = d;
-            if (c + 1 < R) tri[c + 1].y = f.alpha;
-        }
-    };
-    keep_row(std::integral_constant<int, 0>(), 0);
-    keep_row(std::integral_constant<int, 0>(), 1);
-    __syncthreads();
-    if (wave == 0) {
-        const double zero[Q] = {};
-        reflect(0, zero, zero, 0.0, 0.0, 0.0, 0.0);
-    }
-    __syncthreads();
-    for (int k = 0; k + 1 < r; ++k) {
-        const double *v = vbuf[k & 1];
-        // v along the columns of this thread's tiles and, from lane x of its row, along their rows
-        double cv[N];
-#pragma unroll
-        for (int i = 0; i < N; ++i) cv[i] = v[16 * (2 * i + par) + tj];
-        const double rv = v[16 * row_lane + ti];
-        {
-            const int live = (k + 1) >> 4;  // tile rows and columns before it are done
-            double cp[(N + 3) / 4 * 4] = {};
-            unrolled<NT / 4>([&](auto bc) {
-                constexpr int x0 = 4 * decltype(bc)::value;
-                if (x0 + 3 < live) return;
-                double rp[4];
-                unrolled<4>([&](auto uc) {
-                    constexpr int u = decltype(uc)::value, x = x0 + u, i0 = x / 2;
-                    const double rx = row_bcast<x>(rv);
-                    // the first tile: on the diagonal (row part only) for h = x % 2; none for x odd and h = 0
-                    rp[u] = t[x][i0] * (x % 2 == 0 || par == 1 ? cv[i0] : 0.0);
-                    if (x % 2 == 0) cp[i0] = fma(t[x][i0], par == 1 ? rx : 0.0, cp[i0]);
-#pragma unroll
-                    for (int i = i0 + 1; i < N; ++i) {
-                        rp[u] = fma(t[x][i], cv[i], rp[u]);
-                        cp[i] = fma(t[x][i], rx, cp[i]);
-                    }
-                });
-                const double rs = row_sums(rp, tj);
-                if ((tj & 3) == 0) rowpart[par][16 * (x0 + (tj >> 2)) + ti] = rs;
-            });
-#pragma unroll
-            for (int i = 0; i < N; i += 4) {
-                if (2 * i + 7 < live) continue;
-                const double cs = add_rows(add_halves(cp[i], cp[i + 2]), add_halves(cp[i + 1], cp[i + 3]));
-                if (i + g < N) colpart[quarter][16 * (2 * (i + g) + par) + tj] = cs;
-            }
-        }
-        __syncthreads();
-        if (wave < NT / 2) {
-            const int e = 32 * wave + (lane & 31), hh = lane >> 5;
-            const double s = (colpart[2 * hh][e] + colpart[2 * hh + 1][e]) + rowpart[hh][e];
-            const double p = add_halves(s, s);
-            if (hh == 0) pbuf[e] = e > k ? p : 0.0;  // rows that are done
-        }
-        __syncthreads();
-        const double beta = betas[k & 1];
-        double kk, cw[N], rw = pbuf[16 * row_lane + ti];
-#pragma unroll
-        for (int i = 0; i < N; ++i) cw[i] = pbuf[16 * (2 * i + par) + tj];
-        {
-            double lv[Q], lp[Q], dot = 0.0;
-            const double vc = v[k + 1], pc = pbuf[k + 1], v1 = v[k + 2], p1 = pbuf[k + 2];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                lv[q] = v[lane + 64 * q];
-                lp[q] = pbuf[lane + 64 * q];
-                dot = fma(lp[q], lv[q], dot);
-            }
-            kk = 0.5 * beta * (beta * wave_sum(dot));  // (beta^2 may overflow)
-            if (wave == 0) {  // the others wait for it: ahead of the wavefront beside it on the SIMD
-                __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-                for (int q = 0; q < Q; ++q) lp[q] = fma(beta, lp[q], -kk * lv[q]);
-                reflect(k + 1, lv, lp, vc, fma(beta, pc, -kk * vc), v1, fma(beta, p1, -kk * v1));
-            }
-        }
-        {
-            const int live = (k + 2) >> 4;
-#pragma unroll
-            for (int i = 0; i < N; ++i) cw[i] = fma(beta, cw[i], -kk * cv[i]);
-            rw = fma(beta, rw, -kk * rv);
-            unrolled<NT / 4>([&](auto bc) {
-                constexpr int x0 = 4 * decltype(bc)::value;
-                if (x0 + 3 < live) return;
-                unrolled<4>([&](auto uc) {
-                    constexpr int x = x0 + decltype(uc)::value;
-                    const double rx = row_bcast<x>(rv), wx = row_bcast<x>(rw);
-#pragma unroll
-                    for (int i = x / 2; i < N; ++i) t[x][i] = fma(-rx, cw[i], fma(-wx, cv[i], t[x][i]));
-                });
-                unrolled<4>([&](auto uc) {
-                    if (x0 + decltype(uc)::value == live)
-                        keep_row(std::integral_constant<int, x0 + decltype(uc)::value>(), k + 2);
-                });
-            });
-        }
-        __builtin_amdgcn_s_setprio(0);
-        __syncthreads();
-    }
-    if (wave == 0) {
-        const Interval in = gershgorin(tri, r, lane);
-        for (int i = lane; i < 16 * sturm_blocks(r) + 8; i += 64)
-            tri_of(it)[i] = i < r ? sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0)
-                                  : sturm_fill();
-        if (lane == 0) {
-            bounds_of(it)[0] = in.lo;
-            bounds_of(it)[1] = in.hi;
-            bounds_of(it)[2] = r;
-        }
-    }
-}
+__device__ __forceinline__ double *low_of(const FactorItem &it) { return eig_of(it) + DLCX_MAX_RANK; }
+__device__ __forceinline__ double *high_of(const FactorItem &it) { return eig_of(it) + 2 * DLCX_MAX_RANK; }
 
 // The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
 // a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
@@ -710,6 +481,283 @@ __device__ __forceinline__ void reduce32(F &&element, int r, double2 *tri, int l
     reduce_steps<Rows32, 8>(t, x, k, r, r, tri, lane);
 }
 
+// The same for r <= 64; the last 32 rows go through `sm`, which element() may read as well
+template <typename F, int P>
+__device__ __forceinline__ void reduce64(F &&element, int r, double2 *tri, double (*sm)[P], int lane) {
+    if (r <= 32) {
+        reduce32(element, r, tri, lane);
+        return;
+    }
+    double t[64];
+    const int row = Rows64::row(lane);
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+        const double e = element(row < r ? row : 0, j < r ? j : 0);
+        t[16 * (j & 3) + (j >> 2)] = row < r && j < r ? e : 0.0;
+    }
+    double x = t[0];
+    int k = 0;
+    reduce_steps<Rows64, 16>(t, x, k, (r - 29) & ~3, r, tri, lane);  // to 32 rows or fewer
+#pragma unroll
+    for (int j = 0; j < 32; ++j)
+        if (row < 32) sm[row][j] = t[16 * (j & 3) + (j >> 2)];
+    wave_sync();
+    reduce32([&](int i, int j) { return sm[i][j]; }, r - k, tri + k, lane);
+}
+
+// Householder reduction of S to tridiagonal form, one workgroup per matrix, S in registers.
+// S is cut into 16 x 16 tiles, of which the upper ones (x <= y) exist; thread (h, ti, tj) holds element
+// (ti, tj) of the tiles whose column y has parity h.  An off-diagonal tile serves S v twice, along its
+// rows and its columns.  Step k, with v of row k in LDS:
+//   S v      row parts added over the 16 lanes of tj, column parts over ti: four rows of lanes in a
+//            wavefront, four wavefronts and two parities in LDS                              | barrier
+//   p = S v  the parts added up, two lanes per entry                                         | barrier
+//   S -= v w^T + w v^T  with w = beta p - (beta^2 v.p / 2) v, formed where it is used; before its own
+//            share one wavefront works out the next v and beta from row k + 1, which the update before
+//            has left in LDS                                                                 | barrier
+// Rows that are done have zeros in v and w; groups of four tile rows that are done are skipped (a branch for
+// every row took as long as the work it saved).
+// The last kTail rows go to one wavefront (reduce64), 0.45 - 0.7 us a step and no barrier, where they took 1.2 - 2
+// here: whole calls, us before | after (the 20 - 30 of the eigenvalue bounds in it), 2048 x 66 133 | 76, 8192 x 100
+// 196 | 149, 5008 x 130 302 | 226, seven factors at r = 190 471 | 407, at 256 739 | 672.
+// Bound by the instructions of a step, two wavefronts to a SIMD, and by the chain of the reflection, 191
+// steps in a row at r = 256.  Eight wavefronts of 256 registers, 144 of them tiles at r = 256: with one wavefront per
+// SIMD half of the tiles sat in the accumulator file, which vector instructions cannot name, two moves for
+// every use.  v and w along the rows come from one lane of each row of 16 (row_bcast): read from LDS row by
+// row they kept the LDS busy for a third of a step.  Seven factors at r = 256: 2.4 us a step, of which
+// S v 0.75, sums and barriers 0.45, the reflection 0.5 and the update behind it 0.4 (one wavefront per SIMD:
+// 783 us; whole tile rows dealt to the wavefronts, which need fewer sums across lanes but differ in work and
+// branch at every tile: 725 us).
+template <int NT>
+__global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
+    constexpr int R = 16 * NT;
+    constexpr int N = NT / 2;   // tile columns of one parity
+    constexpr int Q = R / 64;   // entries per lane where one wavefront has a whole row
+    constexpr int W = kTri / 64;
+    __shared__ double vbuf[2][R + 1];   // v of even and odd steps, zeros up to the diagonal
+    __shared__ double betas[2];         // 0: the row is tridiagonal already
+    __shared__ double arow[2][R + 1];   // row k + 1 of S before the update of step k, from the diagonal on
+    __shared__ double pbuf[R + 1];
+    __shared__ double rowpart[2][R];
+    __shared__ double colpart[4][R];
+    __shared__ double2 tri[R + kSturmPad], unused[64 + kTail + kSturmPad];  // d_k and the off-diagonal element before it
+    __shared__ double sm[kTail][kTail + 1];  // the last rows
+    __shared__ int order[R];            // the rows of S that are not zero
+    __shared__ int counts[W];
+    const FactorItem it = batch.it[blockIdx.x];
+    const int nchunks = it.nchunks;
+    const double *__restrict__ part = it.part;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int par = wave & 1, quarter = wave >> 1;  // parity h; ti / 4
+    const int tj = lane & 15, g = lane >> 4, ti = quarter * 4 + g;
+    const int row_lane = tj < NT ? tj : 0;
+    const int64_t pitch = it.r, rr = pitch * pitch;
+    if (it.r <= kFusedRank) return;
+
+    // The zero columns of the factor: left out, their eigenvalues are zero.  (Reflected with the others
+    // they would come back as rounding, and count at tau = 1.)
+    bool on = false, odd = false;
+    if (tid < it.r) {
+        double s = 0.0;
+        for (int c = 0; c < nchunks; ++c) s += part[tid * pitch + tid + c * rr];
+        on = s != 0.0;
+        odd = !(s < __builtin_inf());
+    }
+    const uint64_t mask = __ballot(on);
+    const bool wave_odd = __ballot(odd) != 0;  // a NaN or an infinity in the factor: no rows, r' = 0
+    if (lane == 0) counts[wave] = wave_odd ? -kTri : __popcll(mask);
+    if (tid < 2) {
+        vbuf[tid][R] = 0.0;
+        arow[tid][R] = 0.0;
+        pbuf[R] = 0.0;
+    }
+    __syncthreads();
+    int before = 0, r = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        before += q < wave ? counts[q] : 0;
+        r += counts[q];
+    }
+    if (on && before >= 0) order[before + __popcll(mask & ((1ull << lane) - 1))] = tid;
+    r = __builtin_amdgcn_readfirstlane(r < 0 ? 0 : r);
+    __syncthreads();
+
+    // t[x][i]: tile (x, 2 i + h).  Where x is odd, i starts with the diagonal tile of h = 1; beside it
+    // h = 0 has the tile left of the diagonal, which takes no part in S v.
+    double t[NT][N];
+#pragma unroll
+    for (int x = 0; x < NT; ++x) {
+        const int a = 16 * x + ti, oa = a < r ? order[a] : 0;
+#pragma unroll
+        for (int i = x / 2; i < N; ++i) {
+            const int b = 16 * (2 * i + par) + tj, ob = b < r ? order[b] : 0;
+            const bool in = a < r && b < r;  // order[] rises
+            const double *src = part + (in ? (oa < ob ? oa * pitch + ob : ob * pitch + oa) : 0);
+            double s = src[0];
+            for (int c = 1; c < nchunks; ++c) s += src[c * rr];
+            t[x][i] = in ? s : 0.0;
+        }
+    }
+    // Row `row`, whose tile row is x, from its tile on.
+    auto keep_row = [&](auto xc, int row) {
+        constexpr int x = decltype(xc)::value;
+        if (((row & 15) >> 2) != quarter || g != (row & 3)) return;
+        double *dst = &arow[row & 1][tj];
+#pragma unroll
+        for (int i = x / 2; i < N; ++i)
+            if (i > x / 2 || x % 2 == 0 || par == 1) dst[16 * (2 * i + par)] = t[x][i];
+    };
+    // The reflection of row c, by one wavefront, R / 64 entries per lane (lv, lw: v and w there; vc, v1, wc,
+    // w1: at c and c + 1; all zero for the first).  c + 1 may be R: nothing is right of the last row.
+    auto reflect = [&](int c, const double (&lv)[Q], const double (&lw)[Q], double vc,
+                       double wc, double v1, double w1) {
+        const double *ar = arow[c & 1];
+        double a[Q], tail = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const double x = fma(-lv[q], wc, fma(-lw[q], vc, ar[lane + 64 * q]));
+            a[q] = lane + 64 * q > c + 1 ? x : 0.0;  // arow has nothing left of the diagonal tile
+            tail = fma(a[q], a[q], tail);
+        }
+        const double x0 = fma(-v1, wc, fma(-w1, vc, ar[c + 1])), d = fma(-vc, wc, fma(-wc, vc, ar[c]));
+        const Reflection f = reflection(x0, wave_sum(tail));
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int e = lane + 64 * q;
+            const double y = e == c + 1 ? x0 - f.alpha : a[q];
+            vbuf[c & 1][e] = f.beta == 0.0 ? 0.0 : y;
+        }
+        if (lane == 0) {
+            betas[c & 1] = f.beta;
+            tri[c].x = d;
+            if (c + 1 < R) tri[c + 1].y = f.alpha;
+        }
+    };
+    keep_row(std::integral_constant<int, 0>(), 0);
+    keep_row(std::integral_constant<int, 0>(), 1);
+    __syncthreads();
+    const int stop = r > kTail ? r - kTail : 0;
+    if (wave == 0 && stop > 0) {
+        const double zero[Q] = {};
+        reflect(0, zero, zero, 0.0, 0.0, 0.0, 0.0);
+    }
+    __syncthreads();
+    for (int k = 0; k < stop; ++k) {
+        const double *v = vbuf[k & 1];
+        // v along the columns of this thread's tiles and, from lane x of its row, along their rows
+        double cv[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) cv[i] = v[16 * (2 * i + par) + tj];
+        const double rv = v[16 * row_lane + ti];
+        {
+            const int live = (k + 1) >> 4;  // tile rows and columns before it are done
+            double cp[(N + 3) / 4 * 4] = {};
+            unrolled<NT / 4>([&](auto bc) {
+                constexpr int x0 = 4 * decltype(bc)::value;
+                if (x0 + 3 < live) return;
+                double rp[4];
+                unrolled<4>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value, x = x0 + u, i0 = x / 2;
+                    const double rx = row_bcast<x>(rv);
+                    // the first tile: on the diagonal (row part only) for h = x % 2; none for x odd and h = 0
+                    rp[u] = t[x][i0] * (x % 2 == 0 || par == 1 ? cv[i0] : 0.0);
+                    if (x % 2 == 0) cp[i0] = fma(t[x][i0], par == 1 ? rx : 0.0, cp[i0]);
+#pragma unroll
+                    for (int i = i0 + 1; i < N; ++i) {
+                        rp[u] = fma(t[x][i], cv[i], rp[u]);
+                        cp[i] = fma(t[x][i], rx, cp[i]);
+                    }
+                });
+                const double rs = row_sums(rp, tj);
+                if ((tj & 3) == 0) rowpart[par][16 * (x0 + (tj >> 2)) + ti] = rs;
+            });
+#pragma unroll
+            for (int i = 0; i < N; i += 4) {
+                if (2 * i + 7 < live) continue;
+                const double cs = add_rows(add_halves(cp[i], cp[i + 2]), add_halves(cp[i + 1], cp[i + 3]));
+                if (i + g < N) colpart[quarter][16 * (2 * (i + g) + par) + tj] = cs;
+            }
+        }
+        __syncthreads();
+        if (wave < NT / 2) {
+            const int e = 32 * wave + (lane & 31), hh = lane >> 5;
+            const double s = (colpart[2 * hh][e] + colpart[2 * hh + 1][e]) + rowpart[hh][e];
+            const double p = add_halves(s, s);
+            if (hh == 0) pbuf[e] = e > k ? p : 0.0;  // rows that are done
+        }
+        __syncthreads();
+        const double beta = betas[k & 1];
+        double kk, cw[N], rw = pbuf[16 * row_lane + ti];
+#pragma unroll
+        for (int i = 0; i < N; ++i) cw[i] = pbuf[16 * (2 * i + par) + tj];
+        {
+            double lv[Q], lp[Q], dot = 0.0;
+            const double vc = v[k + 1], pc = pbuf[k + 1], v1 = v[k + 2], p1 = pbuf[k + 2];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                lv[q] = v[lane + 64 * q];
+                lp[q] = pbuf[lane + 64 * q];
+                dot = fma(lp[q], lv[q], dot);
+            }
+            kk = 0.5 * beta * (beta * wave_sum(dot));  // (beta^2 may overflow)
+            if (wave == 0) {  // the others wait for it: ahead of the wavefront beside it on the SIMD
+                __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) lp[q] = fma(beta, lp[q], -kk * lv[q]);
+                reflect(k + 1, lv, lp, vc, fma(beta, pc, -kk * vc), v1, fma(beta, p1, -kk * v1));
+            }
+        }
+        {
+            const int live = (k + 2) >> 4;
+#pragma unroll
+            for (int i = 0; i < N; ++i) cw[i] = fma(beta, cw[i], -kk * cv[i]);
+            rw = fma(beta, rw, -kk * rv);
+            unrolled<NT / 4>([&](auto bc) {
+                constexpr int x0 = 4 * decltype(bc)::value;
+                if (x0 + 3 < live) return;
+                unrolled<4>([&](auto uc) {
+                    constexpr int x = x0 + decltype(uc)::value;
+                    const double rx = row_bcast<x>(rv), wx = row_bcast<x>(rw);
+#pragma unroll
+                    for (int i = x / 2; i < N; ++i) t[x][i] = fma(-rx, cw[i], fma(-wx, cv[i], t[x][i]));
+                });
+                unrolled<4>([&](auto uc) {
+                    if (x0 + decltype(uc)::value == live)
+                        keep_row(std::integral_constant<int, x0 + decltype(uc)::value>(), k + 2);
+                });
+            });
+        }
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();
+    }
+    // what is left, rows `stop` and on, in one wavefront
+#pragma unroll
+    for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int i = x / 2; i < N; ++i) {
+            const int y = 2 * i + par, p = 16 * x + ti - stop, q = 16 * y + tj - stop;
+            if (y >= x && p >= 0 && q >= 0 && p < kTail && q < kTail) {
+                sm[p][q] = t[x][i];
+                if (y > x) sm[q][p] = t[x][i];
+            }
+        }
+    __syncthreads();
+    if (wave == 0 && r > 0) {
+        reduce64([&](int i, int j) { return sm[i][j]; }, r - stop, lane == 0 ? tri + stop : unused + lane, sm, lane);
+        wave_sync();
+        const Interval in = gershgorin(tri, r, lane);
+        for (int i = lane; i < 16 * sturm_blocks(r) + 8; i += 64)
+            tri_of(it)[i] = i < r ? sturm_term(ldexp(tri[i].x, in.ex), i > 0 ? ldexp(tri[i].y, in.ex) : 0.0)
+                                  : sturm_fill();
+        if (lane == 0) {
+            bounds_of(it)[0] = in.lo;
+            bounds_of(it)[1] = in.hi;
+        }
+    }
+    if (tid == 0) bounds_of(it)[2] = r;
+}
+
 // Ranks up to kFusedRank: the reduction in one wavefront, then the eigenvalues in all four, in bounds first: the
 // share is nearly always decided after a third of their rounds.  Bound by latency: at r = 32 the reduction 32 K
 // clocks (1040 a step), the eigenvalues 12 K, 5 K around them (one lane to a row, v and w through the LDS and
@@ -795,26 +843,8 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
     if (wave == 0 && r > 0) {
         double2 *to = lane == 0 ? tri : unused + lane;
         auto element = [&](int i, int j) { return sm[order[i]][order[j]]; };
-        if constexpr (RC <= 32) {
-            reduce32(element, r, to, lane);
-        } else {
-            double t[64];
-            const int row = Rows64::row(lane);
-#pragma unroll
-            for (int j = 0; j < 64; ++j) {
-                const double e = element(row < r ? row : 0, j < r ? j : 0);
-                t[16 * (j & 3) + (j >> 2)] = row < r && j < r ? e : 0.0;
-            }
-            double x = t[0];
-            int k = 0;
-            if (r > 32) reduce_steps<Rows64, 16>(t, x, k, (r - 29) & ~3, r, to, lane);
-            // 32 rows or fewer are left
-#pragma unroll
-            for (int j = 0; j < 32; ++j)
-                if (row < 32) sm[row][j] = t[16 * (j & 3) + (j >> 2)];
-            wave_sync();
-            reduce32([&](int i, int j) { return sm[i][j]; }, r - k, to + k, lane);
-        }
+        if constexpr (RC <= 32) reduce32(element, r, to, lane);
+        else reduce64(element, r, to, sm, lane);
     }
     __syncthreads();
     if (r == 0) {  // nothing but zeros
@@ -869,27 +899,60 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
 }
 
 // Ranks above kFusedRank: one wavefront per eigenvalue, 64 points a round.  All lanes read the same terms, through
-// the scalar cache.  Bound by the instructions of the sequence, four a term, two wavefronts to some SIMDs: 64 us
-// for seven matrices at r = 256.  (32 lanes per eigenvalue, one wavefront to a SIMD: 54 us, but how many lanes there
-// are for one would then depend on the batch, and with it the last bit of an eigenvalue, which decides where tau
-// falls on a whole number of equal ones.)
-__global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch) {
+// the scalar cache.  Bound by the instructions of the sequence, four a term, two wavefronts to some SIMDs: 6.4 us a
+// round for seven matrices at r = 256.  (32 lanes per eigenvalue, one wavefront to a SIMD: 5.4 us, but how many
+// lanes there are for one would then depend on the batch, and with it the last bit of an eigenvalue, which decides
+// where tau falls on a whole number of equal ones.)  After kEarlyRounds, at 2^-29, the bounds nearly always tell
+// already which sums hold the share (at four, 2^-23, one factor in ten would go on).
+constexpr int kEarlyRounds = 5;
+__global__ __launch_bounds__(256) void eigenvalue_bounds_kernel(FactorBatch batch) {
     const FactorItem it = batch.it[blockIdx.y];
     if (it.r <= kFusedRank) return;
     const int r = live_of(it);
-    const double2 *__restrict__ tri = tri_of(it);
     const int lane = threadIdx.x & 63;
     const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (c >= r) return;
+    const double2 *__restrict__ tri = tri_of(it);
     double lo = bounds_of(it)[0], hi = bounds_of(it)[1];
-    narrow<64>(tri, r, c, lo, hi, lane, Rounds<64>::kAll);
+    narrow<64>(tri, r, c, lo, hi, lane, kEarlyRounds);
+    if (lane == 0) {
+        low_of(it)[c] = lo;
+        high_of(it)[c] = hi;
+    }
+}
+
+// r' from those bounds, or else the eigenvalues to the end and r' by count_kernel (open_of: 1).
+__global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch, double tau) {
+    const FactorItem it = batch.it[blockIdx.y];
+    if (it.r <= kFusedRank) return;
+    const int r = live_of(it);
+    const int lane = threadIdx.x & 63;
+    const int c = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double *__restrict__ low = low_of(it), *__restrict__ high = high_of(it);
+    constexpr int N = DLCX_MAX_RANK / 64;
+    double l[N], h[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int e = 64 * q + lane < r ? 64 * q + lane : 0;
+        l[q] = low[e];
+        h[q] = high[e];
+    }
+    const int k = r > 0 ? decided(l, h, r, tau, lane) : -1;
+    if (c == 0 && lane == 0) {
+        *open_of(it) = k < 0 ? 1.0 : 0.0;
+        if (k >= 0) *it.out = k;
+    }
+    if (k >= 0 || c >= r) return;
+    const double2 *__restrict__ tri = tri_of(it);
+    double lo = low[c], hi = high[c];
+    narrow<64>(tri, r, c, lo, hi, lane, Rounds<64>::kAll - kEarlyRounds);
     if (lane == 0) eig_of(it)[c] = eigenvalue(lo, hi);
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {
     __shared__ double eig[DLCX_MAX_RANK];
     const FactorItem it = batch.it[blockIdx.x];
-    if (it.r <= kFusedRank) return;
+    if (it.r <= kFusedRank || *open_of(it) == 0.0) return;
     const int r = live_of(it);
     for (int c = threadIdx.x; c < DLCX_MAX_RANK; c += 64) eig[c] = c < r ? eig_of(it)[c] : 0.0;
     __syncthreads();
@@ -949,8 +1012,9 @@ int launch_effective_rank_batch(const FactorBatch &batch, double tau, hipStream_
             hipLaunchKernelGGL(tridiag_kernel<12>, grid, dim3(kTri), 0, st, summed);
         else
             hipLaunchKernelGGL(tridiag_kernel<16>, grid, dim3(kTri), 0, st, summed);
-        hipLaunchKernelGGL(eigenvalues_kernel, dim3((unsigned)ceil_div(rmax, 4), (unsigned)batch.n),
-                           dim3(256), 0, st, summed);
+        const dim3 each((unsigned)ceil_div(rmax, 4), (unsigned)batch.n);
+        hipLaunchKernelGGL(eigenvalue_bounds_kernel, each, dim3(256), 0, st, summed);
+        hipLaunchKernelGGL(eigenvalues_kernel, each, dim3(256), 0, st, summed, tau);
         hipLaunchKernelGGL(count_kernel, grid, dim3(64), 0, st, summed, tau);
     }
     return check_launch("effective_rank");

@@ -861,6 +861,22 @@ def test_effective_rank_where_a_share_is_reached_by_a_hair(r, kind):
             assert int(out.item()) == want == ref.effective_rank(q, tau), (j, tau)
 
 
+@pytest.mark.parametrize("r,live", [(66, 1), (100, 31), (100, 33), (128, 64), (128, 65), (129, 66), (130, 80),
+                                    (192, 81), (193, 96), (250, 97), (256, 128), (256, 193)])
+def test_effective_rank_where_one_wavefront_takes_the_last_rows(r, live):
+    # Above rank 64 the last 64 of the columns that are not zero are left to one wavefront: none, one or many before
+    # them, cut at every offset in a 16 x 16 tile, and fewer than 64 in all.
+    n = 512
+    g = rng(r * live)
+    q = (g.standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.6)).astype(np.float32)
+    q[g.permutation(r)[live:]] = 0.0
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    for tau in (0.3, 0.9, 0.99, 0.9999):
+        dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
+        assert int(out.item()) == ref.effective_rank(q, tau), tau
+
+
 @pytest.mark.parametrize("r", [1, 3, 16, 31, 32, 33, 64, 65, 130, 256])
 def test_effective_rank_of_a_factor_that_is_not_finite(r):
     # A NaN anywhere: no eigenvalue is a number and no share is ever reached, r' = 0.  An infinity: up
