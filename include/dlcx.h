@@ -97,6 +97,14 @@ int dlcx_compress_batched(const dlcx_desc *desc, int phase, int K,
                           uint8_t *const *codes_out_host, float *const *scales_out_host,
                           void *workspace, void *stream);
 
+/* dlcx_compress_batched followed by dlcx_dequant_average of its payloads, bit for bit, for callers
+ * that hold the payloads of all workers: the quantiser forms the mean (r x L) as well.  mean_out
+ * must not overlap the workspace, the payloads or the basis. */
+int dlcx_compress_average(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
+                          const float *basis, uint8_t *const *codes_out_host,
+                          float *const *scales_out_host, float *mean_out, void *workspace,
+                          void *stream);
+
 /* The AllReduce-average of Alg. 2 over the K data-parallel workers, on payloads held in this
  * GPU's memory: factor_out = (1/K) sum_k dequant(codes_k, scales_k), workers added in index
  * order.  For phase P the mean is then orthonormalised in place (see dlcx_orthonormalize),
@@ -169,6 +177,16 @@ int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const fl
                                  float *v, float lr, float mu, const float *basis,
                                  uint8_t *const *codes_out_host, float *const *scales_out_host,
                                  void *workspace, void *stream);
+
+/* The same followed by dlcx_dequant_average of the payloads, bit for bit, as dlcx_compress_average.
+ * mean_out may be p_hat: the previous round's factor is read before the mean is written. */
+int dlcx_ef_delta_apply_compress_average(const dlcx_desc *desc, int32_t r_prev, const float *p_hat,
+                                         const float *q_bar, int K, const void *const *theta_l_host,
+                                         int theta_l_dtype, float *const *ef_inout_host,
+                                         float *theta_g, float *v, float lr, float mu,
+                                         const float *basis, uint8_t *const *codes_out_host,
+                                         float *const *scales_out_host, float *mean_out,
+                                         void *workspace, void *stream);
 
 /* Outer step t of Alg. 2 for one tensor whose compressor is the quantiser alone: Alg. 1 with
  * the LOWRANK step left out, C(delta) = QUANTIZE(delta | q), the Int4-only setting the paper

@@ -44,6 +44,7 @@ SYMBOLS = {
     "dlcx_delta_ef": (_int, [_vp, _vp, _int, _vp, _i64, _vp]),
     "dlcx_compress": (_int, [_dp, _int, _vp, _vp, _vp, _vp, _vp, _vp]),
     "dlcx_compress_batched": (_int, [_dp, _int, _int, _vp, _vp, _vp, _vp, _vp, _vp]),
+    "dlcx_compress_average": (_int, [_dp, _int, _int, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),
     "dlcx_average": (_int, [_dp, _int, _int, _vp, _vp, _vp, _vp, _vp]),
     "dlcx_average_static": (_int, [_dp, _int, _int, _vp, _vp, _vp, _vp]),
     "dlcx_static_scratch_bytes": (C.c_size_t, []),
@@ -55,6 +56,9 @@ SYMBOLS = {
                                    C.c_float, _vp, _vp]),
     "dlcx_ef_delta_apply_compress": (_int, [_dp, _i32, _vp, _vp, _int, _vp, _int, _vp, _vp, _vp,
                                             C.c_float, C.c_float, _vp, _vp, _vp, _vp, _vp]),
+    "dlcx_ef_delta_apply_compress_average": (_int, [_dp, _i32, _vp, _vp, _int, _vp, _int, _vp, _vp,
+                                                    _vp, C.c_float, C.c_float, _vp, _vp, _vp, _vp,
+                                                    _vp, _vp]),
     "dlcx_outer_nesterov": (_int, [_vp, _vp, _vp, _i64, C.c_float, C.c_float, _vp]),
     "dlcx_quant_round": (_int, [_i64, _int, _int, _int, _vp, _int, _vp, _vp, _vp, C.c_double,
                                 C.c_double, _vp, _vp, _int, _vp, _vp, _vp]),
@@ -164,6 +168,16 @@ def dlcx_compress_batched(d, phase, deltas, basis, codes_out, scales_out, worksp
                                        _ptr(workspace), _stream(stream)), "dlcx_compress_batched")
 
 
+def dlcx_compress_average(d, phase, deltas, basis, codes_out, scales_out, mean_out, workspace,
+                          stream=None):
+    dp, k1 = _ptr_array(deltas)
+    cp, k2 = _ptr_array(codes_out)
+    sp, k3 = _ptr_array(scales_out)
+    _check(lib().dlcx_compress_average(C.byref(d), phase, len(deltas), dp, _ptr(basis), cp, sp,
+                                       _ptr(mean_out), _ptr(workspace), _stream(stream)),
+           "dlcx_compress_average")
+
+
 def dlcx_average(d, phase, codes, scales, factor_out, workspace, stream=None):
     cp, k1 = _ptr_array(codes)
     sp, k2 = _ptr_array(scales)
@@ -222,6 +236,20 @@ def dlcx_ef_delta_apply_compress(d, r_prev, p_hat, q_bar, theta_l, ef_inout, the
         C.byref(d), r_prev, _ptr(p_hat), _ptr(q_bar), len(ef_inout), tp, dt, ep, _ptr(theta_g),
         _ptr(v), lr, mu, _ptr(basis), cp, sp, _ptr(workspace), _stream(stream)),
         "dlcx_ef_delta_apply_compress")
+
+
+def dlcx_ef_delta_apply_compress_average(d, r_prev, p_hat, q_bar, theta_l, ef_inout, theta_g, v, lr,
+                                         mu, basis, codes_out, scales_out, mean_out, workspace,
+                                         stream=None):
+    dt = BF16 if theta_l[0].dtype == torch.bfloat16 else F32
+    tp, k1 = _ptr_array(list(theta_l))
+    ep, k2 = _ptr_array(list(ef_inout))
+    cp, k3 = _ptr_array(list(codes_out))
+    sp, k4 = _ptr_array(list(scales_out))
+    _check(lib().dlcx_ef_delta_apply_compress_average(
+        C.byref(d), r_prev, _ptr(p_hat), _ptr(q_bar), len(ef_inout), tp, dt, ep, _ptr(theta_g),
+        _ptr(v), lr, mu, _ptr(basis), cp, sp, _ptr(mean_out), _ptr(workspace), _stream(stream)),
+        "dlcx_ef_delta_apply_compress_average")
 
 
 def dlcx_outer_nesterov(theta_g, v, delta_hat, lr, mu, numel=None, stream=None):

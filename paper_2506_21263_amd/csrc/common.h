@@ -59,7 +59,7 @@ int launch_nesterov(float *theta, float *v, const float *g, int64_t numel, float
 // K factors of `count` floats each; x.p[k] -> codes.p[k], scales.p[k].
 int launch_quantize(int K, const PtrPack<const float *> &x, int64_t count, int qbits, int group,
                     const PtrPack<uint8_t *> &codes, const PtrPack<float *> &scales,
-                    hipStream_t st);
+                    hipStream_t st, float *mean = nullptr);
 // The same on sums that are still partial: x[k] = sum_s slabs[k][s] in slab order (S slabs `stride`
 // floats apart) is written to sums.p[k] and quantised in one pass.
 struct PartialSums {
@@ -104,9 +104,10 @@ __device__ __forceinline__ float4 sum_partials(const float *__restrict__ x, int6
     }
     return make_float4((float)t[0], (float)t[1], (float)t[2], (float)t[3]);
 }
+// mean: where the mean of what the K payloads decode to goes as well, or nullptr
 int launch_sum_quantize(int K, const PartialSums &part, const PtrPack<float *> &sums,
                         int64_t count, int qbits, int group, const PtrPack<uint8_t *> &codes,
-                        const PtrPack<float *> &scales, hipStream_t st);
+                        const PtrPack<float *> &scales, float *mean, hipStream_t st);
 int launch_dequant_average(int K, const PtrPack<const uint8_t *> &codes,
                            const PtrPack<const float *> &scales, int64_t count, int qbits,
                            int group, float *mean_out, hipStream_t st);

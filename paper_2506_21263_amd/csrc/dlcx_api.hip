@@ -472,10 +472,10 @@ int dlcx_quantize(const float *x, int64_t count, int qbits, int group, uint8_t *
     return launch_quantize(1, xs, count, qbits, group, cs, ss, as_stream(stream));
 }
 
-int dlcx_compress_batched(const dlcx_desc *desc, int phase, int K,
-                          const float *const *deltas_host, const float *basis,
-                          uint8_t *const *codes_out_host, float *const *scales_out_host,
-                          void *workspace, void *stream) {
+// mean: the mean of the payloads as well, unless nullptr
+static int compress(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host, const float *basis,
+                    uint8_t *const *codes_out_host, float *const *scales_out_host, float *mean, void *workspace,
+                    void *stream) {
     int rc = check_desc(desc);
     if (rc != DLCX_OK) return rc;
     if (phase != DLCX_PHASE_P && phase != DLCX_PHASE_Q) return DLCX_EINVAL;
@@ -499,8 +499,22 @@ int dlcx_compress_batched(const dlcx_desc *desc, int phase, int K,
     PartialSums partial;
     rc = project(desc, phase, K, deltas_host, basis, factors.p, inner, &partial, stream);
     if (rc != DLCX_OK) return rc;
-    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss,
+    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss, mean,
                                as_stream(stream));
+}
+
+int dlcx_compress_batched(const dlcx_desc *desc, int phase, int K,
+                          const float *const *deltas_host, const float *basis,
+                          uint8_t *const *codes_out_host, float *const *scales_out_host,
+                          void *workspace, void *stream) {
+    return compress(desc, phase, K, deltas_host, basis, codes_out_host, scales_out_host, nullptr, workspace, stream);
+}
+
+int dlcx_compress_average(const dlcx_desc *desc, int phase, int K, const float *const *deltas_host,
+                          const float *basis, uint8_t *const *codes_out_host, float *const *scales_out_host,
+                          float *mean_out, void *workspace, void *stream) {
+    if (!mean_out || !aligned16(mean_out)) return DLCX_EINVAL;
+    return compress(desc, phase, K, deltas_host, basis, codes_out_host, scales_out_host, mean_out, workspace, stream);
 }
 
 int dlcx_compress(const dlcx_desc *desc, int phase, const float *delta, const float *basis,
@@ -670,12 +684,11 @@ int dlcx_ef_delta_apply(const dlcx_desc *desc, const float *p_hat, const float *
                              theta_l_dtype, theta_g, v, 1, lr, mu, workspace, stream);
 }
 
-int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const float *p_hat,
-                                 const float *q_bar, int K, const void *const *theta_l_host,
-                                 int theta_l_dtype, float *const *ef_inout_host, float *theta_g,
-                                 float *v, float lr, float mu, const float *basis,
-                                 uint8_t *const *codes_out_host, float *const *scales_out_host,
-                                 void *workspace, void *stream) {
+static int ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const float *p_hat, const float *q_bar, int K,
+                                   const void *const *theta_l_host, int theta_l_dtype, float *const *ef_inout_host,
+                                   float *theta_g, float *v, float lr, float mu, const float *basis,
+                                   uint8_t *const *codes_out_host, float *const *scales_out_host, float *mean,
+                                   void *workspace, void *stream) {
     int rc = check_desc(desc);
     if (rc != DLCX_OK) return rc;
     if (r_prev < 0 || r_prev > DLCX_MAX_RANK || r_prev > desc->m || r_prev > desc->n)
@@ -721,8 +734,8 @@ int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const fl
                 if (rc != DLCX_OK) return rc;
             }
         }
-        return dlcx_compress_batched(desc, DLCX_PHASE_P, K, ef_inout_host, basis, codes_out_host,
-                                     scales_out_host, workspace, stream);
+        return compress(desc, DLCX_PHASE_P, K, ef_inout_host, basis, codes_out_host, scales_out_host, mean, workspace,
+                        stream);
     }
     const int64_t count = (int64_t)desc->r * desc->m;
     ReconEpilogue ep;
@@ -750,8 +763,29 @@ int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const fl
     rc = launch_round_mfma(desc->mma, desc->m, desc->n, desc->r, r_prev, p_hat, q_bar, basis, ep,
                            factors, inner, &partial, as_stream(stream));
     if (rc != DLCX_OK) return rc;
-    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss,
+    return launch_sum_quantize(K, partial, factors, count, desc->qbits, desc->group, cs, ss, mean,
                                as_stream(stream));
+}
+
+int dlcx_ef_delta_apply_compress(const dlcx_desc *desc, int32_t r_prev, const float *p_hat,
+                                 const float *q_bar, int K, const void *const *theta_l_host,
+                                 int theta_l_dtype, float *const *ef_inout_host, float *theta_g,
+                                 float *v, float lr, float mu, const float *basis,
+                                 uint8_t *const *codes_out_host, float *const *scales_out_host,
+                                 void *workspace, void *stream) {
+    return ef_delta_apply_compress(desc, r_prev, p_hat, q_bar, K, theta_l_host, theta_l_dtype, ef_inout_host, theta_g, v,
+                                   lr, mu, basis, codes_out_host, scales_out_host, nullptr, workspace, stream);
+}
+
+int dlcx_ef_delta_apply_compress_average(const dlcx_desc *desc, int32_t r_prev, const float *p_hat,
+                                         const float *q_bar, int K, const void *const *theta_l_host,
+                                         int theta_l_dtype, float *const *ef_inout_host, float *theta_g,
+                                         float *v, float lr, float mu, const float *basis,
+                                         uint8_t *const *codes_out_host, float *const *scales_out_host,
+                                         float *mean_out, void *workspace, void *stream) {
+    if (!mean_out || !aligned16(mean_out)) return DLCX_EINVAL;
+    return ef_delta_apply_compress(desc, r_prev, p_hat, q_bar, K, theta_l_host, theta_l_dtype, ef_inout_host, theta_g, v,
+                                   lr, mu, basis, codes_out_host, scales_out_host, mean_out, workspace, stream);
 }
 
 int dlcx_effective_rank(int64_t L, int32_t r, const float *q_bar, double tau,

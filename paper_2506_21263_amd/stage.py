@@ -4,12 +4,12 @@ Only sequencing lives here: which entry point of the HIP library runs on which b
 which HIP stream, in the order of Alg. 2 with the one-step delay.  Every arithmetic step is a
 kernel of libdlcx_hip.so.
 
-    t >= 2 :  e_i <- delta_i - Delta_hat^{t-1}                 \\
-              delta_i <- (theta_g - theta_l,i) + e_i            > dlcx_ef_delta_apply_compress, or
-    t >= 2 :  theta_g <- OuterOpt(theta_g, Delta_hat^{t-1})    /  dlcx_decompress, dlcx_delta_ef,
+    t >= 2 :  e_i <- delta_i - Delta_hat^{t-1}                 \\  dlcx_ef_delta_apply_compress_average
+              delta_i <- (theta_g - theta_l,i) + e_i            > (with the P phase up to the average),
+    t >= 2 :  theta_g <- OuterOpt(theta_g, Delta_hat^{t-1})    /  or dlcx_decompress, dlcx_delta_ef,
                                                                   dlcx_outer_nesterov
-              P phase: compress, average (+ orthonormalise)     dlcx_compress_batched, dlcx_average
-              Q phase: compress, average                        dlcx_compress_batched, dlcx_average
+              P phase: compress, average, orthonormalise        dlcx_compress_average, dlcx_orthonormalize
+              Q phase: compress, average                        dlcx_compress_average
               r' of the new average (Alg. 3)                    dlcx_effective_rank
 
 The matrices of a stage are independent, so consecutive runs of them are dealt to a few HIP
@@ -20,11 +20,11 @@ import ctypes as C
 
 import torch
 
-from . import (PHASE_P, PHASE_Q, desc, dlcx_average, dlcx_batched_workspace_bytes,
-               dlcx_compress_batched, dlcx_decompress, dlcx_delta_ef, dlcx_dequant_average,
-               dlcx_effective_rank, dlcx_effective_rank_batched, dlcx_ef_delta_apply_compress,
-               dlcx_orthonormalize, dlcx_orthonormalize_batched, dlcx_outer_nesterov,
-               dlcx_payload_bytes, dlcx_requantize, dlcx_select_rank_from, dlcx_workspace_bytes)
+from . import (PHASE_P, PHASE_Q, desc, dlcx_batched_workspace_bytes, dlcx_compress_average,
+               dlcx_decompress, dlcx_delta_ef, dlcx_effective_rank, dlcx_effective_rank_batched,
+               dlcx_ef_delta_apply_compress_average, dlcx_orthonormalize,
+               dlcx_orthonormalize_batched, dlcx_outer_nesterov, dlcx_payload_bytes,
+               dlcx_requantize, dlcx_select_rank_from, dlcx_workspace_bytes)
 
 
 def plan_lanes(sizes, nstreams, chunk=0):
@@ -155,9 +155,10 @@ class Stage:
         # (the caller has filled columns beyond the previous rank with fresh draws)
         basis = M.q_bar if (self.warm_start and t >= 2) else M.q_in
         if self.fused:
-            dlcx_ef_delta_apply_compress(d, M.r_prev if t >= 2 else 0, M.p_hat, M.q_bar, theta_l,
-                                         M.ef, M.theta_g, M.v, self.lr, self.mu, basis,
-                                         M.codes_p, M.scales_p, ws, stream=stream)
+            dlcx_ef_delta_apply_compress_average(d, M.r_prev if t >= 2 else 0, M.p_hat, M.q_bar,
+                                                 theta_l, M.ef, M.theta_g, M.v, self.lr, self.mu,
+                                                 basis, M.codes_p, M.scales_p, M.p_hat, ws,
+                                                 stream=stream)
         else:
             if t >= 2:
                 dlcx_decompress(M.desc(M.r_prev), M.p_hat, M.q_bar, d_hat, M.ef, workspace=ws,
@@ -167,26 +168,20 @@ class Stage:
             if t >= 2:
                 dlcx_outer_nesterov(M.theta_g, M.v, d_hat, self.lr, self.mu, numel=M.m * M.n,
                                     stream=stream)
-            dlcx_compress_batched(d, PHASE_P, M.ef, basis, M.codes_p, M.scales_p, ws,
+            dlcx_compress_average(d, PHASE_P, M.ef, basis, M.codes_p, M.scales_p, M.p_hat, ws,
                                   stream=stream)
-        self._p_average(M, ws, stream, orthonormalize)
+        self._p_averaged(M, ws, stream, orthonormalize)
 
     def _p_phase_again(self, a, lane, stream, orthonormalize):
         """P phase of a further power iteration: basis = the Q average just formed."""
         M = self.mats[a]
         ws = self.workspaces[lane]
-        dlcx_compress_batched(M.desc(), PHASE_P, M.ef, M.q_bar, M.codes_p, M.scales_p, ws,
+        dlcx_compress_average(M.desc(), PHASE_P, M.ef, M.q_bar, M.codes_p, M.scales_p, M.p_hat, ws,
                               stream=stream)
-        self._p_average(M, ws, stream, orthonormalize)
+        self._p_averaged(M, ws, stream, orthonormalize)
 
-    def _p_average(self, M, ws, stream, orthonormalize):
-        d = M.desc()
-        if orthonormalize and not self.requant:
-            dlcx_average(d, PHASE_P, M.codes_p, M.scales_p, M.p_hat, ws, stream=stream)
-            return
-        # mean only; orthonormalised below, or by the stage in one batch afterwards
-        dlcx_dequant_average(M.codes_p, M.scales_p, M.r * M.m, M.qbits, M.group, M.p_hat,
-                             stream=stream)
+    def _p_averaged(self, M, ws, stream, orthonormalize):
+        # p_hat holds the mean; orthonormalised below, or by the stage in one batch afterwards
         if self.requant:
             dlcx_requantize(M.p_hat, M.r * M.m, M.qbits, M.group, stream=stream)
         if orthonormalize:
@@ -195,8 +190,8 @@ class Stage:
     def _q_phase(self, a, lane, stream, rank):
         M = self.mats[a]
         ws, d = self.workspaces[lane], M.desc()
-        dlcx_compress_batched(d, PHASE_Q, M.ef, M.p_hat, M.codes_q, M.scales_q, ws, stream=stream)
-        dlcx_average(d, PHASE_Q, M.codes_q, M.scales_q, M.q_bar, ws, stream=stream)
+        dlcx_compress_average(d, PHASE_Q, M.ef, M.p_hat, M.codes_q, M.scales_q, M.q_bar, ws,
+                              stream=stream)
         if self.requant:
             dlcx_requantize(M.q_bar, M.r * M.n, M.qbits, M.group, stream=stream)
         M.r_prev = M.r

@@ -942,3 +942,38 @@ def test_batched_orthonormalize_and_rank_mixed_shapes():
     for i in (0, 3, 17, 69):
         assert int(out[i].item()) == ref.effective_rank(to_np(qs[i]), 0.9)
         assert rel_l2(to_np(ps[i]), ref.orthonormalize(to_np(qs[i]))) <= 1e-5
+
+
+@pytest.mark.parametrize("mma", [dlcx.MMA_FMA, dlcx.MMA_F32, dlcx.MMA_BF16, dlcx.MMA_F16])
+@pytest.mark.parametrize("m,n,r,K,qbits,group", [
+    (16, 16, 1, 1, 4, 16),          # one group
+    (272, 528, 3, 2, 8, 16),        # a last wavefront that is partly idle
+    (512, 512, 8, 3, 4, 64), (512, 768, 33, 5, 8, 256), (1024, 256, 70, 4, 4, 32), (256, 1280, 130, 16, 4, 128),
+])
+def test_quantise_and_average_in_one_launch_is_both(mma, m, n, r, K, qbits, group):
+    # Codes, scales, factors and mean bit for bit those of the two calls: with and without partial sums, with
+    # the fp16 form in and out of its range, payloads with zeros, infinities and NaN.
+    g = rng(m + n + r + K)
+    d = dlcx.desc(m, n, r, qbits, group, mma)
+    scale = 1e3 if K == 3 else 1.0
+    deltas = [to_dev((scale * g.standard_normal((m, n))).astype(np.float32)) for _ in range(K)]
+    deltas[0][:, : n // 2] = 0.0
+    deltas[0][: m // 2] = 0.0
+    if K == 2:
+        deltas[1][0, 0], deltas[1][m - 1, n - 1] = float("inf"), float("nan")
+    ws = torch.zeros(dlcx.dlcx_workspace_bytes(d, K), device=DEV, dtype=torch.uint8)
+    for phase, length, other in ((dlcx.PHASE_P, m, n), (dlcx.PHASE_Q, n, m)):
+        basis = to_dev(g.standard_normal((r, other)).astype(np.float32))
+        got = []
+        for fused in (False, True):
+            codes, scales = payload_buffers(d, phase, K)
+            mean = torch.full((r, length), -1.0, device=DEV)
+            ws.fill_(255)
+            if fused:
+                dlcx.dlcx_compress_average(d, phase, deltas, basis, codes, scales, mean, ws)
+            else:
+                dlcx.dlcx_compress_batched(d, phase, deltas, basis, codes, scales, ws)
+                dlcx.dlcx_dequant_average(codes, scales, r * length, qbits, group, mean)
+            got.append([to_np(x).view(np.uint8) for x in codes + scales + [mean, ws[: 4 * K * r * length]]])
+        for a, b in zip(*got):
+            assert np.array_equal(a, b), phase
