@@ -29,8 +29,10 @@ __device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_ca
 // all r outputs; each wavefront sums a quarter of the columns j, the four sums are added in order.
 // (One wavefront per row group and no split leaves most SIMDs idle below 16 K rows.)  Two row
 // blocks share a basis operand once that still gives every compute unit a workgroup.
-// 2048 x 2048, four workers, r = 32: 33 us (scalar fp64 FMAs on LDS operands: 693 us); the
-// matrix cores' own time is 14 us.
+// 2048 x 2048, four workers, r = 32: 27 us with the quantiser (scalar fp64 FMAs on LDS operands: 693 us); the
+// matrix cores' own time is 14 us.  Two sets of operands are requested before the one that is multiplied, and the
+// requests do not sink behind products: with one set ahead, left to the compiler, 33 us; 2480 x 2480 five workers r =
+// 64 120 | 107, 2048 x 2048 four r = 100 94 | 77, two r = 200 108 | 89 (one set ahead there: registers).
 // ---------------------------------------------------------------------------------------------
 template <int CB, int RB>
 __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *> deltas,
@@ -38,6 +40,7 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r) {
     constexpr int U = CB <= 4 ? 2 : 1;  // steps of 16 columns per set of operands
+    constexpr int kAhead = CB <= 8 ? 2 : 1;  // sets requested before the one that is multiplied
     __shared__ double red[4][RB * 4][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y];
@@ -78,27 +81,34 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
                 if (cb * 16 < r) s.a[u][cb] = load4(pq[cb] + st * 16);
         }
     };
-    if (begin < end) {
-        Set cur, next;
-        load(cur, begin);
-        for (int64_t st = begin; st < end; st += U) {
-            load(next, st + U);
+    auto multiply = [&](const Set &cur, int64_t st) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (st + u >= end) break;
+        for (int u = 0; u < U; ++u) {
+            if (st + u >= end) break;
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-                    if (cb * 16 < r) {
+            for (int cb = 0; cb < CB; ++cb)
+                if (cb * 16 < r) {
 #pragma unroll
-                        for (int s = 0; s < 4; ++s)
+                    for (int s = 0; s < 4; ++s)
 #pragma unroll
-                            for (int rb = 0; rb < RB; ++rb)
-                                acc[cb][rb] = mfma64(part_of(cur.a[u][cb], s),
-                                                     part_of(cur.b[u][rb], s), acc[cb][rb]);
-                    }
-            }
-            cur = next;
+                        for (int rb = 0; rb < RB; ++rb)
+                            acc[cb][rb] = mfma64(part_of(cur.a[u][cb], s), part_of(cur.b[u][rb], s), acc[cb][rb]);
+                }
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (begin < end) {
+        Set set[kAhead + 1];
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) load(set[d], begin + d * U);
+        for (int64_t st = begin; st < end; st += (kAhead + 1) * U)
+#pragma unroll
+            for (int d = 0; d <= kAhead; ++d) {
+                if (st + d * U >= end) break;
+                load(set[(d + kAhead) % (kAhead + 1)], st + (d + kAhead) * U);
+                __builtin_amdgcn_sched_barrier(0);  // requested before the products they do not belong to
+                multiply(set[d], st + d * U);
+            }
     }
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
@@ -123,8 +133,9 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
 // Q_k = delta_k^T * P_hat:  D[c][j] = sum_i P_hat[c][i] delta[i][j].  Workgroup: 64 columns of delta
 // over the row range of split blockIdx.z; partial results go to slab blockIdx.z (summed afterwards
 // in slab order).  The wavefronts are WC groups of CBW blocks of outputs by WK = 4 / WC quarters or
-// halves of the rows, added in order.  2048 x 2048, four workers, r = 32: 36 us with
-// the sum of the eight slabs (scalar fp64 FMAs on LDS operands: 114 us).
+// halves of the rows, added in order.  2048 x 2048, four workers, r = 32: 30 us with
+// the quantiser (scalar fp64 FMAs on LDS operands: 114 us).  Operands as in the P kernel, one set ahead | two, us: r =
+// 64 64 | 58, r = 100 104 | 90; 2480 x 2480 five workers r = 64 127 | 106 (three 109).
 // ---------------------------------------------------------------------------------------------
 template <int CBW, int WC>
 __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *> deltas,
@@ -133,6 +144,7 @@ __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *
                                                            int64_t n, int r, int64_t rows_per_split,
                                                            int64_t slab_stride) {
     constexpr int WK = 4 / WC;
+    constexpr int kAhead = 2;  // sets of operands requested before the one that is multiplied
     __shared__ double red[4][16][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y] + (int64_t)blockIdx.z * slab_stride;
@@ -170,21 +182,27 @@ __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *
             if (cfirst + cb * 16 < r) s.a[cb] = load4(pp[cb] + i);
     };
     if (begin < end) {
-        Set cur, next;
-        load(cur, begin);
-        for (int64_t i = begin; i < end; i += 16) {
-            load(next, i + 16 < end ? i + 16 : i);
+        Set set[kAhead + 1];
 #pragma unroll
-            for (int cb = 0; cb < CBW; ++cb)
-                if (cfirst + cb * 16 < r) {
+        for (int d = 0; d < kAhead; ++d) load(set[d], begin + 16 * d < end ? begin + 16 * d : begin);
+        for (int64_t first = begin; first < end; first += 16 * (kAhead + 1))
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
+            for (int d = 0; d <= kAhead; ++d) {
+                const int64_t i = first + 16 * d, then = i + 16 * kAhead;
+                if (i >= end) break;
+                load(set[(d + kAhead) % (kAhead + 1)], then < end ? then : i);
+                __builtin_amdgcn_sched_barrier(0);  // requested before the products they do not belong to
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            acc[cb][q] = mfma64(part_of(cur.a[cb], s), part_of(cur.b[s], q), acc[cb][q]);
-                }
-            cur = next;
-        }
+                for (int cb = 0; cb < CBW; ++cb)
+                    if (cfirst + cb * 16 < r) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                acc[cb][q] = mfma64(part_of(set[d].a[cb], s), part_of(set[d].b[s], q), acc[cb][q]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
     }
 #pragma unroll
     for (int cb = 0; cb < CBW; ++cb) {
@@ -357,7 +375,13 @@ int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
     };
     typedef std::integral_constant<int, 1> one;
     typedef std::integral_constant<int, 2> two;
-    const bool pair = ceil_div(m, 32) * K >= 512;  // two workgroups per compute unit
+    // Two row blocks to a workgroup, half as many conversions and basis operands to a product, take nine tenths of the
+    // time of two workgroups with one, if as many units are busy: rounds of the launch on 256 units, by either kind,
+    // while one round or two is all there is.  One | two, us: 2048 x 2048 four workers r = 32 31.4 | 28.1, r = 64 52.0
+    // | 49.5; 2480 x 2480 five r = 64 107 | 97; 3376 x 2000 four r = 32 48 | 44, 2400 x 2000 38 | 44, 4800 x 2000 77 |
+    // 68; 1008 x 2000 four r = 48 28 | 37.
+    const int64_t pairs = ceil_div(m, 32) * K, singles = ceil_div(m, 16) * K;
+    const bool pair = pairs >= 512 || 2 * ceil_div(pairs, 256) * 9 <= ceil_div(singles, 256) * 10;
     if (r <= 16) pair ? go(one(), two()) : go(one(), one());
     else if (r <= 32) pair ? go(two(), two()) : go(two(), one());
     else if (r <= 64) pair ? go(std::integral_constant<int, 4>(), two()) : go(std::integral_constant<int, 4>(), one());

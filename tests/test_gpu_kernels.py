@@ -261,6 +261,23 @@ def test_fp64_products_at_tile_edges(m, n, r, K):
     assert close(to_np(out), p.astype(np.float64).T @ q.astype(np.float64), 2.0 ** -23)
 
 
+@pytest.mark.parametrize("steps", [1, 3, 5, 8, 9, 12, 13, 24, 25, 28, 49])
+@pytest.mark.parametrize("m,r", [(48, 20), (4128, 9), (16, 100), (32, 200)])
+def test_fp64_products_over_every_length_of_the_operand_pipeline(m, r, steps):
+    # Reductions of `steps` times 16: a wavefront's share is none, one, or any remainder of the three sets of
+    # operands that it keeps.  Tolerance as above.
+    n = 16 * steps
+    g = rng(m + r + steps)
+    x = g.standard_normal((m, n)).astype(np.float32)
+    b = g.standard_normal((r, n)).astype(np.float32)
+    want = b.astype(np.float64) @ x.T.astype(np.float64)
+    for phase, delta in ((dlcx.PHASE_P, x), (dlcx.PHASE_Q, np.ascontiguousarray(x.T))):
+        d = dlcx.desc(*delta.shape, min(r, *delta.shape), 4, 16, dlcx.MMA_FMA)
+        out = torch.zeros(d.r, m, device=DEV)
+        dlcx.dlcx_project(d, phase, [to_dev(delta)], to_dev(b[: d.r]), [out], ws_for(d, 1))
+        assert close(to_np(out), want[: d.r], 2.0 ** -23), phase
+
+
 @pytest.mark.parametrize("mma", MODES, ids=MODE_IDS)
 @pytest.mark.parametrize("value", [np.nan, np.inf], ids=["nan", "inf"])
 @pytest.mark.parametrize("m,n,r", [(48, 80, 17), (272, 144, 100)])
