@@ -709,7 +709,8 @@ __global__ __launch_bounds__(kTri, 1) void tridiag_kernel(FactorBatch batch) {
             }
         }
         {
-            const int live = (k + 2) >> 4;
+            // (row k + 1 is on its way through arow, but behind the last step the tail takes it from the tiles)
+            const int live = min(k + 2, stop) >> 4;
 #pragma unroll
             for (int i = 0; i < N; ++i) cw[i] = fma(beta, cw[i], -kk * cv[i]);
             rw = fma(beta, rw, -kk * rv);

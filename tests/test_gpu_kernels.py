@@ -859,7 +859,7 @@ def test_effective_rank_at_tau_one_stops_where_the_sum_does(r):
     assert int(out.item()) == min(r, 27) == ref.effective_rank(q, 1.0)
 
 
-@pytest.mark.parametrize("r", [3, 4, 7, 8, 14, 16, 18, 30, 32, 34, 47, 62, 64, 66, 128, 190, 256])
+@pytest.mark.parametrize("r", [3, 4, 7, 8, 14, 16, 18, 30, 32, 34, 47, 62, 64, 66, 127, 128, 190, 191, 255, 256])
 @pytest.mark.parametrize("kind", ["dense", "equal"])
 def test_effective_rank_where_a_share_is_reached_by_a_hair(r, kind):
     # tau 1e-9 below and above the share of the j largest eigenvalues: bounds of 2^-19 .. 2^-23 cannot
@@ -882,7 +882,7 @@ def test_effective_rank_where_a_share_is_reached_by_a_hair(r, kind):
                                     (192, 81), (193, 96), (250, 97), (256, 128), (256, 193)])
 def test_effective_rank_where_one_wavefront_takes_the_last_rows(r, live):
     # Above rank 64 the last 64 of the columns that are not zero are left to one wavefront: none, one or many before
-    # them, cut at every offset in a 16 x 16 tile, and fewer than 64 in all.
+    # them, and fewer than 64 in all.
     n = 512
     g = rng(r * live)
     q = (g.standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.6)).astype(np.float32)
@@ -892,6 +892,29 @@ def test_effective_rank_where_one_wavefront_takes_the_last_rows(r, live):
     for tau in (0.3, 0.9, 0.99, 0.9999):
         dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
         assert int(out.item()) == ref.effective_rank(q, tau), tau
+
+
+@pytest.mark.parametrize("r", [128, 192, 256])  # one for each form of the reduction above rank 64
+def test_effective_rank_of_the_last_rows_at_every_cut(r):
+    # The 64 rows left to one wavefront begin anywhere in a 16 x 16 tile and in a group of four tiles: every number
+    # of columns that are not zero from 65 on, with eigenvalues that hardly fall.  tau 1e-9 below and above the
+    # share of the j largest, so that an eigenvalue that is off by 1e-8 of the sum is another r' (fp64 here and
+    # there: sums of at most 256 eigenvalues good to about 256 2^-52 of the largest, 1e-13).
+    n = 512
+    g = rng(r)
+    ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
+    out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
+    wrong = []
+    for live in range(65, r + 1):
+        q = g.standard_normal((r, n)).astype(np.float32)
+        q[g.permutation(r)[live:]] = 0.0
+        s = np.cumsum(np.linalg.eigvalsh(q.astype(np.float64) @ q.T.astype(np.float64))[::-1])
+        for j in (1, live // 2, live - 1):
+            for side in (0, 1):
+                dlcx.dlcx_effective_rank(n, r, to_dev(q), s[j - 1] / s[-1] + (side - 0.5) * 2e-9, out, ws)
+                if int(out.item()) != j + side:
+                    wrong.append((live, j, side, int(out.item())))
+    assert not wrong, wrong
 
 
 @pytest.mark.parametrize("r", [1, 3, 16, 31, 32, 33, 64, 65, 130, 256])
