@@ -23,24 +23,29 @@ __device__ __forceinline__ float part_of(const float4 &v, int s) {
     return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w;
 }
 __device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+// What was requested before this stays before the products behind it.
+template <bool kOrdered>
+__device__ __forceinline__ void keep_order() {
+    if constexpr (kOrdered) __builtin_amdgcn_sched_barrier(0);
+}
 
 // ---------------------------------------------------------------------------------------------
 // P_k = delta_k * Q_in:  D[c][i] = sum_j Q[c][j] delta[i][j].  Workgroup: 16 RB rows of delta and
 // all r outputs; each wavefront sums a quarter of the columns j, the four sums are added in order.
-// (One wavefront per row group and no split leaves most SIMDs idle below 16 K rows.)  Two row
-// blocks share a basis operand once that still gives every compute unit a workgroup.
+// (One wavefront per row group and no split leaves most SIMDs idle below 16 K rows.)
 // 2048 x 2048, four workers, r = 32: 27 us with the quantiser (scalar fp64 FMAs on LDS operands: 693 us); the
-// matrix cores' own time is 14 us.  Two sets of operands are requested before the one that is multiplied, and the
-// requests do not sink behind products: with one set ahead, left to the compiler, 33 us; 2480 x 2480 five workers r =
-// 64 120 | 107, 2048 x 2048 four r = 100 94 | 77, two r = 200 108 | 89 (one set ahead there: registers).
+// matrix cores' own time is 14 us.  kAhead sets of operands are requested before the one that is multiplied.  Two
+// for long reductions, and the requests do not sink behind products: with one set ahead, left to the compiler, 33
+// us; 2480 x 2480 five workers r = 64 120 | 107, 2048 x 2048 four r = 100 94 | 77, two r = 200 108 | 89 (one set
+// ahead there, in order: registers).  One, left to the compiler, for short ones (p_sets_ahead).
 // ---------------------------------------------------------------------------------------------
-template <int CB, int RB>
+template <int CB, int RB, int kAhead>
 __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *> deltas,
                                                            const float *__restrict__ q_in,
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r) {
     constexpr int U = CB <= 4 ? 2 : 1;  // steps of 16 columns per set of operands
-    constexpr int kAhead = CB <= 8 ? 2 : 1;  // sets requested before the one that is multiplied
+    constexpr bool kOrdered = kAhead > 1 || CB > 8;
     __shared__ double red[4][RB * 4][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y];
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
                             acc[cb][rb] = mfma64(part_of(cur.a[u][cb], s), part_of(cur.b[u][rb], s), acc[cb][rb]);
                 }
         }
-        __builtin_amdgcn_sched_barrier(0);
+        keep_order<kOrdered>();
     };
     if (begin < end) {
         Set set[kAhead + 1];
@@ -106,7 +111,7 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
             for (int d = 0; d <= kAhead; ++d) {
                 if (st + d * U >= end) break;
                 load(set[(d + kAhead) % (kAhead + 1)], st + (d + kAhead) * U);
-                __builtin_amdgcn_sched_barrier(0);  // requested before the products they do not belong to
+                keep_order<kOrdered>();
                 multiply(set[d], st + d * U);
             }
     }
@@ -134,17 +139,15 @@ __global__ __launch_bounds__(kT) void project_p_f64_kernel(PtrPack<const float *
 // over the row range of split blockIdx.z; partial results go to slab blockIdx.z (summed afterwards
 // in slab order).  The wavefronts are WC groups of CBW blocks of outputs by WK = 4 / WC quarters or
 // halves of the rows, added in order.  2048 x 2048, four workers, r = 32: 30 us with
-// the quantiser (scalar fp64 FMAs on LDS operands: 114 us).  Operands as in the P kernel, one set ahead | two, us: r =
-// 64 64 | 58, r = 100 104 | 90; 2480 x 2480 five workers r = 64 127 | 106 (three 109).
+// the quantiser (scalar fp64 FMAs on LDS operands: 114 us).  Operands as in the P kernel.
 // ---------------------------------------------------------------------------------------------
-template <int CBW, int WC>
+template <int CBW, int WC, int kAhead>
 __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *> deltas,
                                                            const float *__restrict__ p_hat,
                                                            PtrPack<float *> outs, int64_t m,
                                                            int64_t n, int r, int64_t rows_per_split,
                                                            int64_t slab_stride) {
     constexpr int WK = 4 / WC;
-    constexpr int kAhead = 2;  // sets of operands requested before the one that is multiplied
     __shared__ double red[4][16][64];
     const float *__restrict__ delta = deltas.p[blockIdx.y];
     float *__restrict__ out = outs.p[blockIdx.y] + (int64_t)blockIdx.z * slab_stride;
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *
                 const int64_t i = first + 16 * d, then = i + 16 * kAhead;
                 if (i >= end) break;
                 load(set[(d + kAhead) % (kAhead + 1)], then < end ? then : i);
-                __builtin_amdgcn_sched_barrier(0);  // requested before the products they do not belong to
+                keep_order<(kAhead > 1)>();
 #pragma unroll
                 for (int cb = 0; cb < CBW; ++cb)
                     if (cfirst + cb * 16 < r) {
@@ -201,7 +204,7 @@ __global__ __launch_bounds__(kT) void project_q_f64_kernel(PtrPack<const float *
                             for (int q = 0; q < 4; ++q)
                                 acc[cb][q] = mfma64(part_of(set[d].a[cb], s), part_of(set[d].b[s], q), acc[cb][q]);
                     }
-                __builtin_amdgcn_sched_barrier(0);
+                keep_order<(kAhead > 1)>();
             }
     }
 #pragma unroll
@@ -365,13 +368,21 @@ size_t fma_project_workspace_bytes(int64_t m, int64_t n, int r, int K) {
     return (size_t)slabs * (size_t)r * (size_t)n * sizeof(float);
 }
 
+// Sets of operands that a wavefront of the P kernel requests ahead, at ranks up to 64.  A wavefront has a quarter of
+// the n / 16 steps: up to 768 columns two sets are most of it and the registers they take cost more than they hide;
+// with one basis block and more than one workgroup of two row blocks to a unit, up to 2048 columns, other wavefronts
+// hide what one set leaves.  One | two, us: 2480 x 192 eight workers r = 9 7.9 | 9.6, 688 x 256 three r = 16 4.3 | 4.5,
+// 4800 x 768 eight r = 32 41.9 | 44.1, 2480 x 2048 eight r = 16 39.1 | 40.7; 1264 x 1024 five r = 17 15.7 | 14.4, 1264
+// x 2048 five r = 32 27.6 | 24.8, 2480 x 4096 eight r = 48 186 | 175.
+static int p_sets_ahead(int64_t n, int r, int64_t pairs) { return n <= 768 || (r <= 16 && pairs > 256 && n <= 2048) ? 1 : 2; }
+
 int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const float *> &delta,
                          const float *q_in, const PtrPack<float *> &out, hipStream_t st) {
     Timed timed(KID_PROJECT_P, st);
-    auto go = [&](auto cb, auto rb) {
+    auto go = [&](auto cb, auto rb, auto ahead) {
         const dim3 grid((unsigned)ceil_div(m, 16 * decltype(rb)::value), (unsigned)K);
-        hipLaunchKernelGGL((project_p_f64_kernel<decltype(cb)::value, decltype(rb)::value>), grid,
-                           dim3(kT), 0, st, delta, q_in, out, m, n, r);
+        hipLaunchKernelGGL((project_p_f64_kernel<decltype(cb)::value, decltype(rb)::value, decltype(ahead)::value>),
+                           grid, dim3(kT), 0, st, delta, q_in, out, m, n, r);
     };
     typedef std::integral_constant<int, 1> one;
     typedef std::integral_constant<int, 2> two;
@@ -382,11 +393,16 @@ int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
     // 68; 1008 x 2000 four r = 48 28 | 37.
     const int64_t pairs = ceil_div(m, 32) * K, singles = ceil_div(m, 16) * K;
     const bool pair = pairs >= 512 || 2 * ceil_div(pairs, 256) * 9 <= ceil_div(singles, 256) * 10;
-    if (r <= 16) pair ? go(one(), two()) : go(one(), one());
-    else if (r <= 32) pair ? go(two(), two()) : go(two(), one());
-    else if (r <= 64) pair ? go(std::integral_constant<int, 4>(), two()) : go(std::integral_constant<int, 4>(), one());
-    else if (r <= 128) go(std::integral_constant<int, 8>(), one());
-    else go(std::integral_constant<int, 16>(), one());
+    const bool far = p_sets_ahead(n, r, pairs) > 1;
+    auto rows = [&](auto cb) {
+        if (pair) far ? go(cb, two(), two()) : go(cb, two(), one());
+        else far ? go(cb, one(), two()) : go(cb, one(), one());
+    };
+    if (r <= 16) rows(one());
+    else if (r <= 32) rows(two());
+    else if (r <= 64) rows(std::integral_constant<int, 4>());
+    else if (r <= 128) go(std::integral_constant<int, 8>(), one(), two());
+    else go(std::integral_constant<int, 16>(), one(), one());
     return check_launch("project_p_f64");
 }
 
@@ -402,19 +418,24 @@ int launch_project_q_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
     int rc;
     {
         Timed timed(KID_PROJECT_Q, st);
-        auto go = [&](auto cbw, auto wc) {
+        auto launch = [&](auto cbw, auto wc, auto ahead) {
             const dim3 grid((unsigned)ceil_div(n, 64), (unsigned)K, (unsigned)S);
-            hipLaunchKernelGGL((project_q_f64_kernel<decltype(cbw)::value, decltype(wc)::value>), grid,
-                               dim3(kT), 0, st, delta, p_hat, dst, m, n, r, rows, slab);
+            hipLaunchKernelGGL((project_q_f64_kernel<decltype(cbw)::value, decltype(wc)::value, decltype(ahead)::value>),
+                               grid, dim3(kT), 0, st, delta, p_hat, dst, m, n, r, rows, slab);
         };
         typedef std::integral_constant<int, 1> one;
         typedef std::integral_constant<int, 2> two;
         typedef std::integral_constant<int, 4> four;
-        if (r <= 16) go(one(), one());
+        // Sets of operands requested ahead: two from more than 512 rows to a workgroup on and above rank 128, never
+        // with one block of outputs.  One | two, us: 64 x 1072 three workers r = 64 6.8 | 7.4, 2480 x 2480 five r = 32
+        // 48.4 | 50.7, 8192 x 8192 r = 16 49.5 | 53.4; 8192 x 8192 r = 32 79.5 | 77.7, r = 64 177 | 165, 2480 x 2480 five
+        // r = 200 310 | 300.
+        auto go = [&](auto cbw, auto wc) { rows > 512 ? launch(cbw, wc, two()) : launch(cbw, wc, one()); };
+        if (r <= 16) launch(one(), one(), one());
         else if (r <= 32) go(two(), one());
         else if (r <= 64) go(four(), one());
         else if (r <= 128) go(four(), two());
-        else go(four(), four());
+        else launch(four(), four(), two());
         rc = check_launch("project_q_f64");
     }
     if (rc != DLCX_OK || S == 1) return rc;

@@ -261,11 +261,12 @@ def test_fp64_products_at_tile_edges(m, n, r, K):
     assert close(to_np(out), p.astype(np.float64).T @ q.astype(np.float64), 2.0 ** -23)
 
 
-@pytest.mark.parametrize("steps", [1, 3, 5, 8, 9, 12, 13, 24, 25, 28, 49])
-@pytest.mark.parametrize("m,r", [(48, 20), (4128, 9), (16, 100), (32, 200)])
+@pytest.mark.parametrize("steps", [1, 3, 5, 8, 9, 12, 13, 24, 25, 28, 48, 49, 50, 52, 53, 57, 61, 65, 69])
+@pytest.mark.parametrize("m,r", [(48, 20), (4128, 9), (8224, 7), (16, 100), (32, 200)])
 def test_fp64_products_over_every_length_of_the_operand_pipeline(m, r, steps):
-    # Reductions of `steps` times 16: a wavefront's share is none, one, or any remainder of the three sets of
-    # operands that it keeps.  Tolerance as above.
+    # Reductions of `steps` times 16: a wavefront's share is none, one, or any remainder of the two or three sets of
+    # operands that it keeps (P: three from 49 on, but two with one basis block and more than 8192 rows; Q: two).
+    # Tolerance as above.
     n = 16 * steps
     g = rng(m + r + steps)
     x = g.standard_normal((m, n)).astype(np.float32)
@@ -276,6 +277,22 @@ def test_fp64_products_over_every_length_of_the_operand_pipeline(m, r, steps):
         out = torch.zeros(d.r, m, device=DEV)
         dlcx.dlcx_project(d, phase, [to_dev(delta)], to_dev(b[: d.r]), [out], ws_for(d, 1))
         assert close(to_np(out), want[: d.r], 2.0 ** -23), phase
+
+
+@pytest.mark.parametrize("steps", [32, 33, 34, 35, 36, 37, 40, 44, 48])
+@pytest.mark.parametrize("r", [20, 50, 100, 200])
+def test_fp64_q_projection_of_many_workers_over_long_reductions(r, steps):
+    # 16 workers of 4112 columns leave the rows in one piece, and from more than 512 of them on a wavefront keeps
+    # three sets of operands.  Tolerance as above.
+    m, n, K = 16 * steps, 4112, 16
+    g = rng(r + steps)
+    x = g.standard_normal((m, n)).astype(np.float32)
+    b = g.standard_normal((r, m)).astype(np.float32)
+    d = dlcx.desc(m, n, r, 4, 16, dlcx.MMA_FMA)
+    outs = [torch.zeros(r, n, device=DEV) for _ in range(K)]
+    dlcx.dlcx_project(d, dlcx.PHASE_Q, [to_dev(x)] * K, to_dev(b), outs, ws_for(d, K))
+    assert close(to_np(outs[0]), b.astype(np.float64) @ x.astype(np.float64), 2.0 ** -23)
+    assert all(torch.equal(o, outs[0]) for o in outs)
 
 
 @pytest.mark.parametrize("mma", MODES, ids=MODE_IDS)
