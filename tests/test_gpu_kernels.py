@@ -879,13 +879,15 @@ def test_effective_rank_at_tau_one_stops_where_the_sum_does(r):
 @pytest.mark.parametrize("r", [3, 4, 7, 8, 14, 16, 18, 30, 32, 34, 47, 62, 64, 66, 127, 128, 190, 191, 255, 256])
 @pytest.mark.parametrize("kind", ["dense", "equal"])
 def test_effective_rank_where_a_share_is_reached_by_a_hair(r, kind):
-    # tau 1e-9 below and above the share of the j largest eigenvalues: bounds of 2^-19 .. 2^-23 cannot
-    # tell on which side it falls, eigenvalues to 2^-56 (of sums of at most 256) can.
+    # tau 1e-9 below and above the share of the j largest eigenvalues: eigenvalues to 2^-56 (of sums of at most 256)
+    # tell on which side it falls, the bounds before them (2^-19 .. 2^-23 up to rank 64, 2^-29 above) as a rule do not.
+    # "equal": all but two eigenvalues coincide, with room around them in the interval that the search starts from.
     n = 512
     q = (rng(7 * r).standard_normal((r, n)) * (np.arange(1, r + 1)[:, None] ** -0.6)).astype(np.float32)
     if kind == "equal":
         q = np.zeros((r, n), np.float32)
         q[np.arange(r), np.arange(r)] = 1.0
+        q[0, 0], q[1, 0] = 2.0, 0.5
     s = np.cumsum(np.linalg.eigvalsh(q.astype(np.float64) @ q.T.astype(np.float64))[::-1])
     ws = torch.empty(dlcx.dlcx_workspace_bytes(dlcx.desc(n, n, r, 4, 16), 1), device=DEV, dtype=torch.uint8)
     out = torch.full((1,), -1, device=DEV, dtype=torch.int32)
