@@ -939,15 +939,17 @@ __global__ __launch_bounds__(256) void eigenvalues_kernel(FactorBatch batch, dou
         h[q] = high[e];
     }
     const int k = r > 0 ? decided(l, h, r, tau, lane) : -1;
+    if (k < 0 && c < r) {
+        const double2 *__restrict__ tri = tri_of(it);
+        double lo = low[c], hi = high[c];
+        narrow<64>(tri, r, c, lo, hi, lane, Rounds<64>::kAll - kEarlyRounds);
+        if (lane == 0) eig_of(it)[c] = eigenvalue(lo, hi);
+    }
+    // Behind all that is read: the table goes through the scalar cache as long as nothing is stored before it.
     if (c == 0 && lane == 0) {
         *open_of(it) = k < 0 ? 1.0 : 0.0;
         if (k >= 0) *it.out = k;
     }
-    if (k >= 0 || c >= r) return;
-    const double2 *__restrict__ tri = tri_of(it);
-    double lo = low[c], hi = high[c];
-    narrow<64>(tri, r, c, lo, hi, lane, Rounds<64>::kAll - kEarlyRounds);
-    if (lane == 0) eig_of(it)[c] = eigenvalue(lo, hi);
 }
 
 __global__ __launch_bounds__(64) void count_kernel(FactorBatch batch, double tau) {

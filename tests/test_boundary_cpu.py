@@ -273,3 +273,14 @@ def test_two_workgroups_of_the_short_p_projections_share_a_unit():
         seen += 1
         assert k[".vgpr_count"] <= 128 and k[".vgpr_spill_count"] == 0, (name, k)
     assert seen == 5
+
+
+def test_the_eigenvalue_search_reads_its_table_as_scalars():
+    # Every lane reads the same terms, eight at a time and eight ahead: 64 scalar registers, or as many vector
+    # registers and slower loads where something is stored before they are read.
+    seen = 0
+    for name, k in kernel_metadata().items():
+        if re.search(r"eigenvalue(s|_bounds)_kernel", name):
+            seen += 1
+            assert k[".vgpr_count"] <= 64 and k[".sgpr_count"] >= 64, (name, k)
+    assert seen == 2

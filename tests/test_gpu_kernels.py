@@ -861,6 +861,8 @@ def test_effective_rank_counts_no_zero_column_at_tau_one(r):
         for tau in (0.9, 0.99):
             dlcx.dlcx_effective_rank(n, r, to_dev(q), tau, out, ws)
             assert int(out.item()) == ref.effective_rank(q, tau), (trial, tau)
+    dlcx.dlcx_effective_rank(n, r, torch.zeros(r, n, device=DEV), 1.0, out, ws)
+    assert int(out.item()) == 0
 
 
 @pytest.mark.parametrize("r", [16, 31, 60, 120, 250])
