@@ -321,8 +321,15 @@ __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (
 // (row_newbcast); the rows are dealt to the lanes so that such a register is a copy of rows of lanes of the
 // vector itself.  After four steps rows and columns are renumbered: register and lane indices are constants.
 // ---------------------------------------------------------------------------------------------
-// acc[i % 2] += element C + i of src (one lane of each row of 16) * by[i], i = 0 .. 3.  A DPP operand has to be two
-// wait states behind the vector instruction that wrote it.
+// What other lanes read (DPP, permlane, readlane) has to be up to two wait states behind the vector instruction that
+// wrote it.  The compiler sees to that between its own instructions but does not look into these: two at the front
+// for src, w and v, and what is read so of their results goes through settle() before.  (Two behind every one of them:
+// 2048 x 64 64.7 | 68.4 us.)  Results are written before the last operand is read: no register in common.
+__device__ __forceinline__ void settle(double &x) { asm("s_nop 1" : "+v"(x)); }
+__device__ __forceinline__ void settle8(double *t) {
+    asm("s_nop 1" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]), "+v"(t[4]), "+v"(t[5]), "+v"(t[6]), "+v"(t[7]));
+}
+// acc[i % 2] += element C + i of src (one lane of each row of 16) * by[i], i = 0 .. 3.  Not for other lanes to read.
 template <int C>
 __device__ __forceinline__ void dot_bcast4(double (&acc)[2], double src, const double *by) {
     asm("s_nop 1\n\t"
@@ -330,7 +337,7 @@ __device__ __forceinline__ void dot_bcast4(double (&acc)[2], double src, const d
         "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
-        : "+v"(acc[0]), "+v"(acc[1])
+        : "+&v"(acc[0]), "+&v"(acc[1])
         : "v"(src), "v"(by[0]), "v"(by[1]), "v"(by[2]), "v"(by[3]), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
 }
 // t[i] += (element C + i of w) * a + (element C + i of v) * b, i = 0 .. 3
@@ -345,7 +352,7 @@ __device__ __forceinline__ void update_bcast4(double *t, double w, double a, dou
         "v_fmac_f64_dpp %1, %6, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %2, %6, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %3, %6, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
-        : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3])
+        : "+&v"(t[0]), "+&v"(t[1]), "+&v"(t[2]), "+&v"(t[3])
         : "v"(w), "v"(a), "v"(v), "v"(b), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
 }
 struct Two {
@@ -380,7 +387,8 @@ struct Rows32 {
     }
     static __device__ __forceinline__ double gather(double x) { return add_halves(x, x); }
     template <int J>
-    static __device__ __forceinline__ double column(const double *t) {
+    static __device__ __forceinline__ double column(double *t) {
+        settle(t[J >> 1]);
         const Two x = halves_of(t[J >> 1]);
         return (J & 1) ? x.b : x.a;
     }
@@ -400,7 +408,10 @@ struct Rows64 {
     static __device__ __forceinline__ double sum(double x) { return wave_sum(x); }
     static __device__ __forceinline__ double gather(double x) { return x; }
     template <int J>
-    static __device__ __forceinline__ double column(const double *t) { return t[16 * (J & 3) + (J >> 2)]; }
+    static __device__ __forceinline__ double column(double *t) {
+        settle(t[16 * (J & 3) + (J >> 2)]);
+        return t[16 * (J & 3) + (J >> 2)];
+    }
     static __device__ __forceinline__ void spread(double x, int, double (&to)[4]) {
         const Two r = rows_of(x), even = halves_of(r.a), odd = halves_of(r.b);
         to[0] = even.a;
@@ -457,6 +468,10 @@ __device__ __forceinline__ void reduce_steps(double *t, double &x, int &k, int s
             });
             x = fma(c, -w, fma(read_lane(w, Rows::lane(s + 1)), -v, s1));  // as the same element of t
         });
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int c = 0; c < C; c += 8) settle8(t + 16 * q + c);
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll

@@ -284,3 +284,20 @@ def test_the_eigenvalue_search_reads_its_table_as_scalars():
             seen += 1
             assert k[".vgpr_count"] <= 64 and k[".sgpr_count"] >= 64, (name, k)
     assert seen == 2
+
+
+def test_inline_assembly_shares_no_register_and_waits_for_its_dpp_operands():
+    # Where a block writes a result before it has read its last operand the two may share a register unless the
+    # result is marked early-clobber, and the compiler puts no wait states before a DPP operand inside a block.
+    csrc, seen = os.path.join(os.path.dirname(dlcx.__file__), "csrc"), 0
+    for name in sorted(os.listdir(csrc)):
+        text = re.sub(r"//.*", "", open(os.path.join(csrc, name)).read())
+        for block in re.findall(r"\basm\s*(?:volatile\s*)?\((.*?)\);", text, flags=re.S):
+            body, *operands = re.split(r'"\s*:', block, maxsplit=1)
+            outputs = re.findall(r'"([+=][^"]*)"', "".join(operands))
+            if "\\n" in body and outputs:
+                assert all("&" in o for o in outputs), (name, block)
+            if "_dpp" in body:
+                seen += 1
+                assert body.startswith('"s_nop 1\\n'), (name, block)
+    assert seen == 2
