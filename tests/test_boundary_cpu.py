@@ -115,6 +115,34 @@ def test_null_misaligned_and_range_arguments():
     assert dlcx.lib().dlcx_strerror(dlcx.EINVAL) == b"invalid argument"
 
 
+def test_compression_with_the_average_rejects_what_its_two_calls_reject():
+    L = dlcx.lib()
+    fake = 0x1000  # never dereferenced: nothing is launched
+    two = C.cast((C.c_void_p * 2)(fake, fake), C.c_void_p)
+    null, odd = (C.cast((C.c_void_p * 2)(fake, x), C.c_void_p) for x in (None, fake + 4))
+    d = dlcx.desc(512, 512, 8, 4, 64, dlcx.MMA_BF16)
+
+    def average(desc=d, phase=0, K=2, deltas=two, basis=fake, codes=two, scales=two, mean=fake, ws=fake):
+        return L.dlcx_compress_average(C.byref(desc), phase, K, deltas, basis, codes, scales, mean, ws, None)
+
+    for bad in (dict(mean=None), dict(mean=fake + 4), dict(K=0), dict(K=17), dict(phase=2), dict(deltas=None),
+                dict(deltas=null), dict(deltas=odd), dict(basis=None), dict(basis=fake + 4), dict(codes=None),
+                dict(codes=null), dict(codes=odd), dict(scales=None), dict(scales=null), dict(scales=odd),
+                dict(ws=None), dict(ws=fake + 4), dict(desc=dlcx.desc(512, 520, 8, 4, 64))):
+        assert average(**bad) == dlcx.EINVAL, bad
+
+    def step(desc=d, r_prev=8, p_hat=fake, q_bar=fake, K=2, tl=two, dtype=0, ef=two, theta=fake, v=fake, lr=0.7,
+             mu=0.9, basis=fake, codes=two, scales=two, mean=fake, ws=fake):
+        return L.dlcx_ef_delta_apply_compress_average(C.byref(desc), r_prev, p_hat, q_bar, K, tl, dtype, ef, theta, v,
+                                                      lr, mu, basis, codes, scales, mean, ws, None)
+
+    for bad in (dict(mean=None), dict(mean=fake + 4), dict(r_prev=-1), dict(r_prev=257), dict(p_hat=None),
+                dict(q_bar=fake + 4), dict(K=0), dict(K=17), dict(tl=null), dict(tl=odd), dict(dtype=2), dict(ef=null),
+                dict(ef=odd), dict(theta=None), dict(v=None), dict(lr=float("nan")), dict(basis=None), dict(codes=odd),
+                dict(scales=null), dict(ws=None), dict(ws=fake + 4), dict(desc=dlcx.desc(512, 512, 8, 3, 64))):
+        assert step(**bad) == dlcx.EINVAL, bad
+
+
 def test_select_rank_window_rule_on_the_host(golden):
     g = golden("adagradcmp_window.txt")
     c, r1, H1 = int(g["c"][0]), int(g["r1"][0]), int(g["H1"][0])

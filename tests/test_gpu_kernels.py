@@ -1038,3 +1038,36 @@ def test_quantise_and_average_in_one_launch_is_both(mma, m, n, r, K, qbits, grou
             got.append([to_np(x).view(np.uint8) for x in codes + scales + [mean, ws[: 4 * K * r * length]]])
         for a, b in zip(*got):
             assert np.array_equal(a, b), phase
+
+
+@pytest.mark.parametrize("mma", [dlcx.MMA_FMA, dlcx.MMA_F32, dlcx.MMA_BF16, dlcx.MMA_F16])
+@pytest.mark.parametrize("m,n,r,r_prev,K,dtype", [
+    (48, 80, 5, 0, 2, torch.float32), (272, 528, 8, 8, 3, torch.bfloat16), (512, 256, 64, 20, 1, torch.float32),
+    (256, 512, 33, 70, 5, torch.bfloat16), (256, 272, 100, 64, 16, torch.float32),   # above rank 64: two passes
+])
+def test_round_with_the_average_is_the_two_calls(mma, m, n, r, r_prev, K, dtype):
+    # State, codes, scales and mean bit for bit those of the round and the average of its payloads, the mean written
+    # over the factor of the round before, of the same rank, a lower one or a higher one.
+    g = rng(m + n + r + K)
+    d = dlcx.desc(m, n, r, 4, 16, mma)
+    up = lambda *shape: to_dev(g.standard_normal(shape).astype(np.float32))
+    theta_l = [up(m, n).to(dtype) for _ in range(K)]
+    state = [up(m, n) for _ in range(K + 2)]   # error buffers, theta, momentum
+    factor, q_bar, basis = up(max(r, r_prev, 1), m), up(max(r_prev, 1), n), up(r, n)
+    ws = torch.zeros(max(dlcx.dlcx_workspace_bytes(d, K), dlcx.dlcx_workspace_bytes(dlcx.desc(m, n, max(r_prev, 1), 4, 16, mma), K)),
+                     device=DEV, dtype=torch.uint8)
+    got = []
+    for one in (False, True):
+        codes, scales = payload_buffers(d, dlcx.PHASE_P, K)
+        *ef, theta, v = [x.clone() for x in state]
+        p_hat = factor.clone()
+        ws.fill_(255)
+        args = (d, r_prev, p_hat, q_bar, theta_l, ef, theta, v, 0.7, 0.9, basis, codes, scales)
+        if one:
+            dlcx.dlcx_ef_delta_apply_compress_average(*args, p_hat, ws)
+        else:
+            dlcx.dlcx_ef_delta_apply_compress(*args, ws)
+            dlcx.dlcx_dequant_average(codes, scales, r * m, 4, 16, p_hat)
+        got.append([to_np(x).view(np.uint8) for x in codes + scales + ef + [theta, v, p_hat]])
+    for i, (a, b) in enumerate(zip(*got)):
+        assert np.array_equal(a, b), i
