@@ -388,9 +388,12 @@ int launch_project_p_fma(int64_t m, int64_t n, int r, int K, const PtrPack<const
     typedef std::integral_constant<int, 2> two;
     // Two row blocks to a workgroup, half as many conversions and basis operands to a product, take nine tenths of the
     // time of two workgroups with one, if as many units are busy: rounds of the launch on 256 units, by either kind,
-    // while one round or two is all there is.  One | two, us: 2048 x 2048 four workers r = 32 31.4 | 28.1, r = 64 52.0
-    // | 49.5; 2480 x 2480 five r = 64 107 | 97; 3376 x 2000 four r = 32 48 | 44, 2400 x 2000 38 | 44, 4800 x 2000 77 |
-    // 68; 1008 x 2000 four r = 48 28 | 37.
+    // while one round or two is all there is: one round of pairs for two of singles (129 .. 256 pairs), two for four
+    // (from 385 on).  One | two, us, four workers (five at 2480): 128 pairs 1024 x 2000 r = 8 11.6 | 15.0, r = 48 25.4 |
+    // 34.8; 136 .. 256 pairs 1088 x 512 r = 8 6.5 | 6.1, r = 64 15.8 | 15.7, 1088 x 2000 r = 1 14.7 | 15.1, r = 16 15.8 |
+    // 15.4, r = 64 44.9 | 45.1, 1616 x 8192 r = 16 61.0 | 50.0, 2048 x 8192 r = 32 105 | 83; 260 pairs 2064 x 2000 r = 16
+    // 21.3 | 23.1, r = 64 69.9 | 74.8; 390 .. 512 pairs 2480 x 2000 r = 16 27.5 | 23.6, r = 64 84.1 | 76.5, 4080 x 2000 r =
+    // 32 46.5 | 42.2.
     const int64_t pairs = ceil_div(m, 32) * K, singles = ceil_div(m, 16) * K;
     const bool pair = pairs >= 512 || 2 * ceil_div(pairs, 256) * 9 <= ceil_div(singles, 256) * 10;
     const bool far = p_sets_ahead(n, r, pairs) > 1;

@@ -113,7 +113,11 @@ struct Mean4 {
 // elements of one worker (of every kAvgWaves-th), the first one adds up what they decode to.  The same codes,
 // scales and mean as the two kernels leave, without a launch and the payloads' way through memory between them: bound by
 // latency at most sizes.  An outer step of one 512 x 512 matrix, which has two of them in its chain of launches, 74 - 79 us
-// with a launch each, 61 in one; of an OPT-1.3B-like layer 1055 | 1015.
+// with a launch each, 61 in one; of an OPT-1.3B-like layer 1055 | 1015.  Above four workers a wavefront takes several of
+// them one after the other, and one launch is still the shorter way for all of them.  P in bf16, us, two launches | one:
+// 512 x 512 r = 8 K = 1 11.5 | 10.0, K = 8 15.1 | 12.2, K = 16 18.2 | 14.9; 8192 x 1024 r = 64 K = 4 40.4 | 37.1, K = 16
+// 147 | 139; 8192 x 8192 r = 64 K = 8 416 | 392; 256 x 1280 r = 130 K = 16 37.5 | 34.4 (Q
+// 35.8 | 29.7).
 constexpr int kAvgWaves = 4;
 template <int kQbits, int kLanes, bool kSum>
 __global__ __launch_bounds__(64 * kAvgWaves) void quantize_average_kernel(

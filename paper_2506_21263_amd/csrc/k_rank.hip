@@ -288,9 +288,9 @@ __device__ __forceinline__ double *high_of(const FactorItem &it) { return eig_of
 // The Gram sums over chunk c of a factor of at most 16 columns by the workgroup that goes on with them,
 // a quarter of the chunk per wavefront, as gram_partial_kernel forms them, bit for bit (whether a factor's
 // sums come from there depends on the batch).  Up to kSmallGramLength rows that is no longer than a launch before
-// this one, us without | with it, in a graph: 512 x 8 14.9 | 16.5, 512 x 16 21.4 | 23.3, 1024 x 8 17.0 | 16.7, 1024
-// x 16 23.7 | 23.8; from the host 1024 x 8 17.2 | 17.8.  Above it is longer, as a chunk takes 2 us: 1040 x 8 17.7 |
-// 17.0, 1536 x 8 19.1 | 17.0, 1536 x 16 25.7 | 23.9, 2048 x 16 27.9 | 23.9.
+// this one, us without | with it, from the host: 512 x 8 9.7 | 11.7, 512 x 16 13.2 | 15.3, 1024 x 8 11.8 | 11.9, 1024 x
+// 16 15.4 | 15.7; in a graph 512 x 8 10.3 | 11.9, 1024 x 8 12.4 | 12.1, 1024 x 16 16.1 | 15.7.  Above it is longer, as a
+// chunk takes 2 us (in a graph): 1040 x 8 13.1 | 12.2, 1536 x 8 14.6 | 12.4, 1536 x 16 18.2 | 15.7, 2048 x 16 20.4 | 16.1.
 constexpr int kSmallGramRank = 16;
 constexpr int kSmallGramLength = 1024;
 __device__ __forceinline__ void small_gram(const FactorItem &it, int c, double (&gram)[4][kSmallGramRank][kSmallGramRank + 1]) {
@@ -815,8 +815,8 @@ __global__ __launch_bounds__(kTT) void tridiag_small_kernel(FactorBatch batch, d
             }
         }
     // Chunk by chunk in order, kAhead requested at a time, with the sums' launch, us at two | four | eight:
-    // 8192 x 32 49.3 | 48.6 | 48.9, 2048 x 8 17.6 | 17.3 | 18.3, 512 x 32 45.9 | 46.1 | 46.9; with 64 columns two |
-    // four: 512 x 48 78.2 | 79.5, 2048 x 64 106.4 | 106.7.
+    // 8192 x 32 31.5 | 30.5 | 30.6, 2048 x 8 12.7 | 12.3 | 13.0, 512 x 32 28.3 | 27.9 | 28.7; with 64 columns one | two |
+    // four: 512 x 48 48.1 | 48.2 | 49.3, 2048 x 64 65.2 | 65.0 | 64.9, 8192 x 64 65.9 | 66.0 | 67.3.
     constexpr int kAhead = RC <= 32 ? 4 : 2;
     for (int c = 0; c < nchunks; c += kAhead) {
         double p[kAhead][E];
