@@ -88,8 +88,9 @@ class MatrixState:
 class Stage:
     """All matrices of one pipeline stage plus shared scratch; `step` is one outer step.
 
-    fused=True uses dlcx_ef_delta_apply_compress (one pass for error buffers, pseudo-gradients,
-    outer update and the P-phase projection, the decompressed average never written);
+    fused=True uses dlcx_ef_delta_apply_compress_average (one pass for error buffers,
+    pseudo-gradients, outer update and the P-phase projection, the decompressed average never
+    written; then the payloads and their average);
     fused=False runs the separate entry points.  warm_start=True takes Q_bar of the previous
     round as the basis of the P phase.  streams > 1 deals consecutive runs of matrices to that
     many HIP streams.  measure_rank=True also launches the effective-rank kernel of Alg. 3 for
