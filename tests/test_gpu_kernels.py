@@ -1010,6 +1010,7 @@ def test_batched_orthonormalize_and_rank_mixed_shapes():
     (16, 16, 1, 1, 4, 16),          # one group
     (272, 528, 3, 2, 8, 16),        # a last wavefront that is partly idle
     (512, 512, 8, 3, 4, 64), (512, 768, 33, 5, 8, 256), (1024, 256, 70, 4, 4, 32), (256, 1280, 130, 16, 4, 128),
+    (256, 512, 100, 3, 4, 16),      # three workers: 1e3 times larger, beyond what the fp16 form above rank 64 takes
 ])
 def test_quantise_and_average_in_one_launch_is_both(mma, m, n, r, K, qbits, group):
     # Codes, scales, factors and mean bit for bit those of the two calls: with and without partial sums, with
